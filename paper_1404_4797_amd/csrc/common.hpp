@@ -154,6 +154,12 @@ __device__ __forceinline__ uint64_t shfl_u64(uint64_t v, int src) {
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
+__device__ __forceinline__ unsigned long long shfl_up_u64(unsigned long long v, int o) {
+    const uint32_t lo = __shfl_up(static_cast<uint32_t>(v), o, 64);
+    const uint32_t hi = __shfl_up(static_cast<uint32_t>(v >> 32), o, 64);
+    return (static_cast<unsigned long long>(hi) << 32) | lo;
+}
+
 __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {

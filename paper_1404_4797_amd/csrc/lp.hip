@@ -64,23 +64,18 @@ constexpr int kHubDenseChunk = 8192;     // slots per hub workgroup with dense b
 constexpr int kHubTChunk = 4096;         // HBM table entries per scan workgroup
 constexpr int kSmallLabels = 4096;       // LDS-private histograms up to this many labels
 constexpr int kMaxBlocks = 512;          // grid cap of the grid-stride candidate kernels
-constexpr int kSmallSeg = 4096;          // segments up to this length: one selecting workgroup
+constexpr int kSmallSeg = 16384;         // large colours: segments up to this length have one selecting workgroup
 constexpr int kSegChunk = 16384;         // entries per workgroup in the multi-workgroup selection
 constexpr int kLargeBlocks = 256;        // grid of the multi-workgroup selection kernel
 constexpr int kLargeThreads = 1024;      // and its workgroup size
 
 struct Counters {
-    uint32_t ncand;        // candidates of the sub-round
-    uint32_t nslow;        // candidates aimed at targets that cannot take them all
-    int32_t gmin;          // gain range of those candidates
+    unsigned long long segs;  // segments claimed (high word), entries reserved in them (low word)
+    int32_t gmin;             // gain range of the entries
     int32_t gmax;
+    uint32_t nlarge;    // segments longer than one workgroup selects from
+    uint32_t nlchunks;  // kSegChunk-entry chunks of those segments
     uint32_t bad_color;
-    uint32_t nseg;         // targets that cannot take all their candidates
-    uint32_t slow_total;   // entries reserved in their segments
-    uint32_t unused;
-    uint32_t nlarge;       // segments longer than kSmallSeg
-    uint32_t nlchunks;     // kSegChunk-entry chunks of those segments
-    int32_t gkey;          // gmax of the sub-round's keys, kept past the counter reset
     uint32_t pad;
 };
 
@@ -1226,6 +1221,19 @@ __device__ __forceinline__ int32_t block_sum_i32(int32_t v) {
 }
 
 // ------------------------------------------------- candidates and admission
+//
+// After the evaluation a sub-round needs three launches (more only when a
+// target may have more candidates than one workgroup selects):
+//   accumulate  per-target weight and count of the candidates
+//   admit       candidates whose target takes all of its candidates are
+//               admitted, the others are written into their target's segment
+//   finish      moves the admitted ones; every segment finds its target's
+//               boundary and moves the entries below it
+// A launch that follows another on the same stream costs about 2.3 us on this
+// GPU before it does any work, and an atomic on an address that other
+// workgroups also add to costs 12 ns per add (4096 adds to one address:
+// 50 us; spread over 4096 addresses: 2.4 us), so the chain is short, grids
+// stay at a few hundred workgroups, and sums are combined in LDS first.
 
 // Bound of a target label: one scalar, or per graph through the label's graph.
 struct Bounds {
@@ -1238,42 +1246,52 @@ __device__ __forceinline__ int64_t bound_of(const Bounds& B, int32_t t) {
     return B.lgid ? B.g_bound[B.lgid[t]] : B.bound;
 }
 
-// Block-local LDS index of label t: t itself for small label spaces, else an
-// open-addressing slot (kAggTable entries, at most kAggChunk keys per chunk,
-// so the table is never more than half full).
-constexpr int kAggChunk = 2048;
-constexpr int kAggTable = 4096;
+// Candidate total of a target: count in the high word, weight in the low one
+// (a label's weight never exceeds c(V) <= 2^31 - 1, so no carry).
+__device__ __forceinline__ unsigned long long acc_of(int32_t cnt, int32_t weight) {
+    return (static_cast<unsigned long long>(static_cast<uint32_t>(cnt)) << 32) | static_cast<uint32_t>(weight);
+}
 
-
-template <bool kSmall>
-__device__ __forceinline__ int32_t agg_slot(int32_t* keys, int32_t t, bool insert) {
-    if (kSmall) return t;
-    uint32_t h = slot_hash(static_cast<uint32_t>(t)) & (kAggTable - 1);
+// Slot of label t in a block-local open-addressing table of T entries (T at
+// least twice the keys a block inserts).
+template <int T>
+__device__ __forceinline__ int32_t agg_insert(int32_t* keys, int32_t t) {
+    uint32_t h = slot_hash(static_cast<uint32_t>(t)) & (T - 1);
     while (true) {
-        const int32_t k = insert ? atomicCAS(&keys[h], -1, t) : keys[h];
-        if (k == t || (insert && k == -1)) return static_cast<int32_t>(h);
-        h = (h + 1) & (kAggTable - 1);
+        const int32_t k = atomicCAS(&keys[h], -1, t);
+        if (k == t || k == -1) return static_cast<int32_t>(h);
+        h = (h + 1) & (T - 1);
     }
 }
 
-// tsum[t] += c(v) and cnt[t] += 1 over the candidates of the sub-round, summed
-// per block in LDS first so that a label many nodes aim at (a hub's cluster)
-// costs one global atomic per block and chunk, not one per candidate.
-template <bool kSmall, int R>
-__global__ void __launch_bounds__(256) cand_accum_kernel(const int32_t* __restrict__ ct,
+// Label spaces up to this size (blocks of a refinement): LDS sums are indexed
+// by the label itself, every workgroup lays the segments out by itself, and the
+// counters all workgroups add to stand one per 128-byte line (adds to one line
+// are served one after the other, some 3 ns each).
+constexpr int kDirectLabels = 1024;
+constexpr int kAccShift = 4;    // acc[t << kAccShift] (8-byte entries)
+constexpr int kFillShift = 5;   // seg_fill[t << kFillShift] (4-byte entries)
+
+// acc[t] += (1, c(v)) over the candidates of the sub-round, summed per block
+// in LDS first so that a label many nodes aim at (a hub's cluster) costs one
+// global atomic per block and chunk, not one per candidate.  Each block takes
+// R * 256 consecutive entries at a time.
+template <bool kDirect, int R>
+__global__ void __launch_bounds__(256) accumulate_kernel(const int32_t* __restrict__ ct,
                                                          const int32_t* __restrict__ nodes, int32_t count,
-                                                         const int32_t* __restrict__ vw, int32_t* __restrict__ tsum,
-                                                         int32_t* __restrict__ cnt, int32_t nw, Counters* ctr,
+                                                         const int32_t* __restrict__ vw,
+                                                         unsigned long long* __restrict__ acc, int32_t nw,
                                                          const uint32_t* __restrict__ gate,
                                                          uint32_t* __restrict__ round_cnt) {
     if (stopped(gate)) return;  // uniform over the grid
-    constexpr int kSlots = kSmall ? kSmallLabels : kAggTable;
-    __shared__ int32_t keys[kSmall ? 1 : kAggTable];
+    constexpr int T = 512 * R;
+    constexpr int kSlots = kDirect ? kDirectLabels : T;
+    __shared__ int32_t keys[kDirect ? 1 : T];
     __shared__ int32_t lsum[kSlots];
     __shared__ int32_t lcnt[kSlots];
-    const int32_t nslots = kSmall ? nw : kAggTable;
+    const int32_t nslots = kDirect ? nw : T;
     for (int j = threadIdx.x; j < nslots; j += 256) {
-        if (!kSmall) keys[j] = -1;
+        if (!kDirect) keys[j] = -1;
         lsum[j] = 0;
         lcnt[j] = 0;
     }
@@ -1297,52 +1315,65 @@ __global__ void __launch_bounds__(256) cand_accum_kernel(const int32_t* __restri
         for (int r = 0; r < R; ++r) {
             if (tr[r] < 0) continue;
             ++found;
-            const int32_t i = agg_slot<kSmall>(keys, tr[r], true);
+            const int32_t i = kDirect ? tr[r] : agg_insert<T>(keys, tr[r]);
             if (cr[r]) atomicAdd(&lsum[i], cr[r]);
             atomicAdd(&lcnt[i], 1);
         }
-        if (!kSmall) {  // flush this chunk's labels
+        if (!kDirect) {  // flush this chunk's labels
             __syncthreads();
-            for (int j = threadIdx.x; j < kAggTable; j += 256) {
+            const bool more = base + static_cast<int64_t>(gridDim.x) * (R * 256) < count;  // uniform
+            for (int j = threadIdx.x; j < T; j += 256) {
                 const int32_t t = keys[j];
                 if (t >= 0) {
-                    if (lsum[j]) atomicAdd(&tsum[t], lsum[j]);
-                    atomicAdd(&cnt[t], lcnt[j]);
-                    keys[j] = -1;
-                    lsum[j] = 0;
-                    lcnt[j] = 0;
+                    atomicAdd(&acc[t], acc_of(lcnt[j], lsum[j]));
+                    if (more) {
+                        keys[j] = -1;
+                        lsum[j] = 0;
+                        lcnt[j] = 0;
+                    }
                 }
             }
-            __syncthreads();
+            if (more) __syncthreads();
         }
     }
-    if (kSmall) {
+    if (kDirect) {
         __syncthreads();
-        for (int j = threadIdx.x; j < nw; j += 256) {
-            if (lsum[j]) atomicAdd(&tsum[j], lsum[j]);
-            if (lcnt[j]) atomicAdd(&cnt[j], lcnt[j]);
-        }
+        for (int j = threadIdx.x; j < nw; j += 256)
+            if (lcnt[j]) atomicAdd(&acc[j << kAccShift], acc_of(lcnt[j], lsum[j]));
     }
     const int32_t tot = block_sum_i32(found);
-    if (threadIdx.x == 0 && tot) {
-        atomicAdd(&ctr->ncand, static_cast<uint32_t>(tot));
-        atomicAdd(round_cnt, static_cast<uint32_t>(tot));
-    }
+    if (threadIdx.x == 0 && tot) atomicAdd(round_cnt, static_cast<uint32_t>(tot));
 }
 
-// ------------------------------------------------------------- admission
-//
-// Outcome of a candidate in ok[p]: 0 not a candidate (or rejected), 1
-// admitted, kOkSlow aimed at a target that cannot take all its candidates.
-// The apply kernel decides those from the target's boundary key bnd[t]: a
-// candidate is admitted when its key [gmax - gain][node] is below it.
-constexpr uint8_t kOkSlow = 2;
+// Outcome of a candidate in ok[p]: 0 not a candidate or in a segment, 1
+// admitted.  Segment entries are decided by the target's boundary.
+
+// A target that cannot take all its candidates: `len` entries from `base` in
+// the segment arrays, of which the longest prefix in key order whose weight
+// stays within `room` moves.
+struct Segment {
+    int32_t t, base, len, room;
+};
+
+// An entry is stored as [gain][node] and ordered by the key
+// (gmax - gain) << bits_v | node (gain descending, node ascending), which is
+// formed when it is read: gmax, the largest gain in a segment, is known only
+// once every entry has been written.
+__device__ __forceinline__ uint64_t entry_of(int32_t gain, int32_t v) {
+    return (static_cast<uint64_t>(static_cast<uint32_t>(gain)) << 32) | static_cast<uint32_t>(v);
+}
+
+__device__ __forceinline__ uint64_t key_of(uint64_t e, int32_t gmax, int bits_v) {
+    return (static_cast<uint64_t>(static_cast<int64_t>(gmax) - static_cast<int32_t>(e >> 32)) << bits_v) |
+           (e & 0xFFFFFFFFULL);
+}
+
+__device__ __forceinline__ int32_t node_of(uint64_t e) { return static_cast<int32_t>(e & 0xFFFFFFFFULL); }
 
 // Multi-workgroup selection for segments longer than the single-workgroup
-// limit: the same most-significant-digit-first selection with kLDigit-bit
-// digits and per-segment histograms in HBM. A segment is registered when its
-// target claims it: it takes the next large index l and a run of
-// kSegChunk-entry chunks.
+// limit: most-significant-digit-first with kLDigit-bit digits and per-segment
+// histograms in HBM. A segment is registered when its target claims it: it
+// takes the next large index l and a run of kSegChunk-entry chunks.
 constexpr int kLDigit = 12;
 constexpr int kLBins = 1 << kLDigit;
 
@@ -1353,98 +1384,74 @@ struct LargeSel {
     int32_t* chunk0;    // [nlarge] its first chunk
     int32_t* owner;     // [nlchunks] large segment of each chunk
     uint32_t* hist;     // [nlarge][kLBins] weight per digit
-    uint64_t* prefix;   // [nlarge] digits fixed so far
-    int64_t* room;      // [nlarge] weight still admissible below the prefix
+    uint64_t* prefix;   // [nlarge] digits fixed so far, at the end the boundary key
+    int32_t* room;      // [nlarge] weight still admissible below the prefix
     uint32_t* done;     // [nlarge] chunks finished with the current digit
 };
 
 __device__ __forceinline__ int32_t seg_chunks(int32_t len) { return (len + kSegChunk - 1) / kSegChunk; }
 
-// Gives target t (room = bound - w(t)) a segment of cnt[t] entries, and a
-// large index when that is longer than small_max.
-__device__ void claim_segment(int32_t t, int32_t len, int64_t room, int32_t* seg_off, int32_t* seg_list,
-                              const LargeSel& L, int32_t small_max, Counters* ctr) {
-    const int32_t base = static_cast<int32_t>(atomicAdd(&ctr->slow_total, static_cast<uint32_t>(len)));
-    seg_off[t] = base;
-    seg_list[atomicAdd(&ctr->nseg, 1u)] = t;
-    if (len <= small_max) return;
-    const uint32_t l = atomicAdd(&ctr->nlarge, 1u);
-    const int32_t nch = seg_chunks(len);
-    const int32_t c0 = static_cast<int32_t>(atomicAdd(&ctr->nlchunks, static_cast<uint32_t>(nch)));
-    L.target[l] = t;
-    L.base[l] = base;
-    L.len[l] = len;
-    L.chunk0[l] = c0;
-    L.prefix[l] = 0;
-    L.room[l] = room;
-    for (int32_t c = 0; c < nch; ++c) L.owner[c0 + c] = static_cast<int32_t>(l);
+// Per-colour admission state shared by the kernels below.
+struct Admission {
+    const int32_t* ct;     // per entry of the colour: target or -1
+    const int32_t* cg;     // per entry: gain
+    const int32_t* nodes;  // per entry: node
+    int32_t count;
+    const int32_t* vw;
+    int32_t* w;
+    int32_t nw;
+    unsigned long long* acc;
+    Bounds B;
+    uint8_t* ok;
+    int32_t* seg_off;   // [nw] first entry of the target's segment, -1 none, -2 being claimed
+    int32_t* seg_fill;  // per label: entries written
+    Segment* seg;
+    uint64_t* sent;  // segment entries and their weights
+    int32_t* swt;
+    LargeSel L;
+    int32_t small_max;  // longer segments: multi-workgroup selection
+    int32_t acc_shift;   // acc[t << acc_shift], seg_fill[t << fill_shift]: kAccShift
+    int32_t fill_shift;  // and kFillShift for at most kDirectLabels labels (no seg_off then), else 0
+    int bits_v;
+    int32_t* label;
+    uint8_t* label8;
+    uint16_t* label16;
+    Counters* ctr;       // this sub-round's counters
+    Counters* ctr_next;  // the next sub-round's: cleared here, no kernel reads them any more
+    const uint32_t* gate;
+};
+
+// Records segment sid and, when it is longer than small_max, gives it a large
+// index.
+__device__ __forceinline__ void record_segment(const Admission& A, uint32_t sid, const Segment& g) {
+    A.seg[sid] = g;
+    if (g.len <= A.small_max) return;
+    const uint32_t l = atomicAdd(&A.ctr->nlarge, 1u);
+    const int32_t nch = seg_chunks(g.len);
+    const int32_t c0 = static_cast<int32_t>(atomicAdd(&A.ctr->nlchunks, static_cast<uint32_t>(nch)));
+    A.L.target[l] = g.t;
+    A.L.base[l] = g.base;
+    A.L.len[l] = g.len;
+    A.L.chunk0[l] = c0;
+    A.L.prefix[l] = 0;
+    A.L.room[l] = g.room;
+    for (int32_t c = 0; c < nch; ++c) A.L.owner[c0 + c] = static_cast<int32_t>(l);
 }
 
-// Fast path of admission: if everything aimed at t fits, admit it all;
-// otherwise the candidate goes to the slow list and its target gets a
-// segment (small label spaces: the grid walks the labels; otherwise the first
-// slow candidate of a target claims it).
-template <bool kSmall, int kAdmitIters>
-__global__ void __launch_bounds__(256) admit_kernel(const int32_t* __restrict__ ct, const int32_t* __restrict__ cg,
-                                                    int32_t count, const int32_t* __restrict__ w,
-                                                    const int32_t* __restrict__ tsum,
-                                                    const int32_t* __restrict__ cnt, Bounds B,
-                                                    uint8_t* __restrict__ ok, uint32_t* __restrict__ slow_idx,
-                                                    int32_t* __restrict__ seg_off, int32_t* __restrict__ seg_list,
-                                                    LargeSel L, int32_t small_max, int32_t nw, Counters* ctr,
-                                                    const uint32_t* __restrict__ gate) {
+// Gives target t a segment and publishes seg_off[t] last.
+__device__ __forceinline__ void claim_segment(const Admission& A, int32_t t) {
+    const unsigned long long a = A.acc[t];
+    const int32_t len = static_cast<int32_t>(a >> 32);
+    const int32_t room = static_cast<int32_t>(bound_of(A.B, t) - A.w[t]);  // below the candidates' weight: fits
+    const unsigned long long at = atomicAdd(&A.ctr->segs, acc_of(1, len));
+    const int32_t base = static_cast<int32_t>(at & 0xFFFFFFFFULL);
+    record_segment(A, static_cast<uint32_t>(at >> 32), Segment{t, base, len, room});
+    __hip_atomic_store(&A.seg_off[t], base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The workgroup's gain range into the counters, one pair of atomics.
+__device__ __forceinline__ void note_gains(Counters* ctr, int32_t gmin, int32_t gmax) {
     __shared__ int32_t s_min[4], s_max[4];
-    if (stopped(gate)) return;  // uniform over the grid
-    if (kSmall) {
-        for (int32_t t = blockIdx.x * 256 + threadIdx.x; t < nw; t += gridDim.x * 256) {
-            if (cnt[t] == 0) continue;
-            const int64_t room = bound_of(B, t) - static_cast<int64_t>(w[t]);
-            if (tsum[t] > room) claim_segment(t, cnt[t], room, seg_off, seg_list, L, small_max, ctr);
-        }
-    }
-    // each block takes kAdmitIters * 256 consecutive candidates at a time
-    // and appends its slow ones with one atomic
-    int32_t gmin = INT_MAX, gmax = INT_MIN;
-    for (int32_t base = blockIdx.x * (kAdmitIters * 256); base < count; base += gridDim.x * (kAdmitIters * 256)) {
-        uint32_t mask = 0;
-        // the thread's targets and gains first (loads in flight together),
-        // then the decisions
-        int32_t tt[kAdmitIters], gg[kAdmitIters];
-#pragma unroll
-        for (int it = 0; it < kAdmitIters; ++it) {
-            const int32_t p = base + it * 256 + static_cast<int32_t>(threadIdx.x);
-            tt[it] = p < count ? ct[p] : -2;
-            gg[it] = p < count ? cg[p] : 0;
-        }
-#pragma unroll
-        for (int it = 0; it < kAdmitIters; ++it) {
-            const int32_t p = base + it * 256 + static_cast<int32_t>(threadIdx.x);
-            const int32_t t = tt[it];
-            if (t == -2) continue;  // past the end
-            uint8_t o = 0;
-            if (t >= 0) {
-                const int64_t room = bound_of(B, t) - static_cast<int64_t>(w[t]);
-                if (tsum[t] <= room) {
-                    o = 1;
-                } else {
-                    o = kOkSlow;
-                    mask |= 1u << it;
-                    const int32_t gain = gg[it];
-                    gmin = gain < gmin ? gain : gmin;
-                    gmax = gain > gmax ? gain : gmax;
-                    if (!kSmall && seg_off[t] == -1 && atomicCAS(&seg_off[t], -1, -2) == -1)
-                        claim_segment(t, cnt[t], room, seg_off, seg_list, L, small_max, ctr);
-                }
-            }
-            ok[p] = o;
-        }
-        uint32_t j = block_append_count(static_cast<uint32_t>(__popc(mask)), &ctr->nslow);
-        while (mask) {
-            const int it = __ffs(mask) - 1;
-            mask &= mask - 1;
-            slow_idx[j++] = static_cast<uint32_t>(base + it * 256 + static_cast<int32_t>(threadIdx.x));
-        }
-    }
     gmin = wave_min(gmin);
     gmax = wave_max(gmax);
     if (lane_id() == 0) {
@@ -1453,220 +1460,258 @@ __global__ void __launch_bounds__(256) admit_kernel(const int32_t* __restrict__ 
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        int32_t a = INT_MAX, b = INT_MIN;
-        for (int w2 = 0; w2 < 4; ++w2) {
-            a = s_min[w2] < a ? s_min[w2] : a;
-            b = s_max[w2] > b ? s_max[w2] : b;
+        const int32_t a = min(min(s_min[0], s_min[1]), min(s_min[2], s_min[3]));
+        const int32_t b = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+        if (a <= b) {
+            atomicMin(&ctr->gmin, a);
+            atomicMax(&ctr->gmax, b);
         }
-        if (a != INT_MAX) atomicMin(&ctr->gmin, a);
-        if (b != INT_MIN) atomicMax(&ctr->gmax, b);
     }
 }
 
-// Writes every slow candidate into its target's segment as the key
-// [gmax - gain][node] (ascending key = gain desc, node asc), with its weight.
-// Space is reserved once per label per block chunk.
-template <bool kSmall, int R>
-__global__ void __launch_bounds__(256) scatter_kernel(const uint32_t* __restrict__ slow_idx,
-                                                      const int32_t* __restrict__ nodes, const int32_t* __restrict__ ct,
-                                                      const int32_t* __restrict__ cg, const int32_t* __restrict__ vw,
-                                                      int bits_v, int32_t nw, const int32_t* __restrict__ seg_off,
-                                                      int32_t* __restrict__ seg_fill, uint64_t* __restrict__ skey,
-                                                      int32_t* __restrict__ swt, const Counters* ctr) {
-    constexpr int kSlots = kSmall ? kSmallLabels : kAggTable;
-    __shared__ int32_t keys[kSmall ? 1 : kAggTable];
-    __shared__ int32_t lcnt[kSlots];
-    __shared__ int32_t lbase[kSlots];
-    const int32_t nslots = kSmall ? nw : kAggTable;
-    const uint32_t m = ctr->nslow;
-    const int32_t gmax = ctr->gmax;
-    for (int j = threadIdx.x; j < nslots; j += 256) {
-        if (!kSmall) keys[j] = -1;
-        lcnt[j] = 0;
-    }
-    __syncthreads();
-    for (uint32_t base = blockIdx.x * (R * 256); base < m; base += gridDim.x * (R * 256)) {
-        // the thread's slow candidates, their targets, nodes and gains, all
-        // loaded before the LDS work
-        uint32_t pr[R];
-        int32_t tr[R];
+// Admits every candidate whose target takes all its candidates and writes the
+// others into their targets' segments.  The first block to meet such a target
+// claims its segment; a block that meets it while the claim is being
+// published waits for the offset.  That wait ends: a block makes all its
+// claims of a chunk, which wait for nothing, before it reads any offset, and
+// a claim is published by a wave that is already running.
+template <int R>
+__global__ void __launch_bounds__(256) admit_kernel(Admission A) {
+    constexpr int T = 512 * R;
+    __shared__ int32_t keys[T];
+    __shared__ int32_t lcnt[T];
+    __shared__ int32_t lbase[T];
+    if (stopped(A.gate)) return;  // uniform over the grid
+    int32_t gmin = INT_MAX, gmax = INT_MIN;
+    for (int64_t base = static_cast<int64_t>(blockIdx.x) * (R * 256); base < A.count;
+         base += static_cast<int64_t>(gridDim.x) * (R * 256)) {
+        int32_t tr[R], gr[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const uint32_t j = base + r * 256 + threadIdx.x;
-            pr[r] = j < m ? slow_idx[j] : 0xFFFFFFFFu;
+            const int64_t p = base + r * 256 + threadIdx.x;
+            tr[r] = p < A.count ? A.ct[p] : -1;
+            gr[r] = p < A.count ? A.cg[p] : 0;
         }
-#pragma unroll
-        for (int r = 0; r < R; ++r) tr[r] = pr[r] != 0xFFFFFFFFu ? ct[pr[r]] : -1;
-#pragma unroll
-        for (int r = 0; r < R; ++r)
-            if (tr[r] >= 0) atomicAdd(&lcnt[agg_slot<kSmall>(keys, tr[r], true)], 1);
-        __syncthreads();
-        for (int i = threadIdx.x; i < nslots; i += 256) {
-            const int32_t t = kSmall ? i : keys[i];
-            lbase[i] = (t >= 0 && lcnt[i]) ? atomicAdd(&seg_fill[t], lcnt[i]) : 0;
-            lcnt[i] = 0;
-        }
-        __syncthreads();
-        int32_t vr[R], gr[R], cr[R];
+        unsigned long long ar[R];
+        int32_t wr[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            vr[r] = tr[r] >= 0 ? nodes[pr[r]] : 0;
-            gr[r] = tr[r] >= 0 ? cg[pr[r]] : 0;
+            ar[r] = tr[r] >= 0 ? A.acc[tr[r]] : 0;
+            wr[r] = tr[r] >= 0 ? A.w[tr[r]] : 0;
+        }
+        bool any = false;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t p = base + r * 256 + threadIdx.x;
+            bool slow = false;
+            if (tr[r] >= 0)
+                slow = static_cast<int64_t>(ar[r] & 0xFFFFFFFFULL) > bound_of(A.B, tr[r]) - static_cast<int64_t>(wr[r]);
+            if (p < A.count) A.ok[p] = tr[r] >= 0 && !slow ? 1 : 0;
+            if (!slow) tr[r] = -1;
+            any |= slow;
+        }
+        if (!__syncthreads_or(any)) continue;  // also: the previous chunk's table is no longer in use
+        for (int j = threadIdx.x; j < T; j += 256) {
+            keys[j] = -1;
+            lcnt[j] = 0;
+        }
+        __syncthreads();
+        int32_t slot[R], rank[R], vr[R], cr[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int64_t p = base + r * 256 + threadIdx.x;
+            vr[r] = tr[r] >= 0 ? A.nodes[p] : 0;
         }
 #pragma unroll
-        for (int r = 0; r < R; ++r) cr[r] = tr[r] >= 0 ? (vw ? vw[vr[r]] : 1) : 0;
+        for (int r = 0; r < R; ++r) {
+            slot[r] = tr[r] >= 0 ? agg_insert<T>(keys, tr[r]) : 0;
+            rank[r] = tr[r] >= 0 ? atomicAdd(&lcnt[slot[r]], 1) : 0;
+            cr[r] = tr[r] >= 0 ? (A.vw ? A.vw[vr[r]] : 1) : 0;
+        }
+        __syncthreads();
+        for (int j = threadIdx.x; j < T; j += 256) {
+            const int32_t t = keys[j];
+            if (t >= 0 && atomicCAS(&A.seg_off[t], -1, -2) == -1) claim_segment(A, t);
+        }
+        __syncthreads();
+        for (int j = threadIdx.x; j < T; j += 256) {
+            const int32_t t = keys[j];
+            if (t < 0) continue;
+            int32_t o = __hip_atomic_load(&A.seg_off[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            while (o < 0) {
+                __builtin_amdgcn_s_sleep(1);
+                o = __hip_atomic_load(&A.seg_off[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            lbase[j] = o + atomicAdd(&A.seg_fill[t], lcnt[j]);
+        }
+        __syncthreads();
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (tr[r] < 0) continue;
-            const int32_t t = tr[r];
-            const int32_t i = agg_slot<kSmall>(keys, t, false);
-            const int32_t at = seg_off[t] + lbase[i] + atomicAdd(&lcnt[i], 1);
-            skey[at] = (static_cast<uint64_t>(static_cast<int64_t>(gmax) - gr[r]) << bits_v) |
-                       static_cast<uint64_t>(static_cast<uint32_t>(vr[r]));
-            swt[at] = cr[r];
+            const int32_t at = lbase[slot[r]] + rank[r];
+            A.sent[at] = entry_of(gr[r], vr[r]);
+            A.swt[at] = cr[r];
+            gmin = gr[r] < gmin ? gr[r] : gmin;
+            gmax = gr[r] > gmax ? gr[r] : gmax;
         }
-        __syncthreads();
-        for (int i = threadIdx.x; i < nslots; i += 256) {
-            if (!kSmall) keys[i] = -1;
-            lcnt[i] = 0;
-        }
-        __syncthreads();
     }
+    note_gains(A.ctr, gmin, gmax);
+}
+
+// The same for at most kDirectLabels labels: the segments' layout follows from
+// the candidate totals alone (a prefix sum over the labels), so every
+// workgroup computes it, claims and waits are not needed, and each workgroup
+// reserves its entries of a segment once, for a whole run of the colour.  With
+// claims and a reservation per 2048 entries, 500 workgroups adding to the same
+// 64 or 100 labels took 74-128 us a sub-round on R-MAT 2^21 and 2^24.
+__global__ void __launch_bounds__(256) admit_direct_kernel(Admission A) {
+    constexpr int kPer = kDirectLabels / 256;
+    __shared__ int32_t lcnt[kDirectLabels];
+    __shared__ int32_t lbase[kDirectLabels];  // first entry of the label's segment, -1: takes all its candidates
+    __shared__ unsigned long long s_wave[4];
+    if (stopped(A.gate)) return;  // uniform over the grid
+    const int tid = threadIdx.x;
+    // thread tid: labels kPer * tid ..
+    unsigned long long mine = 0;  // segments (high word) and their entries
+    Segment g[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        const int32_t t = kPer * tid + q;
+        g[q] = Segment{t, 0, 0, 0};
+        if (t >= A.nw) continue;
+        const unsigned long long a = A.acc[t << kAccShift];
+        if (a == 0) continue;
+        const int64_t room = bound_of(A.B, t) - static_cast<int64_t>(A.w[t]);
+        if (static_cast<int64_t>(a & 0xFFFFFFFFULL) <= room) continue;
+        g[q].len = static_cast<int32_t>(a >> 32);
+        g[q].room = static_cast<int32_t>(room);
+        mine += acc_of(1, g[q].len);
+    }
+    unsigned long long incl = mine;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long u = shfl_up_u64(incl, o);
+        if (lane_id() >= o) incl += u;
+    }
+    if (lane_id() == 63) s_wave[tid >> 6] = incl;
+    __syncthreads();
+    unsigned long long run = incl - mine, total = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        run += q < (tid >> 6) ? s_wave[q] : 0;
+        total += s_wave[q];
+    }
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+        g[q].base = static_cast<int32_t>(run & 0xFFFFFFFFULL);
+        lcnt[kPer * tid + q] = 0;
+        lbase[kPer * tid + q] = g[q].len ? g[q].base : -1;
+        if (g[q].len) {
+            if (blockIdx.x == 0) record_segment(A, static_cast<uint32_t>(run >> 32), g[q]);
+            run += acc_of(1, g[q].len);
+        }
+    }
+    if (blockIdx.x == 0 && tid == 0) A.ctr->segs = total;
+    __syncthreads();
+    // this workgroup's run of the colour, U entries per thread at a time
+    constexpr int U = 4;
+    const int64_t per = ((A.count + gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
+    const int64_t p_begin = blockIdx.x * per + tid;
+    const int64_t p_end = blockIdx.x * per + per < A.count ? blockIdx.x * per + per : A.count;
+    bool any = false;
+    for (int64_t p0 = p_begin; p0 < p_end; p0 += 256 * U) {
+        int32_t tr[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) tr[u] = p0 + u * 256 < p_end ? A.ct[p0 + u * 256] : -1;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (p0 + u * 256 >= p_end) continue;
+            const bool slow = tr[u] >= 0 && lbase[tr[u]] >= 0;
+            A.ok[p0 + u * 256] = tr[u] >= 0 && !slow ? 1 : 0;
+            if (slow) atomicAdd(&lcnt[tr[u]], 1);
+            any |= slow;
+        }
+    }
+    if (!__syncthreads_or(any)) return;
+    for (int j = tid; j < A.nw; j += 256) {
+        const int32_t c = lcnt[j];
+        if (c) lbase[j] += atomicAdd(&A.seg_fill[j << kFillShift], c);
+        lcnt[j] = 0;
+    }
+    __syncthreads();
+    int32_t gmin = INT_MAX, gmax = INT_MIN;
+    for (int64_t p0 = p_begin; p0 < p_end; p0 += 256 * U) {
+        int32_t tr[U], gr[U], vr[U], cr[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            tr[u] = p0 + u * 256 < p_end ? A.ct[p0 + u * 256] : -1;
+            if (tr[u] >= 0 && lbase[tr[u]] < 0) tr[u] = -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            gr[u] = tr[u] >= 0 ? A.cg[p0 + u * 256] : 0;
+            vr[u] = tr[u] >= 0 ? A.nodes[p0 + u * 256] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) cr[u] = tr[u] >= 0 ? (A.vw ? A.vw[vr[u]] : 1) : 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (tr[u] < 0) continue;
+            const int32_t at = lbase[tr[u]] + atomicAdd(&lcnt[tr[u]], 1);
+            A.sent[at] = entry_of(gr[u], vr[u]);
+            A.swt[at] = cr[u];
+            gmin = gr[u] < gmin ? gr[u] : gmin;
+            gmax = gr[u] > gmax ? gr[u] : gmax;
+        }
+    }
+    note_gains(A.ctr, gmin, gmax);
 }
 
 __device__ __forceinline__ int bits_of(uint64_t x) { return x ? 64 - __clzll(static_cast<long long>(x)) : 0; }
 
-__device__ __forceinline__ int64_t shfl_up_i64(int64_t v, int o) {
-    const uint32_t lo = __shfl_up(static_cast<uint32_t>(static_cast<uint64_t>(v)), o, 64);
-    const uint32_t hi = __shfl_up(static_cast<uint32_t>(static_cast<uint64_t>(v) >> 32), o, 64);
-    return static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo);
-}
-
-// One workgroup per overflowing target (grid-stride over the segments):
-// finds the smallest key whose inclusive weight prefix, in key order, exceeds
-// the target's room bound - w(t), by a most-significant-digit-first radix
-// selection on weight histograms, and stores it as the target's boundary:
-// every candidate with a smaller key is admitted (node weights are >= 0, so
-// that is exactly the admitted prefix).  Block 0 also keeps the sub-round's
-// gmax for the apply kernel.
-__global__ void __launch_bounds__(256) select_kernel(const int32_t* __restrict__ seg_list,
-                                                     int32_t* __restrict__ seg_off, int32_t* __restrict__ seg_fill,
-                                                     const int32_t* __restrict__ cnt, const int32_t* __restrict__ w,
-                                                     Bounds B, int bits_v, const uint64_t* __restrict__ skey,
-                                                     const int32_t* __restrict__ swt, uint64_t* __restrict__ bnd,
-                                                     int32_t small_max, Counters* ctr) {
-    __shared__ unsigned long long hist[256];
-    __shared__ uint64_t s_prefix, s_mask;
-    __shared__ int64_t s_room;
-    if (blockIdx.x == 0 && threadIdx.x == 0) ctr->gkey = ctr->gmax;
-    const uint32_t nseg = ctr->nseg;
-    const int total_bits = bits_of(static_cast<uint64_t>(static_cast<int64_t>(ctr->gmax) - ctr->gmin)) + bits_v;
-    const int passes = total_bits > 0 ? (total_bits + 7) / 8 : 1;
-    for (uint32_t sid = blockIdx.x; sid < nseg; sid += gridDim.x) {
-        const int32_t t = seg_list[sid];
-        const int32_t base = seg_off[t];
-        const int32_t len = cnt[t];
-        if (len > small_max) {  // selected by the multi-workgroup kernels, which keep their own copy of the range
-            if (threadIdx.x == 0) {
-                seg_off[t] = -1;
-                seg_fill[t] = 0;
-            }
-            continue;
-        }
-        if (threadIdx.x == 0) {
-            s_prefix = 0;
-            s_mask = 0;
-            s_room = bound_of(B, t) - static_cast<int64_t>(w[t]);
-        }
-        __syncthreads();
-        for (int pass = passes - 1; pass >= 0; --pass) {
-            const int shift = 8 * pass;
-            hist[threadIdx.x] = 0;
-            __syncthreads();
-            const uint64_t prefix = s_prefix, pmask = s_mask;
-            for (int32_t i = threadIdx.x; i < len; i += 256) {
-                const uint64_t k = skey[base + i];
-                const int32_t c = swt[base + i];
-                if ((k & pmask) == prefix && c) atomicAdd(&hist[(k >> shift) & 255], static_cast<unsigned long long>(c));
-            }
-            __syncthreads();
-            if (threadIdx.x < 64) {
-                // boundary digit: the first whose cumulative weight exceeds the
-                // room (digit 255 when none of 0..254 does); lane j holds digits
-                // 4j .. 4j+3
-                const int lane = threadIdx.x;
-                const int64_t room = s_room;
-                int64_t h[4], local = 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    h[q] = static_cast<int64_t>(hist[4 * lane + q]);
-                    local += h[q];
-                }
-                int64_t incl = local;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int64_t u = shfl_up_i64(incl, o);
-                    if (lane >= o) incl += u;
-                }
-                int64_t run = incl - local;
-                int d = 256;
-                int64_t rund = 0;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    if (d != 256) continue;
-                    if (run + h[q] > room) {
-                        d = 4 * lane + q;
-                        rund = run;
-                    } else {
-                        run += h[q];
-                    }
-                }
-                const int dmin = wave_min(d);
-                const bool mine = dmin == 256 ? lane == 63 : d == dmin;
-                if (mine) {
-                    const int dd = dmin == 256 ? 255 : dmin;
-                    const int64_t before = dmin == 256 ? incl - h[3] : rund;
-                    s_room = room - before;
-                    s_prefix = prefix | (static_cast<uint64_t>(dd) << shift);
-                    s_mask = pmask | (255ULL << shift);
-                }
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            bnd[t] = s_prefix;  // smallest key that does not fit
-            seg_off[t] = -1;
-            seg_fill[t] = 0;
-        }
-    }
+// Bits of the sub-round's keys: the gain range, then the node id.
+__device__ __forceinline__ int key_bits(const Counters* ctr, int bits_v) {
+    return bits_of(static_cast<uint64_t>(static_cast<int64_t>(ctr->gmax) - ctr->gmin)) + bits_v;
 }
 
 // Boundary digit of a histogram held as kPerT consecutive digits per thread
-// (hv, summing to local): the first digit whose cumulative weight exceeds
-// room (the last digit when none below it does); *s_d and *s_run (the weight
-// of the digits before it) are set for the whole block.
+// (hv): the first digit whose cumulative weight exceeds room (the last digit
+// when none below it does); *s_d and *s_run (the weight of the digits before
+// it) are set for the whole block.  Weights sum to at most 2^31 - 1.
 template <int NT, int kPerT>
-__device__ __forceinline__ void block_pick_digit(const int64_t* hv, int64_t local, int64_t room, int64_t* sc,
-                                                 int* s_d, int64_t* s_run) {
+__device__ __forceinline__ void block_pick_digit(const int32_t* hv, int32_t room, int32_t* s_wave, int* s_d,
+                                                 int32_t* s_run) {
     const int j = threadIdx.x;
-    sc[j] = local;
-    __syncthreads();
-    for (int o = 1; o < NT; o <<= 1) {  // inclusive scan
-        const int64_t add = j >= o ? sc[j - o] : 0;
-        __syncthreads();
-        sc[j] += add;
-        __syncthreads();
+    const int lane = lane_id();
+    int32_t local = 0;
+#pragma unroll
+    for (int q = 0; q < kPerT; ++q) local += hv[q];
+    int32_t incl = local;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t u = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += u;
     }
-    const int64_t incl = sc[j];
-    const int64_t excl = incl - local;
-    if (j == NT - 1) {  // no digit below the last one exceeds the room
-        *s_d = NT * kPerT - 1;
-        *s_run = incl - hv[kPerT - 1];
-    }
+    if (lane == 63) s_wave[j >> 6] = incl;
     __syncthreads();
-    // the digit where the admissible weight runs out (monotone: one thread)
-    if (incl > room && excl <= room) {
-        int64_t run = excl;
+    int32_t before = 0, total = 0;
+#pragma unroll
+    for (int q = 0; q < NT / 64; ++q) {
+        const int32_t x = s_wave[q];
+        before += q < (j >> 6) ? x : 0;
+        total += x;
+    }
+    incl += before;
+    const int32_t excl = incl - local;
+    // the digit where the admissible weight runs out (monotone: one thread),
+    // else the last digit
+    if (total <= room) {
+        if (j == NT - 1) {
+            *s_d = NT * kPerT - 1;
+            *s_run = incl - hv[kPerT - 1];
+        }
+    } else if (incl > room && excl <= room) {
+        int32_t run = excl;
         int d = kPerT * j + kPerT - 1;
         for (int q = 0; q < kPerT - 1; ++q) {
             if (run + hv[q] > room) {
@@ -1688,19 +1733,20 @@ __device__ __forceinline__ void block_pick_digit(const int64_t* hv, int64_t loca
 // waits for another).  Keys rarely need more digits than the host launches;
 // when they do, the last block of each segment in the final launch finishes
 // the remaining digits alone, over the whole segment.  After the last digit
-// the segment's boundary key is stored.
+// L.prefix holds the segment's boundary key.
 __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, int launch, int nlaunch, int bits_v,
-                                                                   const uint64_t* __restrict__ skey,
+                                                                   const uint64_t* __restrict__ sent,
                                                                    const int32_t* __restrict__ swt,
-                                                                   uint64_t* __restrict__ bnd, const Counters* ctr) {
+                                                                   const Counters* ctr) {
     constexpr int NT = kLargeThreads;
     constexpr int kPerT = kLBins / NT;
     constexpr int U = 4;
     __shared__ uint32_t h[kLBins];
-    __shared__ int64_t sc[NT];
+    __shared__ int32_t s_wave[NT / 64];
     __shared__ int s_last, s_d;
-    __shared__ int64_t s_run;
-    const int total_bits = bits_of(static_cast<uint64_t>(static_cast<int64_t>(ctr->gmax) - ctr->gmin)) + bits_v;
+    __shared__ int32_t s_run;
+    const int total_bits = key_bits(ctr, bits_v);
+    const int32_t gmax = ctr->gmax;
     const int passes = total_bits > 0 ? (total_bits + kLDigit - 1) / kLDigit : 1;
     const int pass = passes - 1 - launch;
     const uint32_t nlarge = ctr->nlarge;
@@ -1719,12 +1765,15 @@ __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, i
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int32_t x = i + u * NT;
-                k[u] = x < i1 ? skey[base + x] : 0;
+                k[u] = x < i1 ? sent[base + x] : 0;
                 wt[u] = x < i1 ? swt[base + x] : 0;
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if ((k[u] & ab) == prefix && wt[u]) atomicAdd(&h[(k[u] >> sh) & (kLBins - 1)], static_cast<uint32_t>(wt[u]));
+            for (int u = 0; u < U; ++u) {
+                const uint64_t key = key_of(k[u], gmax, bits_v);
+                if (wt[u] && (key & ab) == prefix)
+                    atomicAdd(&h[(key >> sh) & (kLBins - 1)], static_cast<uint32_t>(wt[u]));
+            }
         }
     };
     for (int32_t c = blockIdx.x; c < nch; c += gridDim.x) {
@@ -1756,15 +1805,13 @@ __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, i
         __syncthreads();
         if (s_last) {  // block-uniform
             // thread j holds digits kPerT*j .. kPerT*j + kPerT-1
-            int64_t hv[kPerT];
-            int64_t local = 0;
+            int32_t hv[kPerT];
 #pragma unroll
-            for (int q = 0; q < kPerT; ++q) {
-                hv[q] = __hip_atomic_load(&hl[kPerT * j + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                local += hv[q];
-            }
-            int64_t room = L.room[l];
-            block_pick_digit<NT, kPerT>(hv, local, room, sc, &s_d, &s_run);
+            for (int q = 0; q < kPerT; ++q)
+                hv[q] = static_cast<int32_t>(
+                    __hip_atomic_load(&hl[kPerT * j + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            int32_t room = L.room[l];
+            block_pick_digit<NT, kPerT>(hv, room, s_wave, &s_d, &s_run);
 #pragma unroll
             for (int q = 0; q < kPerT; ++q) hl[kPerT * j + q] = 0;
             uint64_t np = prefix | (static_cast<uint64_t>(s_d) << shift);
@@ -1777,13 +1824,9 @@ __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, i
                     __syncthreads();
                     accumulate(base, 0, len, np, ~0ULL << (sh + kLDigit), sh);
                     __syncthreads();
-                    local = 0;
 #pragma unroll
-                    for (int q = 0; q < kPerT; ++q) {
-                        hv[q] = h[kPerT * j + q];
-                        local += hv[q];
-                    }
-                    block_pick_digit<NT, kPerT>(hv, local, room, sc, &s_d, &s_run);
+                    for (int q = 0; q < kPerT; ++q) hv[q] = static_cast<int32_t>(h[kPerT * j + q]);
+                    block_pick_digit<NT, kPerT>(hv, room, s_wave, &s_d, &s_run);
                     np |= static_cast<uint64_t>(s_d) << sh;
                     room -= s_run;
                 }
@@ -1792,118 +1835,254 @@ __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, i
                 L.room[l] = room;
                 L.prefix[l] = np;
                 L.done[l] = 0;
-                if (pass == 0 || finish) bnd[L.target[l]] = np;  // smallest key that does not fit
             }
         }
         __syncthreads();
     }
 }
 
-// The per-sub-round counters back to their empty state (the round's
-// candidate count and the kept gmax are not touched).
+// The per-sub-round counters back to their empty state.
 __device__ __forceinline__ void clear_subround(Counters* ctr) {
-    ctr->ncand = 0;
-    ctr->nslow = 0;
+    ctr->segs = 0;
     ctr->gmin = INT_MAX;
     ctr->gmax = INT_MIN;
-    ctr->nseg = 0;
-    ctr->slow_total = 0;
     ctr->nlarge = 0;
     ctr->nlchunks = 0;
 }
 
-// Decides the slow candidates from their targets' boundary keys, moves the
-// admitted candidates and updates the label weights; also clears the
-// per-target candidate sums and counts and the sub-round counters for the
-// next sub-round (no kernel of this one reads them any more).
+// Moves node v (weight c) to label t.  The departure goes to delta (LDS, small
+// label spaces) or to the label's weight; the caller books the arrivals.
 template <bool kSmall>
-__global__ void __launch_bounds__(256) apply_kernel(const int32_t* __restrict__ ct, uint8_t* __restrict__ ok,
-                                                    const int32_t* __restrict__ nodes, int32_t count,
-                                                    const int32_t* __restrict__ cg, int bits_v,
-                                                    const uint64_t* __restrict__ bnd,
-                                                    const int32_t* __restrict__ vw, int32_t* __restrict__ label,
-                                                    uint8_t* __restrict__ label8, uint16_t* __restrict__ label16,
-                                                    int32_t* __restrict__ w, int32_t* __restrict__ tsum,
-                                                    int32_t* __restrict__ cnt, int32_t nw, Counters* ctr,
-                                                    const uint32_t* __restrict__ gate) {
-    __shared__ int32_t delta[kSmall ? kSmallLabels : 1];
-    const int32_t gkey = ctr->gkey;
-    if (blockIdx.x == 0) {
-        if (threadIdx.x == 0) clear_subround(ctr);
-        if (kSmall)
-            for (int j = threadIdx.x; j < nw; j += 256) {
-                tsum[j] = 0;
-                cnt[j] = 0;
-            }
+__device__ __forceinline__ void depart_and_move(const Admission& A, int32_t v, int32_t a, int32_t t, int32_t c,
+                                                int32_t* delta) {
+    A.label[v] = t;
+    if (A.label8) A.label8[v] = static_cast<uint8_t>(t);
+    if (A.label16) A.label16[v] = static_cast<uint16_t>(t);
+    if (c) {
+        if (kSmall) atomicSub(&delta[a], c);
+        else atomicSub(&A.w[a], c);
     }
-    if (stopped(gate)) return;  // uniform over the grid
+}
+
+template <bool kSmall>
+__device__ __forceinline__ void arrive(const Admission& A, int32_t t, int32_t c, int32_t* delta) {
+    if (!c) return;
+    if (kSmall) atomicAdd(&delta[t], c);
+    else atomicAdd(&A.w[t], c);
+}
+
+constexpr int kFinishThreads = 1024;
+constexpr int kFinishMax = 65536;  // longest segment one workgroup of finish_kernel selects from
+constexpr int kFinishBlocks = 256;
+// small label spaces: every workgroup adds to the same few lines of weights
+constexpr int kFinishBlocksSmall = 96;
+
+// Moves the admitted candidates, and selects and moves the admitted prefix of
+// every segment of up to small_max entries: the entries whose inclusive
+// weight prefix in key order stays within the target's room (node weights are
+// >= 0, so those are exactly the ones below the first that does not fit).
+// Up to 64 entries: one wave, every lane sums the entries not above its own.
+// Longer ones: the workgroup finds the boundary key most significant digit
+// first, 12 bits at a time, in an LDS histogram, and moves what is below it.
+// Segments hold 2-50 entries in most sub-rounds and thousands in the first
+// ones; one launch for all lengths replaced a scatter, a selection and an
+// apply launch of about 5 us each.
+template <bool kSmall>
+__global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A) {
+    constexpr int NT = kFinishThreads;
+    constexpr int kPerT = kLBins / NT;
+    __shared__ uint32_t hist[kLBins];
+    __shared__ int32_t delta[kSmall ? kSmallLabels : 1];
+    __shared__ int32_t s_wave[NT / 64];
+    __shared__ int s_d;
+    __shared__ int32_t s_run;
+    if (stopped(A.gate)) return;  // uniform over the grid: nothing was counted either
+    const int tid = threadIdx.x;
+    const int lane = lane_id();
+    if (blockIdx.x == 0 && tid == 0) clear_subround(A.ctr_next);
     if (kSmall) {
-        for (int j = threadIdx.x; j < nw; j += 256) delta[j] = 0;
+        for (int j = tid; j < A.nw; j += NT) delta[j] = 0;
         __syncthreads();
     }
-    // U grid-stride positions per thread at a time: their loads are issued
-    // together, level by level, before the updates
-    constexpr int U = 4;
-    const int32_t stride = gridDim.x * 256;
-    for (int32_t p0 = blockIdx.x * 256 + threadIdx.x; p0 < count; p0 += stride * U) {
-        int32_t tq[U], vq[U], aq[U], cq[U];
-        uint8_t oq[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t p = p0 + u * stride;
-            tq[u] = p < count ? ct[p] : -1;
+    const uint32_t nseg = static_cast<uint32_t>(A.ctr->segs >> 32);
+    const int32_t gmax = A.ctr->gmax;
+    // segments of up to 64 entries, one wave each (bookkeeping of the others)
+    for (uint32_t sid = blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane(tid >> 6); sid < nseg;
+         sid += gridDim.x * (NT / 64)) {
+        const Segment sg = A.seg[sid];
+        if (lane == 0) {
+            if (A.seg_off) A.seg_off[sg.t] = -1;
+            A.seg_fill[sg.t << A.fill_shift] = 0;
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t p = p0 + u * stride;
-            oq[u] = tq[u] >= 0 ? ok[p] : 0;
-            vq[u] = tq[u] >= 0 ? nodes[p] : 0;
+        if (sg.len > 64 || sg.len > A.small_max) continue;
+        const uint64_t e = lane < sg.len ? A.sent[sg.base + lane] : 0;
+        const int32_t c = lane < sg.len ? A.swt[sg.base + lane] : 0;
+        const int32_t v = node_of(e);
+        const int32_t a = lane < sg.len ? A.label[v] : 0;
+        const uint64_t k = key_of(e, gmax, A.bits_v);
+        int32_t incl = 0;
+        for (int j = 0; j < sg.len; ++j) {
+            const uint32_t klo = __builtin_amdgcn_readlane(static_cast<uint32_t>(k), j);
+            const uint32_t khi = __builtin_amdgcn_readlane(static_cast<uint32_t>(k >> 32), j);
+            const int32_t cj = static_cast<int32_t>(__builtin_amdgcn_readlane(static_cast<uint32_t>(c), j));
+            incl += ((static_cast<uint64_t>(khi) << 32) | klo) <= k ? cj : 0;
         }
+        const bool in = lane < sg.len && incl <= sg.room;
+        if (in) depart_and_move<kSmall>(A, v, a, sg.t, c, delta);
+        const int32_t sum = wave_sum(in ? c : 0);
+        if (lane == 0) arrive<kSmall>(A, sg.t, sum, delta);
+    }
+    // longer ones, one workgroup each
+    const int total_bits = key_bits(A.ctr, A.bits_v);
+    const int passes = total_bits > 0 ? (total_bits + kLDigit - 1) / kLDigit : 1;
+    for (uint32_t sid = blockIdx.x; sid < nseg; sid += gridDim.x) {
+        const Segment sg = A.seg[sid];
+        if (sg.len <= 64 || sg.len > A.small_max) continue;  // uniform over the workgroup
+        // the first entry per thread stays in registers over the passes
+        const uint64_t e0 = tid < sg.len ? A.sent[sg.base + tid] : 0;
+        const int32_t c0 = tid < sg.len ? A.swt[sg.base + tid] : 0;
+        const uint64_t k0 = key_of(e0, gmax, A.bits_v);
+        uint64_t np = 0;
+        int32_t room = sg.room;
+        for (int pass = passes - 1; pass >= 0; --pass) {
+            const int sh = kLDigit * pass;
+            const uint64_t above = sh + kLDigit >= 64 ? 0ULL : ~0ULL << (sh + kLDigit);
+            for (int q = tid; q < kLBins; q += NT) hist[q] = 0;
+            __syncthreads();
+            if (c0 && (k0 & above) == np) atomicAdd(&hist[(k0 >> sh) & (kLBins - 1)], static_cast<uint32_t>(c0));
+            constexpr int U = 4;
+            for (int32_t i = tid + NT; i < sg.len; i += NT * U) {
+                uint64_t e[U];
+                int32_t c[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t p = p0 + u * stride;
-            if (oq[u] == kOkSlow) {
-                const uint64_t key = (static_cast<uint64_t>(static_cast<int64_t>(gkey) - cg[p]) << bits_v) |
-                                     static_cast<uint64_t>(static_cast<uint32_t>(vq[u]));
-                oq[u] = key < bnd[tq[u]] ? 1 : 0;
-                ok[p] = oq[u];
-            }
-        }
+                for (int u = 0; u < U; ++u) {
+                    const int32_t x = i + u * NT;
+                    e[u] = x < sg.len ? A.sent[sg.base + x] : 0;
+                    c[u] = x < sg.len ? A.swt[sg.base + x] : 0;
+                }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            aq[u] = oq[u] ? label[vq[u]] : 0;
-            cq[u] = oq[u] ? (vw ? vw[vq[u]] : 1) : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t t = tq[u];
-            if (t < 0) continue;
-            if (!kSmall) {
-                tsum[t] = 0;
-                cnt[t] = 0;
-            }
-            if (!oq[u]) continue;
-            const int32_t v = vq[u];
-            const int32_t a = aq[u];
-            const int32_t c = cq[u];
-            label[v] = t;
-            if (label8) label8[v] = static_cast<uint8_t>(t);
-            if (label16) label16[v] = static_cast<uint16_t>(t);
-            if (c) {
-                if (kSmall) {
-                    atomicAdd(&delta[t], c);
-                    atomicSub(&delta[a], c);
-                } else {
-                    atomicAdd(&w[t], c);
-                    atomicSub(&w[a], c);
+                for (int u = 0; u < U; ++u) {
+                    const uint64_t k = key_of(e[u], gmax, A.bits_v);
+                    if (c[u] && (k & above) == np)
+                        atomicAdd(&hist[(k >> sh) & (kLBins - 1)], static_cast<uint32_t>(c[u]));
                 }
             }
+            __syncthreads();
+            int32_t hv[kPerT];
+#pragma unroll
+            for (int q = 0; q < kPerT; ++q) hv[q] = static_cast<int32_t>(hist[kPerT * tid + q]);
+            block_pick_digit<NT, kPerT>(hv, room, s_wave, &s_d, &s_run);
+            np |= static_cast<uint64_t>(s_d) << sh;
+            room -= s_run;
+            __syncthreads();  // s_d, s_run and hist are written again by the next pass
+        }
+        int32_t sum = 0;
+        for (int32_t i = tid; i < sg.len; i += NT) {
+            const uint64_t e = i == tid ? e0 : A.sent[sg.base + i];
+            if (key_of(e, gmax, A.bits_v) >= np) continue;
+            const int32_t c = i == tid ? c0 : A.swt[sg.base + i];
+            const int32_t v = node_of(e);
+            depart_and_move<kSmall>(A, v, A.label[v], sg.t, c, delta);
+            sum += c;
+        }
+        sum = wave_sum(sum);
+        if (lane == 0) arrive<kSmall>(A, sg.t, sum, delta);
+    }
+    // admitted candidates, U grid-stride positions per thread at a time: their
+    // loads are issued together, level by level, before the updates
+    constexpr int U = 4;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * NT;
+    for (int64_t p0 = static_cast<int64_t>(blockIdx.x) * NT + tid; p0 < A.count; p0 += stride * U) {
+        int32_t tq[U], vq[U], aq[U], cq[U];
+        bool oq[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t p = p0 + u * stride;
+            tq[u] = p < A.count ? A.ct[p] : -1;
+            oq[u] = p < A.count && A.ok[p];
+            vq[u] = p < A.count ? A.nodes[p] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            aq[u] = oq[u] ? A.label[vq[u]] : 0;
+            cq[u] = oq[u] ? (A.vw ? A.vw[vq[u]] : 1) : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (tq[u] < 0) continue;
+            A.acc[tq[u] << A.acc_shift] = 0;
+            if (!oq[u]) continue;
+            depart_and_move<kSmall>(A, vq[u], aq[u], tq[u], cq[u], delta);
+            arrive<kSmall>(A, tq[u], cq[u], delta);
         }
     }
     if (kSmall) {
         __syncthreads();
-        for (int j = threadIdx.x; j < nw; j += 256)
-            if (delta[j]) atomicAdd(&w[j], delta[j]);
+        for (int j = tid; j < A.nw; j += NT)
+            if (delta[j]) atomicAdd(&A.w[j], delta[j]);
+    }
+}
+
+// Moves the admitted prefix of the segments selected by large_pass_kernel.
+template <bool kSmall>
+__global__ void __launch_bounds__(256) large_move_kernel(Admission A) {
+    __shared__ int32_t delta[kSmall ? kSmallLabels : 1];
+    if (A.ctr->nlarge == 0) return;  // uniform over the grid
+    if (kSmall) {
+        for (int j = threadIdx.x; j < A.nw; j += 256) delta[j] = 0;
+        __syncthreads();
+    }
+    const int32_t gmax = A.ctr->gmax;
+    const int32_t nch = static_cast<int32_t>(A.ctr->nlchunks);
+    constexpr int kParts = kSegChunk / 1024;  // a workgroup takes 1024 entries of a chunk at a time
+    for (int32_t cp = blockIdx.x; cp < nch * kParts; cp += gridDim.x) {
+        const int32_t c = cp / kParts;
+        const int32_t l = A.L.owner[c];
+        const int32_t base = A.L.base[l];
+        const int32_t i0 = (c - A.L.chunk0[l]) * kSegChunk + (cp % kParts) * 1024;
+        const int32_t i1 = min(i0 + 1024, A.L.len[l]);
+        const uint64_t end = A.L.prefix[l];
+        const int32_t t = A.L.target[l];
+        int32_t sum = 0;
+        for (int32_t i = i0 + static_cast<int32_t>(threadIdx.x); i < i1; i += 256) {
+            const uint64_t e = A.sent[base + i];
+            if (key_of(e, gmax, A.bits_v) >= end) continue;
+            const int32_t wt = A.swt[base + i];
+            const int32_t v = node_of(e);
+            depart_and_move<kSmall>(A, v, A.label[v], t, wt, delta);
+            sum += wt;
+        }
+        sum = wave_sum(sum);
+        if (lane_id() == 0) arrive<kSmall>(A, t, sum, delta);
+    }
+    if (kSmall) {
+        __syncthreads();
+        for (int j = threadIdx.x; j < A.nw; j += 256)
+            if (delta[j]) atomicAdd(&A.w[j], delta[j]);
+    }
+}
+
+// Admission state before the first sub-round: no candidates, no segments, no
+// large segments in progress, no candidates counted in any round.
+__global__ void __launch_bounds__(256) init_admission_kernel(unsigned long long* __restrict__ acc,
+                                                             int64_t acc_n, int32_t* __restrict__ seg_off,
+                                                             int64_t off_n, int32_t* __restrict__ seg_fill,
+                                                             int64_t fill_n,
+                                                             uint32_t* __restrict__ lhist, int64_t lhist_n,
+                                                             uint32_t* __restrict__ ldone, int64_t ldone_n,
+                                                             uint32_t* __restrict__ rcnt, int32_t rounds,
+                                                             Counters* ctr) {
+    const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
+    for (int64_t i = i0; i < acc_n; i += stride) acc[i] = 0;
+    for (int64_t i = i0; i < off_n; i += stride) seg_off[i] = -1;
+    for (int64_t i = i0; i < fill_n; i += stride) seg_fill[i] = 0;
+    for (int64_t i = i0; i < lhist_n; i += stride) lhist[i] = 0;
+    for (int64_t i = i0; i < ldone_n; i += stride) ldone[i] = 0;
+    for (int64_t i = i0; i < rounds; i += stride) rcnt[i] = 0;
+    if (i0 == 0) {
+        clear_subround(ctr);
+        clear_subround(ctr + 1);
     }
 }
 
@@ -1915,7 +2094,8 @@ __global__ void narrow_kernel(const int32_t* __restrict__ label, int32_t n, T* _
 
 // After a sub-round: every neighbour of a node that moved is no longer quiet.
 // One wave per 64 schedule positions; the wave walks each mover's row.
-__global__ void __launch_bounds__(256) unquiet_kernel(const int32_t* __restrict__ ct, const uint8_t* __restrict__ ok,
+__global__ void __launch_bounds__(256) unquiet_kernel(const int32_t* __restrict__ ct,
+                                                      const int32_t* __restrict__ label,
                                                       const int32_t* __restrict__ nodes, int32_t count,
                                                       const int64_t* __restrict__ xadj,
                                                       const int32_t* __restrict__ adj, uint8_t* __restrict__ quiet,
@@ -1925,7 +2105,8 @@ __global__ void __launch_bounds__(256) unquiet_kernel(const int32_t* __restrict_
     const int64_t base = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) & ~63LL;
     const int lane = lane_id();
     const int64_t p = base + lane;
-    const bool mover = p < count && ct[p] >= 0 && ok[p];
+    // a candidate that holds its target label now (its own differed before)
+    const bool mover = p < count && ct[p] >= 0 && label[nodes[p]] == ct[p];
     uint64_t m = __ballot(mover);
     while (m) {
         const int i = __ffsll(static_cast<long long>(m)) - 1;
@@ -1935,8 +2116,6 @@ __global__ void __launch_bounds__(256) unquiet_kernel(const int32_t* __restrict_
         for (int64_t j = xadj[u] + lane; j < e; j += 64) quiet[adj[j]] = 0;
     }
 }
-
-__global__ void reset_counters_kernel(Counters* ctr) { clear_subround(ctr); }
 
 // --------------------------------------------------------------- schedule
 
@@ -2293,10 +2472,10 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     DBuf<uint32_t> order(n, s), order_tmp(n, s);
     DBuf<uint32_t> cat_count(ncat + 1, s);
     DBuf<unsigned long long> cat_slots(ncat + 1, s);
-    DBuf<Counters> ctr(1, s);
+    DBuf<Counters> ctr(2, s);
     fill_u32(cat_count.get(), 0, ncat + 1, s);
     HIPCHK(hipMemsetAsync(cat_slots.get(), 0, (ncat + 1) * sizeof(unsigned long long), s));
-    HIPCHK(hipMemsetAsync(ctr.get(), 0, sizeof(Counters), s));
+    HIPCHK(hipMemsetAsync(ctr.get(), 0, 2 * sizeof(Counters), s));
     const uint64_t hc = hash_prefix({seed, 1, static_cast<uint64_t>(static_cast<uint32_t>(level)),
                                      static_cast<uint64_t>(static_cast<uint32_t>(phase))});
     const uint64_t lvl64 = static_cast<uint64_t>(static_cast<uint32_t>(level));
@@ -2446,40 +2625,44 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     int64_t max_color = 0;
     for (int32_t sc = 0; sc < nsub; ++sc) max_color = std::max(max_color, off[(sc + 1) * kNB] - off[sc * kNB]);
     const int64_t cap = std::max<int64_t>(max_color, 1);
-    DBuf<int32_t> ct(cap, s), cg(cap, s), tsum(nw, s), tcnt(nw, s), seg_off(nw, s), seg_fill(nw, s);
-    DBuf<int32_t> seg_list(std::min<int64_t>(cap, nw), s), swt(cap, s);
+    const bool direct = nw <= kDirectLabels;
+    const int64_t acc_n = static_cast<int64_t>(nw) << (direct ? kAccShift : 0);
+    const int64_t fill_n = static_cast<int64_t>(nw) << (direct ? kFillShift : 0);
+    DBuf<int32_t> ct(cap, s), cg(cap, s), seg_off(direct ? 0 : nw, s), seg_fill(fill_n, s), swt(cap, s);
+    DBuf<unsigned long long> acc(acc_n, s);
+    DBuf<Segment> seg(std::min<int64_t>(cap, nw), s);
     DBuf<uint8_t> ok(cap, s);
-    DBuf<uint32_t> slow_idx(cap, s);
-    DBuf<uint64_t> skey(cap, s);
-    // multi-workgroup selection state: at most cap / kSmallSeg large segments
-    const int32_t small_max = std::max(1, std::min(tune.select_small_max, kSmallSeg));
-    const int64_t max_large = cap / small_max + 1;
-    const int64_t max_lchunks = cap / kSegChunk + max_large;
+    DBuf<uint64_t> sent(cap, s);
+    // segments longer than small_max are selected by several workgroups.  By
+    // default a colour of up to kFinishMax nodes leaves every segment to one
+    // workgroup and launches no further kernel (three to four launches of
+    // 2 us each, against 20-80 us in the first sub-rounds, whose segments
+    // alone are that long); larger colours split segments over kSmallSeg.
+    const int32_t small_max = tune.select_small_max > 0 ? std::min(tune.select_small_max, kFinishMax)
+                              : cap <= kFinishMax       ? kFinishMax
+                                                        : kSmallSeg;
+    const bool use_large = cap > small_max;
+    const int64_t max_large = use_large ? cap / small_max + 1 : 0;
+    const int64_t max_lchunks = use_large ? cap / kSegChunk + max_large : 0;
     DBuf<int32_t> ltarget(max_large, s), lbase(max_large, s), llen(max_large, s), lchunk0(max_large, s);
     DBuf<int32_t> lowner(max_lchunks, s);
     DBuf<uint32_t> lhist(max_large * kLBins, s);
     DBuf<uint64_t> lprefix(max_large, s);
-    DBuf<int64_t> lroom(max_large, s);
+    DBuf<int32_t> lroom(max_large, s);
     DBuf<uint32_t> ldone(max_large, s);
-    fill_u32(lhist.get(), 0, max_large * kLBins, s);
-    fill_u32(ldone.get(), 0, max_large, s);
-    LargeSel LS{ltarget.get(), lbase.get(), llen.get(), lchunk0.get(), lowner.get(), lhist.get(), lprefix.get(),
-                lroom.get(),
-                ldone.get()};
-    // digits of the selection key: node id bits plus at most 32 bits of gain range
     // launches of the multi-workgroup selection: enough digits for node ids
-    // plus a 12-bit gain range; wider keys finish in the last launch
+    // plus a 12-bit gain range; wider keys (node id bits plus at most 32 bits
+    // of gain range) finish in the last launch
     const int max_launches = (bits_for(static_cast<uint64_t>(n - 1)) + 32 + kLDigit - 1) / kLDigit;
     const int sel_launches =
         tune.select_launches > 0
             ? std::min(tune.select_launches, max_launches)
             : std::min(max_launches, (bits_for(static_cast<uint64_t>(n - 1)) + 12 + kLDigit - 1) / kLDigit);
-    // boundary key of every target that cannot take all its candidates
-    DBuf<uint64_t> bnd(nw, s);
-    fill_i32(tsum.get(), 0, nw, s);
-    fill_i32(tcnt.get(), 0, nw, s);
-    fill_i32(seg_off.get(), -1, nw, s);
-    fill_i32(seg_fill.get(), 0, nw, s);
+    DBuf<uint32_t> rcnt(std::max(rounds, 1), s);  // candidates per round, read back one round late (see stopped())
+    init_admission_kernel<<<capped_grid(std::max<int64_t>(fill_n, max_large * kLBins)), 256, 0, s>>>(
+        acc.get(), acc_n, seg_off.get(), direct ? 0 : nw, seg_fill.get(), fill_n, lhist.get(), max_large * kLBins, ldone.get(), max_large,
+        rcnt.get(), rounds, ctr.get());
+    LAUNCHCHK();
 
     EvalArgs A;
     A.xadj = g.xadj;
@@ -2543,14 +2726,9 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     auto eval_bytes = [&](int64_t nodes_in, unsigned long long slots_in) {
         return node_bytes * static_cast<double>(nodes_in) + slot_bytes * static_cast<double>(slots_in);
     };
-    reset_counters_kernel<<<1, 1, 0, s>>>(ctr.get());
-    LAUNCHCHK();
     const int bits_v = bits_for(static_cast<uint64_t>(n - 1));
     EvalStreams& evs = eval_streams();
 
-    // candidates per round, read back one round late (see stopped())
-    DBuf<uint32_t> rcnt(std::max(rounds, 1), s);
-    fill_u32(rcnt.get(), 0, std::max(rounds, 1), s);
     A.rcnt = rcnt.get();
     uint32_t* hrc = host_round_counts(rounds);
     RoundEvents& rev = round_events();
@@ -2577,6 +2755,31 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     const hipStream_t caller = s;
     if (capture) s = capture_stream();
     GraphCapture rounds_graph(s, caller, capture);
+
+    Admission M;
+    M.ct = ct.get();
+    M.cg = cg.get();
+    M.vw = g.vw;
+    M.w = w;
+    M.nw = nw;
+    M.acc = acc.get();
+    M.B = BB;
+    M.ok = ok.get();
+    M.seg_off = seg_off.get();
+    M.seg_fill = seg_fill.get();
+    M.seg = seg.get();
+    M.sent = sent.get();
+    M.swt = swt.get();
+    M.L = LargeSel{ltarget.get(), lbase.get(), llen.get(),    lchunk0.get(), lowner.get(),
+                   lhist.get(),   lprefix.get(), lroom.get(), ldone.get()};
+    M.small_max = small_max;
+    M.acc_shift = direct ? kAccShift : 0;
+    M.fill_shift = direct ? kFillShift : 0;
+    M.bits_v = bits_v;
+    M.label = label;
+    M.label8 = lab8.get();
+    M.label16 = lab16.get();
+    int32_t step = 0;  // sub-rounds enqueued: they use the two counter sets in turn
 
     for (int32_t r = 0; r < rounds && !halted; ++r) {
         const uint32_t* gate = r > 0 ? rcnt.get() + (r - 1) : nullptr;
@@ -2749,77 +2952,72 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             }
             if (side) evs.join(s);
 
-            // colours below 2^16 entries: one entry per thread and pass, so
-            // that every workgroup of the grid has work; larger ones keep
-            // several loads in flight per thread
-            const bool fine = ccount < (1 << 16);
-            // per-target candidate weight and count, then admission: targets
-            // that can take all their candidates admit them; the others
-            // select the admitted prefix on the device
+            // Entries per thread of the accumulating and admitting kernels: one
+            // up to 2^16 entries, so that a small colour still has a workgroup
+            // per 256 entries; more above, so that at most some 500 workgroups
+            // add to the same counters and each thread has several loads in
+            // flight.
+            M.nodes = cnodes;
+            M.count = static_cast<int32_t>(ccount);
+            M.ctr = ctr.get() + (step & 1);
+            M.ctr_next = ctr.get() + (~step & 1);
+            M.gate = gate;
+            ++step;
+            const int per = ccount <= (1 << 16) ? 1 : (ccount <= (1 << 18) ? 4 : 8);
+            const unsigned gc = static_cast<unsigned>(std::min<int64_t>(grid_for(ccount, 256 * per), kMaxBlocks));
             {
                 ProfScope ps(A.refine ? "lp_refine_admit" : "lp_admit", 0, s);
-                const unsigned gc = capped_grid(ccount);
-                auto accum = small ? (fine ? cand_accum_kernel<true, 1> : cand_accum_kernel<true, kAggChunk / 256>)
-                                   : (fine ? cand_accum_kernel<false, 1> : cand_accum_kernel<false, kAggChunk / 256>);
-                accum<<<gc, 256, 0, s>>>(ct.get(), cnodes, ccount, g.vw, tsum.get(), tcnt.get(), nw, ctr.get(), gate,
-                                         rcnt.get() + r);
+                auto accum = direct ? (per == 1   ? accumulate_kernel<true, 1>
+                                       : per == 4 ? accumulate_kernel<true, 4>
+                                                  : accumulate_kernel<true, 8>)
+                                    : (per == 1   ? accumulate_kernel<false, 1>
+                                       : per == 4 ? accumulate_kernel<false, 4>
+                                                  : accumulate_kernel<false, 8>);
+                accum<<<gc, 256, 0, s>>>(ct.get(), cnodes, M.count, g.vw, acc.get(), nw, gate, rcnt.get() + r);
                 LAUNCHCHK();
-                auto admit = small ? (fine ? admit_kernel<true, 1> : admit_kernel<true, 16>)
-                                   : (fine ? admit_kernel<false, 1> : admit_kernel<false, 16>);
-                admit<<<gc, 256, 0, s>>>(ct.get(), cg.get(), ccount, w, tsum.get(), tcnt.get(), BB, ok.get(),
-                                         slow_idx.get(), seg_off.get(), seg_list.get(), LS, small_max, nw, ctr.get(),
-                                         gate);
+                auto admit = direct     ? admit_direct_kernel
+                             : per == 1 ? admit_kernel<1>
+                             : per == 4 ? admit_kernel<4>
+                                        : admit_kernel<8>;
+                admit<<<std::min(gc, direct ? 256u : gc), 256, 0, s>>>(M);
                 LAUNCHCHK();
-            }
-            {
-                ProfScope ps(A.refine ? "lp_refine_admit_select" : "lp_admit_select", 0, s);
-                const unsigned gc = capped_grid(ccount);
-                auto scatter = small ? (fine ? scatter_kernel<true, 1> : scatter_kernel<true, kAggChunk / 256>)
-                                     : (fine ? scatter_kernel<false, 1> : scatter_kernel<false, kAggChunk / 256>);
-                scatter<<<gc, 256, 0, s>>>(slow_idx.get(), cnodes, ct.get(), cg.get(), g.vw, bits_v, nw, seg_off.get(),
-                                           seg_fill.get(), skey.get(), swt.get(), ctr.get());
-                LAUNCHCHK();
-                select_kernel<<<kMaxBlocks, 256, 0, s>>>(seg_list.get(), seg_off.get(), seg_fill.get(), tcnt.get(), w,
-                                                         BB, bits_v, skey.get(), swt.get(), bnd.get(), small_max,
-                                                         ctr.get());
-                LAUNCHCHK();
-                // a target has at most ccount candidates: no large segment
-                // unless the colour has more than the single-workgroup limit
-                if (ccount > small_max) {
-                    for (int launch = 0; launch < sel_launches; ++launch) {
-                        large_pass_kernel<<<kLargeBlocks, kLargeThreads, 0, s>>>(
-                            LS, launch, sel_launches, bits_v, skey.get(), swt.get(), bnd.get(), ctr.get());
-                        LAUNCHCHK();
-                    }
-                }
             }
             if (trace) {
-                HIPCHK(hipMemcpyAsync(hctr, ctr.get(), sizeof(Counters), hipMemcpyDeviceToHost, s));
+                HIPCHK(hipMemcpyAsync(hctr, M.ctr, sizeof(Counters), hipMemcpyDeviceToHost, s));
+                HIPCHK(hipMemcpyAsync(hrc + r, rcnt.get() + r, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
                 HIPCHK(hipStreamSynchronize(s));
-                fprintf(stderr, "[sclap] %s L%d r%d s%d n=%lld cand=%u slow=%u targets=%u gain=[%d,%d] hubs=%d\n",
+                const uint32_t slow = static_cast<uint32_t>(hctr->segs);
+                fprintf(stderr, "[sclap] %s L%d r%d s%d n=%lld round cand=%u slow=%u targets=%u gain=[%d,%d] hubs=%d\n",
                         phase != kCluster ? "refine" : "cluster", level, r, sc, static_cast<long long>(ccount),
-                        hctr->ncand, hctr->nslow, hctr->nseg, hctr->nslow ? hctr->gmin : 0,
-                        hctr->nslow ? hctr->gmax : 0, plans[sc].count);
+                        hrc[r], slow, static_cast<uint32_t>(hctr->segs >> 32), slow ? hctr->gmin : 0,
+                        slow ? hctr->gmax : 0, plans[sc].count);
             }
             {
                 ProfScope ps("lp_apply", 0, s);
-                if (small) {
-                    apply_kernel<true><<<capped_grid(ccount), 256, 0, s>>>(ct.get(), ok.get(), cnodes, ccount,
-                                                                           cg.get(), bits_v, bnd.get(), g.vw, label,
-                                                                           lab8.get(), lab16.get(), w, tsum.get(),
-                                                                           tcnt.get(), nw, ctr.get(), gate);
-                    LAUNCHCHK();
-                } else {
-                    apply_kernel<false><<<grid_for(ccount, 256), 256, 0, s>>>(ct.get(), ok.get(), cnodes, ccount,
-                                                                              cg.get(), bits_v, bnd.get(), g.vw, label,
-                                                                              lab8.get(), lab16.get(), w, tsum.get(),
-                                                                              tcnt.get(), nw, ctr.get(), gate);
+                // at least 64 workgroups, whose waves share the short segments
+                const unsigned gf = static_cast<unsigned>(
+                    std::min<int64_t>(std::max<int64_t>(grid_for(ccount, kFinishThreads), 64),
+                                      small ? kFinishBlocksSmall : kFinishBlocks));
+                if (small) finish_kernel<true><<<gf, kFinishThreads, 0, s>>>(M);
+                else finish_kernel<false><<<gf, kFinishThreads, 0, s>>>(M);
+                LAUNCHCHK();
+            }
+            // a target has at most ccount candidates: no longer segment
+            // unless the colour has more than the single-workgroup limit
+            if (ccount > small_max) {
+                ProfScope ps(A.refine ? "lp_refine_admit_select" : "lp_admit_select", 0, s);
+                for (int launch = 0; launch < sel_launches; ++launch) {
+                    large_pass_kernel<<<kLargeBlocks, kLargeThreads, 0, s>>>(M.L, launch, sel_launches, bits_v,
+                                                                             sent.get(), swt.get(), M.ctr);
                     LAUNCHCHK();
                 }
+                if (small) large_move_kernel<true><<<kMaxBlocks, 256, 0, s>>>(M);
+                else large_move_kernel<false><<<kMaxBlocks, 256, 0, s>>>(M);
+                LAUNCHCHK();
             }
             if (A.quiet) {
                 ProfScope ps("lp_unquiet", 0, s);
-                unquiet_kernel<<<grid_for(ccount, 256), 256, 0, s>>>(ct.get(), ok.get(), cnodes,
+                unquiet_kernel<<<grid_for(ccount, 256), 256, 0, s>>>(ct.get(), label, cnodes,
                                                                       static_cast<int32_t>(ccount), g.xadj, g.adj,
                                                                       A.quiet, gate, rcnt.get(), r, n);
                 LAUNCHCHK();
