@@ -999,7 +999,7 @@ LPTuning autotune(const DevGraph& g_in, int32_t k, const Opts& o, hipStream_t s)
     // searched as well; the capture choice decides whether the rounds run as
     // one HIP graph.  A value is taken only if it is at least 3 % faster than
     // the current best.
-    best.lane_max = 16;
+    best.lane_max = default_lane_max(g.n);
     best.wave_max = 256;
     best.block_max = 8192;
     best.block_table = 10240;
@@ -1020,7 +1020,7 @@ LPTuning autotune(const DevGraph& g_in, int32_t k, const Opts& o, hipStream_t s)
     try_values(&LPTuning::capture, {1, -1});
     try_values(&LPTuning::block_max, {1024, 2048, 4096});
     try_values(&LPTuning::wave_max, {32, 64, 128});
-    try_values(&LPTuning::lane_max, {4, 8});
+    try_values(&LPTuning::lane_max, {4, 8, 16});
     try_values(&LPTuning::block_table, {16384});
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

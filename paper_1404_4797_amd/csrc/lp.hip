@@ -13,15 +13,18 @@
 // thread order.
 //
 // Node evaluation is bucketed by degree:
-//   lane   one lane per node, neighbour labels kept in registers (deg <= 16)
-//   wave   one wave64 per node, open-addressing table in LDS (deg <= 256)
-//   block  one workgroup per node with an LDS table of 16, 64 or 128 KB
+//   lane   one lane per node, neighbour labels kept in registers (deg <= 16;
+//          deg <= 4 on small graphs)
+//   group  16, 32 or 64 lanes per node, open-addressing table in LDS (deg <= 256)
+//   block  one workgroup per node with an LDS table of 16, 64 or 80 KB
 //          (deg <= 1024, 4096, 8192)
-//   hub    the row is cut into 8192-slot chunks; each workgroup sums its
+//   hub    the row is cut into 4096-slot chunks; each workgroup sums its
 //          chunk in an LDS table and appends the chunk's distinct labels to
-//          the hub's entry list; one workgroup per hub then sums that list in
-//          LDS, or, when it is longer than 8192 entries, through an
-//          open-addressing table in HBM that a further pass scans
+//          lists by label partition; one workgroup per partition then sums its
+//          list in LDS, and the launch that counts the candidates picks the
+//          best partition winner
+// Large colours launch the buckets side by side on three streams; small ones
+// run them in one launch, or two where rows need a table over 16 KB.
 // The per-node connection table maps a neighbour label to the summed weight
 // of the edges to it (Section 4.1 uses hashing with linear probing for this).
 //
@@ -61,8 +64,8 @@ constexpr int kBlock2Max = 4096;  // 512 threads, 64 KB table
 constexpr int kHubTable = 8192;          // LDS table of a hub chunk workgroup (64 KB: two per CU)
 constexpr int kHubChunk = kHubTable / 2; // slots per hub workgroup (table load <= 1/2)
 constexpr int kHubDenseChunk = 8192;     // slots per hub workgroup with dense block arrays
-constexpr int kHubTChunk = 4096;         // HBM table entries per scan workgroup
 constexpr int kSmallLabels = 4096;       // LDS-private histograms up to this many labels
+constexpr int kCountInEval = 1 << 14;    // colours up to this size count candidates while they evaluate
 constexpr int kMaxBlocks = 512;          // grid cap of the grid-stride candidate kernels
 constexpr int kSmallSeg = 16384;         // large colours: segments up to this length have one selecting workgroup
 constexpr int kSegChunk = 16384;         // entries per workgroup in the multi-workgroup selection
@@ -79,8 +82,17 @@ struct Counters {
     uint32_t pad;
 };
 
+// One schedule entry: a node and where its row lies.  Laid out in schedule
+// order, so that an evaluation reads 16 consecutive bytes per node instead of
+// the node id and then two offsets somewhere in xadj (one dependent load less
+// at the start of every evaluation).
+struct __align__(16) Row {
+    int64_t begin;
+    int32_t deg;
+    int32_t node;
+};
+
 struct EvalArgs {
-    const int64_t* xadj;
     const int32_t* adj;
     int64_t S;  // slots of the graph (bound of the vector loads of short rows)
     const int32_t* ew;
@@ -113,10 +125,14 @@ struct EvalArgs {
     // round without candidates the state is a fixed point and the evaluation
     // of the later rounds is skipped
     const uint32_t* gate;
-    const int32_t* nodes;  // schedule entries of this launch
+    const Row* rows;  // schedule entries of this launch
     int32_t count;
     int32_t* ct;  // per entry: target label or -1
     int32_t* cg;  // per entry: gain
+    // Candidate totals, counted as the results are stored (null: by a launch of
+    // their own, which sums in LDS first); entry of label t: t << acc_shift
+    unsigned long long* acc;
+    int32_t acc_shift;
 };
 
 // A round runs only while the previous one had candidates (gate: that
@@ -296,11 +312,38 @@ __device__ __forceinline__ bool eligible(const EvalArgs& A, int32_t x, int32_t c
     return static_cast<int64_t>(A.w[x]) + c <= kx.bound;
 }
 
+// Candidate total of a target: count in the high word, weight in the low one
+// (a label's weight never exceeds c(V) <= 2^31 - 1, so no carry).
+__device__ __forceinline__ unsigned long long acc_of(int32_t cnt, int32_t weight) {
+    return (static_cast<unsigned long long>(static_cast<uint32_t>(cnt)) << 32) | static_cast<uint32_t>(weight);
+}
+
+// The eligible labels of a table (or of a lane's registers) are looked at in
+// groups whose label weights are read together: one after the other, each
+// read's latency (some 0.7 us) bounded the evaluation of small colours.
+template <int U>
+__device__ __forceinline__ void consider_group(const EvalArgs& A, const Ctx& kx, const int32_t* x, const int32_t* conn,
+                                               int32_t c, int32_t own, bool over, Best& best, bool& blocked) {
+    int32_t wx[U];
+    bool need[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        blocked |= x[u] >= 0 && conn[u] > own;
+        // a move needs a positive gain unless the own block is overloaded
+        need[u] = x[u] >= 0 && (over || conn[u] > own) && (best.x < 0 || conn[u] >= best.conn);
+        wx[u] = need[u] ? A.w[x[u]] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        if (need[u] && (best.x < 0 || conn[u] >= best.conn) && static_cast<int64_t>(wx[u]) + c <= kx.bound)
+            best_consider(best, x[u], conn[u], kx);
+}
+
 // Decision for a node given its best eligible label (x, conn) and the
 // connection to its own label: a move needs a positive gain, or an overloaded
 // own block during refinement.
 __device__ __forceinline__ void store_result(const EvalArgs& A, int32_t i, int32_t x, int32_t conn, int32_t own,
-                                             bool over) {
+                                             bool over, int32_t c) {
     int32_t t = -1, gain = 0;
     if (x >= 0) {
         gain = conn - own;
@@ -308,6 +351,7 @@ __device__ __forceinline__ void store_result(const EvalArgs& A, int32_t i, int32
     }
     A.ct[i] = t;
     A.cg[i] = gain;
+    if (A.acc && t >= 0) atomicAdd(&A.acc[t << A.acc_shift], acc_of(1, c));
 }
 
 // True if v is quiet and may skip evaluation (its block is not overloaded).
@@ -347,6 +391,39 @@ __device__ __forceinline__ void table_add_sized(int32_t* keys, int32_t* vals, ui
             return;
         }
         h = h + 1 == tsz ? 0u : h + 1;
+    }
+}
+
+// Value of key x in such a table (0: absent; the table has a free entry or
+// holds x).
+template <bool kPow2>
+__device__ __forceinline__ int32_t table_find(const int32_t* keys, const int32_t* vals, uint32_t tsz, int32_t x) {
+    const uint32_t sh = slot_hash(static_cast<uint32_t>(x));
+    uint32_t h = kPow2 ? sh & (tsz - 1) : static_cast<uint32_t>((static_cast<uint64_t>(sh) * tsz) >> 32);
+    while (true) {
+        const int32_t k = keys[h];
+        if (k == x) return vals[h];
+        if (k == -1) return 0;
+        h = h + 1 == tsz ? 0u : h + 1;
+    }
+}
+
+// Looks at entries first, first + STEP, ... of a table of tsz entries, U at a
+// time, for the best eligible label other than a.
+template <int STEP, int U>
+__device__ __forceinline__ void scan_table(const EvalArgs& A, const Ctx& kx, const int32_t* keys, const int32_t* vals,
+                                           uint32_t tsz, uint32_t first, int32_t a, int32_t c, int32_t own, bool over,
+                                           Best& best, bool& blocked) {
+    for (uint32_t j0 = first; j0 < tsz; j0 += STEP * U) {
+        int32_t x[U], cn[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t j = j0 + u * STEP;
+            x[u] = j < tsz ? keys[j] : -1;
+            cn[u] = j < tsz ? vals[j] : 0;
+            if (x[u] == a) x[u] = -1;
+        }
+        consider_group<U>(A, kx, x, cn, c, own, over, best, blocked);
     }
 }
 
@@ -446,44 +523,44 @@ __device__ __forceinline__ void lane_row(const EvalArgs& A, int64_t b, int d, in
 template <int MAXD>
 __device__ __forceinline__ void eval_lane_body(const EvalArgs& A, int32_t bid) {
     const int i = bid * 256 + threadIdx.x;
-    if (i >= A.count || stopped(A.gate)) return;
+    if (i >= A.count) return;
+    const Row row = A.rows[i];
+    if (stopped(A.gate)) return;
     const int qm = quiet_mode(A);
-    const int32_t v = A.nodes[i];
+    const int32_t v = row.node;
     const Ctx kx = ctx_of(A, v);
     if (skip_quiet(A, qm, v, kx)) {
-        store_result(A, i, -1, 0, 0, false);
+        store_result(A, i, -1, 0, 0, false, 0);
         return;
     }
-    const int64_t b = A.xadj[v];
-    const int d = static_cast<int>(A.xadj[v + 1] - b);
+    const int d = row.deg;
     const int32_t a = A.label[v];
     const int32_t c = A.vw ? A.vw[v] : 1;
-    int32_t lab[MAXD], wt[MAXD];
-    lane_row<MAXD>(A, b, d, lab, wt);
+    int32_t lab[MAXD], conn[MAXD];
+    const bool over = A.refine && A.w[a] > kx.bound;
+    lane_row<MAXD>(A, row.begin, d, lab, conn);
     int32_t own = 0;
 #pragma unroll
-    for (int j = 0; j < MAXD; ++j) own += (lab[j] == a) ? wt[j] : 0;
-    const bool over = A.refine && A.w[a] > kx.bound;
+    for (int j = 0; j < MAXD; ++j) own += (lab[j] == a) ? conn[j] : 0;
+    // slot weights to label sums: each slot of the first occurrence of a label
+    // collects the later ones, which drop out
+#pragma unroll
+    for (int j = 0; j < MAXD; ++j) {
+        if (lab[j] == a) lab[j] = -1;
+#pragma unroll
+        for (int j2 = j + 1; j2 < MAXD; ++j2) {
+            const bool same = lab[j] >= 0 && lab[j2] == lab[j];
+            conn[j] += same ? conn[j2] : 0;
+            lab[j2] = same ? -1 : lab[j2];
+        }
+    }
     Best best;
     best_init(best);
     bool blocked = false;  // some other neighbouring label is connected more strongly
+    constexpr int U = MAXD < 8 ? MAXD : 8;
 #pragma unroll
-    for (int j = 0; j < MAXD; ++j) {
-        const int32_t x = lab[j];
-        bool skip = (x < 0) || (x == a);
-#pragma unroll
-        for (int j2 = 0; j2 < j; ++j2) skip |= (lab[j2] == x);
-        if (skip) continue;
-        int32_t conn = 0;
-#pragma unroll
-        for (int j2 = j; j2 < MAXD; ++j2) conn += (lab[j2] == x) ? wt[j2] : 0;
-        blocked |= conn > own;
-        if (!over && conn <= own) continue;  // cannot give a positive gain
-        if (best.x >= 0 && conn < best.conn) continue;
-        if (!eligible(A, x, c, kx)) continue;
-        best_consider(best, x, conn, kx);
-    }
-    store_result(A, i, best.x, best.conn, own, over);
+    for (int j = 0; j < MAXD; j += U) consider_group<U>(A, kx, lab + j, conn + j, c, own, over, best, blocked);
+    store_result(A, i, best.x, best.conn, own, over, c);
     if (qm) A.quiet[v] = (!over && !blocked) ? 1 : 0;
 }
 
@@ -503,51 +580,39 @@ __device__ __forceinline__ void eval_group_body(const EvalArgs& A, int32_t bid, 
     const int grp = threadIdx.x / G;
     const int gl = threadIdx.x % G;
     const int node_i = bid * NG + grp;
-    if (node_i >= A.count || stopped(A.gate)) return;  // uniform per group
+    if (node_i >= A.count) return;  // uniform per group
+    const Row row = A.rows[node_i];
+    if (stopped(A.gate)) return;
     const int qm = quiet_mode(A);
     int32_t* keys = lds + grp * T;
     int32_t* vals = lds + (NG + grp) * T;
-    const int32_t v = A.nodes[node_i];
+    const int32_t v = row.node;
     const Ctx kx = ctx_of(A, v);
     if (skip_quiet(A, qm, v, kx)) {
-        if (gl == 0) store_result(A, node_i, -1, 0, 0, false);
+        if (gl == 0) store_result(A, node_i, -1, 0, 0, false, 0);
         return;
     }
-    const int64_t b = A.xadj[v];
-    const int32_t d = static_cast<int32_t>(A.xadj[v + 1] - b);
     const int32_t a = A.label[v];
     const int32_t c = A.vw ? A.vw[v] : 1;
-    const uint32_t tsz = table_size_for(d, T < 64 ? T : 64, T);
+    const bool over = A.refine && A.w[a] > kx.bound;
+    const uint32_t tsz = table_size_for(row.deg, T < 64 ? T : 64, T);
     for (uint32_t j = gl; j < tsz; j += G) {
         keys[j] = -1;
         vals[j] = 0;
     }
     wave_sync();
-    insert_slots<G, 4>(A, b, d, keys, vals, tsz, gl);
+    insert_slots<G, 4>(A, row.begin, row.deg, keys, vals, tsz, gl);
     wave_sync();
-    int32_t ownp = 0;
-    for (uint32_t j = gl; j < tsz; j += G)
-        if (keys[j] == a) ownp = vals[j];
-    const int32_t own = group_max<G>(ownp);
-    const bool over = A.refine && A.w[a] > kx.bound;
+    const int32_t own = table_find<true>(keys, vals, tsz, a);
     Best best;
     best_init(best);
     bool blocked = false;  // some other neighbouring label is connected more strongly
-    for (uint32_t j = gl; j < tsz; j += G) {
-        const int32_t x = keys[j];
-        if (x < 0 || x == a) continue;
-        const int32_t conn = vals[j];
-        blocked |= conn > own;
-        if (!over && conn <= own) continue;
-        if (best.x >= 0 && conn < best.conn) continue;
-        if (!eligible(A, x, c, kx)) continue;
-        best_consider(best, x, conn, kx);
-    }
+    scan_table<G, 4>(A, kx, keys, vals, tsz, gl, a, c, own, over, best, blocked);
     int32_t bx, bconn;
     group_argmax<G>(best, kx, bx, bconn);
     const bool any_blocked = group_any<G>(blocked);
     if (gl == 0) {
-        store_result(A, node_i, bx, bconn, own, over);
+        store_result(A, node_i, bx, bconn, own, over, c);
         if (qm) A.quiet[v] = (!over && !any_blocked) ? 1 : 0;
     }
 }
@@ -567,8 +632,6 @@ struct BlockScratch {
     uint64_t tie[NT / 64];
     int32_t conn[NT / 64];
     int32_t x[NT / 64];
-    int32_t own;
-    int32_t pad;
 };
 
 // LDS: BlockScratch<NT> then 2 * TABLE int32 (keys, then sums).
@@ -577,53 +640,39 @@ __device__ __forceinline__ void eval_block_body(const EvalArgs& A, int32_t bid, 
     BlockScratch<NT>& S = *reinterpret_cast<BlockScratch<NT>*>(lds);
     int32_t* keys = reinterpret_cast<int32_t*>(lds + sizeof(BlockScratch<NT>));
     int32_t* vals = keys + TABLE;
-    int32_t& s_own = S.own;
     int32_t* s_conn = S.conn;
     int32_t* s_x = S.x;
     uint64_t* s_tie = S.tie;
     const int tid = threadIdx.x;
     const int wid = tid >> 6;
     const int lane = lane_id();
+    const Row row = A.rows[bid];
     if (stopped(A.gate)) return;  // uniform over the grid
     const int qm = quiet_mode(A);
-    const int32_t v = A.nodes[bid];
+    const int32_t v = row.node;
     const Ctx kx = ctx_of(A, v);
     if (skip_quiet(A, qm, v, kx)) {  // uniform over the workgroup
-        if (tid == 0) store_result(A, bid, -1, 0, 0, false);
+        if (tid == 0) store_result(A, bid, -1, 0, 0, false, 0);
         return;
     }
-    const int64_t b = A.xadj[v];
-    const int32_t d = static_cast<int32_t>(A.xadj[v + 1] - b);
+    const int32_t d = row.deg;
     const int32_t a = A.label[v];
     const int32_t c = A.vw ? A.vw[v] : 1;
+    const bool over = A.refine && A.w[a] > kx.bound;
     constexpr bool kPow2 = (TABLE & (TABLE - 1)) == 0;
     const uint32_t tsz = kPow2 ? table_size_for(d, 512, TABLE) : static_cast<uint32_t>(TABLE);
     for (uint32_t j = tid; j < tsz; j += NT) {
         keys[j] = -1;
         vals[j] = 0;
     }
-    if (tid == 0) s_own = 0;
     __syncthreads();
-    insert_slots<NT, 4, kPow2>(A, b, d, keys, vals, tsz, tid);
+    insert_slots<NT, 4, kPow2>(A, row.begin, d, keys, vals, tsz, tid);
     __syncthreads();
-    for (uint32_t j = tid; j < tsz; j += NT)
-        if (keys[j] == a) s_own = vals[j];
-    __syncthreads();
-    const int32_t own = s_own;
-    const bool over = A.refine && A.w[a] > kx.bound;
+    const int32_t own = table_find<kPow2>(keys, vals, tsz, a);
     Best best;
     best_init(best);
     bool blocked = false;
-    for (uint32_t j = tid; j < tsz; j += NT) {
-        const int32_t x = keys[j];
-        if (x < 0 || x == a) continue;
-        const int32_t conn = vals[j];
-        blocked |= conn > own;
-        if (!over && conn <= own) continue;
-        if (best.x >= 0 && conn < best.conn) continue;
-        if (!eligible(A, x, c, kx)) continue;
-        best_consider(best, x, conn, kx);
-    }
+    scan_table<NT, 4>(A, kx, keys, vals, tsz, tid, a, c, own, over, best, blocked);
     int32_t bx, bconn;
     wave_argmax(best, kx, bx, bconn);
     if (lane == 0) {
@@ -636,7 +685,7 @@ __device__ __forceinline__ void eval_block_body(const EvalArgs& A, int32_t bid, 
         int32_t fc = -1, fx = -1;
         uint64_t ft = ~0ULL;
         for (int w = 0; w < NT / 64; ++w) combine_into(fc, ft, fx, s_conn[w], s_tie[w], s_x[w]);
-        store_result(A, bid, fx, fc, own, over);
+        store_result(A, bid, fx, fc, own, over, c);
         if (qm) A.quiet[v] = (!over && !any_blocked) ? 1 : 0;
     }
 }
@@ -650,34 +699,32 @@ __global__ void __launch_bounds__(NT) eval_block_kernel(EvalArgs A) {
 // ------------------------------------------------------------- hub bucket
 
 struct HubArgs {
-    const int32_t* hub_nodes;    // [H]
     const int32_t* hub_plog;     // [H] log2 of the hub's partition count
     const int32_t* hub_pbase;    // [H+1] first partition of each hub
     const int32_t* hub_cap;      // [H] entries per partition region
-    const int32_t* hub_tfirst;   // [H+1] first HBM table chunk of each hub
     const int32_t* chunk_hub;    // [nchunks]
     const int32_t* part_hub;     // [nparts]
-    const int32_t* tchunk_hub;   // [ntchunks]
     const int64_t* hub_rbase;    // [H] first region entry of the hub
     const int64_t* hub_obase;    // [H] first overflow entry of the hub
     const int64_t* hub_toff;     // [H] HBM table offset
     const int64_t* chunk_begin;  // [nchunks] first slot of the chunk
-    const int64_t* tchunk_begin; // [ntchunks] first table entry (absolute)
     const uint32_t* hub_tmask;   // [H] HBM table size - 1
-    int32_t* rcount;   // [nparts] entries reserved per partition    } zeroed
-    int32_t* ocount;   // [H] overflow entries                      } per
-    int32_t* big;      // [H] hub needs the HBM table               } sub-
-    int32_t* hub_own;  // [H] connection to the own label           } round
+    int32_t* rcount;   // [nparts] entries reserved per partition    } zero before
+    int32_t* ocount;   // [H] overflow entries                      } and after
+    int32_t* big;      // [H] hub needs the HBM table               } every
+    int32_t* hub_own;  // [H] connection to the own label           } sub-round
     int32_t* ekeys;    // partition regions (label, summed weight)
     int32_t* evals;
     int32_t* okeys;    // overflow of full regions
     int32_t* ovals;
     int32_t* gkeys;    // HBM tables
     int32_t* gvals;
-    int32_t* w_conn;   // winners per partition, then per table chunk
+    int32_t* w_conn;   // winners per partition
     uint64_t* w_tie;
     int32_t* w_x;
     int32_t part_limit;  // partitions with more entries take the HBM table path
+    int32_t count;       // hubs of the colour (0: none); their entries are the colour's last
+    int32_t* hub_sum;    // dense refinement: a row of dense_k sums per hub, else null
 };
 
 constexpr int kHubThreads = 1024;
@@ -691,18 +738,20 @@ __device__ __forceinline__ uint32_t part_of(int32_t x, int32_t plog) {
 
 // Sums one chunk of a hub row in an LDS table, then scatters the chunk's
 // distinct (label, weight) entries into the hub's label partitions.
-__global__ void __launch_bounds__(kHubThreads) hub_chunk_kernel(EvalArgs A, HubArgs H) {
-    __shared__ int32_t keys[kHubTable];
-    __shared__ int32_t vals[kHubTable];
-    __shared__ uint32_t pcount[1 << kMaxPartLog];
-    __shared__ int32_t pbase[1 << kMaxPartLog];
+// LDS: 2 * kHubTable int32, then 2 << kMaxPartLog.
+constexpr size_t kHubLds = (2 * kHubTable + (2 << kMaxPartLog)) * sizeof(int32_t);
+
+__device__ __forceinline__ void hub_chunk_body(const EvalArgs& A, const HubArgs& H, int32_t bid, unsigned char* lds) {
+    int32_t* keys = reinterpret_cast<int32_t*>(lds);
+    int32_t* vals = keys + kHubTable;
+    uint32_t* pcount = reinterpret_cast<uint32_t*>(vals + kHubTable);
+    int32_t* pbase = vals + kHubTable + (1 << kMaxPartLog);
     constexpr int kPer = kHubTable / kHubThreads;
     if (stopped(A.gate)) return;  // uniform over the grid
     const int tid = threadIdx.x;
-    const int32_t h = H.chunk_hub[blockIdx.x];
-    const int32_t v = H.hub_nodes[h];
-    const int64_t begin = H.chunk_begin[blockIdx.x];
-    const int64_t row_end = A.xadj[v + 1];
+    const int32_t h = H.chunk_hub[bid];
+    const int64_t begin = H.chunk_begin[bid];
+    const int64_t row_end = A.rows[h].begin + A.rows[h].deg;
     const int64_t end = begin + kHubChunk < row_end ? begin + kHubChunk : row_end;
     const uint32_t tsz = table_size_for(static_cast<int32_t>(end - begin), 1024, kHubTable);
     const int32_t plog = H.hub_plog[h];
@@ -743,6 +792,11 @@ __global__ void __launch_bounds__(kHubThreads) hub_chunk_kernel(EvalArgs A, HubA
             H.ovals[at] = vals[e];
         }
     }
+}
+
+__global__ void __launch_bounds__(kHubThreads) hub_chunk_kernel(EvalArgs A, HubArgs H) {
+    __shared__ __align__(16) unsigned char lds[kHubLds];
+    hub_chunk_body(A, H, blockIdx.x, lds);
 }
 
 __device__ __forceinline__ int32_t block_sum_part(int32_t v, int32_t* s_red) {
@@ -796,24 +850,17 @@ __global__ void __launch_bounds__(kPartThreads) hub_part_kernel(EvalArgs A, HubA
         if (part_of(x, plog) == static_cast<uint32_t>(p)) table_add(keys, vals, mask, x, H.ovals[ob + j]);
     }
     __syncthreads();
-    const int32_t v = H.hub_nodes[h];
+    const int32_t v = A.rows[h].node;
     const Ctx kx = ctx_of(A, v);
     const int32_t a = A.label[v];
     const int32_t c = A.vw ? A.vw[v] : 1;
+    // only the partition of a holds a; the others' best labels are compared
+    // with its connection by hub_decide
+    if (tid == 0 && part_of(a, plog) == static_cast<uint32_t>(p)) H.hub_own[h] = table_find<true>(keys, vals, tsz, a);
     Best best;
     best_init(best);
-    for (uint32_t j = tid; j < tsz; j += kPartThreads) {
-        const int32_t x = keys[j];
-        if (x < 0) continue;
-        const int32_t conn = vals[j];
-        if (x == a) {
-            H.hub_own[h] = conn;  // only the partition of a holds a, in one entry
-            continue;
-        }
-        if (best.x >= 0 && conn < best.conn) continue;
-        if (!eligible(A, x, c, kx)) continue;
-        best_consider(best, x, conn, kx);
-    }
+    bool blocked = false;
+    scan_table<kPartThreads, 4>(A, kx, keys, vals, tsz, tid, a, c, 0, true, best, blocked);
     int32_t bx, bconn;
     wave_argmax(best, kx, bx, bconn);
     const int wid = tid >> 6;
@@ -833,114 +880,114 @@ __global__ void __launch_bounds__(kPartThreads) hub_part_kernel(EvalArgs A, HubA
     }
 }
 
-// Decision of a hub from the winners in [first[h], first[h+1]).
-__device__ __forceinline__ void hub_decide(const EvalArgs& A, const HubArgs& H, int32_t h, const int32_t* first) {
-    const int32_t v = H.hub_nodes[h];
-    const Ctx kx = ctx_of(A, v);
-    const int32_t a = A.label[v];
-    int32_t fc = -1, fx = -1;
-    uint64_t ft = ~0ULL;
-    for (int32_t j = first[h] + lane_id(); j < first[h + 1]; j += 64)
-        combine_into(fc, ft, fx, H.w_conn[j], H.w_tie[j], H.w_x[j]);
-    const int32_t maxc = wave_max(fx >= 0 ? fc : -1);
-    int32_t bx = -1;
-    if (maxc >= 0) {
-        const bool top = fx >= 0 && fc == maxc;
-        const uint64_t mt = wave_min_u64(top ? ft : ~0ULL);
-        bx = wave_min((top && ft == mt) ? fx : INT_MAX);
-    }
-    const bool over = A.refine && A.w[a] > kx.bound;
-    if (lane_id() == 0) store_result(A, h, bx, maxc, H.hub_own[h], over);
-}
-
-__global__ void __launch_bounds__(64) hub_finish_kernel(EvalArgs A, HubArgs H) {
-    if (stopped(A.gate) || H.big[blockIdx.x]) return;
-    hub_decide(A, H, blockIdx.x, H.hub_pbase);
-}
-
-// HBM table path for marked hubs: clear the table ...
-__global__ void __launch_bounds__(256) hub_clear_kernel(HubArgs H) {
-    const int32_t h = H.tchunk_hub[blockIdx.x];
-    if (!H.big[h]) return;
-    const int64_t begin = H.tchunk_begin[blockIdx.x];
-    const int64_t tend = H.hub_toff[h] + static_cast<int64_t>(H.hub_tmask[h]) + 1;
-    const int64_t end = begin + kHubTChunk < tend ? begin + kHubTChunk : tend;
-    for (int64_t j = begin + threadIdx.x; j < end; j += 256) {
-        H.gkeys[j] = -1;
-        H.gvals[j] = 0;
-    }
-}
-
-// ... add every partition region (and, from partition 0, the overflow list) ...
-__global__ void __launch_bounds__(256) hub_table_insert_kernel(HubArgs H) {
-    const int32_t gp = blockIdx.x;
-    const int32_t h = H.part_hub[gp];
-    if (!H.big[h]) return;
-    const int32_t p = gp - H.hub_pbase[h];
-    const int32_t cap = H.hub_cap[h];
-    const int32_t in_region = H.rcount[gp] < cap ? H.rcount[gp] : cap;
-    int32_t* gk = H.gkeys + H.hub_toff[h];
-    int32_t* gv = H.gvals + H.hub_toff[h];
-    const uint32_t gmask = H.hub_tmask[h];
-    const int64_t r0 = H.hub_rbase[h] + static_cast<int64_t>(p) * cap;
-    for (int32_t j = threadIdx.x; j < in_region; j += 256) table_add(gk, gv, gmask, H.ekeys[r0 + j], H.evals[r0 + j]);
-    if (p == 0) {
-        const int64_t ob = H.hub_obase[h];
-        for (int32_t j = threadIdx.x; j < H.ocount[h]; j += 256) table_add(gk, gv, gmask, H.okeys[ob + j], H.ovals[ob + j]);
-    }
-}
-
-// ... pick the best entry of each table chunk ...
-__global__ void __launch_bounds__(256) hub_scan_kernel(EvalArgs A, HubArgs H, int32_t wbase) {
+// Best of the threads' candidates for a workgroup of 256; thread 0 has it.
+__device__ __forceinline__ void block_combine(int32_t& fc, uint64_t& ft, int32_t& fx) {
     __shared__ int32_t s_conn[4];
     __shared__ int32_t s_x[4];
     __shared__ uint64_t s_tie[4];
-    const int32_t h = H.tchunk_hub[blockIdx.x];
-    if (stopped(A.gate) || !H.big[h]) return;
-    const int32_t v = H.hub_nodes[h];
-    const Ctx kx = ctx_of(A, v);
-    const int32_t a = A.label[v];
-    const int32_t c = A.vw ? A.vw[v] : 1;
-    const int64_t begin = H.tchunk_begin[blockIdx.x];
-    const int64_t tend = H.hub_toff[h] + static_cast<int64_t>(H.hub_tmask[h]) + 1;
-    const int64_t end = begin + kHubTChunk < tend ? begin + kHubTChunk : tend;
-    Best best;
-    best_init(best);
-    for (int64_t j = begin + threadIdx.x; j < end; j += 256) {
-        const int32_t x = H.gkeys[j];
-        if (x < 0) continue;
-        const int32_t conn = H.gvals[j];
-        if (x == a) {
-            H.hub_own[h] = conn;
-            continue;
-        }
-        if (best.x >= 0 && conn < best.conn) continue;
-        if (!eligible(A, x, c, kx)) continue;
-        best_consider(best, x, conn, kx);
-    }
-    int32_t bx, bconn;
-    wave_argmax(best, kx, bx, bconn);
-    const int wid = threadIdx.x >> 6;
+    const int32_t maxc = wave_max(fx >= 0 ? fc : -1);
+    const bool top = fx >= 0 && fc == maxc;
+    const uint64_t mt = wave_min_u64(top ? ft : ~0ULL);
+    const int32_t bx = wave_min((top && ft == mt) ? fx : INT_MAX);
     if (lane_id() == 0) {
-        s_conn[wid] = bconn;
-        s_x[wid] = bx;
-        s_tie[wid] = bx >= 0 ? tie_of(kx, bx) : ~0ULL;
+        s_conn[threadIdx.x >> 6] = maxc;
+        s_x[threadIdx.x >> 6] = maxc >= 0 ? bx : -1;
+        s_tie[threadIdx.x >> 6] = mt;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        int32_t fc = -1, fx = -1;
-        uint64_t ft = ~0ULL;
+        fc = -1;
+        fx = -1;
+        ft = ~0ULL;
         for (int w = 0; w < 4; ++w) combine_into(fc, ft, fx, s_conn[w], s_tie[w], s_x[w]);
-        H.w_conn[wbase + blockIdx.x] = fc;
-        H.w_tie[wbase + blockIdx.x] = ft;
-        H.w_x[wbase + blockIdx.x] = fx;
     }
 }
 
-// ... and decide from the chunk winners (stored after the partition winners).
-__global__ void __launch_bounds__(64) hub_big_finish_kernel(EvalArgs A, HubArgs H, const int32_t* tfirst_shifted) {
-    if (stopped(A.gate) || !H.big[blockIdx.x]) return;
-    hub_decide(A, H, blockIdx.x, tfirst_shifted);
+// Decision of hub h by one workgroup of 256, from the winners of its
+// partitions; afterwards the hub's counters are zero again.  A hub with a
+// partition too long for its LDS table is summed by this workgroup alone in an
+// exact table in HBM (each partition holds about 1024 entries by its hash, so
+// this is an exception that hardly occurs).
+__device__ void hub_decide(const EvalArgs& A, const HubArgs& H, int32_t h) {
+    const int tid = threadIdx.x;
+    const int32_t v = A.rows[h].node;
+    const Ctx kx = ctx_of(A, v);
+    const int32_t a = A.label[v];
+    const int32_t p0 = H.hub_pbase[h], p1 = H.hub_pbase[h + 1];
+    int32_t fc = -1, fx = -1;
+    uint64_t ft = ~0ULL;
+    int32_t own = H.hub_own[h];
+    if (!H.big[h]) {
+        constexpr int U = 4;
+        for (int32_t j = p0 + tid; j < p1; j += 256 * U) {
+            int32_t cn[U], x[U];
+            uint64_t ti[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const bool in = j + u * 256 < p1;
+                cn[u] = in ? H.w_conn[j + u * 256] : -1;
+                x[u] = in ? H.w_x[j + u * 256] : -1;
+                ti[u] = in ? H.w_tie[j + u * 256] : ~0ULL;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) combine_into(fc, ft, fx, cn[u], ti[u], x[u]);
+        }
+    } else {
+        int32_t* gk = H.gkeys + H.hub_toff[h];
+        int32_t* gv = H.gvals + H.hub_toff[h];
+        const uint32_t gmask = H.hub_tmask[h];
+        for (int64_t j = tid; j <= static_cast<int64_t>(gmask); j += 256) {
+            __hip_atomic_store(&gk[j], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&gv[j], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __threadfence();
+        __syncthreads();
+        const int32_t cap = H.hub_cap[h];
+        for (int32_t gp = p0; gp < p1; ++gp) {
+            const int32_t in_region = H.rcount[gp] < cap ? H.rcount[gp] : cap;
+            const int64_t r0 = H.hub_rbase[h] + static_cast<int64_t>(gp - p0) * cap;
+            for (int32_t j = tid; j < in_region; j += 256) table_add(gk, gv, gmask, H.ekeys[r0 + j], H.evals[r0 + j]);
+        }
+        const int64_t ob = H.hub_obase[h];
+        const int32_t ov = H.ocount[h];
+        for (int32_t j = tid; j < ov; j += 256) table_add(gk, gv, gmask, H.okeys[ob + j], H.ovals[ob + j]);
+        __threadfence();
+        __syncthreads();
+        const int32_t c = A.vw ? A.vw[v] : 1;
+        __shared__ int32_t s_own;
+        if (tid == 0) s_own = 0;
+        __syncthreads();
+        Best best;
+        best_init(best);
+        for (int64_t j = tid; j <= static_cast<int64_t>(gmask); j += 256) {
+            const int32_t x = __hip_atomic_load(&gk[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (x < 0) continue;
+            const int32_t conn = __hip_atomic_load(&gv[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (x == a) {
+                s_own = conn;
+                continue;
+            }
+            if (best.x >= 0 && conn < best.conn) continue;
+            if (!eligible(A, x, c, kx)) continue;
+            best_consider(best, x, conn, kx);
+        }
+        __syncthreads();
+        own = s_own;
+        if (best.x >= 0) {
+            fc = best.conn;
+            fx = best.x;
+            ft = best_tie(best, kx);
+        }
+    }
+    block_combine(fc, ft, fx);
+    if (tid == 0) store_result(A, h, fx, fc, own, A.refine && A.w[a] > kx.bound, A.vw ? A.vw[v] : 1);
+    __syncthreads();  // every thread has read the counters
+    for (int32_t j = p0 + tid; j < p1; j += 256) H.rcount[j] = 0;
+    if (tid == 0) {
+        H.ocount[h] = 0;
+        H.big[h] = 0;
+        H.hub_own[h] = 0;
+    }
 }
 
 // ------------------------------------------------ dense refinement buckets
@@ -974,20 +1021,22 @@ __device__ __forceinline__ void dense_slots(const EvalArgs& A, const Ctx& kx, in
 }
 
 // Best eligible block of a node from its dense connections (lane j of the
-// set scans entries j, j + NT, ...).
+// set scans entries j, j + STEP, ..., four at a time).
+template <int STEP>
 __device__ __forceinline__ void dense_best(const EvalArgs& A, const Ctx& kx, const int32_t* conn, int32_t a,
-                                           int32_t c, int32_t own, bool over, int first, int step, Best& best,
-                                           bool& blocked) {
+                                           int32_t c, int32_t own, bool over, int first, Best& best, bool& blocked) {
+    constexpr int U = 4;
     const int32_t la = a - kx.lbase;
-    for (int32_t j = first; j < A.dense_k; j += step) {
-        const int32_t cn = conn[j];
-        if (cn == 0 || j == la) continue;  // not a neighbouring block, or the own one
-        blocked |= cn > own;
-        if (!over && cn <= own) continue;
-        if (best.x >= 0 && cn < best.conn) continue;
-        const int32_t x = j + kx.lbase;
-        if (!eligible(A, x, c, kx)) continue;
-        best_consider(best, x, cn, kx);
+    for (int j0 = first; j0 < A.dense_k; j0 += STEP * U) {
+        int32_t x[U], cn[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int j = j0 + u * STEP;
+            cn[u] = j < A.dense_k ? conn[j] : 0;
+            // not a neighbouring block, or the own one
+            x[u] = cn[u] == 0 || j == la ? -1 : j + kx.lbase;
+        }
+        consider_group<U>(A, kx, x, cn, c, own, over, best, blocked);
     }
 }
 
@@ -998,34 +1047,34 @@ __device__ __forceinline__ void eval_dense_group_body(const EvalArgs& A, int32_t
     const int grp = threadIdx.x / G;
     const int gl = threadIdx.x % G;
     const int node_i = bid * NG + grp;
-    if (node_i >= A.count || stopped(A.gate)) return;  // uniform per group
+    if (node_i >= A.count) return;  // uniform per group
+    const Row row = A.rows[node_i];
+    if (stopped(A.gate)) return;
     const int qm = quiet_mode(A);
     int32_t* conn = lds + grp * kDenseMax;
-    const int32_t v = A.nodes[node_i];
+    const int32_t v = row.node;
     const Ctx kx = ctx_of(A, v);
     if (skip_quiet(A, qm, v, kx)) {
-        if (gl == 0) store_result(A, node_i, -1, 0, 0, false);
+        if (gl == 0) store_result(A, node_i, -1, 0, 0, false, 0);
         return;
     }
-    const int64_t b = A.xadj[v];
-    const int32_t d = static_cast<int32_t>(A.xadj[v + 1] - b);
     const int32_t a = A.label[v];
     const int32_t c = A.vw ? A.vw[v] : 1;
+    const bool over = A.w[a] > kx.bound;
     for (int32_t j = gl; j < A.dense_k; j += G) conn[j] = 0;
     wave_sync();
-    dense_slots<G>(A, kx, b, d, conn, gl);
+    dense_slots<G>(A, kx, row.begin, row.deg, conn, gl);
     wave_sync();
     const int32_t own = conn[a - kx.lbase];
-    const bool over = A.w[a] > kx.bound;
     Best best;
     best_init(best);
     bool blocked = false;
-    dense_best(A, kx, conn, a, c, own, over, gl, G, best, blocked);
+    dense_best<G>(A, kx, conn, a, c, own, over, gl, best, blocked);
     int32_t bx, bconn;
     group_argmax<G>(best, kx, bx, bconn);
     const bool any_blocked = group_any<G>(blocked);
     if (gl == 0) {
-        store_result(A, node_i, bx, bconn, own, over);
+        store_result(A, node_i, bx, bconn, own, over, c);
         if (qm) A.quiet[v] = (!over && !any_blocked) ? 1 : 0;
     }
 }
@@ -1046,28 +1095,27 @@ __device__ __forceinline__ void eval_dense_block_body(const EvalArgs& A, int32_t
     uint64_t* s_tie = S.tie;
     const int tid = threadIdx.x;
     const int wid = tid >> 6;
+    const Row row = A.rows[bid];
     if (stopped(A.gate)) return;  // uniform over the grid
     const int qm = quiet_mode(A);
-    const int32_t v = A.nodes[bid];
+    const int32_t v = row.node;
     const Ctx kx = ctx_of(A, v);
     if (skip_quiet(A, qm, v, kx)) {  // uniform over the workgroup
-        if (tid == 0) store_result(A, bid, -1, 0, 0, false);
+        if (tid == 0) store_result(A, bid, -1, 0, 0, false, 0);
         return;
     }
-    const int64_t b = A.xadj[v];
-    const int32_t d = static_cast<int32_t>(A.xadj[v + 1] - b);
     const int32_t a = A.label[v];
     const int32_t c = A.vw ? A.vw[v] : 1;
+    const bool over = A.w[a] > kx.bound;
     for (int32_t j = tid; j < A.dense_k; j += NT) conn[j] = 0;
     __syncthreads();
-    dense_slots<NT>(A, kx, b, d, conn, tid);
+    dense_slots<NT>(A, kx, row.begin, row.deg, conn, tid);
     __syncthreads();
     const int32_t own = conn[a - kx.lbase];
-    const bool over = A.w[a] > kx.bound;
     Best best;
     best_init(best);
     bool blocked = false;
-    dense_best(A, kx, conn, a, c, own, over, tid, NT, best, blocked);
+    dense_best<NT>(A, kx, conn, a, c, own, over, tid, best, blocked);
     int32_t bx, bconn;
     wave_argmax(best, kx, bx, bconn);
     if (lane_id() == 0) {
@@ -1080,7 +1128,7 @@ __device__ __forceinline__ void eval_dense_block_body(const EvalArgs& A, int32_t
         int32_t fc = -1, fx = -1;
         uint64_t ft = ~0ULL;
         for (int w = 0; w < NT / 64; ++w) combine_into(fc, ft, fx, s_conn[w], s_tie[w], s_x[w]);
-        store_result(A, bid, fx, fc, own, over);
+        store_result(A, bid, fx, fc, own, over, c);
         if (qm) A.quiet[v] = (!over && !any_blocked) ? 1 : 0;
     }
 }
@@ -1091,21 +1139,72 @@ __global__ void __launch_bounds__(NT) eval_dense_block_kernel(EvalArgs A) {
     eval_dense_block_body<NT>(A, blockIdx.x, lds);
 }
 
-// ------------------------------------------------- small buckets, fused
+// Hubs: every chunk of a hub's row adds its dense sums to the hub's row of
+// hub_sum (dense_k entries per hub) ...
+template <int NT>
+__device__ __forceinline__ void hub_dense_chunk_body(const EvalArgs& A, const HubArgs& H, int32_t bid, int32_t* conn) {
+    if (stopped(A.gate)) return;  // uniform over the grid
+    const int tid = threadIdx.x;
+    const int32_t h = H.chunk_hub[bid];
+    const Row row = A.rows[h];
+    const Ctx kx = ctx_of(A, row.node);
+    const int64_t begin = H.chunk_begin[bid];
+    const int64_t row_end = row.begin + row.deg;
+    const int64_t end = begin + kHubDenseChunk < row_end ? begin + kHubDenseChunk : row_end;
+    for (int32_t j = tid; j < A.dense_k; j += NT) conn[j] = 0;
+    __syncthreads();
+    dense_slots<NT>(A, kx, begin, static_cast<int32_t>(end - begin), conn, tid);
+    __syncthreads();
+    for (int32_t j = tid; j < A.dense_k; j += NT)
+        if (conn[j]) atomicAdd(&H.hub_sum[static_cast<int64_t>(h) * A.dense_k + j], conn[j]);
+}
 
-// The buckets of up to 1 024 slots (one lane, 16, 32 or 64 lanes, or one
-// 256-thread workgroup per node) of a small colour in one launch: consecutive
-// workgroup ranges belong to the buckets in order, and each workgroup runs its
-// bucket's body on an LDS buffer sized for the largest.  A small colour
-// otherwise pays one launch per bucket on one stream.
-constexpr int kFusedBuckets = 6;
+__global__ void __launch_bounds__(kHubThreads) hub_dense_chunk_kernel(EvalArgs A, HubArgs H) {
+    __shared__ int32_t conn[kDenseMax];
+    hub_dense_chunk_body<kHubThreads>(A, H, blockIdx.x, conn);
+}
+
+// ... then a workgroup of 256 decides and clears the hub's row.
+__device__ void hub_dense_decide(const EvalArgs& A, const HubArgs& H, int32_t h) {
+    const int tid = threadIdx.x;
+    const int32_t v = A.rows[h].node;
+    const Ctx kx = ctx_of(A, v);
+    const int32_t a = A.label[v];
+    const int32_t c = A.vw ? A.vw[v] : 1;
+    int32_t* conn = H.hub_sum + static_cast<int64_t>(h) * A.dense_k;
+    const int32_t own = conn[a - kx.lbase];
+    const bool over = A.w[a] > kx.bound;
+    Best best;
+    best_init(best);
+    bool blocked = false;
+    dense_best<256>(A, kx, conn, a, c, own, over, tid, best, blocked);
+    int32_t fc = best.conn, fx = best.x;
+    uint64_t ft = best.x >= 0 ? best_tie(best, kx) : ~0ULL;
+    block_combine(fc, ft, fx);
+    if (tid == 0) store_result(A, h, fx, fc, own, over, c);
+    __syncthreads();  // every thread has read the row
+    for (int32_t j = tid; j < A.dense_k; j += 256) conn[j] = 0;
+}
+
+// ------------------------------------------------- small colours, fused
+
+// The buckets of a small colour in one launch: consecutive workgroup ranges
+// belong to the buckets, the longest rows first, and each workgroup runs its
+// bucket's body on an LDS buffer sized for the largest.  Separate launches, one
+// after the other on one stream, cost 2.3 us each before they do any work and
+// leave most of the device idle.  Hash tables: rows of up to 1 024 slots (one
+// lane, 16, 32 or 64 lanes, or one 256-thread workgroup per node).  Dense
+// refinement: rows of any length, hub chunks among them, since the sums take
+// only dense_k entries.
+constexpr int kFusedHash = 6;    // buckets 0..5
+constexpr int kFusedDense = 9;   // buckets 0..7 and the hub chunks
 
 struct FusedBuckets {
-    const int32_t* nodes[kFusedBuckets];
-    int32_t* ct[kFusedBuckets];
-    int32_t* cg[kFusedBuckets];
-    int32_t count[kFusedBuckets];
-    int32_t first[kFusedBuckets + 1];  // first workgroup of each bucket, then the total
+    const Row* rows[kFusedDense];
+    int32_t* ct[kFusedDense];
+    int32_t* cg[kFusedDense];
+    int32_t count[kFusedDense];
+    int32_t end[kFusedDense];  // workgroups up to and including the bucket's, from the last bucket down
 };
 
 constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
@@ -1115,12 +1214,13 @@ constexpr size_t kFusedLds =
               cmax(16 * kDenseMax * sizeof(int32_t), sizeof(BlockScratch<256>) + kDenseMax * sizeof(int32_t))));
 
 template <bool kDense>
-__global__ void __launch_bounds__(256) eval_fused_kernel(EvalArgs A, FusedBuckets F) {
+__global__ void __launch_bounds__(256) eval_fused_kernel(EvalArgs A, FusedBuckets F, HubArgs H) {
     __shared__ __align__(16) unsigned char lds[kFusedLds];
-    int b = 0;
-    while (b + 1 < kFusedBuckets && static_cast<int32_t>(blockIdx.x) >= F.first[b + 1]) ++b;
-    const int32_t bid = static_cast<int32_t>(blockIdx.x) - F.first[b];
-    A.nodes = F.nodes[b];
+    int b = (kDense ? kFusedDense : kFusedHash) - 1;
+    int32_t first = 0;
+    while (b > 0 && static_cast<int32_t>(blockIdx.x) >= F.end[b]) first = F.end[b--];
+    const int32_t bid = static_cast<int32_t>(blockIdx.x) - first;
+    A.rows = F.rows[b];
     A.count = F.count[b];
     A.ct = F.ct[b];
     A.cg = F.cg[b];
@@ -1144,6 +1244,9 @@ __global__ void __launch_bounds__(256) eval_fused_kernel(EvalArgs A, FusedBucket
             if (kDense) eval_dense_group_body<64>(A, bid, l32);
             else eval_group_body<64, kWaveTable>(A, bid, l32);
             break;
+        case kFusedDense - 1:
+            if (kDense) hub_dense_chunk_body<256>(A, H, bid, l32);
+            break;
         default:
             if (kDense) eval_dense_block_body<256>(A, bid, lds);
             else eval_block_body<256, 2 * kBlock1Max>(A, bid, lds);
@@ -1151,73 +1254,27 @@ __global__ void __launch_bounds__(256) eval_fused_kernel(EvalArgs A, FusedBucket
     }
 }
 
-// Hubs: every chunk of a hub's row adds its dense sums to the hub's row of
-// hub_sum (dense_k entries per hub) ...
-__global__ void __launch_bounds__(kHubThreads) hub_dense_chunk_kernel(EvalArgs A, HubArgs H,
-                                                                      int32_t* __restrict__ hub_sum) {
-    __shared__ int32_t conn[kDenseMax];
-    if (stopped(A.gate)) return;  // uniform over the grid
-    const int tid = threadIdx.x;
-    const int32_t h = H.chunk_hub[blockIdx.x];
-    const int32_t v = H.hub_nodes[h];
-    const Ctx kx = ctx_of(A, v);
-    const int64_t begin = H.chunk_begin[blockIdx.x];
-    const int64_t row_end = A.xadj[v + 1];
-    const int64_t end = begin + kHubDenseChunk < row_end ? begin + kHubDenseChunk : row_end;
-    for (int32_t j = tid; j < A.dense_k; j += kHubThreads) conn[j] = 0;
-    __syncthreads();
-    dense_slots<kHubThreads>(A, kx, begin, static_cast<int32_t>(end - begin), conn, tid);
-    __syncthreads();
-    for (int32_t j = tid; j < A.dense_k; j += kHubThreads)
-        if (conn[j]) atomicAdd(&hub_sum[static_cast<int64_t>(h) * A.dense_k + j], conn[j]);
-}
+// The rows of a small colour that need a larger table, in one launch: hub
+// chunks first, then the rows of up to 8 192 and of up to 4 096 slots.  80 KB
+// of LDS: two workgroups per compute unit.
+constexpr size_t kBigLds = kHubLds;
+constexpr int kBigTable = static_cast<int>((kBigLds - sizeof(BlockScratch<kHubThreads>)) / (2 * sizeof(int32_t)));
 
-// ... then one workgroup per hub decides and clears the hub's row.
-__global__ void __launch_bounds__(256) hub_dense_finish_kernel(EvalArgs A, HubArgs H, int32_t* __restrict__ hub_sum) {
-    __shared__ int32_t s_conn[4];
-    __shared__ int32_t s_x[4];
-    __shared__ uint64_t s_tie[4];
-    if (stopped(A.gate)) return;  // uniform over the grid
-    const int tid = threadIdx.x;
-    const int32_t h = blockIdx.x;
-    const int32_t v = H.hub_nodes[h];
-    const Ctx kx = ctx_of(A, v);
-    const int32_t a = A.label[v];
-    const int32_t c = A.vw ? A.vw[v] : 1;
-    int32_t* conn = hub_sum + static_cast<int64_t>(h) * A.dense_k;
-    const int32_t own = conn[a - kx.lbase];
-    const bool over = A.w[a] > kx.bound;
-    Best best;
-    best_init(best);
-    bool blocked = false;
-    dense_best(A, kx, conn, a, c, own, over, tid, 256, best, blocked);
-    int32_t bx, bconn;
-    wave_argmax(best, kx, bx, bconn);
-    if (lane_id() == 0) {
-        s_conn[tid >> 6] = bconn;
-        s_x[tid >> 6] = bx;
-        s_tie[tid >> 6] = bx >= 0 ? tie_of(kx, bx) : ~0ULL;
+__global__ void __launch_bounds__(kHubThreads) eval_big_kernel(EvalArgs A, FusedBuckets F, HubArgs H) {
+    __shared__ __align__(16) unsigned char lds[kBigLds];
+    const int32_t bid = blockIdx.x;
+    if (bid < F.end[kHubBucket]) {
+        A.rows = F.rows[kHubBucket];
+        hub_chunk_body(A, H, bid, lds);
+        return;
     }
-    __syncthreads();
-    for (int32_t j = tid; j < A.dense_k; j += 256) conn[j] = 0;
-    if (tid == 0) {
-        int32_t fc = -1, fx = -1;
-        uint64_t ft = ~0ULL;
-        for (int w = 0; w < 4; ++w) combine_into(fc, ft, fx, s_conn[w], s_tie[w], s_x[w]);
-        store_result(A, h, fx, fc, own, over);
-    }
-}
-
-// ------------------------------------------------------- block utilities
-
-__device__ __forceinline__ int32_t block_sum_i32(int32_t v) {
-    __shared__ int32_t s[4];
-    v = wave_sum(v);
-    if (lane_id() == 0) s[threadIdx.x >> 6] = v;
-    __syncthreads();
-    const int32_t t = s[0] + s[1] + s[2] + s[3];
-    __syncthreads();
-    return t;
+    const int b = bid < F.end[7] ? 7 : 6;
+    A.rows = F.rows[b];
+    A.count = F.count[b];
+    A.ct = F.ct[b];
+    A.cg = F.cg[b];
+    if (b == 7) eval_block_body<kHubThreads, kBigTable>(A, bid - F.end[kHubBucket], lds);
+    else eval_block_body<kHubThreads, 2 * kBlock2Max>(A, bid - F.end[7], lds);
 }
 
 // ------------------------------------------------- candidates and admission
@@ -1246,12 +1303,6 @@ __device__ __forceinline__ int64_t bound_of(const Bounds& B, int32_t t) {
     return B.lgid ? B.g_bound[B.lgid[t]] : B.bound;
 }
 
-// Candidate total of a target: count in the high word, weight in the low one
-// (a label's weight never exceeds c(V) <= 2^31 - 1, so no carry).
-__device__ __forceinline__ unsigned long long acc_of(int32_t cnt, int32_t weight) {
-    return (static_cast<unsigned long long>(static_cast<uint32_t>(cnt)) << 32) | static_cast<uint32_t>(weight);
-}
-
 // Slot of label t in a block-local open-addressing table of T entries (T at
 // least twice the keys a block inserts).
 template <int T>
@@ -1272,18 +1323,30 @@ constexpr int kDirectLabels = 1024;
 constexpr int kAccShift = 4;    // acc[t << kAccShift] (8-byte entries)
 constexpr int kFillShift = 5;   // seg_fill[t << kFillShift] (4-byte entries)
 
+// Decides the hubs of the colour (workgroup h < H.count: hub h, from what the
+// evaluation launches left), and counts the candidates:
 // acc[t] += (1, c(v)) over the candidates of the sub-round, summed per block
 // in LDS first so that a label many nodes aim at (a hub's cluster) costs one
 // global atomic per block and chunk, not one per candidate.  Each block takes
 // R * 256 consecutive entries at a time.
 template <bool kDirect, int R>
-__global__ void __launch_bounds__(256) accumulate_kernel(const int32_t* __restrict__ ct,
+__global__ void __launch_bounds__(256) accumulate_kernel(EvalArgs E, HubArgs H, const int32_t* __restrict__ ct,
                                                          const int32_t* __restrict__ nodes, int32_t count,
-                                                         const int32_t* __restrict__ vw,
-                                                         unsigned long long* __restrict__ acc, int32_t nw,
-                                                         const uint32_t* __restrict__ gate,
-                                                         uint32_t* __restrict__ round_cnt) {
-    if (stopped(gate)) return;  // uniform over the grid
+                                                         unsigned long long* __restrict__ acc, int32_t nw) {
+    if (stopped(E.gate)) return;  // uniform over the grid
+    const int32_t* vw = E.vw;
+    if (static_cast<int32_t>(blockIdx.x) < H.count) {
+        const int32_t h = blockIdx.x;
+        if (H.hub_sum) hub_dense_decide(E, H, h);
+        else hub_decide(E, H, h);
+        if (threadIdx.x == 0 && E.ct[h] >= 0) {
+            const int32_t t = E.ct[h];
+            atomicAdd(&acc[kDirect ? t << kAccShift : t], acc_of(1, vw ? vw[E.rows[h].node] : 1));
+        }
+        return;
+    }
+    const int32_t bid = static_cast<int32_t>(blockIdx.x) - H.count;
+    const int32_t nblocks = static_cast<int32_t>(gridDim.x) - H.count;
     constexpr int T = 512 * R;
     constexpr int kSlots = kDirect ? kDirectLabels : T;
     __shared__ int32_t keys[kDirect ? 1 : T];
@@ -1296,9 +1359,8 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const int32_t* __restri
         lcnt[j] = 0;
     }
     __syncthreads();
-    int32_t found = 0;
-    for (int64_t base = static_cast<int64_t>(blockIdx.x) * (R * 256); base < count;
-         base += static_cast<int64_t>(gridDim.x) * (R * 256)) {
+    for (int64_t base = static_cast<int64_t>(bid) * (R * 256); base < count;
+         base += static_cast<int64_t>(nblocks) * (R * 256)) {
         // all of the thread's loads of the chunk first, then the LDS updates
         int32_t tr[R], cr[R];
 #pragma unroll
@@ -1314,14 +1376,13 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const int32_t* __restri
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             if (tr[r] < 0) continue;
-            ++found;
             const int32_t i = kDirect ? tr[r] : agg_insert<T>(keys, tr[r]);
             if (cr[r]) atomicAdd(&lsum[i], cr[r]);
             atomicAdd(&lcnt[i], 1);
         }
         if (!kDirect) {  // flush this chunk's labels
             __syncthreads();
-            const bool more = base + static_cast<int64_t>(gridDim.x) * (R * 256) < count;  // uniform
+            const bool more = base + static_cast<int64_t>(nblocks) * (R * 256) < count;  // uniform
             for (int j = threadIdx.x; j < T; j += 256) {
                 const int32_t t = keys[j];
                 if (t >= 0) {
@@ -1341,8 +1402,6 @@ __global__ void __launch_bounds__(256) accumulate_kernel(const int32_t* __restri
         for (int j = threadIdx.x; j < nw; j += 256)
             if (lcnt[j]) atomicAdd(&acc[j << kAccShift], acc_of(lcnt[j], lsum[j]));
     }
-    const int32_t tot = block_sum_i32(found);
-    if (threadIdx.x == 0 && tot) atomicAdd(round_cnt, static_cast<uint32_t>(tot));
 }
 
 // Outcome of a candidate in ok[p]: 0 not a candidate or in a segment, 1
@@ -1419,6 +1478,7 @@ struct Admission {
     Counters* ctr;       // this sub-round's counters
     Counters* ctr_next;  // the next sub-round's: cleared here, no kernel reads them any more
     const uint32_t* gate;
+    uint32_t* round_cnt;  // candidates of the round
 };
 
 // Records segment sid and, when it is longer than small_max, gives it a large
@@ -1438,34 +1498,36 @@ __device__ __forceinline__ void record_segment(const Admission& A, uint32_t sid,
     for (int32_t c = 0; c < nch; ++c) A.L.owner[c0 + c] = static_cast<int32_t>(l);
 }
 
-// Gives target t a segment and publishes seg_off[t] last.
-__device__ __forceinline__ void claim_segment(const Admission& A, int32_t t) {
-    const unsigned long long a = A.acc[t];
-    const int32_t len = static_cast<int32_t>(a >> 32);
-    const int32_t room = static_cast<int32_t>(bound_of(A.B, t) - A.w[t]);  // below the candidates' weight: fits
+// Gives target t a segment of len entries and publishes seg_off[t] last.
+__device__ __forceinline__ void claim_segment(const Admission& A, int32_t t, int32_t len, int32_t room) {
     const unsigned long long at = atomicAdd(&A.ctr->segs, acc_of(1, len));
     const int32_t base = static_cast<int32_t>(at & 0xFFFFFFFFULL);
     record_segment(A, static_cast<uint32_t>(at >> 32), Segment{t, base, len, room});
     __hip_atomic_store(&A.seg_off[t], base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The workgroup's gain range into the counters, one pair of atomics.
-__device__ __forceinline__ void note_gains(Counters* ctr, int32_t gmin, int32_t gmax) {
-    __shared__ int32_t s_min[4], s_max[4];
+// The workgroup's candidates and its segment entries' gain range into the
+// counters.
+__device__ __forceinline__ void note_gains(const Admission& A, int32_t found, int32_t gmin, int32_t gmax) {
+    __shared__ int32_t s_min[4], s_max[4], s_cnt[4];
     gmin = wave_min(gmin);
     gmax = wave_max(gmax);
+    found = wave_sum(found);
     if (lane_id() == 0) {
         s_min[threadIdx.x >> 6] = gmin;
         s_max[threadIdx.x >> 6] = gmax;
+        s_cnt[threadIdx.x >> 6] = found;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
         const int32_t a = min(min(s_min[0], s_min[1]), min(s_min[2], s_min[3]));
         const int32_t b = max(max(s_max[0], s_max[1]), max(s_max[2], s_max[3]));
+        const int32_t n = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];
         if (a <= b) {
-            atomicMin(&ctr->gmin, a);
-            atomicMax(&ctr->gmax, b);
+            atomicMin(&A.ctr->gmin, a);
+            atomicMax(&A.ctr->gmax, b);
         }
+        if (n) atomicAdd(A.round_cnt, static_cast<uint32_t>(n));
     }
 }
 
@@ -1480,9 +1542,11 @@ __global__ void __launch_bounds__(256) admit_kernel(Admission A) {
     constexpr int T = 512 * R;
     __shared__ int32_t keys[T];
     __shared__ int32_t lcnt[T];
-    __shared__ int32_t lbase[T];
+    __shared__ int32_t lbase[T];  // room of the target, then its first entry for this block
+    __shared__ int32_t llen[T];
     if (stopped(A.gate)) return;  // uniform over the grid
     int32_t gmin = INT_MAX, gmax = INT_MIN;
+    int32_t found = 0;
     for (int64_t base = static_cast<int64_t>(blockIdx.x) * (R * 256); base < A.count;
          base += static_cast<int64_t>(gridDim.x) * (R * 256)) {
         int32_t tr[R], gr[R];
@@ -1504,8 +1568,12 @@ __global__ void __launch_bounds__(256) admit_kernel(Admission A) {
         for (int r = 0; r < R; ++r) {
             const int64_t p = base + r * 256 + threadIdx.x;
             bool slow = false;
-            if (tr[r] >= 0)
-                slow = static_cast<int64_t>(ar[r] & 0xFFFFFFFFULL) > bound_of(A.B, tr[r]) - static_cast<int64_t>(wr[r]);
+            if (tr[r] >= 0) {
+                const int64_t room = bound_of(A.B, tr[r]) - static_cast<int64_t>(wr[r]);
+                slow = static_cast<int64_t>(ar[r] & 0xFFFFFFFFULL) > room;
+                wr[r] = static_cast<int32_t>(room);  // used where it is below the candidates' weight
+                ++found;
+            }
             if (p < A.count) A.ok[p] = tr[r] >= 0 && !slow ? 1 : 0;
             if (!slow) tr[r] = -1;
             any |= slow;
@@ -1526,12 +1594,16 @@ __global__ void __launch_bounds__(256) admit_kernel(Admission A) {
         for (int r = 0; r < R; ++r) {
             slot[r] = tr[r] >= 0 ? agg_insert<T>(keys, tr[r]) : 0;
             rank[r] = tr[r] >= 0 ? atomicAdd(&lcnt[slot[r]], 1) : 0;
+            if (tr[r] >= 0) {  // the same values from every candidate of the target
+                lbase[slot[r]] = wr[r];
+                llen[slot[r]] = static_cast<int32_t>(ar[r] >> 32);
+            }
             cr[r] = tr[r] >= 0 ? (A.vw ? A.vw[vr[r]] : 1) : 0;
         }
         __syncthreads();
         for (int j = threadIdx.x; j < T; j += 256) {
             const int32_t t = keys[j];
-            if (t >= 0 && atomicCAS(&A.seg_off[t], -1, -2) == -1) claim_segment(A, t);
+            if (t >= 0 && atomicCAS(&A.seg_off[t], -1, -2) == -1) claim_segment(A, t, llen[j], lbase[j]);
         }
         __syncthreads();
         for (int j = threadIdx.x; j < T; j += 256) {
@@ -1555,7 +1627,7 @@ __global__ void __launch_bounds__(256) admit_kernel(Admission A) {
             gmax = gr[r] > gmax ? gr[r] : gmax;
         }
     }
-    note_gains(A.ctr, gmin, gmax);
+    note_gains(A, found, gmin, gmax);
 }
 
 // The same for at most kDirectLabels labels: the segments' layout follows from
@@ -1619,6 +1691,7 @@ __global__ void __launch_bounds__(256) admit_direct_kernel(Admission A) {
     const int64_t p_begin = blockIdx.x * per + tid;
     const int64_t p_end = blockIdx.x * per + per < A.count ? blockIdx.x * per + per : A.count;
     bool any = false;
+    int32_t found = 0;
     for (int64_t p0 = p_begin; p0 < p_end; p0 += 256 * U) {
         int32_t tr[U];
 #pragma unroll
@@ -1630,17 +1703,18 @@ __global__ void __launch_bounds__(256) admit_direct_kernel(Admission A) {
             A.ok[p0 + u * 256] = tr[u] >= 0 && !slow ? 1 : 0;
             if (slow) atomicAdd(&lcnt[tr[u]], 1);
             any |= slow;
+            found += tr[u] >= 0;
         }
     }
-    if (!__syncthreads_or(any)) return;
-    for (int j = tid; j < A.nw; j += 256) {
+    any = __syncthreads_or(any);
+    for (int j = tid; any && j < A.nw; j += 256) {
         const int32_t c = lcnt[j];
         if (c) lbase[j] += atomicAdd(&A.seg_fill[j << kFillShift], c);
         lcnt[j] = 0;
     }
     __syncthreads();
     int32_t gmin = INT_MAX, gmax = INT_MIN;
-    for (int64_t p0 = p_begin; p0 < p_end; p0 += 256 * U) {
+    for (int64_t p0 = p_begin; any && p0 < p_end; p0 += 256 * U) {
         int32_t tr[U], gr[U], vr[U], cr[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -1664,7 +1738,7 @@ __global__ void __launch_bounds__(256) admit_direct_kernel(Admission A) {
             gmax = gr[u] > gmax ? gr[u] : gmax;
         }
     }
-    note_gains(A.ctr, gmin, gmax);
+    note_gains(A, found, gmin, gmax);
 }
 
 __device__ __forceinline__ int bits_of(uint64_t x) { return x ? 64 - __clzll(static_cast<long long>(x)) : 0; }
@@ -1873,9 +1947,12 @@ __device__ __forceinline__ void arrive(const Admission& A, int32_t t, int32_t c,
 
 constexpr int kFinishThreads = 1024;
 constexpr int kFinishMax = 65536;  // longest segment one workgroup of finish_kernel selects from
-constexpr int kFinishBlocks = 256;
-// small label spaces: every workgroup adds to the same few lines of weights
-constexpr int kFinishBlocksSmall = 96;
+// workgroups for the segments and (at most) for the admitted candidates; in
+// small label spaces every workgroup adds to the same few lines of weights
+constexpr int kSegBlocks = 96;
+constexpr int kMoveBlocks = 192;
+constexpr int kSegBlocksSmall = 32;
+constexpr int kMoveBlocksSmall = 64;
 
 // Moves the admitted candidates, and selects and moves the admitted prefix of
 // every segment of up to small_max entries: the entries whose inclusive
@@ -1888,7 +1965,7 @@ constexpr int kFinishBlocksSmall = 96;
 // ones; one launch for all lengths replaced a scatter, a selection and an
 // apply launch of about 5 us each.
 template <bool kSmall>
-__global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A) {
+__global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uint32_t seg_blocks) {
     constexpr int NT = kFinishThreads;
     constexpr int kPerT = kLBins / NT;
     __shared__ uint32_t hist[kLBins];
@@ -1904,11 +1981,14 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A) {
         for (int j = tid; j < A.nw; j += NT) delta[j] = 0;
         __syncthreads();
     }
-    const uint32_t nseg = static_cast<uint32_t>(A.ctr->segs >> 32);
+    // the first workgroups take the segments, the others the admitted
+    // candidates: both are chains of dependent reads, which then overlap
+    const bool takes_segs = blockIdx.x < seg_blocks;
+    const uint32_t nseg = takes_segs ? static_cast<uint32_t>(A.ctr->segs >> 32) : 0;
     const int32_t gmax = A.ctr->gmax;
     // segments of up to 64 entries, one wave each (bookkeeping of the others)
     for (uint32_t sid = blockIdx.x * (NT / 64) + __builtin_amdgcn_readfirstlane(tid >> 6); sid < nseg;
-         sid += gridDim.x * (NT / 64)) {
+         sid += seg_blocks * (NT / 64)) {
         const Segment sg = A.seg[sid];
         if (lane == 0) {
             if (A.seg_off) A.seg_off[sg.t] = -1;
@@ -1935,7 +2015,7 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A) {
     // longer ones, one workgroup each
     const int total_bits = key_bits(A.ctr, A.bits_v);
     const int passes = total_bits > 0 ? (total_bits + kLDigit - 1) / kLDigit : 1;
-    for (uint32_t sid = blockIdx.x; sid < nseg; sid += gridDim.x) {
+    for (uint32_t sid = blockIdx.x; sid < nseg; sid += seg_blocks) {
         const Segment sg = A.seg[sid];
         if (sg.len <= 64 || sg.len > A.small_max) continue;  // uniform over the workgroup
         // the first entry per thread stays in registers over the passes
@@ -1991,8 +2071,9 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A) {
     // admitted candidates, U grid-stride positions per thread at a time: their
     // loads are issued together, level by level, before the updates
     constexpr int U = 4;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * NT;
-    for (int64_t p0 = static_cast<int64_t>(blockIdx.x) * NT + tid; p0 < A.count; p0 += stride * U) {
+    const int64_t stride = static_cast<int64_t>(gridDim.x - seg_blocks) * NT;
+    for (int64_t p0 = takes_segs ? A.count : static_cast<int64_t>(blockIdx.x - seg_blocks) * NT + tid; p0 < A.count;
+         p0 += stride * U) {
         int32_t tq[U], vq[U], aq[U], cq[U];
         bool oq[U];
 #pragma unroll
@@ -2184,14 +2265,15 @@ __global__ void __launch_bounds__(256) classify_kernel(int32_t n, const int64_t*
     }
 }
 
-// rows[2i] = first slot of nodes[i], rows[2i+1] = its degree
-__global__ void gather_rows_kernel(const int32_t* __restrict__ nodes, int32_t count, const int64_t* __restrict__ xadj,
-                                   int64_t* __restrict__ rows) {
+// The schedule's rows.  A row of 2^31 slots or more does not occur: its slots
+// would be distinct neighbours or repeated edges whose weights sum past 2^31-1.
+__global__ void schedule_rows_kernel(const int32_t* __restrict__ nodes, int32_t count, const int64_t* __restrict__ xadj,
+                                     Row* __restrict__ rows) {
     const int32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i < count) {
-        rows[2 * i] = xadj[nodes[i]];
-        rows[2 * i + 1] = xadj[nodes[i] + 1] - xadj[nodes[i]];
-    }
+    if (i >= count) return;
+    const int32_t v = nodes[i];
+    const int64_t b = xadj[v];
+    rows[i] = Row{b, static_cast<int32_t>(xadj[v + 1] - b), v};
 }
 
 // Per-graph hash prefixes H(seed_g, tag, level, phase[, round]).
@@ -2280,13 +2362,12 @@ struct HubPlan {
     int32_t count = 0;
     int32_t nchunks = 0;
     int32_t nparts = 0;
-    int32_t ntchunks = 0;
     int64_t region_entries = 0;
     int64_t overflow_entries = 0;
     int64_t table_entries = 0;
-    // hub_nodes | plog | pbase[H+1] | cap | tfirst_shifted[H+1] | chunk_hub | part_hub | tchunk_hub
+    // plog | pbase[H+1] | cap | chunk_hub | part_hub
     DBuf<int32_t> i32;
-    // rbase | obase | toff | chunk_begin | tchunk_begin
+    // rbase | obase | toff | chunk_begin
     DBuf<int64_t> i64;
     DBuf<uint32_t> u32;  // tmask
 };
@@ -2442,6 +2523,13 @@ void label_weights(const DevGraph& g, const int32_t* label, int32_t* w, int32_t 
     }
 }
 
+// One lane per node is the cheapest form, but the slowest one when there are
+// too few nodes to fill the device: up to 2^17 nodes only rows of up to 4 slots
+// take it (40 sub-rounds of clustering / of refinement, power-law graph of
+// 2^14 nodes: 1.40 -> 1.14 / 1.64 -> 1.33 ms; of 2^20 nodes: 5.76 -> 5.92 /
+// 4.96 -> 5.11 ms, so larger graphs keep 16).
+int32_t default_lane_max(int32_t n) { return n <= (1 << 17) ? kLaneSmall : kLaneMax; }
+
 LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, int32_t nsub, int32_t rounds,
                 int64_t bound, int32_t* label, int32_t* w, int32_t nw, const int32_t* color_override,
                 const LPTuning& tune, hipStream_t s, const MultiGraph* mg) {
@@ -2456,7 +2544,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     const int32_t ncat = nsub * kNB;
     Thresholds th;
     {
-        const int32_t lane = std::max(1, std::min(tune.lane_max, kLaneMax));
+        const int32_t lane = std::max(1, std::min(tune.lane_max > 0 ? tune.lane_max : default_lane_max(n), kLaneMax));
         const int32_t wave = std::max(lane, std::min(tune.wave_max, kWaveMaxDeg));
         const int32_t block = std::max(wave, std::min(tune.block_max, kBlockMaxDeg));
         th.t[0] = std::min(kLaneSmall, lane);
@@ -2514,6 +2602,11 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     for (int32_t j = 0; j <= ncat; ++j) off[j + 1] = off[j] + cnt[j];
     const int32_t* nodes = reinterpret_cast<const int32_t*>(order.get());
 
+    DBuf<Row> sched(n, s);
+    const Row* rows = sched.get();
+    schedule_rows_kernel<<<grid_for(n, 256), 256, 0, s>>>(nodes, n, g.xadj, sched.get());
+    LAUNCHCHK();
+
     // --- hub plans per colour
     std::vector<HubPlan> plans(nsub);
     int64_t max_region = 0, max_over = 0, max_table = 0, max_win = 0, max_hub_ints = 0;
@@ -2527,25 +2620,19 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
         HubPlan& P = plans[sc];
         P.count = H;
         if (H == 0) continue;
-        std::vector<int32_t> hn(H);
-        std::vector<int64_t> rows(2 * static_cast<size_t>(H)), hd(H), xs(H);
-        HIPCHK(hipMemcpyAsync(hn.data(), nodes + off[cat], H * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        {
-            DBuf<int64_t> drows(2 * static_cast<size_t>(H), s);
-            gather_rows_kernel<<<grid_for(H, 256), 256, 0, s>>>(nodes + off[cat], H, g.xadj, drows.get());
-            LAUNCHCHK();
-            HIPCHK(hipMemcpyAsync(rows.data(), drows.get(), 2 * H * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
-        }
+        std::vector<Row> hrow(H);
+        HIPCHK(hipMemcpyAsync(hrow.data(), rows + off[cat], H * sizeof(Row), hipMemcpyDeviceToHost, s));
+        HIPCHK(hipStreamSynchronize(s));
+        std::vector<int64_t> hd(H), xs(H);
         for (int32_t h = 0; h < H; ++h) {
-            xs[h] = rows[2 * h];
-            hd[h] = rows[2 * h + 1];
+            xs[h] = hrow[h].begin;
+            hd[h] = hrow[h].deg;
         }
-        std::vector<int32_t> plog(H), pbase(H + 1), cap(H), tfirst(H + 1), chub, phub, thub;
-        std::vector<int64_t> rbase(H), obase(H), toff(H), cbeg, tbeg;
+        std::vector<int32_t> plog(H), pbase(H + 1), cap(H), chub, phub;
+        std::vector<int64_t> rbase(H), obase(H), toff(H), cbeg;
         std::vector<uint32_t> tmask(H);
         int64_t rtot = 0, otot = 0, ttot = 0;
-        int32_t np = 0, ntc = 0;
+        int32_t np = 0;
         for (int32_t h = 0; h < H; ++h) {
             // at most 1024 entries per label partition on average (half the
             // LDS table's limit), at most 2048 partitions
@@ -2570,29 +2657,19 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 chub.push_back(h);
                 cbeg.push_back(xs[h] + sl);
             }
-            tfirst[h] = ntc;
-            for (int64_t e = 0; e < static_cast<int64_t>(tsz); e += kHubTChunk) {
-                thub.push_back(h);
-                tbeg.push_back(ttot + e);
-                ++ntc;
-            }
             ttot += static_cast<int64_t>(tsz);
         }
         pbase[H] = np;
-        tfirst[H] = ntc;
         P.nchunks = static_cast<int32_t>(chub.size());
         P.nparts = np;
-        P.ntchunks = ntc;
         P.region_entries = rtot;
         P.overflow_entries = otot;
         P.table_entries = ttot;
-        // table-chunk winners are stored after the partition winners
-        for (int32_t h = 0; h <= H; ++h) tfirst[h] += np;
         std::vector<int32_t> i32;
-        for (const auto* vec : {&hn, &plog, &pbase, &cap, &tfirst, &chub, &phub, &thub})
+        for (const auto* vec : {&plog, &pbase, &cap, &chub, &phub})
             i32.insert(i32.end(), vec->begin(), vec->end());
         std::vector<int64_t> i64;
-        for (const auto* vec : {&rbase, &obase, &toff, &cbeg, &tbeg}) i64.insert(i64.end(), vec->begin(), vec->end());
+        for (const auto* vec : {&rbase, &obase, &toff, &cbeg}) i64.insert(i64.end(), vec->begin(), vec->end());
         P.i32.alloc(i32.size(), s);
         P.i64.alloc(i64.size(), s);
         P.u32.alloc(tmask.size(), s);
@@ -2603,7 +2680,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
         max_region = std::max(max_region, rtot);
         max_over = std::max(max_over, otot);
         max_table = std::max(max_table, ttot);
-        max_win = std::max(max_win, static_cast<int64_t>(np) + ntc);
+        max_win = std::max(max_win, static_cast<int64_t>(np));
         max_hub_ints = std::max(max_hub_ints, static_cast<int64_t>(np) + 3 * static_cast<int64_t>(H));
     }
     DBuf<int32_t> ekeys, evals, okeys, ovals, gkeys, gvals, hub_ints, w_conn, w_x;
@@ -2616,6 +2693,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
         gkeys.alloc(max_table, s);
         gvals.alloc(max_table, s);
         hub_ints.alloc(max_hub_ints, s);
+        fill_i32(hub_ints.get(), 0, max_hub_ints, s);
         w_conn.alloc(max_win, s);
         w_x.alloc(max_win, s);
         w_tie.alloc(max_win, s);
@@ -2665,7 +2743,6 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     LAUNCHCHK();
 
     EvalArgs A;
-    A.xadj = g.xadj;
     A.adj = g.adj;
     A.S = g.S;
     A.ew = g.ew;
@@ -2808,26 +2885,21 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             // longest, so its workgroups should be dispatched before the
             // other buckets fill the device
             const HubPlan& P = plans[sc];
-            const hipStream_t hs = s;
+            HubArgs H = {};
             if (P.count > 0) {
                 const int32_t Hn = P.count;
-                HubArgs H;
+                H.count = Hn;
                 const int32_t* i32 = P.i32.get();
-                H.hub_nodes = i32;
-                H.hub_plog = i32 + Hn;
-                H.hub_pbase = i32 + 2 * Hn;
-                H.hub_cap = i32 + 3 * Hn + 1;
-                const int32_t* tfirst_shifted = i32 + 4 * Hn + 1;
-                H.hub_tfirst = tfirst_shifted;
-                H.chunk_hub = i32 + 5 * Hn + 2;
+                H.hub_plog = i32;
+                H.hub_pbase = i32 + Hn;
+                H.hub_cap = i32 + 2 * Hn + 1;
+                H.chunk_hub = i32 + 3 * Hn + 1;
                 H.part_hub = H.chunk_hub + P.nchunks;
-                H.tchunk_hub = H.part_hub + P.nparts;
                 const int64_t* i64 = P.i64.get();
                 H.hub_rbase = i64;
                 H.hub_obase = i64 + Hn;
                 H.hub_toff = i64 + 2 * Hn;
                 H.chunk_begin = i64 + 3 * Hn;
-                H.tchunk_begin = H.chunk_begin + P.nchunks;
                 H.hub_tmask = P.u32.get();
                 H.rcount = hub_ints.get();
                 H.ocount = H.rcount + P.nparts;
@@ -2843,77 +2915,90 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 H.w_tie = w_tie.get();
                 H.w_x = w_x.get();
                 H.part_limit = std::max(1, std::min(tune.hub_part_limit, kPartTable / 2));
-                fill_i32(H.rcount, 0, static_cast<int64_t>(P.nparts) + 3 * Hn, hs);
-                A.nodes = H.hub_nodes;
-                A.count = Hn;
-                A.ct = ct.get() + (off[c0 + kHubBucket] - off[c0]);
-                A.cg = cg.get() + (off[c0 + kHubBucket] - off[c0]);
-                if (dense) {
-                    ProfScope ps("lp_refine_hub_dense", eval_bytes(Hn, cslots[c0 + kHubBucket]), hs);
-                    hub_dense_chunk_kernel<<<P.nchunks, kHubThreads, 0, hs>>>(A, H, hub_sum.get());
-                    LAUNCHCHK();
-                    hub_dense_finish_kernel<<<Hn, 256, 0, hs>>>(A, H, hub_sum.get());
-                    LAUNCHCHK();
-                } else {
-                {
-                    ProfScope ps(A.refine ? "lp_refine_hub_chunk" : "lp_eval_hub_chunk", eval_bytes(Hn, cslots[c0 + kHubBucket]), hs);
-                    hub_chunk_kernel<<<P.nchunks, kHubThreads, 0, hs>>>(A, H);
-                    LAUNCHCHK();
+                H.hub_sum = hub_sum.get();
+            }
+            FusedBuckets F;
+            for (int32_t bk = 0; bk < kNB; ++bk) {
+                F.rows[bk] = rows + off[c0 + bk];
+                F.ct[bk] = ct.get() + (off[c0 + bk] - off[c0]);
+                F.cg[bk] = cg.get() + (off[c0 + bk] - off[c0]);
+                F.count[bk] = static_cast<int32_t>(off[c0 + bk + 1] - off[c0 + bk]);
+                F.end[bk] = 0;
+            }
+            auto use_bucket = [&](int32_t bk) {
+                A.rows = F.rows[bk];
+                A.count = F.count[bk];
+                A.ct = F.ct[bk];
+                A.cg = F.cg[bk];
+            };
+            // workgroups of buckets hi..lo, the longest rows first
+            auto lay_out = [&](int32_t hi, int32_t lo, double* bytes) {
+                static const int32_t kPerBlock[kNB] = {256, 256, 16, 8, 4, 1, 1, 1, 1};  // nodes per workgroup
+                int32_t blocks = 0;
+                *bytes = 0;
+                for (int32_t bk = hi; bk >= lo; --bk) {
+                    blocks += bk == kHubBucket ? P.nchunks : (F.count[bk] + kPerBlock[bk] - 1) / kPerBlock[bk];
+                    F.end[bk] = blocks;
+                    *bytes += eval_bytes(F.count[bk], cslots[c0 + bk]);
                 }
-                {
-                    ProfScope ps(A.refine ? "lp_refine_hub_part" : "lp_eval_hub_part", 0, hs);
-                    hub_part_kernel<<<P.nparts, kPartThreads, 0, hs>>>(A, H);
+                return blocks;
+            };
+            // a small colour: the buckets of small tables in one launch, the
+            // others in a second one
+            const bool fused = !side && tune.fuse >= 0;
+            // A small colour without hubs counts its candidates as the results
+            // are stored: one launch less.  Adds to one address are served one
+            // every 12 ns, so the colour has at most 2^14 nodes and its
+            // candidates at least eight targets to spread over.
+            const bool count_in_eval = fused && P.count == 0 && ccount <= kCountInEval && nw >= 8;
+            A.acc = count_in_eval ? acc.get() : nullptr;
+            A.acc_shift = direct ? kAccShift : 0;
+            const bool big = fused && !dense && tune.block_table != kBlockTablePow2;
+            int32_t bk_from = 0;
+            if (fused) {
+                bk_from = dense ? kNB : kFusedHash;
+                double bytes;
+                const int32_t blocks = lay_out(bk_from - 1, 0, &bytes);
+                if (blocks > 0) {
+                    ProfScope ps(A.refine ? "lp_refine_fused" : "lp_eval_fused", bytes, s);
+                    if (dense) eval_fused_kernel<true><<<blocks, 256, 0, s>>>(A, F, H);
+                    else eval_fused_kernel<false><<<blocks, 256, 0, s>>>(A, F, H);
                     LAUNCHCHK();
-                    hub_finish_kernel<<<Hn, 64, 0, hs>>>(A, H);
-                    LAUNCHCHK();
-                }
-                {
-                    ProfScope ps(A.refine ? "lp_refine_hub_table" : "lp_eval_hub_table", 0, hs);
-                    hub_clear_kernel<<<P.ntchunks, 256, 0, hs>>>(H);
-                    LAUNCHCHK();
-                    hub_table_insert_kernel<<<P.nparts, 256, 0, hs>>>(H);
-                    LAUNCHCHK();
-                    hub_scan_kernel<<<P.ntchunks, 256, 0, hs>>>(A, H, P.nparts);
-                    LAUNCHCHK();
-                    hub_big_finish_kernel<<<Hn, 64, 0, hs>>>(A, H, tfirst_shifted);
-                    LAUNCHCHK();
-                }
                 }
             }
-            int32_t bk_from = 0;
-            if (!side && tune.fuse >= 0) {  // buckets 0..5 of a small colour in one launch
-                FusedBuckets F;
-                static const int32_t kPerBlock[kFusedBuckets] = {256, 256, 16, 8, 4, 1};  // nodes per workgroup
-                int32_t blocks = 0, fnodes = 0;
-                unsigned long long fslots = 0;
-                for (int32_t bk = 0; bk < kFusedBuckets; ++bk) {
-                    const int64_t count = off[c0 + bk + 1] - off[c0 + bk];
-                    F.nodes[bk] = nodes + off[c0 + bk];
-                    F.ct[bk] = ct.get() + (off[c0 + bk] - off[c0]);
-                    F.cg[bk] = cg.get() + (off[c0 + bk] - off[c0]);
-                    F.count[bk] = static_cast<int32_t>(count);
-                    F.first[bk] = blocks;
-                    blocks += static_cast<int32_t>((count + kPerBlock[bk] - 1) / kPerBlock[bk]);
-                    fnodes += static_cast<int32_t>(count);
-                    fslots += cslots[c0 + bk];
-                }
-                F.first[kFusedBuckets] = blocks;
+            if (big) {
+                double bytes;
+                const int32_t blocks = lay_out(kHubBucket, kFusedHash, &bytes);
+                bk_from = kNB;
                 if (blocks > 0) {
-                    ProfScope ps(A.refine ? "lp_refine_fused" : "lp_eval_fused", eval_bytes(fnodes, fslots), s);
-                    if (dense) eval_fused_kernel<true><<<blocks, 256, 0, s>>>(A, F);
-                    else eval_fused_kernel<false><<<blocks, 256, 0, s>>>(A, F);
+                    ProfScope ps(A.refine ? "lp_refine_big" : "lp_eval_big", bytes, s);
+                    eval_big_kernel<<<blocks, kHubThreads, 0, s>>>(A, F, H);
                     LAUNCHCHK();
                 }
-                bk_from = kFusedBuckets;
+            }
+            if (P.count > 0 && !(fused && dense)) {
+                use_bucket(kHubBucket);
+                if (dense) {
+                    ProfScope ps("lp_refine_hub_dense", eval_bytes(P.count, cslots[c0 + kHubBucket]), s);
+                    hub_dense_chunk_kernel<<<P.nchunks, kHubThreads, 0, s>>>(A, H);
+                    LAUNCHCHK();
+                } else {
+                    if (!big) {
+                        ProfScope ps(A.refine ? "lp_refine_hub_chunk" : "lp_eval_hub_chunk",
+                                     eval_bytes(P.count, cslots[c0 + kHubBucket]), s);
+                        hub_chunk_kernel<<<P.nchunks, kHubThreads, 0, s>>>(A, H);
+                        LAUNCHCHK();
+                    }
+                    ProfScope ps(A.refine ? "lp_refine_hub_part" : "lp_eval_hub_part", 0, s);
+                    hub_part_kernel<<<P.nparts, kPartThreads, 0, s>>>(A, H);
+                    LAUNCHCHK();
+                }
             }
             for (int32_t bk = bk_from; bk < kHubBucket; ++bk) {
                 const hipStream_t bs = side ? evs.bucket(bk) : s;
-                const int64_t count = off[c0 + bk + 1] - off[c0 + bk];
+                const int64_t count = F.count[bk];
                 if (count == 0) continue;
-                A.nodes = nodes + off[c0 + bk];
-                A.count = static_cast<int32_t>(count);
-                A.ct = ct.get() + (off[c0 + bk] - off[c0]);
-                A.cg = cg.get() + (off[c0 + bk] - off[c0]);
+                use_bucket(bk);
                 static const char* const kNames[2][kHubBucket] = {
                     {"lp_eval_lane4", "lp_eval_lane16", "lp_eval_group16", "lp_eval_group32", "lp_eval_wave",
                      "lp_eval_block1k", "lp_eval_block4k", "lp_eval_block8k"},
@@ -2962,19 +3047,23 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             M.ctr = ctr.get() + (step & 1);
             M.ctr_next = ctr.get() + (~step & 1);
             M.gate = gate;
+            M.round_cnt = rcnt.get() + r;
             ++step;
             const int per = ccount <= (1 << 16) ? 1 : (ccount <= (1 << 18) ? 4 : 8);
             const unsigned gc = static_cast<unsigned>(std::min<int64_t>(grid_for(ccount, 256 * per), kMaxBlocks));
             {
                 ProfScope ps(A.refine ? "lp_refine_admit" : "lp_admit", 0, s);
-                auto accum = direct ? (per == 1   ? accumulate_kernel<true, 1>
-                                       : per == 4 ? accumulate_kernel<true, 4>
-                                                  : accumulate_kernel<true, 8>)
-                                    : (per == 1   ? accumulate_kernel<false, 1>
-                                       : per == 4 ? accumulate_kernel<false, 4>
-                                                  : accumulate_kernel<false, 8>);
-                accum<<<gc, 256, 0, s>>>(ct.get(), cnodes, M.count, g.vw, acc.get(), nw, gate, rcnt.get() + r);
-                LAUNCHCHK();
+                if (!count_in_eval) {
+                    auto accum = direct ? (per == 1   ? accumulate_kernel<true, 1>
+                                           : per == 4 ? accumulate_kernel<true, 4>
+                                                      : accumulate_kernel<true, 8>)
+                                        : (per == 1   ? accumulate_kernel<false, 1>
+                                           : per == 4 ? accumulate_kernel<false, 4>
+                                                      : accumulate_kernel<false, 8>);
+                    use_bucket(kHubBucket);
+                    accum<<<gc + H.count, 256, 0, s>>>(A, H, ct.get(), cnodes, M.count - H.count, acc.get(), nw);
+                    LAUNCHCHK();
+                }
                 auto admit = direct     ? admit_direct_kernel
                              : per == 1 ? admit_kernel<1>
                              : per == 4 ? admit_kernel<4>
@@ -2994,12 +3083,11 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             }
             {
                 ProfScope ps("lp_apply", 0, s);
-                // at least 64 workgroups, whose waves share the short segments
-                const unsigned gf = static_cast<unsigned>(
-                    std::min<int64_t>(std::max<int64_t>(grid_for(ccount, kFinishThreads), 64),
-                                      small ? kFinishBlocksSmall : kFinishBlocks));
-                if (small) finish_kernel<true><<<gf, kFinishThreads, 0, s>>>(M);
-                else finish_kernel<false><<<gf, kFinishThreads, 0, s>>>(M);
+                const unsigned gseg = small ? kSegBlocksSmall : kSegBlocks;
+                const unsigned gmov = static_cast<unsigned>(std::min<int64_t>(
+                    grid_for(ccount, kFinishThreads), small ? kMoveBlocksSmall : kMoveBlocks));
+                if (small) finish_kernel<true><<<gseg + gmov, kFinishThreads, 0, s>>>(M, gseg);
+                else finish_kernel<false><<<gseg + gmov, kFinishThreads, 0, s>>>(M, gseg);
                 LAUNCHCHK();
             }
             // a target has at most ccount candidates: no longer segment

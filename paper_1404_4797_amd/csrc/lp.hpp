@@ -20,7 +20,7 @@ struct DevGraph {
 };
 
 struct LPTuning {
-    int32_t lane_max = 16;    // <= 16
+    int32_t lane_max = 0;     // <= 16; 0: by the number of nodes
     int32_t wave_max = 256;   // <= 256
     int32_t block_max = 8192; // <= 8192
     int32_t hub_part_limit = 4096;  // <= 4096; larger hub partitions use the HBM table
@@ -60,6 +60,9 @@ struct LPResult {
 LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, int32_t nsub, int32_t rounds,
                 int64_t bound, int32_t* label, int32_t* w, int32_t nw, const int32_t* color_override,
                 const LPTuning& tune, hipStream_t s, const MultiGraph* mg = nullptr);
+
+// The row length up to which a graph of n nodes evaluates one node per lane.
+int32_t default_lane_max(int32_t n);
 
 // w[x] = sum of c(v) over label(v) = x, for x in [0, nw).
 void label_weights(const DevGraph& g, const int32_t* label, int32_t* w, int32_t nw, hipStream_t s);

@@ -1,4 +1,5 @@
-"""Admission at the sizes where its kernels change: segment lengths around one
+"""Evaluation and admission at the sizes where their kernels change: row lengths
+around every bucket, segment lengths around one
 wave, one entry per thread, one workgroup's limit, and colours and label spaces
 around the limits of the per-thread entry counts and of the direct LDS sums.
 Integer results, compared with the oracle element by element."""
@@ -56,3 +57,39 @@ def test_label_spaces(sc, n, k):
     p, rr = sc.refine_dev(sc.to_device(g), k, lmax, torch.from_numpy(part.copy()).cuda(), rounds=2, seed=k, subrounds=1)
     ref, rr_ref, _ = oracle.refine(g, k, lmax, part, rounds=2, seed=k, nsub=1)
     assert rr == rr_ref and np.array_equal(p.cpu().numpy(), ref)
+
+
+def centres(n, degrees, seed):
+    """One node per entry of ``degrees`` joined to that many others, every bucket's first and last row length."""
+    rng = np.random.default_rng(seed)
+    k = len(degrees)
+    u = np.repeat(np.arange(k), degrees)
+    v = np.concatenate([k + rng.choice(n - k, size=d, replace=False) for d in degrees])
+    w = rng.integers(1, 5, size=len(u))
+    src, dst, wt = np.concatenate([u, v]), np.concatenate([v, u]), np.concatenate([w, w])
+    order = np.argsort(src * n + dst)
+    xadj = np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int64)
+    return {"n": n, "xadj": xadj, "adjncy": dst[order].astype(np.int32), "adjwgt": wt[order].astype(np.int32),
+            "vwgt": np.ones(n, dtype=np.int32)}
+
+
+DEGREES = [1, 4, 5, 16, 17, 32, 33, 64, 65, 256, 257, 1024, 1025, 4096, 4097, 8192, 8193, 16385, 25000]
+
+
+@pytest.mark.parametrize("k", [0, 3, 64, 300])
+@pytest.mark.parametrize("knobs", [dict(), dict(lane_max_degree=16), dict(fused_eval=-1), dict(block_table=16384),
+                                   dict(hub_part_limit=1), dict(skip_quiet=1)])
+def test_row_lengths(sc, k, knobs):
+    g = centres(30000, DEGREES, 7)
+    d = sc.to_device(g)
+    for nsub in (1, 4):
+        if k == 0:  # clustering
+            lab, rr = sc.cluster_dev(d, 40, rounds=3, seed=5, subrounds=nsub, **knobs)
+            ref, rr_ref, _ = oracle.cluster(g, 40, rounds=3, seed=5, nsub=nsub)
+        else:
+            part = np.random.default_rng(k).integers(0, k, size=g["n"]).astype(np.int32)
+            lmax = -(-g["n"] // k) + g["n"] // (8 * k)
+            lab, rr = sc.refine_dev(d, k, lmax, torch.from_numpy(part.copy()).cuda(), rounds=3, seed=5, subrounds=nsub,
+                                    **knobs)
+            ref, rr_ref, _ = oracle.refine(g, k, lmax, part, rounds=3, seed=5, nsub=nsub)
+        assert rr == rr_ref and np.array_equal(lab.cpu().numpy(), ref)
