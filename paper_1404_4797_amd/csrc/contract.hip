@@ -898,8 +898,7 @@ void hash_block_rows(const int32_t* list, uint32_t count, const int64_t* rowoff,
         list, count, rowcnt, sub.get(), count, cnt.get());
     LAUNCHCHK();
     uint32_t hc[5];
-    HIPCHK(hipMemcpyAsync(hc, cnt.get(), sizeof(hc), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(hc, cnt.get(), sizeof(hc), s);
     const int32_t* l = sub.get();
     if (hc[0]) block_hash_rows_kernel<512><<<hc[0], 256, 0, s>>>(l, rowoff, rowcnt, tk, tw, dcnt);
     if (hc[1]) block_hash_rows_kernel<1024><<<hc[1], 256, 0, s>>>(l + count, rowoff, rowcnt, tk, tw, dcnt);
@@ -922,8 +921,7 @@ bool bucket_merge_long_rows(uint32_t nl, const int32_t* llist, int64_t nch, cons
     LAUNCHCHK();
     exclusive_scan_i32_to_i64(nbk.get(), bfirst.get(), nl, tot.get(), s);
     int64_t NB = 0;
-    HIPCHK(hipMemcpyAsync(&NB, tot.get(), sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&NB, tot.get(), sizeof(int64_t), s);
     if (NB == 0) return true;  // every long row was one chunk
     fill_i64(bfirst.get() + nl, NB, 1, s);
     DBuf<int32_t> brow(NB, s), bcount(NB, s), bfill(NB, s), qcnt(NB, s);
@@ -948,8 +946,7 @@ bool bucket_merge_long_rows(uint32_t nl, const int32_t* llist, int64_t nch, cons
                                                                       overflow.get());
     LAUNCHCHK();
     uint32_t over = 0;
-    HIPCHK(hipMemcpyAsync(&over, overflow.get(), sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&over, overflow.get(), sizeof(uint32_t), s);
     if (over) return false;
     exclusive_scan_i32_to_i64(qcnt.get(), qoff.get(), NB, tot.get() + 1, s);
     HIPCHK(hipMemcpyAsync(qoff.get() + NB, tot.get() + 1, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
@@ -976,8 +973,7 @@ void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* row
         row_classify_kernel<<<std::min(grid_for(nc, 256 * kClassifyIters), 1024u), 256, 0, s>>>(
             nc, rowcnt, dcnt, lists.get(), nc, counts.get());
         LAUNCHCHK();
-        HIPCHK(hipMemcpyAsync(hc, counts.get(), sizeof(hc), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        read_back(hc, counts.get(), sizeof(hc), s);
         if (hc[0] > 0) {
             wave_rows_kernel<<<grid_for(static_cast<int64_t>(hc[0]) * 64, 256), 256, 0, s>>>(
                 lists.get(), hc[0], rowoff, rowcnt, tk, tw, dcnt);
@@ -1002,8 +998,7 @@ void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* row
         LAUNCHCHK();
         exclusive_scan_i32_to_i64(lens.get(), cfirst.get(), nl, ctot.get(), s);
         int64_t nch = 0;
-        HIPCHK(hipMemcpyAsync(&nch, ctot.get(), sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        read_back(&nch, ctot.get(), sizeof(int64_t), s);
         fill_i64(cfirst.get() + nl, nch, 1, s);
         DBuf<int32_t> crow(nch, s), ccnt(nch, s);
         DBuf<int64_t> coff(static_cast<size_t>(nch) + 1, s), mtot2(1, s), loff(static_cast<size_t>(nl) + 1, s);
@@ -1017,8 +1012,7 @@ void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* row
         }
         exclusive_scan_i32_to_i64(ccnt.get(), coff.get(), nch, mtot2.get(), s);
         int64_t ml = 0;
-        HIPCHK(hipMemcpyAsync(&ml, mtot2.get(), sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        read_back(&ml, mtot2.get(), sizeof(int64_t), s);
         fill_i64(coff.get() + nch, ml, 1, s);
         long_offsets_kernel<<<grid_for(static_cast<int64_t>(nl) + 1, 256), 256, 0, s>>>(nl, cfirst.get(), coff.get(),
                                                                                          loff.get());
@@ -1037,9 +1031,9 @@ void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* row
             inclusive_scan_i64(tsz.get(), toff.get() + 1, nl, s);
             inclusive_scan_i64(tch.get(), tcfirst.get() + 1, nl, s);
             int64_t hts[2] = {0, 0};
-            HIPCHK(hipMemcpyAsync(&hts[0], toff.get() + nl, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipMemcpyAsync(&hts[1], tcfirst.get() + nl, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
+            const ReadItem items[2] = {{&hts[0], toff.get() + nl, sizeof(int64_t)},
+                                       {&hts[1], tcfirst.get() + nl, sizeof(int64_t)}};
+            read_back(items, 2, s);
             const int64_t ttot = hts[0], nq = hts[1];
             DBuf<int32_t> gk(ttot, s), gv(ttot, s), tl(nq, s), qcnt(nq, s);
             DBuf<int64_t> qoff(static_cast<size_t>(nq) + 1, s), qt(1, s);
@@ -1122,8 +1116,7 @@ void contract(const DevGraph& g, const int32_t* labels, int32_t* C, OwnedDevGrap
         LAUNCHCHK();
     }
     int32_t nc = 0;
-    HIPCHK(hipMemcpyAsync(&nc, total.get(), sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&nc, total.get(), sizeof(int32_t), s);
     coarse.n = nc;
     coarse.vw.alloc(nc, s);
     fill_i32(coarse.vw.get(), 0, nc, s);
@@ -1152,8 +1145,7 @@ void contract(const DevGraph& g, const int32_t* labels, int32_t* C, OwnedDevGrap
         LAUNCHCHK();
     }
     exclusive_scan_i32_to_i64(rowcnt.get(), rowoff.get(), nc, mtot.get(), s);
-    HIPCHK(hipMemcpyAsync(&m, mtot.get(), sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&m, mtot.get(), sizeof(int64_t), s);
     if (m == 0) {
         coarse.S = 0;
         coarse.adj.alloc(1, s);
@@ -1187,8 +1179,7 @@ void contract(const DevGraph& g, const int32_t* labels, int32_t* C, OwnedDevGrap
     DBuf<int64_t> stot(1, s);
     exclusive_scan_i32_to_i64(dcnt.get(), coarse.xadj.get(), nc, stot.get(), s);
     int64_t Sc = 0;
-    HIPCHK(hipMemcpyAsync(&Sc, stot.get(), sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&Sc, stot.get(), sizeof(int64_t), s);
     fill_i64(coarse.xadj.get() + nc, Sc, 1, s);
     coarse.S = Sc;
     coarse.adj.alloc(std::max<int64_t>(Sc, 1), s);

@@ -78,8 +78,7 @@ DevGraph dev_view(const sclap_graph* g, hipStream_t s) {
     d.vw = g->vwgt;
     if (g->n > 0) {
         if (!g->xadj) fail(SCLAP_ERR_INVALID, "xadj is NULL");
-        HIPCHK(hipMemcpyAsync(&d.S, g->xadj + g->n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        read_back(&d.S, g->xadj + g->n, sizeof(int64_t), s);
         if (d.S < 0) fail(SCLAP_ERR_INVALID, "xadj[n] < 0");
         if (d.S > 0 && !g->adjncy) fail(SCLAP_ERR_INVALID, "adjncy is NULL");
     }
@@ -1368,8 +1367,7 @@ LPResult batch_device_initial(const DevGraph& g, const int32_t* gid, const std::
     LAUNCHCHK();
     exclusive_scan_i32(flag.get(), rank.get(), n, tot.get(), s);
     int32_t ncand = 0;
-    HIPCHK(hipMemcpyAsync(&ncand, tot.get(), sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&ncand, tot.get(), sizeof(int32_t), s);
     if (ncand > 0) {
         DBuf<uint64_t> keys(ncand, s), ktmp(ncand, s);
         DBuf<uint32_t> vals(ncand, s), vtmp(ncand, s);
@@ -1384,8 +1382,7 @@ LPResult batch_device_initial(const DevGraph& g, const int32_t* gid, const std::
         radix_sort_pairs(keys.get(), vals.get(), ktmp.get(), vtmp.get(), ncand, 0,
                          std::max(1, bits_for(static_cast<uint64_t>(std::max(G - 1, 1)))), rs, s);
         std::vector<int32_t> gc(G), start(G, 0);
-        HIPCHK(hipMemcpyAsync(gc.data(), d_gcount.get(), G * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        read_back(gc.data(), d_gcount.get(), G * sizeof(int32_t), s);
         for (int32_t x = 1; x < G; ++x) start[x] = start[x - 1] + gc[x - 1];
         upload_vec(d_start, start, s);
         batch_place_seeds_kernel<<<grid_for(ncand, 256), 256, 0, s>>>(ncand, vals.get(), gid, d_start.get(),
@@ -1411,8 +1408,7 @@ LPResult batch_device_initial(const DevGraph& g, const int32_t* gid, const std::
                               &mg);
     // pools fill their graph's remaining room
     std::vector<int32_t> hw(static_cast<size_t>(std::max(K2, 1)));
-    HIPCHK(hipMemcpyAsync(hw.data(), w.get(), std::max(K2, 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(hw.data(), w.get(), std::max(K2, 1) * sizeof(int32_t), s);
     std::vector<int64_t> cum(static_cast<size_t>(std::max(K2, 1)), 0);
     for (int32_t x = 0; x < G; ++x) {
         if (!act[x]) continue;
@@ -1612,8 +1608,7 @@ int partition_batch_impl(const DevGraph& g0_in, int32_t G, const int32_t* node_b
             OwnedDevGraph coarse;
             contract(B.g, labels.get(), C.get(), coarse, s, probe.get(), M + 1, qb.get(), false, o.bucket_mean);
             std::vector<int32_t> cb(M + 1);
-            HIPCHK(hipMemcpyAsync(cb.data(), qb.get(), (M + 1) * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
+            read_back(cb.data(), qb.get(), (M + 1) * sizeof(int32_t), s);
             labels.release();
             std::vector<int32_t> keep;
             for (int32_t m = 0; m < M; ++m) {

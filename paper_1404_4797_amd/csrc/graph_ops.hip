@@ -220,8 +220,7 @@ void cut_and_weights(const DevGraph& g, const int32_t* part, int32_t k, int64_t*
         LAUNCHCHK();
     }
     std::vector<unsigned long long> h(1 + static_cast<size_t>(k));
-    HIPCHK(hipMemcpyAsync(h.data(), acc.get(), h.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(h.data(), acc.get(), h.size() * sizeof(unsigned long long), s);
     *cut = static_cast<int64_t>(h[0] / 2);
     for (int32_t b = 0; b < k; ++b) bw[b] = static_cast<int64_t>(h[1 + b]);
 }
@@ -377,9 +376,8 @@ int validate_graph(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s)
     }
     if (!g.xadj) return -1;
     int64_t ends[2];
-    HIPCHK(hipMemcpyAsync(&ends[0], g.xadj, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(&ends[1], g.xadj + n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    const ReadItem items[2] = {{&ends[0], g.xadj, sizeof(int64_t)}, {&ends[1], g.xadj + n, sizeof(int64_t)}};
+    read_back(items, 2, s);
     if (ends[0] != 0 || ends[1] != g.S || g.S < 0) return -1;
     if (g.S > 0 && !g.adj) return -1;
     DBuf<VStats> st(1, s);
@@ -387,16 +385,14 @@ int validate_graph(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s)
     validate_nodes_kernel<<<capped_nodes(n), kTileThreads, 0, s>>>(n, g.xadj, g.vw, st.get());
     LAUNCHCHK();
     VStats h;
-    HIPCHK(hipMemcpyAsync(&h, st.get(), sizeof(VStats), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&h, st.get(), sizeof(VStats), s);
     if (h.bad) return -1;  // offsets not monotone or negative node weight
     if (g.S > 0) {
         TileRows tr(g.xadj, n, g.S, s);  // offsets checked monotone above
         validate_slots_kernel<<<capped_tiles(g.S), kTileThreads, 0, s>>>(g.xadj, g.adj, g.ew, n, g.S, st.get(),
                                                                           tr.trow.get());
         LAUNCHCHK();
-        HIPCHK(hipMemcpyAsync(&h, st.get(), sizeof(VStats), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        read_back(&h, st.get(), sizeof(VStats), s);
     }
     if (h.bad) return -1;
     if (h.cV > 2147483647ULL || h.wsum / 2 > 2147483647ULL) return -3;
@@ -417,8 +413,7 @@ void node_weight_stats(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_
     validate_nodes_kernel<<<capped_nodes(g.n), kTileThreads, 0, s>>>(g.n, g.xadj, g.vw, st.get());
     LAUNCHCHK();
     VStats h;
-    HIPCHK(hipMemcpyAsync(&h, st.get(), sizeof(VStats), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&h, st.get(), sizeof(VStats), s);
     *cV = static_cast<int64_t>(h.cV);
     *cmax = h.cmax;
 }
@@ -431,8 +426,7 @@ bool all_in_range(const int32_t* a, int64_t count, int32_t lo, int32_t hi, hipSt
                                                                                                     bad.get());
     LAUNCHCHK();
     uint32_t h = 0;
-    HIPCHK(hipMemcpyAsync(&h, bad.get(), sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&h, bad.get(), sizeof(uint32_t), s);
     return h == 0;
 }
 
@@ -659,8 +653,7 @@ std::vector<int64_t> member_slot_bases(const int64_t* xadj, const std::vector<in
     HIPCHK(hipMemcpyAsync(pos.get(), nb.data(), M1 * sizeof(int32_t), hipMemcpyHostToDevice, s));
     gather_offsets_kernel<<<grid_for(M1, 256), 256, 0, s>>>(xadj, pos.get(), M1, out.get());
     LAUNCHCHK();
-    HIPCHK(hipMemcpyAsync(sb.data(), out.get(), M1 * sizeof(int64_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(sb.data(), out.get(), M1 * sizeof(int64_t), s);
     return sb;
 }
 
@@ -677,8 +670,7 @@ bool members_closed(const DevGraph& g, const std::vector<int32_t>& nb, const std
     members_closed_kernel<<<capped_grid_s(g.S), 256, 0, s>>>(g.S, M, dsb.get(), dnb.get(), g.adj, bad.get());
     LAUNCHCHK();
     uint32_t h = 0;
-    HIPCHK(hipMemcpyAsync(&h, bad.get(), sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&h, bad.get(), sizeof(uint32_t), s);
     return h == 0;
 }
 
@@ -691,8 +683,7 @@ void graph_node_stats(int32_t n, const int32_t* gid, const int32_t* vw, int32_t 
         LAUNCHCHK();
     }
     std::vector<unsigned long long> h(2 * static_cast<size_t>(std::max(G, 1)));
-    HIPCHK(hipMemcpyAsync(h.data(), d.get(), h.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(h.data(), d.get(), h.size() * sizeof(unsigned long long), s);
     for (int32_t g = 0; g < G; ++g) {
         cV[g] = static_cast<int64_t>(h[g]);
         cmax[g] = static_cast<int64_t>(h[G + g]);
@@ -711,8 +702,7 @@ void graph_cuts(const DevGraph& g, const int32_t* part, const int32_t* gid, int3
         LAUNCHCHK();
     }
     std::vector<unsigned long long> h(std::max(G, 1));
-    HIPCHK(hipMemcpyAsync(h.data(), d.get(), h.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(h.data(), d.get(), h.size() * sizeof(unsigned long long), s);
     for (int32_t i = 0; i < G; ++i) cut[i] = static_cast<int64_t>(h[i] / 2);
 }
 
@@ -921,8 +911,7 @@ void within_blocks(const DevGraph& g, const int32_t* blk, OwnedDevGraph& out, hi
                                                                                   tcnt.get(), trow.get());
         LAUNCHCHK();
         exclusive_scan_i32_to_i64(tcnt.get(), tbase.get(), tiles, total.get(), s);
-        HIPCHK(hipMemcpyAsync(&St, total.get(), sizeof(int64_t), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        read_back(&St, total.get(), sizeof(int64_t), s);
     } else {
         fill_i64(total.get(), 0, 1, s);
     }
@@ -1133,8 +1122,7 @@ LPResult device_initial_partition(const DevGraph& g, int32_t k, int64_t T, int64
     LAUNCHCHK();
     exclusive_scan_i32(flag.get(), rank.get(), n, tot.get(), s);
     int32_t npos = 0;
-    HIPCHK(hipMemcpyAsync(&npos, tot.get(), sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(&npos, tot.get(), sizeof(int32_t), s);
     fill_i32(part, k, n, s);  // everything starts in the pool
     if (npos > 0) {
         ProfScope ps("initial_seeds", 0, s);
@@ -1156,8 +1144,7 @@ LPResult device_initial_partition(const DevGraph& g, int32_t k, int64_t T, int64
     res = run_lp(g, kInitial, level, seed, nsub, rounds, Lmax, part, w.get(), k + 1, nullptr, tune, s);
     // the pool fills the blocks' remaining room in block order
     std::vector<int32_t> hw(static_cast<size_t>(k));
-    HIPCHK(hipMemcpyAsync(hw.data(), w.get(), k * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
+    read_back(hw.data(), w.get(), k * sizeof(int32_t), s);
     std::vector<int64_t> cum(static_cast<size_t>(k));
     int64_t run = 0;
     for (int32_t b = 0; b < k; ++b) {

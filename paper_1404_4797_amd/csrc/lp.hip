@@ -34,6 +34,7 @@
 #include <climits>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 
 #include "lp.hpp"
 #include "profile.hpp"
@@ -1479,6 +1480,7 @@ struct Admission {
     Counters* ctr_next;  // the next sub-round's: cleared here, no kernel reads them any more
     const uint32_t* gate;
     uint32_t* round_cnt;  // candidates of the round
+    uint32_t* host_cnt;   // where the round's last sub-round reports them to the host (null: not the last)
 };
 
 // Records segment sid and, when it is longer than small_max, gives it a large
@@ -1973,8 +1975,9 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uin
     __shared__ int32_t s_wave[NT / 64];
     __shared__ int s_d;
     __shared__ int32_t s_run;
-    if (stopped(A.gate)) return;  // uniform over the grid: nothing was counted either
     const int tid = threadIdx.x;
+    if (A.host_cnt && blockIdx.x == 0 && tid == 0) *A.host_cnt = *A.round_cnt;
+    if (stopped(A.gate)) return;  // uniform over the grid: nothing was counted either
     const int lane = lane_id();
     if (blockIdx.x == 0 && tid == 0) clear_subround(A.ctr_next);
     if (kSmall) {
@@ -2362,14 +2365,7 @@ struct HubPlan {
     int32_t count = 0;
     int32_t nchunks = 0;
     int32_t nparts = 0;
-    int64_t region_entries = 0;
-    int64_t overflow_entries = 0;
-    int64_t table_entries = 0;
-    // plog | pbase[H+1] | cap | chunk_hub | part_hub
-    DBuf<int32_t> i32;
-    // rbase | obase | toff | chunk_begin
-    DBuf<int64_t> i64;
-    DBuf<uint32_t> u32;  // tmask
+    int64_t at[10] = {};  // first 8-byte word of each array in the plans' buffer
 };
 
 // Side streams for the independent evaluation launches of a sub-round
@@ -2417,13 +2413,6 @@ EvalStreams& eval_streams() {
     return e;
 }
 
-thread_local Counters* t_host_ctr = nullptr;
-
-Counters* host_counters() {
-    if (!t_host_ctr) HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&t_host_ctr), sizeof(Counters), hipHostMallocDefault));
-    return t_host_ctr;
-}
-
 // Pinned host copies of the per-round candidate counts (grown as needed,
 // kept for the thread's lifetime).
 thread_local uint32_t* t_host_rc = nullptr;
@@ -2434,7 +2423,7 @@ uint32_t* host_round_counts(int32_t rounds) {
         if (t_host_rc) HIPCHK(hipHostFree(t_host_rc));
         t_host_rc_cap = std::max(rounds, 64);
         HIPCHK(hipHostMalloc(reinterpret_cast<void**>(&t_host_rc), sizeof(uint32_t) * t_host_rc_cap,
-                             hipHostMallocDefault));
+                             hipHostMallocPortable | hipHostMallocCoherent));
     }
     return t_host_rc;
 }
@@ -2591,13 +2580,14 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     order_tmp.release();
     std::vector<uint32_t> cnt(ncat + 1);
     std::vector<unsigned long long> cslots(ncat + 1);
-    HIPCHK(hipMemcpyAsync(cnt.data(), cat_count.get(), (ncat + 1) * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipMemcpyAsync(cslots.data(), cat_slots.get(), (ncat + 1) * sizeof(unsigned long long),
-                          hipMemcpyDeviceToHost, s));
-    Counters* hctr = host_counters();
-    HIPCHK(hipMemcpyAsync(hctr, ctr.get(), sizeof(Counters), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    if (hctr->bad_color) fail(-1, "color_override value outside [0, subrounds)");
+    Counters hctr;
+    {
+        const ReadItem items[3] = {{cnt.data(), cat_count.get(), (ncat + 1) * sizeof(uint32_t)},
+                                   {cslots.data(), cat_slots.get(), (ncat + 1) * sizeof(unsigned long long)},
+                                   {&hctr, ctr.get(), sizeof(Counters)}};
+        read_back(items, 3, s);
+    }
+    if (hctr.bad_color) fail(-1, "color_override value outside [0, subrounds)");
     std::vector<int64_t> off(ncat + 2, 0);
     for (int32_t j = 0; j <= ncat; ++j) off[j + 1] = off[j] + cnt[j];
     const int32_t* nodes = reinterpret_cast<const int32_t*>(order.get());
@@ -2607,81 +2597,90 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     schedule_rows_kernel<<<grid_for(n, 256), 256, 0, s>>>(nodes, n, g.xadj, sched.get());
     LAUNCHCHK();
 
-    // --- hub plans per colour
+    // --- hub plans per colour: the hubs' rows in one read, all plans in one copy
     std::vector<HubPlan> plans(nsub);
     int64_t max_region = 0, max_over = 0, max_table = 0, max_win = 0, max_hub_ints = 0;
     // refinement labels fit dense arrays when there are few enough blocks
     // (the same test sets EvalArgs::dense_k below); hub chunks are then longer
     const int32_t dense_labels = phase != kCluster ? (mg ? mg->max_labels : nw) : 0;
     const int64_t hub_chunk = dense_labels > 0 && dense_labels <= kDenseMax ? kHubDenseChunk : kHubChunk;
+    std::vector<std::vector<Row>> hub_rows(nsub);
+    std::vector<ReadItem> hub_reads;
     for (int32_t sc = 0; sc < nsub; ++sc) {
         const int32_t cat = sc * kNB + kHubBucket;
-        const int32_t H = static_cast<int32_t>(cnt[cat]);
-        HubPlan& P = plans[sc];
-        P.count = H;
-        if (H == 0) continue;
-        std::vector<Row> hrow(H);
-        HIPCHK(hipMemcpyAsync(hrow.data(), rows + off[cat], H * sizeof(Row), hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        std::vector<int64_t> hd(H), xs(H);
-        for (int32_t h = 0; h < H; ++h) {
-            xs[h] = hrow[h].begin;
-            hd[h] = hrow[h].deg;
-        }
-        std::vector<int32_t> plog(H), pbase(H + 1), cap(H), chub, phub;
-        std::vector<int64_t> rbase(H), obase(H), toff(H), cbeg;
-        std::vector<uint32_t> tmask(H);
-        int64_t rtot = 0, otot = 0, ttot = 0;
-        int32_t np = 0;
-        for (int32_t h = 0; h < H; ++h) {
-            // at most 1024 entries per label partition on average (half the
-            // LDS table's limit), at most 2048 partitions
-            int32_t lg = 0;
-            while (lg < kMaxPartLog && (static_cast<int64_t>(1024) << lg) < hd[h]) ++lg;
-            plog[h] = lg;
-            const int64_t per = (hd[h] + (1LL << lg) - 1) >> lg;
-            cap[h] = static_cast<int32_t>(std::min<int64_t>(2 * per + 64, hd[h]));
-            if (tune.hub_region_cap > 0) cap[h] = std::min(cap[h], tune.hub_region_cap);
-            pbase[h] = np;
-            for (int32_t p = 0; p < (1 << lg); ++p) phub.push_back(h);
-            np += 1 << lg;
-            rbase[h] = rtot;
-            rtot += static_cast<int64_t>(cap[h]) << lg;
-            obase[h] = otot;
-            otot += hd[h];
-            uint64_t tsz = 1;
-            while (tsz < 2 * static_cast<uint64_t>(hd[h])) tsz <<= 1;
-            toff[h] = ttot;
-            tmask[h] = static_cast<uint32_t>(tsz - 1);
-            for (int64_t sl = 0; sl < hd[h]; sl += hub_chunk) {
-                chub.push_back(h);
-                cbeg.push_back(xs[h] + sl);
+        hub_rows[sc].resize(cnt[cat]);
+        if (cnt[cat]) hub_reads.push_back(ReadItem{hub_rows[sc].data(), rows + off[cat], cnt[cat] * sizeof(Row)});
+    }
+    DBuf<int64_t> plan_buf;
+    if (!hub_reads.empty()) {
+        read_back(hub_reads.data(), static_cast<int>(hub_reads.size()), s);
+        std::vector<int64_t> all;  // the plans' arrays, each from a multiple of 8 bytes
+        auto put = [&](const auto& vec) {
+            const size_t at = all.size();
+            const size_t bytes = vec.size() * sizeof(vec[0]);
+            all.resize(at + (bytes + 7) / 8, 0);
+            if (bytes) std::memcpy(all.data() + at, vec.data(), bytes);
+            return static_cast<int64_t>(at);
+        };
+        for (int32_t sc = 0; sc < nsub; ++sc) {
+            const std::vector<Row>& hr = hub_rows[sc];
+            const int32_t H = static_cast<int32_t>(hr.size());
+            HubPlan& P = plans[sc];
+            P.count = H;
+            if (H == 0) continue;
+            std::vector<int32_t> plog(H), pbase(H + 1), cap(H), chub, phub;
+            std::vector<int64_t> rbase(H), obase(H), toff(H), cbeg;
+            std::vector<uint32_t> tmask(H);
+            int64_t rtot = 0, otot = 0, ttot = 0;
+            int32_t np = 0;
+            for (int32_t h = 0; h < H; ++h) {
+                const int64_t hd = hr[h].deg;
+                // at most 1024 entries per label partition on average (half the
+                // LDS table's limit), at most 2048 partitions
+                int32_t lg = 0;
+                while (lg < kMaxPartLog && (static_cast<int64_t>(1024) << lg) < hd) ++lg;
+                plog[h] = lg;
+                const int64_t per = (hd + (1LL << lg) - 1) >> lg;
+                cap[h] = static_cast<int32_t>(std::min<int64_t>(2 * per + 64, hd));
+                if (tune.hub_region_cap > 0) cap[h] = std::min(cap[h], tune.hub_region_cap);
+                pbase[h] = np;
+                phub.insert(phub.end(), static_cast<size_t>(1) << lg, h);
+                np += 1 << lg;
+                rbase[h] = rtot;
+                rtot += static_cast<int64_t>(cap[h]) << lg;
+                obase[h] = otot;
+                otot += hd;
+                uint64_t tsz = 1;
+                while (tsz < 2 * static_cast<uint64_t>(hd)) tsz <<= 1;
+                toff[h] = ttot;
+                tmask[h] = static_cast<uint32_t>(tsz - 1);
+                ttot += static_cast<int64_t>(tsz);
+                for (int64_t sl = 0; sl < hd; sl += hub_chunk) {
+                    chub.push_back(h);
+                    cbeg.push_back(hr[h].begin + sl);
+                }
             }
-            ttot += static_cast<int64_t>(tsz);
+            pbase[H] = np;
+            P.nchunks = static_cast<int32_t>(chub.size());
+            P.nparts = np;
+            P.at[0] = put(plog);
+            P.at[1] = put(pbase);
+            P.at[2] = put(cap);
+            P.at[3] = put(chub);
+            P.at[4] = put(phub);
+            P.at[5] = put(rbase);
+            P.at[6] = put(obase);
+            P.at[7] = put(toff);
+            P.at[8] = put(cbeg);
+            P.at[9] = put(tmask);
+            max_region = std::max(max_region, rtot);
+            max_over = std::max(max_over, otot);
+            max_table = std::max(max_table, ttot);
+            max_win = std::max(max_win, static_cast<int64_t>(np));
+            max_hub_ints = std::max(max_hub_ints, static_cast<int64_t>(np) + 3 * static_cast<int64_t>(H));
         }
-        pbase[H] = np;
-        P.nchunks = static_cast<int32_t>(chub.size());
-        P.nparts = np;
-        P.region_entries = rtot;
-        P.overflow_entries = otot;
-        P.table_entries = ttot;
-        std::vector<int32_t> i32;
-        for (const auto* vec : {&plog, &pbase, &cap, &chub, &phub})
-            i32.insert(i32.end(), vec->begin(), vec->end());
-        std::vector<int64_t> i64;
-        for (const auto* vec : {&rbase, &obase, &toff, &cbeg}) i64.insert(i64.end(), vec->begin(), vec->end());
-        P.i32.alloc(i32.size(), s);
-        P.i64.alloc(i64.size(), s);
-        P.u32.alloc(tmask.size(), s);
-        HIPCHK(hipMemcpyAsync(P.i32.get(), i32.data(), i32.size() * sizeof(int32_t), hipMemcpyHostToDevice, s));
-        HIPCHK(hipMemcpyAsync(P.i64.get(), i64.data(), i64.size() * sizeof(int64_t), hipMemcpyHostToDevice, s));
-        HIPCHK(hipMemcpyAsync(P.u32.get(), tmask.data(), tmask.size() * sizeof(uint32_t), hipMemcpyHostToDevice, s));
-        HIPCHK(hipStreamSynchronize(s));  // host vectors go out of scope
-        max_region = std::max(max_region, rtot);
-        max_over = std::max(max_over, otot);
-        max_table = std::max(max_table, ttot);
-        max_win = std::max(max_win, static_cast<int64_t>(np));
-        max_hub_ints = std::max(max_hub_ints, static_cast<int64_t>(np) + 3 * static_cast<int64_t>(H));
+        plan_buf.alloc(all.size(), s);
+        upload_once(plan_buf.get(), all.data(), all.size() * sizeof(int64_t), s);
     }
     DBuf<int32_t> ekeys, evals, okeys, ovals, gkeys, gvals, hub_ints, w_conn, w_x;
     DBuf<uint64_t> w_tie;
@@ -2808,6 +2807,10 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
 
     A.rcnt = rcnt.get();
     uint32_t* hrc = host_round_counts(rounds);
+    std::fill(hrc, hrc + rounds, 0u);
+    int32_t last_sub = -1;  // the last colour with nodes
+    for (int32_t sc = 0; sc < nsub; ++sc)
+        if (off[(sc + 1) * kNB] > off[sc * kNB]) last_sub = sc;
     RoundEvents& rev = round_events();
     bool halted = false;
     // bookkeeping of a finished round q (read back from the device)
@@ -2889,18 +2892,18 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             if (P.count > 0) {
                 const int32_t Hn = P.count;
                 H.count = Hn;
-                const int32_t* i32 = P.i32.get();
-                H.hub_plog = i32;
-                H.hub_pbase = i32 + Hn;
-                H.hub_cap = i32 + 2 * Hn + 1;
-                H.chunk_hub = i32 + 3 * Hn + 1;
-                H.part_hub = H.chunk_hub + P.nchunks;
-                const int64_t* i64 = P.i64.get();
-                H.hub_rbase = i64;
-                H.hub_obase = i64 + Hn;
-                H.hub_toff = i64 + 2 * Hn;
-                H.chunk_begin = i64 + 3 * Hn;
-                H.hub_tmask = P.u32.get();
+                const int64_t* pb = plan_buf.get();
+                auto i32 = [&](int q) { return reinterpret_cast<const int32_t*>(pb + P.at[q]); };
+                H.hub_plog = i32(0);
+                H.hub_pbase = i32(1);
+                H.hub_cap = i32(2);
+                H.chunk_hub = i32(3);
+                H.part_hub = i32(4);
+                H.hub_rbase = pb + P.at[5];
+                H.hub_obase = pb + P.at[6];
+                H.hub_toff = pb + P.at[7];
+                H.chunk_begin = pb + P.at[8];
+                H.hub_tmask = reinterpret_cast<const uint32_t*>(pb + P.at[9]);
                 H.rcount = hub_ints.get();
                 H.ocount = H.rcount + P.nparts;
                 H.big = H.ocount + Hn;
@@ -3048,6 +3051,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             M.ctr_next = ctr.get() + (~step & 1);
             M.gate = gate;
             M.round_cnt = rcnt.get() + r;
+            M.host_cnt = sc == last_sub ? hrc + r : nullptr;
             ++step;
             const int per = ccount <= (1 << 16) ? 1 : (ccount <= (1 << 18) ? 4 : 8);
             const unsigned gc = static_cast<unsigned>(std::min<int64_t>(grid_for(ccount, 256 * per), kMaxBlocks));
@@ -3072,14 +3076,15 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 LAUNCHCHK();
             }
             if (trace) {
-                HIPCHK(hipMemcpyAsync(hctr, M.ctr, sizeof(Counters), hipMemcpyDeviceToHost, s));
-                HIPCHK(hipMemcpyAsync(hrc + r, rcnt.get() + r, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-                HIPCHK(hipStreamSynchronize(s));
-                const uint32_t slow = static_cast<uint32_t>(hctr->segs);
+                uint32_t cands = 0;
+                const ReadItem items[2] = {{&hctr, M.ctr, sizeof(Counters)},
+                                           {&cands, rcnt.get() + r, sizeof(uint32_t)}};
+                read_back(items, 2, s);
+                const uint32_t slow = static_cast<uint32_t>(hctr.segs);
                 fprintf(stderr, "[sclap] %s L%d r%d s%d n=%lld round cand=%u slow=%u targets=%u gain=[%d,%d] hubs=%d\n",
                         phase != kCluster ? "refine" : "cluster", level, r, sc, static_cast<long long>(ccount),
-                        hrc[r], slow, static_cast<uint32_t>(hctr->segs >> 32), slow ? hctr->gmin : 0,
-                        slow ? hctr->gmax : 0, plans[sc].count);
+                        cands, slow, static_cast<uint32_t>(hctr.segs >> 32), slow ? hctr.gmin : 0,
+                        slow ? hctr.gmax : 0, plans[sc].count);
             }
             {
                 ProfScope ps("lp_apply", 0, s);
@@ -3112,9 +3117,9 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             }
         }
         // a round without candidates moved nothing (the first candidate of
-        // every target is always admitted) and ends the run; its count is
-        // read while the next round runs
-        HIPCHK(hipMemcpyAsync(hrc + r, rcnt.get() + r, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+        // every target is always admitted) and ends the run; its count, which
+        // the last finish kernel wrote to host memory, is read while the next
+        // round runs
         if (!capture) {
             HIPCHK(hipEventRecord(rev.ev[r & 1], s));
             if (r > 0) finish_round(r - 1);

@@ -6,6 +6,25 @@
 
 namespace sclap {
 
+// A few values from device memory to host variables, once the work enqueued on
+// s so far is done (sizes in multiples of 4 bytes).
+struct ReadItem {
+    void* host;
+    const void* dev;
+    size_t bytes;
+};
+void read_back(const ReadItem* items, int count, hipStream_t s);
+inline void read_back(void* host, const void* dev, size_t bytes, hipStream_t s) {
+    const ReadItem it{host, dev, bytes};
+    read_back(&it, 1, s);
+}
+
+// Copies host data to device memory in stream order; the source may go away
+// when the call returns.  One such copy per thread may be under way: the caller
+// waits for the stream before the next.
+void upload_once(void* dev, const void* host, size_t bytes, hipStream_t s);
+
+
 void fill_i32(int32_t* p, int32_t value, int64_t count, hipStream_t s);
 void fill_i64(int64_t* p, int64_t value, int64_t count, hipStream_t s);
 void fill_u32(uint32_t* p, uint32_t value, int64_t count, hipStream_t s);
