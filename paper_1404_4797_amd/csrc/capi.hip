@@ -108,14 +108,15 @@ void download(T* h, const T* d, int64_t count, hipStream_t s) {
 
 // ------------------------------------------------------ single operations
 
-int cluster_impl(const DevGraph& g, int64_t U, int32_t rounds, uint64_t seed, int32_t level, const Opts& o,
+int cluster_impl(const DevGraph& g_in, int64_t U, int32_t rounds, uint64_t seed, int32_t level, const Opts& o,
                  const int32_t* color_dev, int32_t* labels, int32_t* rounds_run, hipStream_t s,
                  const int32_t* block = nullptr) {
     if (rounds < 0) fail(SCLAP_ERR_INVALID, "rounds < 0");
     if (U < 0) fail(SCLAP_ERR_INVALID, "U < 0");
-    if (g.n > 0 && !labels) fail(SCLAP_ERR_INVALID, "labels is NULL");
+    if (g_in.n > 0 && !labels) fail(SCLAP_ERR_INVALID, "labels is NULL");
     int64_t cV = 0, cmax = 0;
-    check_graph(g, o.validate != 0, &cV, &cmax, s);
+    DevGraph g = g_in;
+    check_graph(g, o.validate != 0, &cV, &cmax, s, o.validate != 0);
     if (color_dev && !all_in_range(color_dev, g.n, 0, o.nsub, s))
         fail(SCLAP_ERR_INVALID, "color_override value outside [0, subrounds)");
     DBuf<int32_t> w(std::max(g.n, 1), s);
@@ -140,13 +141,14 @@ int cluster_impl(const DevGraph& g, int64_t U, int32_t rounds, uint64_t seed, in
     return SCLAP_OK;
 }
 
-int refine_impl(const DevGraph& g, int32_t k, int64_t Lmax, int32_t rounds, uint64_t seed, int32_t level,
+int refine_impl(const DevGraph& g_in, int32_t k, int64_t Lmax, int32_t rounds, uint64_t seed, int32_t level,
                 const Opts& o, const int32_t* color_dev, int32_t* part, int32_t* rounds_run, hipStream_t s) {
     if (k < 1) fail(SCLAP_ERR_INVALID, "k must be >= 1");
     if (rounds < 0) fail(SCLAP_ERR_INVALID, "rounds < 0");
-    if (g.n > 0 && !part) fail(SCLAP_ERR_INVALID, "part is NULL");
+    if (g_in.n > 0 && !part) fail(SCLAP_ERR_INVALID, "part is NULL");
     int64_t cV = 0, cmax = 0;
-    check_graph(g, o.validate != 0, &cV, &cmax, s);
+    DevGraph g = g_in;
+    check_graph(g, o.validate != 0, &cV, &cmax, s, o.validate != 0);
     if (!all_in_range(part, g.n, 0, k, s)) fail(SCLAP_ERR_INVALID, "part value outside [0, k)");
     if (color_dev && !all_in_range(color_dev, g.n, 0, o.nsub, s))
         fail(SCLAP_ERR_INVALID, "color_override value outside [0, subrounds)");
@@ -407,9 +409,8 @@ int sclap_project_dev(int32_t n, int32_t n_coarse, const int32_t* C, const int32
         if (n < 0 || n_coarse < 0) fail(SCLAP_ERR_INVALID, "negative size");
         if (n == 0) return SCLAP_OK;
         if (!C || !coarse_part || !part) fail(SCLAP_ERR_INVALID, "NULL array");
-        if (!all_in_range(C, n, 0, n_coarse, s)) fail(SCLAP_ERR_INVALID, "C value outside [0, n_coarse)");
-        project(n, C, coarse_part, part, s);
-        HIPCHK(hipStreamSynchronize(s));
+        if (!project_checked(n, n_coarse, C, coarse_part, part, s))
+            fail(SCLAP_ERR_INVALID, "C value outside [0, n_coarse)");
         return SCLAP_OK;
     });
 }
@@ -423,8 +424,8 @@ int sclap_project(int32_t n, int32_t n_coarse, const int32_t* C, const int32_t* 
         DBuf<int32_t> dC = upload_array(C, n, s);
         DBuf<int32_t> dcp = upload_array(coarse_part, n_coarse, s);
         DBuf<int32_t> dp(n, s);
-        if (!all_in_range(dC.get(), n, 0, n_coarse, s)) fail(SCLAP_ERR_INVALID, "C value outside [0, n_coarse)");
-        project(n, dC.get(), dcp.get(), dp.get(), s);
+        if (!project_checked(n, n_coarse, dC.get(), dcp.get(), dp.get(), s))
+            fail(SCLAP_ERR_INVALID, "C value outside [0, n_coarse)");
         download(part, dp.get(), n, s);
         return SCLAP_OK;
     });
@@ -437,8 +438,7 @@ int sclap_cut_dev(const sclap_graph* g, const int32_t* part, int32_t k, int64_t*
         if (k < 1 || !cut || !block_w) fail(SCLAP_ERR_INVALID, "bad k or NULL output");
         const DevGraph d = dev_view(g, s);
         if (d.n > 0 && !part) fail(SCLAP_ERR_INVALID, "part is NULL");
-        if (!all_in_range(part, d.n, 0, k, s)) fail(SCLAP_ERR_INVALID, "part value outside [0, k)");
-        cut_and_weights(d, part, k, cut, block_w, s);
+        if (!cut_and_weights(d, part, k, cut, block_w, true, s)) fail(SCLAP_ERR_INVALID, "part value outside [0, k)");
         return SCLAP_OK;
     });
 }
@@ -462,8 +462,8 @@ int sclap_cut(const sclap_graph* g, const int32_t* part, int32_t k, int64_t* cut
         Staged st = upload(g, s);
         if (st.g.n > 0 && !part) fail(SCLAP_ERR_INVALID, "part is NULL");
         DBuf<int32_t> p = upload_array(part, st.g.n, s);
-        if (!all_in_range(p.get(), st.g.n, 0, k, s)) fail(SCLAP_ERR_INVALID, "part value outside [0, k)");
-        cut_and_weights(st.g, p.get(), k, cut, block_w, s);
+        if (!cut_and_weights(st.g, p.get(), k, cut, block_w, true, s))
+            fail(SCLAP_ERR_INVALID, "part value outside [0, k)");
         return SCLAP_OK;
     });
 }
@@ -486,11 +486,11 @@ int sclap_initial_partition_lp_dev(const sclap_graph* g, int32_t k, int64_t T, i
     return guarded([&] {
         hipStream_t s = as_stream(stream);
         const Opts o = resolve(opt);
-        const DevGraph d = dev_view(g, s);
+        DevGraph d = dev_view(g, s);
         if (k < 1 || rounds < 0 || T < 0 || Lmax < 0) fail(SCLAP_ERR_INVALID, "bad k, rounds, T or Lmax");
         if (d.n > 0 && !part) fail(SCLAP_ERR_INVALID, "part is NULL");
         int64_t cV = 0, cmax = 0;
-        check_graph(d, o.validate != 0, &cV, &cmax, s);
+        check_graph(d, o.validate != 0, &cV, &cmax, s, o.validate != 0);
         const LPResult r = device_initial_partition(d, k, T, Lmax, seed, level, o.nsub, rounds, o.tune, part, s);
         HIPCHK(hipStreamSynchronize(s));
         if (visits) *visits = r.visits;

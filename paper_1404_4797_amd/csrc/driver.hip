@@ -85,15 +85,23 @@ DevGraph dev_view(const sclap_graph* g, hipStream_t s) {
     return d;
 }
 
-void check_graph(const DevGraph& g, bool validate, int64_t* cV, int64_t* cmax, hipStream_t s) {
+void check_graph(DevGraph& g, bool validate, int64_t* cV, int64_t* cmax, hipStream_t s, bool drop_units) {
     if (validate) {
-        const int st = validate_graph(g, cV, cmax, s);
+        bool unit[2];
+        const int st = validate_graph(g, cV, cmax, s, unit);
         if (st == SCLAP_ERR_INVALID) fail(st, "invalid graph (offsets, ids, self-loops or weights)");
         if (st == SCLAP_ERR_NOT_SYMMETRIC) fail(st, "graph is not symmetric");
         if (st == SCLAP_ERR_OVERFLOW) fail(st, "node or edge weight total exceeds 2^31-1");
         if (st != 0) fail(st, "graph validation failed");
+        if (drop_units) {
+            if (unit[0]) g.vw = nullptr;
+            if (unit[1]) g.ew = nullptr;
+        }
     } else {
         node_weight_stats(g, cV, cmax, s);
+        if (!drop_units) return;
+        if (g.ew && all_in_range(g.ew, g.S, 1, 2, s)) g.ew = nullptr;
+        if (g.vw && all_in_range(g.vw, g.n, 1, 2, s)) g.vw = nullptr;
     }
 }
 
@@ -743,17 +751,6 @@ double ms_since(Clock::time_point t) { return std::chrono::duration<double, std:
 
 namespace {
 
-// Weight arrays that hold only ones are dropped (read as implicit ones), so
-// the level-0 rounds do not stream them.
-void drop_unit_weights(DevGraph& g, hipStream_t s) {
-    if (g.ew && all_in_range(g.ew, g.S, 1, 2, s)) g.ew = nullptr;
-    if (g.vw && all_in_range(g.vw, g.n, 1, 2, s)) g.vw = nullptr;
-}
-
-}  // namespace
-
-namespace {
-
 // One multilevel cycle (Section 4.5).  blk0 (device) is null in the first
 // cycle; in later ones it holds the previous cycle's partition: clustering
 // then stays inside its blocks (on the subgraph of intra-block slots), every
@@ -929,8 +926,7 @@ int partition_impl(const DevGraph& g0_in, int32_t k, double eps, uint64_t seed, 
     if (!part_out && g0.n > 0) fail(SCLAP_ERR_INVALID, "part is NULL");
     if (!cut || !bw) fail(SCLAP_ERR_INVALID, "cut / block_w is NULL");
     int64_t cV = 0, cmax0 = 0;
-    check_graph(g0, o.validate != 0, &cV, &cmax0, s);
-    drop_unit_weights(g0, s);
+    check_graph(g0, o.validate != 0, &cV, &cmax0, s, true);
     sclap_stats local;
     sclap_stats* st = stats ? stats : &local;
     std::memset(st, 0, sizeof(*st));
@@ -940,7 +936,7 @@ int partition_impl(const DevGraph& g0_in, int32_t k, double eps, uint64_t seed, 
         multilevel_cycle(g0, k, cV, cmax0, Lmax, cycle_seed(seed, c), o, c == 0 ? nullptr : part_out, part_out, st,
                          lp_ms, s);
     auto t_cut = Clock::now();
-    cut_and_weights(g0, part_out, k, cut, bw, s);
+    cut_and_weights(g0, part_out, k, cut, bw, false, s);
     st->ms_refine += ms_since(t_cut);
     st->ms_lp = lp_ms;
     for (int32_t b = 0; b < k; ++b)
@@ -954,8 +950,7 @@ LPTuning autotune(const DevGraph& g_in, int32_t k, const Opts& o, hipStream_t s)
     check_k_eps(k, 0.0);
     DevGraph g = g_in;
     int64_t cV = 0, cmax = 0;
-    check_graph(g, false, &cV, &cmax, s);
-    drop_unit_weights(g, s);
+    check_graph(g, false, &cV, &cmax, s, true);
     LPTuning best = o.tune;
     if (g.n == 0) return best;
     const int64_t U = std::max(cmax, cV / (static_cast<int64_t>(o.divisor) * k));
@@ -1474,12 +1469,10 @@ int partition_batch_impl(const DevGraph& g0_in, int32_t G, const int32_t* node_b
         B.gid.alloc(std::max(g0.n, 1), s);
         member_ids(g0.n, B.nb, B.ids, B.gid.get(), s);
     }
-    if (o.validate) {
-        int64_t cVu = 0, cmu = 0;
-        check_graph(g0, true, &cVu, &cmu, s);
-        if (!members_closed(g0, L[0].nb, L[0].sb, s)) fail(SCLAP_ERR_INVALID, "an edge joins two graphs of the batch");
-    }
-    drop_unit_weights(g0, s);
+    int64_t cVu = 0, cmu = 0;
+    check_graph(g0, o.validate != 0, &cVu, &cmu, s, true);
+    if (o.validate && !members_closed(g0, L[0].nb, L[0].sb, s))
+        fail(SCLAP_ERR_INVALID, "an edge joins two graphs of the batch");
     L[0].g = g0;
     std::vector<int64_t> cV(G), cmax0(G);
     graph_node_stats(g0.n, L[0].gid.get(), g0.vw, G, cV.data(), cmax0.data(), s);

@@ -37,7 +37,9 @@ Opts resolve(const sclap_options* o);
 DevGraph dev_view(const sclap_graph* g, hipStream_t s);
 
 // Validates (or only measures) a device graph: c(V) and max c(v).
-void check_graph(const DevGraph& g, bool validate, int64_t* cV, int64_t* cmax, hipStream_t s);
+// drop_units: weight arrays that hold only ones are dropped from g (read as
+// implicit ones), so that the rounds do not stream them.
+void check_graph(DevGraph& g, bool validate, int64_t* cV, int64_t* cmax, hipStream_t s, bool drop_units = false);
 
 // Lmax = T + floor(T * round(eps * 10^6) / 10^6), T = ceil(cV / k).
 int64_t lmax_of(int64_t cV, int32_t k, double eps);

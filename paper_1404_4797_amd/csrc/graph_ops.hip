@@ -20,6 +20,18 @@ __global__ void project_kernel(int32_t n, const int32_t* __restrict__ C, const i
     if (v < n) part[v] = cp[C[v]];
 }
 
+// The same for ids that nobody has looked at: one outside [0, nc) raises the
+// flag and projects nothing.
+__global__ void project_checked_kernel(int32_t n, int32_t nc, const int32_t* __restrict__ C,
+                                       const int32_t* __restrict__ cp, int32_t* __restrict__ part,
+                                       uint32_t* __restrict__ bad) {
+    const int32_t v = blockIdx.x * 256 + threadIdx.x;
+    if (v >= n) return;
+    const int32_t c = C[v];
+    if (c < 0 || c >= nc) *bad = 1;
+    else part[v] = cp[c];
+}
+
 // ---------------------------------------------------------- cut and weights
 
 __device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v) {
@@ -33,54 +45,87 @@ __device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long v
     return t;
 }
 
+// Sums that every workgroup adds to are kept in kSpread copies, one 128-byte
+// line each, and added up on the host: adds to one address are served one
+// every 12 ns (2 048 workgroups on one counter: 25 us).
+constexpr int kSpread = 16;
+constexpr int kLine64 = 16;  // 8-byte words per line
+
 // Grid-stride over tiles; one atomic per workgroup.  P: the block type read
 // for every neighbour (a byte copy when k <= 256: four times the neighbours
-// per cache line of the random gather).
+// per cache line of the random gather).  Each thread takes 8 consecutive
+// slots: their rows are in registers and all 16 gathers are in flight at once
+// (one slot per thread and step with the rows in LDS: 110 us for the 16.8 M
+// slots of a 2^20-node power-law graph).
 template <typename P>
 __global__ void __launch_bounds__(kTileThreads) cut_kernel(const int64_t* __restrict__ xadj, const int32_t* __restrict__ adj,
                                                            const int32_t* __restrict__ ew, int32_t n, int64_t S,
                                                            const P* __restrict__ part,
-                                                           unsigned long long* __restrict__ cut, const int32_t* __restrict__ trow) {
-    __shared__ int32_t owner[kTile];
+                                                           unsigned long long* __restrict__ cut, int32_t spread,
+                                                           const int32_t* __restrict__ trow) {
+    __shared__ __align__(16) int32_t mark[kTile];
     unsigned long long acc = 0;
     for (int64_t tile = blockIdx.x; tile * kTile < S; tile += gridDim.x) {
         const int64_t i0 = tile * kTile;
         const int64_t i1 = i0 + kTile < S ? i0 + kTile : S;
-        tile_owners(xadj, trow, tile, i0, i1, owner);
-        for (int r = 0; r < kTilePer; ++r) {
-            const int64_t i = i0 + r * kTileThreads + threadIdx.x;
-            if (i < i1 && part[owner[i - i0]] != part[adj[i]]) acc += ew ? static_cast<unsigned long long>(ew[i]) : 1ULL;
+        const int64_t i = i0 + kTilePer * static_cast<int64_t>(threadIdx.x);
+        int32_t row[kTilePer], x[kTilePer], w[kTilePer];
+        tile_load(adj, i, i1, wide_tile(adj, i0, i1), -1, x);
+        if (ew) tile_load(ew, i, i1, wide_tile(ew, i0, i1), 0, w);
+        tile_rows(xadj, trow, tile, i0, i1, mark, row);
+        P px[kTilePer], pu[kTilePer];
+#pragma unroll
+        for (int j = 0; j < kTilePer; ++j) {
+            pu[j] = part[row[j]];
+            px[j] = x[j] >= 0 ? part[x[j]] : pu[j];
         }
-        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kTilePer; ++j)
+            if (px[j] != pu[j]) acc += ew ? static_cast<unsigned long long>(w[j]) : 1ULL;
     }
     acc = block_sum_u64(acc);
-    if (threadIdx.x == 0 && acc) atomicAdd(cut, acc);
+    if (threadIdx.x == 0 && acc) atomicAdd(&cut[(blockIdx.x % spread) * kLine64], acc);
 }
 
-__global__ void to_u8_kernel(int32_t n, const int32_t* __restrict__ part, uint8_t* __restrict__ out) {
-    const int32_t v = blockIdx.x * 256 + threadIdx.x;
-    if (v < n) out[v] = static_cast<uint8_t>(part[v]);
-}
-
+// bw[b] += c(V_b), in `spread` copies of the k sums; raises *bad for a block
+// outside [0, k) (null: the blocks are known to be in range) and keeps a byte
+// copy of the blocks (null: not wanted).
 __global__ void __launch_bounds__(256) block_weight_kernel(int32_t n, const int32_t* __restrict__ part,
                                                            const int32_t* __restrict__ vw, int32_t k,
-                                                           unsigned long long* __restrict__ bw) {
+                                                           unsigned long long* __restrict__ bw, int32_t spread,
+                                                           uint32_t* __restrict__ bad, uint8_t* __restrict__ p8) {
     __shared__ unsigned long long loc[1024];
     const bool use_lds = k <= 1024;
     if (use_lds)
         for (int j = threadIdx.x; j < k; j += 256) loc[j] = 0;
     __syncthreads();
-    for (int32_t v = blockIdx.x * 256 + threadIdx.x; v < n; v += gridDim.x * 256) {
-        const unsigned long long c = vw ? static_cast<unsigned long long>(vw[v]) : 1ULL;
-        if (c) {
-            if (use_lds) atomicAdd(&loc[part[v]], c);
-            else atomicAdd(&bw[part[v]], c);
+    constexpr int U = 8;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
+    for (int64_t v0 = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; v0 < n; v0 += stride * U) {
+        int32_t b[U], c[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = v0 + u * stride;
+            b[u] = v < n ? part[v] : 0;
+            c[u] = v < n ? (vw ? vw[v] : 1) : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = v0 + u * stride;
+            if (bad && (b[u] < 0 || b[u] >= k)) {
+                *bad = 1;
+                continue;
+            }
+            if (p8 && v < n) p8[v] = static_cast<uint8_t>(b[u]);
+            // a negative weight (an unchecked graph) counts modulo 2^64, like any other
+            const unsigned long long cw = static_cast<unsigned long long>(c[u]);
+            if (c[u]) atomicAdd(use_lds ? &loc[b[u]] : &bw[b[u]], cw);
         }
     }
+    if (!use_lds) return;
     __syncthreads();
-    if (use_lds)
-        for (int j = threadIdx.x; j < k; j += 256)
-            if (loc[j]) atomicAdd(&bw[j], loc[j]);
+    for (int j = threadIdx.x; j < k; j += 256)
+        if (loc[j]) atomicAdd(&bw[static_cast<int64_t>(blockIdx.x % spread) * k + j], loc[j]);
 }
 
 // ------------------------------------------------------------- validation
@@ -88,34 +133,68 @@ __global__ void __launch_bounds__(256) block_weight_kernel(int32_t n, const int3
 struct VStats {
     unsigned long long cV;
     unsigned long long wsum;
-    unsigned long long hfwd;
-    unsigned long long hbwd;
+    unsigned long long hlow;   // hash sum of the slots u -> v with u < v
+    unsigned long long hhigh;  // and of the slots with u > v, taken as v -> u
     int32_t cmax;
-    uint32_t bad;  // bit 0: structure / range, bit 1: negative node weight, bit 2: edge weight < 1
-    uint32_t pad[2];
+    uint32_t bad;        // offsets, ids, self-loops, negative node weights or edge weights < 1
+    uint32_t node_unit;  // 0 while every node weight is 1
+    uint32_t edge_unit;  // 0 while every edge weight is 1
+    unsigned long long pad[10];  // one 128-byte line
 };
+static_assert(sizeof(VStats) == 128, "one line per copy");
 
-// Hash of a directed slot (u, v, w): sums over all slots and over all
-// reversed slots agree for a symmetric graph.  One mix of the ordered pair,
-// with the weight spread over all 64 bits by an odd multiplier.
+// The kSpread copies of the counters as one.
+VStats sum_stats(const VStats* st, hipStream_t s) {
+    VStats h[kSpread];
+    read_back(h, st, sizeof(h), s);
+    for (int q = 1; q < kSpread; ++q) {
+        h[0].cV += h[q].cV;
+        h[0].wsum += h[q].wsum;
+        h[0].hlow += h[q].hlow;
+        h[0].hhigh += h[q].hhigh;
+        h[0].cmax = std::max(h[0].cmax, h[q].cmax);
+        h[0].bad |= h[q].bad;
+        h[0].node_unit |= h[q].node_unit;
+        h[0].edge_unit |= h[q].edge_unit;
+    }
+    return h[0];
+}
+
+// Hash of an edge (u, v, w), u < v.  A graph is symmetric when the slots with
+// u < v and the slots with u > v are the same edges, and then the two hash sums
+// agree.  One mix of the ordered pair, with the weight spread over all 64 bits
+// by an odd multiplier.
 __device__ __forceinline__ unsigned long long edge_hash(uint32_t u, uint32_t v, uint32_t w) {
     return mix64(((static_cast<uint64_t>(u) << 32) | v) ^ (static_cast<uint64_t>(w) * 0xD6E8FEB86659FD93ULL));
 }
 
 __global__ void __launch_bounds__(kTileThreads) validate_nodes_kernel(int32_t n, const int64_t* __restrict__ xadj,
-                                                                      const int32_t* __restrict__ vw, VStats* st) {
+                                                                      const int32_t* __restrict__ vw,
+                                                                      VStats* __restrict__ stats) {
     __shared__ int32_t s_max[kTileThreads / kWave];
+    VStats* st = stats + blockIdx.x % kSpread;
     unsigned long long c = 0;
     int32_t cm = 0;
-    uint32_t bad = 0;
-    for (int32_t v = blockIdx.x * kTileThreads + threadIdx.x; v < n; v += gridDim.x * kTileThreads) {
-        if (xadj[v + 1] < xadj[v]) bad |= 1u;
-        const int32_t cv = vw ? vw[v] : 1;
-        if (cv < 0) {
-            bad |= 2u;
-        } else {
-            c += static_cast<unsigned long long>(cv);
-            cm = cv > cm ? cv : cm;
+    bool bad = false, other = false;
+    constexpr int U = 4;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * kTileThreads;
+    for (int64_t v0 = static_cast<int64_t>(blockIdx.x) * kTileThreads + threadIdx.x; v0 < n; v0 += stride * U) {
+        int64_t x0[U], x1[U];
+        int32_t cv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t v = v0 + u * stride;
+            x0[u] = v < n ? xadj[v] : 0;
+            x1[u] = v < n ? xadj[v + 1] : 0;
+            cv[u] = v < n && vw ? vw[v] : 1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (v0 + u * stride >= n) continue;
+            bad |= x1[u] < x0[u] || (v0 + u * stride == 0 && x0[u] != 0) || cv[u] < 0;
+            other |= cv[u] != 1;
+            c += static_cast<unsigned long long>(cv[u] < 0 ? 0 : cv[u]);
+            cm = cv[u] > cm ? cv[u] : cm;
         }
     }
     c = block_sum_u64(c);
@@ -127,57 +206,77 @@ __global__ void __launch_bounds__(kTileThreads) validate_nodes_kernel(int32_t n,
         if (c) atomicAdd(&st->cV, c);
         atomicMax(&st->cmax, cm);
     }
-    if (bad) atomicOr(&st->bad, bad);
+    if (bad) st->bad = 1;  // plain stores: every writer writes the same
+    if (other) st->node_unit = 1;
 }
 
+// 8 consecutive slots per thread and one mix per slot (a slot's edge is hashed
+// in one direction only): half the arithmetic and none of the LDS trips of one
+// slot per step with both directions, which took 101 us for the 13.8 M slots
+// of a 2^20-node mesh.
 __global__ void __launch_bounds__(kTileThreads) validate_slots_kernel(const int64_t* __restrict__ xadj,
                                                                       const int32_t* __restrict__ adj,
                                                                       const int32_t* __restrict__ ew, int32_t n,
-                                                                      int64_t S, VStats* st, const int32_t* __restrict__ trow) {
-    __shared__ int32_t owner[kTile];
-    unsigned long long ws = 0, hf = 0, hb = 0;
-    uint32_t bad = 0;
+                                                                      int64_t S, VStats* __restrict__ stats,
+                                                                      const int32_t* __restrict__ trow) {
+    __shared__ __align__(16) int32_t mark[kTile];
+    VStats* st = stats + blockIdx.x % kSpread;
+    unsigned long long ws = 0, hl = 0, hh = 0;
+    bool bad = false, other = false;
     for (int64_t tile = blockIdx.x; tile * kTile < S; tile += gridDim.x) {
         const int64_t i0 = tile * kTile;
         const int64_t i1 = i0 + kTile < S ? i0 + kTile : S;
-        tile_owners(xadj, trow, tile, i0, i1, owner);
-        for (int r = 0; r < kTilePer; ++r) {
-            const int64_t i = i0 + r * kTileThreads + threadIdx.x;
-            if (i >= i1) continue;
-            const int32_t u = owner[i - i0];
-            const int32_t x = adj[i];
-            const int32_t w = ew ? ew[i] : 1;
-            if (x < 0 || x >= n || x == u) bad |= 1u;
-            if (w < 1) bad |= 4u;
-            ws += static_cast<unsigned long long>(w > 0 ? w : 0);
-            hf += edge_hash(static_cast<uint32_t>(u), static_cast<uint32_t>(x), static_cast<uint32_t>(w));
-            hb += edge_hash(static_cast<uint32_t>(x), static_cast<uint32_t>(u), static_cast<uint32_t>(w));
+        const int64_t i = i0 + kTilePer * static_cast<int64_t>(threadIdx.x);
+        int32_t row[kTilePer], x[kTilePer], w[kTilePer];
+        tile_load(adj, i, i1, wide_tile(adj, i0, i1), 0, x);
+        if (ew) tile_load(ew, i, i1, wide_tile(ew, i0, i1), 1, w);
+        tile_rows(xadj, trow, tile, i0, i1, mark, row);
+#pragma unroll
+        for (int j = 0; j < kTilePer; ++j) {
+            if (i + j >= i1) continue;
+            const int32_t wj = ew ? w[j] : 1;
+            bad |= x[j] < 0 || x[j] >= n || x[j] == row[j] || wj < 1;
+            other |= wj != 1;
+            ws += static_cast<unsigned long long>(wj > 0 ? wj : 0);
+            const uint32_t lo = static_cast<uint32_t>(row[j] < x[j] ? row[j] : x[j]);
+            const uint32_t hi = static_cast<uint32_t>(row[j] < x[j] ? x[j] : row[j]);
+            const unsigned long long h = edge_hash(lo, hi, static_cast<uint32_t>(wj));
+            hl += row[j] < x[j] ? h : 0;
+            hh += row[j] < x[j] ? 0 : h;
         }
-        __syncthreads();
     }
     ws = block_sum_u64(ws);
-    hf = block_sum_u64(hf);
-    hb = block_sum_u64(hb);
+    hl = block_sum_u64(hl);
+    hh = block_sum_u64(hh);
     if (threadIdx.x == 0) {
         if (ws) atomicAdd(&st->wsum, ws);
-        atomicAdd(&st->hfwd, hf);
-        atomicAdd(&st->hbwd, hb);
+        atomicAdd(&st->hlow, hl);
+        atomicAdd(&st->hhigh, hh);
     }
-    if (bad) atomicOr(&st->bad, bad);
+    if (bad) st->bad = 1;
+    if (other) st->edge_unit = 1;
 }
 
-// Flags any value outside [lo, hi) with at most one atomic per wave (a
-// per-element atomic on the one flag serialises when most values are out,
-// as in the unit-weight test of a weighted graph).
-__global__ void range_kernel(const int32_t* __restrict__ a, int64_t count, int32_t lo, int32_t hi,
-                             uint32_t* __restrict__ bad) {
-    bool b = false;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < count;
-         i += static_cast<int64_t>(gridDim.x) * 256) {
-        const int32_t x = a[i];
-        b |= x < lo || x >= hi;
+// Flags any value outside [lo, hi): a plain store (every writer writes the
+// same), and nothing more is read once the flag is up.  An atomic per wave on
+// the one flag took 190 us where most values are out, as in the unit-weight
+// test of a weighted graph.
+__global__ void __launch_bounds__(256) range_kernel(const int32_t* __restrict__ a, int64_t count, int32_t lo,
+                                                    int32_t hi, uint32_t* bad) {
+    constexpr int U = 8;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < count; i += stride * U) {
+        bool b = false;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t x = i + u * stride < count ? a[i + u * stride] : lo;
+            b |= x < lo || x >= hi;
+        }
+        if (__any(b)) {
+            if (lane_id() == 0) *bad = 1;
+            return;
+        }
     }
-    if (__any(b) && lane_id() == 0) atomicOr(bad, 1u);
 }
 
 unsigned capped_tiles(int64_t S) {
@@ -198,31 +297,56 @@ void project(int32_t n, const int32_t* C, const int32_t* coarse_part, int32_t* p
     LAUNCHCHK();
 }
 
-void cut_and_weights(const DevGraph& g, const int32_t* part, int32_t k, int64_t* cut, int64_t* bw, hipStream_t s) {
-    DBuf<unsigned long long> acc(1 + static_cast<size_t>(k), s);
-    HIPCHK(hipMemsetAsync(acc.get(), 0, (1 + static_cast<size_t>(k)) * sizeof(unsigned long long), s));
+bool project_checked(int32_t n, int32_t nc, const int32_t* C, const int32_t* coarse_part, int32_t* part,
+                     hipStream_t s) {
+    if (n <= 0) return true;
+    DBuf<uint32_t> bad(1, s);
+    fill_u32(bad.get(), 0, 1, s);
+    project_checked_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, nc, C, coarse_part, part, bad.get());
+    LAUNCHCHK();
+    uint32_t h = 0;
+    read_back(&h, bad.get(), sizeof(h), s);
+    return h == 0;
+}
+
+bool cut_and_weights(const DevGraph& g, const int32_t* part, int32_t k, int64_t* cut, int64_t* bw, bool check,
+                     hipStream_t s) {
+    // kSpread copies of the cut, then `copies` of the block weights, then the flag
+    const int32_t copies = k <= 256 ? 8 : 1;
+    const size_t words = kSpread * kLine64 + static_cast<size_t>(copies) * k + 1;
+    DBuf<unsigned long long> acc(words, s);
+    fill_u32(reinterpret_cast<uint32_t*>(acc.get()), 0, 2 * static_cast<int64_t>(words), s);
+    unsigned long long* wacc = acc.get() + kSpread * kLine64;
+    uint32_t* bad = reinterpret_cast<uint32_t*>(acc.get() + words - 1);
+    DBuf<uint8_t> p8;
+    if (g.n > 0) {
+        if (g.S > 0 && k <= 256) p8.alloc(g.n, s);
+        block_weight_kernel<<<std::min(capped_nodes(g.n), 256u), 256, 0, s>>>(g.n, part, g.vw, k, wacc, copies,
+                                                                              check ? bad : nullptr, p8.get());
+        LAUNCHCHK();
+    }
     if (g.S > 0) {
         TileRows tr(g.xadj, g.n, g.S, s);
-        if (k <= 256) {
-            DBuf<uint8_t> p8(g.n, s);
-            to_u8_kernel<<<grid_for(g.n, 256), 256, 0, s>>>(g.n, part, p8.get());
-            LAUNCHCHK();
+        if (p8.get())
             cut_kernel<uint8_t><<<capped_tiles(g.S), kTileThreads, 0, s>>>(g.xadj, g.adj, g.ew, g.n, g.S, p8.get(),
-                                                                          acc.get(), tr.trow.get());
-        } else {
+                                                                          acc.get(), kSpread, tr.trow.get());
+        else
             cut_kernel<int32_t><<<capped_tiles(g.S), kTileThreads, 0, s>>>(g.xadj, g.adj, g.ew, g.n, g.S, part,
-                                                                          acc.get(), tr.trow.get());
-        }
+                                                                          acc.get(), kSpread, tr.trow.get());
         LAUNCHCHK();
     }
-    if (g.n > 0) {
-        block_weight_kernel<<<capped_nodes(g.n), 256, 0, s>>>(g.n, part, g.vw, k, acc.get() + 1);
-        LAUNCHCHK();
+    std::vector<unsigned long long> h(words);
+    read_back(h.data(), acc.get(), words * sizeof(unsigned long long), s);
+    if (check && h[words - 1]) return false;
+    unsigned long long c2 = 0;
+    for (int q = 0; q < kSpread; ++q) c2 += h[q * kLine64];
+    *cut = static_cast<int64_t>(c2 / 2);
+    for (int32_t b = 0; b < k; ++b) {
+        unsigned long long t = 0;
+        for (int32_t q = 0; q < copies; ++q) t += h[kSpread * kLine64 + static_cast<size_t>(q) * k + b];
+        bw[b] = static_cast<int64_t>(t);
     }
-    std::vector<unsigned long long> h(1 + static_cast<size_t>(k));
-    read_back(h.data(), acc.get(), h.size() * sizeof(unsigned long long), s);
-    *cut = static_cast<int64_t>(h[0] / 2);
-    for (int32_t b = 0; b < k; ++b) bw[b] = static_cast<int64_t>(h[1 + b]);
+    return true;
 }
 
 // ------------------------------------------- cut without device allocation
@@ -289,11 +413,13 @@ void cut_and_weights_noalloc(const DevGraph& g, const int32_t* part, int32_t k, 
     if (ntiles > 0) {
         tile_rows_kernel<<<grid_for(ntiles + 1, 256), 256, 0, s>>>(g.xadj, g.n, g.S, ntiles, trow);
         LAUNCHCHK();
-        cut_kernel<int32_t><<<capped_tiles(g.S), kTileThreads, 0, s>>>(g.xadj, g.adj, g.ew, g.n, g.S, part, acc, trow);
+        cut_kernel<int32_t><<<capped_tiles(g.S), kTileThreads, 0, s>>>(g.xadj, g.adj, g.ew, g.n, g.S, part, acc, 1,
+                                                                      trow);
         LAUNCHCHK();
     }
     if (g.n > 0) {
-        block_weight_kernel<<<capped_nodes(g.n), 256, 0, s>>>(g.n, part, g.vw, k, acc + 1);
+        block_weight_kernel<<<std::min(capped_nodes(g.n), 256u), 256, 0, s>>>(g.n, part, g.vw, k, acc + 1, 1, nullptr,
+                                                                              nullptr);
         LAUNCHCHK();
     }
     unsigned long long c2 = 0;
@@ -366,39 +492,39 @@ float gather_probe(const DevGraph& g, int32_t label_bytes, int32_t reps, hipStre
     return ms / static_cast<float>(reps > 0 ? reps : 1);
 }
 
-int validate_graph(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s) {
+int validate_graph(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s, bool* unit) {
     const int32_t n = g.n;
     if (n < 0) return -1;
+    if (unit) unit[0] = unit[1] = true;
     if (n == 0) {
         *cV = 0;
         *cmax = 0;
         return 0;
     }
-    if (!g.xadj) return -1;
-    int64_t ends[2];
-    const ReadItem items[2] = {{&ends[0], g.xadj, sizeof(int64_t)}, {&ends[1], g.xadj + n, sizeof(int64_t)}};
-    read_back(items, 2, s);
-    if (ends[0] != 0 || ends[1] != g.S || g.S < 0) return -1;
+    if (!g.xadj || g.S < 0) return -1;
     if (g.S > 0 && !g.adj) return -1;
-    DBuf<VStats> st(1, s);
-    HIPCHK(hipMemsetAsync(st.get(), 0, sizeof(VStats), s));
-    validate_nodes_kernel<<<capped_nodes(n), kTileThreads, 0, s>>>(n, g.xadj, g.vw, st.get());
+    DBuf<VStats> st(kSpread, s);
+    fill_u32(reinterpret_cast<uint32_t*>(st.get()), 0, kSpread * static_cast<int64_t>(sizeof(VStats) / 4), s);
+    validate_nodes_kernel<<<std::min(capped_nodes(n), 512u), kTileThreads, 0, s>>>(n, g.xadj, g.vw, st.get());
     LAUNCHCHK();
-    VStats h;
-    read_back(&h, st.get(), sizeof(VStats), s);
-    if (h.bad) return -1;  // offsets not monotone or negative node weight
+    VStats h = sum_stats(st.get(), s);
+    if (h.bad) return -1;  // offsets not monotone from 0, or a negative node weight
     if (g.S > 0) {
         TileRows tr(g.xadj, n, g.S, s);  // offsets checked monotone above
         validate_slots_kernel<<<capped_tiles(g.S), kTileThreads, 0, s>>>(g.xadj, g.adj, g.ew, n, g.S, st.get(),
                                                                           tr.trow.get());
         LAUNCHCHK();
-        read_back(&h, st.get(), sizeof(VStats), s);
+        h = sum_stats(st.get(), s);
     }
     if (h.bad) return -1;
     if (h.cV > 2147483647ULL || h.wsum / 2 > 2147483647ULL) return -3;
-    if (h.hfwd != h.hbwd) return -2;
+    if (h.hlow != h.hhigh) return -2;
     *cV = static_cast<int64_t>(h.cV);
     *cmax = h.cmax;
+    if (unit) {
+        unit[0] = h.node_unit == 0;
+        unit[1] = h.edge_unit == 0;
+    }
     return 0;
 }
 
@@ -408,12 +534,11 @@ void node_weight_stats(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_
         *cmax = 0;
         return;
     }
-    DBuf<VStats> st(1, s);
-    HIPCHK(hipMemsetAsync(st.get(), 0, sizeof(VStats), s));
-    validate_nodes_kernel<<<capped_nodes(g.n), kTileThreads, 0, s>>>(g.n, g.xadj, g.vw, st.get());
+    DBuf<VStats> st(kSpread, s);
+    fill_u32(reinterpret_cast<uint32_t*>(st.get()), 0, kSpread * static_cast<int64_t>(sizeof(VStats) / 4), s);
+    validate_nodes_kernel<<<std::min(capped_nodes(g.n), 512u), kTileThreads, 0, s>>>(g.n, g.xadj, g.vw, st.get());
     LAUNCHCHK();
-    VStats h;
-    read_back(&h, st.get(), sizeof(VStats), s);
+    const VStats h = sum_stats(st.get(), s);
     *cV = static_cast<int64_t>(h.cV);
     *cmax = h.cmax;
 }
@@ -422,8 +547,8 @@ bool all_in_range(const int32_t* a, int64_t count, int32_t lo, int32_t hi, hipSt
     if (count <= 0) return true;
     DBuf<uint32_t> bad(1, s);
     fill_u32(bad.get(), 0, 1, s);
-    range_kernel<<<static_cast<unsigned>(std::min<int64_t>((count + 255) / 256, 8192)), 256, 0, s>>>(a, count, lo, hi,
-                                                                                                    bad.get());
+    range_kernel<<<static_cast<unsigned>(std::min<int64_t>((count + 2047) / 2048, 4096)), 256, 0, s>>>(a, count, lo, hi,
+                                                                                                      bad.get());
     LAUNCHCHK();
     uint32_t h = 0;
     read_back(&h, bad.get(), sizeof(uint32_t), s);
@@ -468,68 +593,95 @@ __global__ void members_closed_kernel(int64_t S, int32_t M, const int64_t* __res
     if (__any(b) && lane_id() == 0) atomicOr(bad, 1u);
 }
 
-// One atomic per wave when the wave's items belong to one graph (graphs are
-// contiguous), else one per item.
-__device__ __forceinline__ void add_by_graph(bool valid, int32_t g, unsigned long long val,
-                                             unsigned long long* __restrict__ out) {
-    const int32_t lo = wave_min(valid ? g : INT_MAX);
-    const int32_t hi = wave_max(valid ? g : -1);
-    if (lo == hi) {
-        const unsigned long long t = wave_sum(valid ? val : 0ULL);
-        if (lane_id() == 0 && t) atomicAdd(&out[lo], t);
-    } else if (valid && val) {
-        atomicAdd(&out[g], val);
+// Node weight total and maximum of every graph: each workgroup takes a run of
+// consecutive nodes, 256 at a time, and sums while they lie in one graph.
+__global__ void __launch_bounds__(256) graph_node_stats_kernel(int32_t n, const int32_t* __restrict__ gid,
+                                                               const int32_t* __restrict__ vw,
+                                                               unsigned long long* __restrict__ cV,
+                                                               unsigned long long* __restrict__ cmax) {
+    const int64_t per = ((n + gridDim.x - 1) / gridDim.x + 255) / 256 * 256;
+    const int64_t end = (blockIdx.x + 1) * per < n ? (blockIdx.x + 1) * per : n;
+    int32_t cur = -1;  // graph of the sums so far, the same for the workgroup
+    unsigned long long acc = 0;
+    int32_t cm = 0;
+    auto flush = [&]() {
+        if (cur < 0) return;
+        const unsigned long long t = block_sum_u64(acc);
+        const int32_t m = wave_max(cm);
+        if (threadIdx.x == 0 && t) atomicAdd(&cV[cur], t);
+        if (lane_id() == 0 && m > 0) atomicMax(&cmax[cur], static_cast<unsigned long long>(m));
+        acc = 0;
+        cm = 0;
+    };
+    for (int64_t base = blockIdx.x * per; base < end; base += 256) {
+        const int64_t v = base + threadIdx.x;
+        const int64_t last = base + 255 < end ? base + 255 : end - 1;
+        const int32_t ga = gid[base], gb = gid[last];
+        const int32_t c = v < end ? (vw ? vw[v] : 1) : 0;
+        if (ga == gb) {
+            if (ga != cur) flush();
+            cur = ga;
+            acc += static_cast<unsigned long long>(c < 0 ? 0 : c);
+            cm = c > cm ? c : cm;
+        } else if (v < end && c > 0) {
+            atomicAdd(&cV[gid[v]], static_cast<unsigned long long>(c));
+            atomicMax(&cmax[gid[v]], static_cast<unsigned long long>(c));
+        }
     }
+    flush();
 }
 
-__global__ void graph_node_stats_kernel(int32_t n, const int32_t* __restrict__ gid, const int32_t* __restrict__ vw,
-                                        unsigned long long* __restrict__ cV, unsigned long long* __restrict__ cmax) {
-    const int32_t v = blockIdx.x * 256 + threadIdx.x;
-    const bool valid = v < n;
-    const int32_t g = valid ? gid[v] : 0;
-    const int32_t c = valid ? (vw ? vw[v] : 1) : 0;
-    add_by_graph(valid, g, static_cast<unsigned long long>(c < 0 ? 0 : c), cV);
-    const int32_t lo = wave_min(valid ? g : INT_MAX);
-    const int32_t hi = wave_max(valid ? g : -1);
-    if (lo == hi) {
-        const int32_t m = wave_max(valid ? c : 0);
-        if (lane_id() == 0 && m > 0) atomicMax(&cmax[lo], static_cast<unsigned long long>(m));
-    } else if (valid && c > 0) {
-        atomicMax(&cmax[g], static_cast<unsigned long long>(c));
-    }
-}
-
+// Cut of every graph: each workgroup takes a run of consecutive tiles and sums
+// while they lie in one graph, so a graph gets one atomic per workgroup and
+// not one per wave and tile (64 graphs, 47 M slots: 750 us).
 __global__ void __launch_bounds__(kTileThreads) graph_cut_kernel(const int64_t* __restrict__ xadj,
                                                                  const int32_t* __restrict__ adj,
                                                                  const int32_t* __restrict__ ew, int32_t n, int64_t S,
                                                                  const int32_t* __restrict__ part,
                                                                  const int32_t* __restrict__ gid,
-                                                                 unsigned long long* __restrict__ cut, const int32_t* __restrict__ trow) {
-    __shared__ int32_t owner[kTile];
-    for (int64_t tile = blockIdx.x; tile * kTile < S; tile += gridDim.x) {
+                                                                 unsigned long long* __restrict__ cut,
+                                                                 const int32_t* __restrict__ trow) {
+    __shared__ __align__(16) int32_t mark[kTile];
+    const int64_t ntiles = (S + kTile - 1) / kTile;
+    const int64_t per = (ntiles + gridDim.x - 1) / gridDim.x;
+    const int64_t t_end = (blockIdx.x + 1) * per < ntiles ? (blockIdx.x + 1) * per : ntiles;
+    int32_t cur = -1;  // graph of the sum so far, the same for the workgroup
+    unsigned long long acc = 0;
+    auto flush = [&]() {
+        if (cur < 0) return;
+        const unsigned long long t = block_sum_u64(acc);
+        if (threadIdx.x == 0 && t) atomicAdd(&cut[cur], t);
+        acc = 0;
+    };
+    for (int64_t tile = blockIdx.x * per; tile < t_end; ++tile) {
         const int64_t i0 = tile * kTile;
         const int64_t i1 = i0 + kTile < S ? i0 + kTile : S;
-        tile_owners(xadj, trow, tile, i0, i1, owner);
-        // each lane sums its slots of the tile per graph (its graph changes
-        // at most at a graph boundary), then one atomic per wave when the
-        // wave's lanes ended in one graph
-        int32_t gc = -1;
-        unsigned long long acc = 0;
-        for (int r = 0; r < kTilePer; ++r) {
-            const int64_t i = i0 + r * kTileThreads + threadIdx.x;
-            if (i >= i1) break;
-            const int32_t u = owner[i - i0];
-            const int32_t g = gid[u];
-            if (g != gc) {
-                if (acc) atomicAdd(&cut[gc], acc);
-                gc = g;
-                acc = 0;
-            }
-            if (part[u] != part[adj[i]]) acc += ew ? static_cast<unsigned long long>(ew[i]) : 1ULL;
+        const int64_t i = i0 + kTilePer * static_cast<int64_t>(threadIdx.x);
+        const int32_t ga = gid[trow[tile]], gb = gid[trow[tile + 1]];
+        int32_t row[kTilePer], x[kTilePer], w[kTilePer];
+        tile_load(adj, i, i1, wide_tile(adj, i0, i1), -1, x);
+        if (ew) tile_load(ew, i, i1, wide_tile(ew, i0, i1), 0, w);
+        tile_rows(xadj, trow, tile, i0, i1, mark, row);
+        int32_t px[kTilePer], pu[kTilePer];
+#pragma unroll
+        for (int j = 0; j < kTilePer; ++j) {
+            pu[j] = part[row[j]];
+            px[j] = x[j] >= 0 ? part[x[j]] : pu[j];
         }
-        add_by_graph(gc >= 0, gc, acc, cut);
-        __syncthreads();
+        if (ga == gb) {  // the whole tile in one graph
+            if (ga != cur) flush();
+            cur = ga;
+#pragma unroll
+            for (int j = 0; j < kTilePer; ++j)
+                if (px[j] != pu[j]) acc += ew ? static_cast<unsigned long long>(w[j]) : 1ULL;
+        } else {
+#pragma unroll
+            for (int j = 0; j < kTilePer; ++j)
+                if (px[j] != pu[j])
+                    atomicAdd(&cut[gid[row[j]]], ew ? static_cast<unsigned long long>(w[j]) : 1ULL);
+        }
     }
+    flush();
 }
 
 __global__ void compact_nodes_kernel(int32_t n_new, int32_t Mk, const int32_t* __restrict__ nnb,
@@ -679,7 +831,7 @@ void graph_node_stats(int32_t n, const int32_t* gid, const int32_t* vw, int32_t 
     DBuf<unsigned long long> d(2 * static_cast<size_t>(std::max(G, 1)), s);
     HIPCHK(hipMemsetAsync(d.get(), 0, 2 * std::max(G, 1) * sizeof(unsigned long long), s));
     if (n > 0) {
-        graph_node_stats_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, gid, vw, d.get(), d.get() + G);
+        graph_node_stats_kernel<<<std::min(grid_for(n, 2048), 1024u), 256, 0, s>>>(n, gid, vw, d.get(), d.get() + G);
         LAUNCHCHK();
     }
     std::vector<unsigned long long> h(2 * static_cast<size_t>(std::max(G, 1)));
@@ -695,7 +847,7 @@ void graph_cuts(const DevGraph& g, const int32_t* part, const int32_t* gid, int3
     HIPCHK(hipMemsetAsync(d.get(), 0, std::max(G, 1) * sizeof(unsigned long long), s));
     if (g.S > 0) {
         const int64_t ntiles = (g.S + kTile - 1) / kTile;
-        const unsigned grid = static_cast<unsigned>(ntiles < 2048 ? ntiles : 2048);
+        const unsigned grid = static_cast<unsigned>(ntiles < 1024 ? ntiles : 1024);
         TileRows tr(g.xadj, g.n, g.S, s);
         graph_cut_kernel<<<grid, kTileThreads, 0, s>>>(g.xadj, g.adj, g.ew, g.n, g.S, part, gid, d.get(),
                                                        tr.trow.get());

@@ -46,9 +46,14 @@ void sort_rows(OwnedDevGraph& g, hipStream_t s);
 
 // part[v] = coarse_part[C[v]]
 void project(int32_t n, const int32_t* C, const int32_t* coarse_part, int32_t* part, hipStream_t s);
+// The same with a look at every id: false if one lies outside [0, nc).
+bool project_checked(int32_t n, int32_t nc, const int32_t* C, const int32_t* coarse_part, int32_t* part,
+                     hipStream_t s);
 
 // cut (host out) and block weights bw[k] (host out).
-void cut_and_weights(const DevGraph& g, const int32_t* part, int32_t k, int64_t* cut, int64_t* bw, hipStream_t s);
+// check: returns false, with nothing written, if a block lies outside [0, k).
+bool cut_and_weights(const DevGraph& g, const int32_t* part, int32_t k, int64_t* cut, int64_t* bw, bool check,
+                     hipStream_t s);
 // The same without allocating device memory: a fixed per-device workspace in
 // the library image (k <= 65536, at most 3,932,159 slot tiles of 2048); checks
 // part values itself.  Overlapping calls on one device race.
@@ -57,7 +62,8 @@ void cut_and_weights_noalloc(const DevGraph& g, const int32_t* part, int32_t k, 
 
 // Checks CSR structure, ranges, weights, totals and symmetry (hash test).
 // Returns 0 or a negative status.  Also reports c(V) and max c(v).
-int validate_graph(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s);
+// unit (two flags, may be null): whether all node and all edge weights are 1.
+int validate_graph(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s, bool* unit = nullptr);
 
 // c(V) and max_v c(v) without validation.
 void node_weight_stats(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s);

@@ -92,5 +92,79 @@ __device__ void tile_owners(const int64_t* __restrict__ xadj, const int32_t* __r
     __syncthreads();
 }
 
+// The same for the kTilePer consecutive slots i0 + kTilePer * threadIdx.x ..
+// of each thread, in registers (entries past i1 repeat the last row): no
+// second trip through LDS, and the thread reads its slots' ids and weights 16
+// bytes at a time.  mark: kTile entries of LDS, 16-byte aligned.
+__device__ __forceinline__ void tile_rows(const int64_t* __restrict__ xadj, const int32_t* __restrict__ trow,
+                                          int64_t tile, int64_t i0, int64_t i1, int32_t* mark,
+                                          int32_t (&row)[kTilePer]) {
+    static_assert(kTilePer == 8, "two 16-byte words per thread");
+    __shared__ int32_t s_carry[kTileThreads / kWave];
+    const int tid = threadIdx.x;
+    int4* own = reinterpret_cast<int4*>(mark) + 2 * tid;
+    own[0] = make_int4(-1, -1, -1, -1);
+    own[1] = make_int4(-1, -1, -1, -1);
+    const int32_t u0 = trow[tile], u1 = trow[tile + 1];
+    __syncthreads();
+    for (int64_t u = static_cast<int64_t>(u0) + 1 + tid; u <= u1; u += kTileThreads) {
+        const int64_t st = xadj[u];
+        if (st >= i0 && st < i1) atomicMax(&mark[st - i0], static_cast<int32_t>(u));
+    }
+    __syncthreads();
+    const int4 a = own[0], b = own[1];
+    row[0] = a.x;
+    row[1] = a.y;
+    row[2] = a.z;
+    row[3] = a.w;
+    row[4] = b.x;
+    row[5] = b.y;
+    row[6] = b.z;
+    row[7] = b.w;
+#pragma unroll
+    for (int j = 1; j < kTilePer; ++j) row[j] = row[j] > row[j - 1] ? row[j] : row[j - 1];
+    int32_t incl = row[kTilePer - 1];
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int32_t x = __shfl_up(incl, o, 64);
+        if (lane_id() >= o) incl = x > incl ? x : incl;
+    }
+    if (lane_id() == kWave - 1) s_carry[tid / kWave] = incl;
+    __syncthreads();
+    int32_t run = __shfl_up(incl, 1, 64);
+    if (lane_id() == 0) run = -1;
+    run = u0 > run ? u0 : run;
+#pragma unroll
+    for (int w = 0; w < kTileThreads / kWave; ++w) run = w < tid / kWave && s_carry[w] > run ? s_carry[w] : run;
+#pragma unroll
+    for (int j = 0; j < kTilePer; ++j) row[j] = row[j] > run ? row[j] : run;
+}
+
+// The thread's kTilePer values of a slot array from slot i on; `past` beyond
+// i1.  wide (the same for the whole workgroup): the tile is full and p
+// 16-byte aligned.
+__device__ __forceinline__ bool wide_tile(const void* p, int64_t i0, int64_t i1) {
+    return i1 - i0 == kTile && (reinterpret_cast<uintptr_t>(p) & 15u) == 0;
+}
+
+__device__ __forceinline__ void tile_load(const int32_t* __restrict__ p, int64_t i, int64_t i1, bool wide, int32_t past,
+                                          int32_t (&x)[kTilePer]) {
+    if (wide) {
+        const int4 a = reinterpret_cast<const int4*>(p + i)[0];
+        const int4 b = reinterpret_cast<const int4*>(p + i)[1];
+        x[0] = a.x;
+        x[1] = a.y;
+        x[2] = a.z;
+        x[3] = a.w;
+        x[4] = b.x;
+        x[5] = b.y;
+        x[6] = b.z;
+        x[7] = b.w;
+    } else {
+#pragma unroll
+        for (int j = 0; j < kTilePer; ++j) x[j] = i + j < i1 ? p[i + j] : past;
+    }
+}
+
 }  // namespace
 }  // namespace sclap
