@@ -120,8 +120,7 @@ int cluster_impl(const DevGraph& g_in, int64_t U, int32_t rounds, uint64_t seed,
     if (color_dev && !all_in_range(color_dev, g.n, 0, o.nsub, s))
         fail(SCLAP_ERR_INVALID, "color_override value outside [0, subrounds)");
     DBuf<int32_t> w(std::max(g.n, 1), s);
-    iota_u32(reinterpret_cast<uint32_t*>(labels), g.n, s);
-    label_weights(g, labels, w.get(), g.n, s);
+    singletons(g, labels, w.get(), s);
     OwnedDevGraph inside;
     DevGraph gc = g;
     if (block) {

@@ -9,13 +9,14 @@
 //   2. scan the row counts into row offsets, give every node a block of its
 //      row and scatter (C(v), w) of every such slot into its node's block
 //      (each wave's run of a row reserves its part with one atomic);
-//   3. sort each row by C(v) and merge equal neighbours, summing weights:
-//      rows of up to 64 entries in the registers of one wave (bitonic network
-//      over lanes), up to 4096 in the LDS of one workgroup, longer rows by a
-//      radix sort of (row, C(v)) keys over just those rows;
-//   4. scan the merged row lengths into the coarse offsets and copy.
-// The result is canonical (rows ascend by neighbour id) whatever order the
-// atomics of step 2 produced.
+//   3. merge equal neighbours of each row, summing weights: rows of up to 64
+//      entries in the registers of one wave (bitonic network over lanes), up
+//      to 4096 in an LDS table of one workgroup, longer rows by chunks and then
+//      by hash buckets;
+//   4. scan the merged row lengths into the coarse offsets and copy;
+//   5. for the canonical form (rows ascend by neighbour id, whatever order the
+//      atomics of step 2 produced) order every row's distinct entries by an
+//      LDS radix sort, rows of more than 8192 by one over (row, id) keys.
 #include <climits>
 
 #include "graph_ops.hpp"
@@ -27,7 +28,8 @@ namespace sclap {
 namespace {
 
 constexpr int kWaveRow = 64;     // rows up to this length: one wave
-constexpr int kBlockRow = 4096;  // up to this length: one workgroup, LDS sort
+constexpr int kBlockRow = 4096;  // up to this length: one workgroup, LDS table
+constexpr int kRowClasses = 7;   // one wave; tables for up to 256, 512, .. 4096 entries; long
 
 __global__ void mark_used_kernel(int32_t n, const int32_t* __restrict__ labels, int32_t* __restrict__ used) {
     const int32_t v = blockIdx.x * 256 + threadIdx.x;
@@ -160,16 +162,17 @@ __global__ void __launch_bounds__(kTileThreads) row_scatter_kernel(const int64_t
 }
 
 // Rows by length: 0 or 1 entries are final as they are; the others go to the
-// wave, workgroup or long-row lists.
+// list of their class: up to 64 entries (one wave), up to 256, 512, .. 4096 (one
+// workgroup with a table of twice that) or long.
 // (each workgroup takes kClassifyIters * 256 consecutive rows at a time and
-// appends to each list with one atomic: the three counters are few and hot)
+// appends to each list with one atomic: the counters are few and hot)
 constexpr int kClassifyIters = 16;
 
 __global__ void __launch_bounds__(256) row_classify_kernel(int32_t nc, const int32_t* __restrict__ rowcnt,
                                                            int32_t* __restrict__ dcnt, int32_t* __restrict__ lists,
                                                            int32_t cap, uint32_t* __restrict__ counts) {
     for (int32_t base = blockIdx.x * (kClassifyIters * 256); base < nc; base += gridDim.x * (kClassifyIters * 256)) {
-        uint32_t m[3] = {0, 0, 0};
+        uint32_t m[kRowClasses] = {};
         int32_t lens[kClassifyIters];
 #pragma unroll
         for (int it = 0; it < kClassifyIters; ++it) {
@@ -185,15 +188,39 @@ __global__ void __launch_bounds__(256) row_classify_kernel(int32_t nc, const int
                 dcnt[r] = len;
                 continue;
             }
-            m[len <= kWaveRow ? 0 : (len <= kBlockRow ? 1 : 2)] |= 1u << it;
+#pragma unroll
+            for (int c = 0; c < kRowClasses; ++c) {
+                const int32_t lo = c == 0 ? 1 : (c == 1 ? kWaveRow : 128 << (c - 1));
+                const int32_t hi = c == 0 ? kWaveRow : (c == kRowClasses - 1 ? INT_MAX : 128 << c);
+                if (len > lo && len <= hi) m[c] |= 1u << it;
+            }
         }
-        for (int c = 0; c < 3; ++c) {
+#pragma unroll
+        for (int c = 0; c < kRowClasses; ++c) {
             uint32_t bits = m[c];
+            if (!__syncthreads_or(bits != 0)) continue;
             uint32_t j = block_append_count(static_cast<uint32_t>(__popc(bits)), &counts[c]);
             while (bits) {
                 const int it = __ffs(bits) - 1;
                 bits &= bits - 1;
                 lists[static_cast<int64_t>(c) * cap + j++] = base + it * 256 + static_cast<int32_t>(threadIdx.x);
+            }
+        }
+    }
+}
+
+// Sorts (key, w) over the 64 lanes of a wave.
+__device__ __forceinline__ void bitonic_wave(uint32_t& key, int32_t& w, int lane) {
+    for (int k = 2; k <= 64; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            const uint32_t ok = __shfl_xor(key, j, 64);
+            const int32_t ow = __shfl_xor(w, j, 64);
+            const bool up = (lane & k) == 0;
+            const bool low = (lane & j) == 0;
+            const bool take = low == up ? ok < key : ok > key;
+            if (take) {
+                key = ok;
+                w = ow;
             }
         }
     }
@@ -213,19 +240,7 @@ __global__ void __launch_bounds__(256) wave_rows_kernel(const int32_t* __restric
     const int32_t len = rowcnt[row];
     uint32_t key = lane < len ? static_cast<uint32_t>(tk[b + lane]) : 0xFFFFFFFFu;
     int32_t w = lane < len ? tw[b + lane] : 0;
-    for (int k = 2; k <= 64; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            const uint32_t ok = __shfl_xor(key, j, 64);
-            const int32_t ow = __shfl_xor(w, j, 64);
-            const bool up = (lane & k) == 0;
-            const bool low = (lane & j) == 0;
-            const bool take = low == up ? ok < key : ok > key;
-            if (take) {
-                key = ok;
-                w = ow;
-            }
-        }
-    }
+    bitonic_wave(key, w, lane);
     // merge equal neighbours: inclusive sums over the lanes, then per run
     const uint32_t prev = __shfl_up(key, 1, 64);
     const bool valid = lane < len;
@@ -248,73 +263,215 @@ __global__ void __launch_bounds__(256) wave_rows_kernel(const int32_t* __restric
     if (lane == 0) dcnt[row] = __popcll(heads);
 }
 
-// Rows of 65..4096 entries: one workgroup per row, bitonic sort of
-// (C(v) << 32 | w) in LDS, then the merged row to the row's start.
-__global__ void __launch_bounds__(256) block_rows_kernel(const int32_t* __restrict__ list,
-                                                         const int64_t* __restrict__ rowoff,
-                                                         const int32_t* __restrict__ rowcnt, int32_t* __restrict__ tk,
-                                                         int32_t* __restrict__ tw, int32_t* __restrict__ dcnt) {
-    __shared__ uint64_t sk[kBlockRow];
-    __shared__ int32_t s_cnt[256];
+// Orders rows of distinct entries by neighbour id: one workgroup of NW waves
+// per row of up to NW * 512 entries, a stable least-significant-digit-first
+// radix sort of (id, w) with 8-bit digits.  Elements live in registers (8 per
+// thread, a wave holding consecutive ones) and meet in LDS once per digit: a
+// wave ranks its elements by matching digits with ballots against counters of
+// its own.  A bitonic network over the entries before they were merged took
+// 4.0 ms on the rows of 65..4096 entries of a contracted R-MAT 2^22; merging
+// first and ordering the distinct entries like this takes 1.0 ms.
+template <int NW>
+__global__ void __launch_bounds__(NW * 64) order_rows_kernel(const int32_t* __restrict__ list,
+                                                             const int64_t* __restrict__ xadj,
+                                                             int32_t* __restrict__ adj, int32_t* __restrict__ ew,
+                                                             int bits) {
+    constexpr int NT = NW * 64;
+    constexpr int E = 8;
+    constexpr int kD = 256;
+    constexpr int kDT = NT < kD ? kD / NT : 1;  // digits per thread in the scan
+    __shared__ uint64_t buf[NT * E];
+    __shared__ uint32_t cnt[NW][kD];
+    __shared__ uint32_t s_w[NW < 4 ? 1 : 4];
     const int tid = threadIdx.x;
+    const int lane = lane_id();
+    const int w = tid >> 6;
     const int32_t row = list[blockIdx.x];
-    const int64_t b = rowoff[row];
-    const int32_t len = rowcnt[row];
-    int32_t P = 128;
-    while (P < len) P <<= 1;
-    for (int32_t j = tid; j < P; j += 256)
-        sk[j] = j < len ? (static_cast<uint64_t>(static_cast<uint32_t>(tk[b + j])) << 32) |
-                              static_cast<uint32_t>(tw[b + j])
-                        : ~0ULL;
-    for (int32_t k = 2; k <= P; k <<= 1) {
-        for (int32_t j = k >> 1; j > 0; j >>= 1) {
-            __syncthreads();
-            for (int32_t i = tid; i < P; i += 256) {
-                const int32_t p = i ^ j;
-                if (p > i) {
-                    const uint64_t x = sk[i], y = sk[p];
-                    if ((x > y) == ((i & k) == 0)) {
-                        sk[i] = y;
-                        sk[p] = x;
-                    }
+    const int64_t b = xadj[row];
+    const int32_t len = static_cast<int32_t>(xadj[row + 1] - b);
+    const int32_t rounds = (len + NT - 1) / NT;
+    const int32_t first = w * rounds * 64 + lane;  // element r of this thread: first + 64 r
+    uint64_t e[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const int32_t i = first + 64 * r;
+        e[r] = r < rounds && i < len ? (static_cast<uint64_t>(static_cast<uint32_t>(adj[b + i])) << 32) |
+                                           static_cast<uint32_t>(ew[b + i])
+                                     : 0;
+    }
+    const uint64_t lt = lanemask_lt();
+    for (int shift = 0; shift < bits; shift += 8) {
+#pragma unroll
+        for (int q = 0; q < kD * NW / NT; ++q) cnt[w][lane + 64 * q] = 0;
+        __syncthreads();
+        uint32_t rank[E];
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            rank[r] = 0;
+            if (r >= rounds) continue;  // uniform over the workgroup
+            const bool valid = first + 64 * r < len;
+            const uint32_t d = static_cast<uint32_t>(e[r] >> (32 + shift)) & (kD - 1);
+            uint64_t match = __ballot(valid);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const uint64_t bal = __ballot((d >> q) & 1u);
+                match &= ((d >> q) & 1u) ? bal : ~bal;
+            }
+            if (valid) rank[r] = cnt[w][d] + static_cast<uint32_t>(__popcll(match & lt));
+            wave_sync();
+            if (valid && (match & lt) == 0) cnt[w][d] += static_cast<uint32_t>(__popcll(match));
+            wave_sync();
+        }
+        __syncthreads();
+        // counts to first positions: thread t owns digits kDT * t ..
+        uint32_t c[kDT][NW], tot[kDT], mine = 0;
+        if (tid < kD / kDT) {
+#pragma unroll
+            for (int q = 0; q < kDT; ++q) {
+                tot[q] = 0;
+#pragma unroll
+                for (int x = 0; x < NW; ++x) {
+                    c[q][x] = cnt[x][kDT * tid + q];
+                    tot[q] += c[q][x];
                 }
+                mine += tot[q];
             }
         }
-    }
-    __syncthreads();
-    // each thread owns a contiguous segment of the sorted row
-    const int32_t per = (len + 255) / 256;
-    const int32_t s0 = tid * per < len ? tid * per : len;
-    const int32_t s1 = s0 + per < len ? s0 + per : len;
-    int32_t mine = 0;
-    for (int32_t i = s0; i < s1; ++i)
-        if (i == 0 || (sk[i] >> 32) != (sk[i - 1] >> 32)) ++mine;
-    s_cnt[tid] = mine;
-    __syncthreads();
-    if (tid == 0) {
-        int32_t run = 0;
-        for (int t = 0; t < 256; ++t) {
-            const int32_t c = s_cnt[t];
-            s_cnt[t] = run;
-            run += c;
+        uint32_t incl = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += u;
         }
-        dcnt[row] = run;
+        uint32_t run = incl - mine;
+        if (NW >= 4) {
+            if (lane == 63 && w < 4) s_w[w] = incl;
+            __syncthreads();
+            for (int x = 0; x < w && x < 4; ++x) run += s_w[x];
+        }
+        if (tid < kD / kDT) {
+#pragma unroll
+            for (int q = 0; q < kDT; ++q)
+#pragma unroll
+                for (int x = 0; x < NW; ++x) {
+                    cnt[x][kDT * tid + q] = run;
+                    run += c[q][x];
+                }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < E; ++r) {
+            if (r >= rounds || first + 64 * r >= len) continue;
+            const uint32_t d = static_cast<uint32_t>(e[r] >> (32 + shift)) & (kD - 1);
+            buf[cnt[w][d] + rank[r]] = e[r];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < E; ++r)
+            if (r < rounds && first + 64 * r < len) e[r] = buf[first + 64 * r];
     }
-    __syncthreads();
-    int32_t pos = s_cnt[tid];
-    for (int32_t i = s0; i < s1; ++i) {
-        const uint64_t key = sk[i] >> 32;
-        if (i != 0 && key == (sk[i - 1] >> 32)) continue;
-        int64_t sum = 0;
-        for (int32_t j = i; j < len && (sk[j] >> 32) == key; ++j) sum += static_cast<int32_t>(sk[j] & 0xFFFFFFFFu);
-        tk[b + pos] = static_cast<int32_t>(key);
-        tw[b + pos] = static_cast<int32_t>(sum);
-        ++pos;
+#pragma unroll
+    for (int r = 0; r < E; ++r) {
+        const int32_t i = first + 64 * r;
+        if (r >= rounds || i >= len) continue;
+        adj[b + i] = static_cast<int32_t>(e[r] >> 32);
+        ew[b + i] = static_cast<int32_t>(e[r] & 0xFFFFFFFFULL);
     }
 }
 
-// Rows longer than 4096 entries: keys (long-row index << bn | C(v)) over just
-// those rows, radix sorted, then merged per row.
+constexpr int kOrderMax = 8192;  // rows up to this length are ordered in LDS
+
+// Rows to order, by length: one wave, up to 512, 2048 or 8192 entries, longer.
+constexpr int kOrderClasses = 5;
+
+__global__ void __launch_bounds__(256) order_classify_kernel(int32_t n, const int64_t* __restrict__ xadj,
+                                                             int32_t* __restrict__ lists,
+                                                             uint32_t* __restrict__ counts) {
+    for (int32_t base = blockIdx.x * (kClassifyIters * 256); base < n; base += gridDim.x * (kClassifyIters * 256)) {
+        uint32_t m[kOrderClasses] = {};
+#pragma unroll
+        for (int it = 0; it < kClassifyIters; ++it) {
+            const int32_t r = base + it * 256 + static_cast<int32_t>(threadIdx.x);
+            const int64_t len = r < n ? xadj[r + 1] - xadj[r] : 0;
+            if (len > 1) {
+                const int c = len <= 64 ? 0 : (len <= 512 ? 1 : (len <= 2048 ? 2 : (len <= kOrderMax ? 3 : 4)));
+#pragma unroll
+                for (int q = 0; q < kOrderClasses; ++q) m[q] |= q == c ? 1u << it : 0u;
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < kOrderClasses; ++c) {
+            uint32_t bits = m[c];
+            if (!__syncthreads_or(bits != 0)) continue;
+            uint32_t j = block_append_count(static_cast<uint32_t>(__popc(bits)), &counts[c]);
+            while (bits) {
+                const int it = __ffs(bits) - 1;
+                bits &= bits - 1;
+                lists[static_cast<int64_t>(c) * n + j++] = base + it * 256 + static_cast<int32_t>(threadIdx.x);
+            }
+        }
+    }
+}
+
+// Rows of 2..64 distinct entries: one wave per row, bitonic network over the
+// lanes.
+__global__ void __launch_bounds__(256) order_wave_rows_kernel(const int32_t* __restrict__ list, uint32_t count,
+                                                              const int64_t* __restrict__ xadj,
+                                                              int32_t* __restrict__ adj, int32_t* __restrict__ ew) {
+    const uint32_t wv = (blockIdx.x * 256 + threadIdx.x) >> 6;
+    if (wv >= count) return;  // uniform per wave
+    const int lane = lane_id();
+    const int32_t row = list[wv];
+    const int64_t b = xadj[row];
+    const int32_t len = static_cast<int32_t>(xadj[row + 1] - b);
+    uint32_t key = lane < len ? static_cast<uint32_t>(adj[b + lane]) : 0xFFFFFFFFu;
+    int32_t w = lane < len ? ew[b + lane] : 0;
+    bitonic_wave(key, w, lane);
+    if (lane < len) {
+        adj[b + lane] = static_cast<int32_t>(key);
+        ew[b + lane] = w;
+    }
+}
+
+// Longer rows: (row's place in the list << bn | id, w) over just those rows ...
+__global__ void __launch_bounds__(256) long_keys_kernel(const int32_t* __restrict__ list, uint32_t l0,
+                                                        const int64_t* __restrict__ loff,
+                                                        const int64_t* __restrict__ xadj,
+                                                        const int32_t* __restrict__ adj, const int32_t* __restrict__ ew,
+                                                        int bn, uint64_t* __restrict__ keys,
+                                                        uint32_t* __restrict__ vals) {
+    const int32_t l = static_cast<int32_t>(l0 + blockIdx.y);
+    const int64_t src = xadj[list[l]], dst = loff[l], len = loff[l + 1] - dst;
+    for (int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; j < len;
+         j += static_cast<int64_t>(gridDim.x) * 256) {
+        keys[dst + j] = (static_cast<uint64_t>(l) << bn) | static_cast<uint32_t>(adj[src + j]);
+        vals[dst + j] = static_cast<uint32_t>(ew[src + j]);
+    }
+}
+
+// ... and back in order.
+__global__ void __launch_bounds__(256) long_write_kernel(const int32_t* __restrict__ list, uint32_t l0,
+                                                         const int64_t* __restrict__ loff,
+                                                         const int64_t* __restrict__ xadj,
+                                                         const uint64_t* __restrict__ keys,
+                                                         const uint32_t* __restrict__ vals, int bn,
+                                                         int32_t* __restrict__ adj, int32_t* __restrict__ ew) {
+    const int32_t l = static_cast<int32_t>(l0 + blockIdx.y);
+    const int64_t dst = xadj[list[l]], src = loff[l], len = loff[l + 1] - src;
+    for (int64_t j = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; j < len;
+         j += static_cast<int64_t>(gridDim.x) * 256) {
+        adj[dst + j] = static_cast<int32_t>(keys[src + j] & ((1ULL << bn) - 1));
+        ew[dst + j] = static_cast<int32_t>(vals[src + j]);
+    }
+}
+
+__global__ void long_degrees_kernel(const int32_t* __restrict__ list, uint32_t nl, const int64_t* __restrict__ xadj,
+                                    int32_t* __restrict__ lens) {
+    const uint32_t l = blockIdx.x * 256 + threadIdx.x;
+    if (l < nl) lens[l] = static_cast<int32_t>(xadj[list[l] + 1] - xadj[list[l]]);
+}
+
+// Rows longer than 4096 entries: chunks of each.
 __global__ void long_lens_kernel(const int32_t* __restrict__ list, uint32_t nl, const int32_t* __restrict__ rowcnt,
                                  int32_t* __restrict__ nchunks, int32_t chunk) {
     const uint32_t l = blockIdx.x * 256 + threadIdx.x;
@@ -400,81 +557,11 @@ __global__ void __launch_bounds__(kDedupThreads) long_dedup_kernel(const int32_t
     }
 }
 
-// Sort keys (long-row index << bn | C(v)) over the merged chunk entries, one
-// chunk per workgroup.
-__global__ void __launch_bounds__(256) long_keys_kernel(const int32_t* __restrict__ list,
-                                                        const int32_t* __restrict__ crow,
-                                                        const int64_t* __restrict__ cfirst,
-                                                        const int32_t* __restrict__ ccnt,
-                                                        const int64_t* __restrict__ coff,
-                                                        const int64_t* __restrict__ rowoff,
-                                                        const int32_t* __restrict__ tk, const int32_t* __restrict__ tw,
-                                                        int bn, uint64_t* __restrict__ keys,
-                                                        uint32_t* __restrict__ vals) {
-    const int64_t c = blockIdx.x;
-    const int32_t l = crow[c];
-    const int64_t src = rowoff[list[l]] + (c - cfirst[l]) * kLongChunk;
-    const int64_t dst = coff[c];
-    for (int32_t j = threadIdx.x; j < ccnt[c]; j += 256) {
-        keys[dst + j] = (static_cast<uint64_t>(l) << bn) | static_cast<uint32_t>(tk[src + j]);
-        vals[dst + j] = static_cast<uint32_t>(tw[src + j]);
-    }
-}
-
-// loff[l] = coff[cfirst[l]]: first sort key of long row l
+// loff[l] = coff[cfirst[l]]: first merged chunk entry of long row l
 __global__ void long_offsets_kernel(uint32_t nl, const int64_t* __restrict__ cfirst, const int64_t* __restrict__ coff,
                                     int64_t* __restrict__ loff) {
     const uint32_t l = blockIdx.x * 256 + threadIdx.x;
     if (l <= nl) loff[l] = coff[cfirst[l]];
-}
-
-// heads of equal-key runs, and the weights as int64 for the prefix sums
-__global__ void long_heads_kernel(const uint64_t* __restrict__ keys, const uint32_t* __restrict__ vals, int64_t m,
-                                  int32_t* __restrict__ head, int64_t* __restrict__ psum) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i < m) {
-        head[i] = (i == 0 || keys[i] != keys[i - 1]) ? 1 : 0;
-        psum[i] = static_cast<int32_t>(vals[i]);
-    }
-}
-
-// Heads write the neighbour at the row-local distinct index and remember
-// where the run starts; the last entry of a run writes its summed weight.
-// pos: exclusive scan of head; psum: inclusive scan of the weights.
-__global__ void long_runs_kernel(const int32_t* __restrict__ list, const int64_t* __restrict__ loff,
-                                 const int64_t* __restrict__ rowoff, const uint64_t* __restrict__ keys, int64_t m,
-                                 const int32_t* __restrict__ head, const int64_t* __restrict__ pos, int bn,
-                                 int64_t* __restrict__ run_start, int32_t* __restrict__ tk,
-                                 int32_t* __restrict__ dcnt) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= m) return;
-    const uint64_t key = keys[i];
-    const uint32_t l = static_cast<uint32_t>(key >> bn);
-    const int32_t row = list[l];
-    const int64_t first = pos[loff[l]];  // distinct index of the row's first run
-    const int64_t d = pos[i] + head[i] - 1;
-    if (head[i]) {
-        run_start[d] = i;
-        tk[rowoff[row] + (d - first)] = static_cast<int32_t>(key & ((1ULL << bn) - 1));
-    }
-    if (i + 1 == loff[l + 1]) dcnt[row] = static_cast<int32_t>(d + 1 - first);
-}
-
-__global__ void long_tails_kernel(const int32_t* __restrict__ list, const int64_t* __restrict__ loff,
-                                  const int64_t* __restrict__ rowoff, const uint64_t* __restrict__ keys, int64_t m,
-                                  const int32_t* __restrict__ head, const int64_t* __restrict__ pos,
-                                  const int64_t* __restrict__ psum, int bn, const int64_t* __restrict__ run_start,
-                                  int32_t* __restrict__ tw) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= m) return;
-    const uint64_t key = keys[i];
-    if (i + 1 < m && keys[i + 1] == key) return;  // not the last entry of its run
-    const uint32_t l = static_cast<uint32_t>(key >> bn);
-    const int32_t row = list[l];
-    const int64_t first = pos[loff[l]];
-    const int64_t d = pos[i] + head[i] - 1;
-    const int64_t st = run_start[d];
-    tw[rowoff[row] + (d - first)] = static_cast<int32_t>(psum[i] - (st > 0 ? psum[st - 1] : 0));
 }
 
 // Unsorted merge of rows of 65..4096 entries: one workgroup per row sums
@@ -534,43 +621,6 @@ __global__ void __launch_bounds__(256) block_hash_rows_kernel(const int32_t* __r
         tk[b + pos] = keys[e];
         tw[b + pos] = sums[e];
         ++pos;
-    }
-}
-
-// Splits the workgroup-row list by length: class c holds rows of at most
-// 256 << c entries (c = 0..4).  Each workgroup takes kClassifyIters * 256
-// list entries at a time and appends to each class with one atomic.
-__global__ void __launch_bounds__(256) block_row_split_kernel(const int32_t* __restrict__ list, uint32_t count,
-                                                              const int32_t* __restrict__ rowcnt,
-                                                              int32_t* __restrict__ out, uint32_t cap,
-                                                              uint32_t* __restrict__ counts) {
-    for (uint32_t base = blockIdx.x * (kClassifyIters * 256); base < count;
-         base += gridDim.x * (kClassifyIters * 256)) {
-        int32_t rows[kClassifyIters], lens[kClassifyIters];
-#pragma unroll
-        for (int it = 0; it < kClassifyIters; ++it) {
-            const uint32_t i = base + it * 256 + threadIdx.x;
-            rows[it] = i < count ? list[i] : -1;
-        }
-#pragma unroll
-        for (int it = 0; it < kClassifyIters; ++it) lens[it] = rows[it] >= 0 ? rowcnt[rows[it]] : 0;
-        uint32_t m[5] = {0, 0, 0, 0, 0};
-#pragma unroll
-        for (int it = 0; it < kClassifyIters; ++it) {
-            if (rows[it] < 0) continue;
-            int cls = 0;
-            while (cls < 4 && lens[it] > (256 << cls)) ++cls;
-            m[cls] |= 1u << it;
-        }
-        for (int c = 0; c < 5; ++c) {
-            uint32_t bits = m[c];
-            uint32_t j = block_append_count(static_cast<uint32_t>(__popc(bits)), &counts[c]);
-            while (bits) {
-                const int it = __ffs(bits) - 1;
-                bits &= bits - 1;
-                out[static_cast<int64_t>(c) * cap + j++] = rows[it];
-            }
-        }
     }
 }
 
@@ -859,11 +909,6 @@ __global__ void __launch_bounds__(256) long_table_write_kernel(const int32_t* __
     if (q == tcfirst[l] && tid == 0) dcnt[row] = static_cast<int32_t>(qoff[tcfirst[l + 1]] - qoff[tcfirst[l]]);
 }
 
-__global__ void row_degrees_kernel(int32_t n, const int64_t* __restrict__ xadj, int32_t* __restrict__ deg) {
-    const int32_t v = blockIdx.x * 256 + threadIdx.x;
-    if (v < n) deg[v] = static_cast<int32_t>(xadj[v + 1] - xadj[v]);
-}
-
 // Step 4: the merged prefix of every row to its place in the coarse CSR.
 __global__ void __launch_bounds__(kTileThreads) row_copy_kernel(const int64_t* __restrict__ rowoff, int32_t nc, int64_t m,
                                                                 const int32_t* __restrict__ dcnt,
@@ -887,27 +932,6 @@ __global__ void __launch_bounds__(kTileThreads) row_copy_kernel(const int64_t* _
     }
 }
 
-// Unsorted merge of the workgroup rows, by length class (table of 512 <<
-// class slots).
-void hash_block_rows(const int32_t* list, uint32_t count, const int64_t* rowoff, const int32_t* rowcnt,
-                     int32_t* tk, int32_t* tw, int32_t* dcnt, hipStream_t s) {
-    DBuf<int32_t> sub(5 * static_cast<size_t>(count), s);
-    DBuf<uint32_t> cnt(5, s);
-    fill_u32(cnt.get(), 0, 5, s);
-    block_row_split_kernel<<<std::min(grid_for(count, 256 * kClassifyIters), 1024u), 256, 0, s>>>(
-        list, count, rowcnt, sub.get(), count, cnt.get());
-    LAUNCHCHK();
-    uint32_t hc[5];
-    read_back(hc, cnt.get(), sizeof(hc), s);
-    const int32_t* l = sub.get();
-    if (hc[0]) block_hash_rows_kernel<512><<<hc[0], 256, 0, s>>>(l, rowoff, rowcnt, tk, tw, dcnt);
-    if (hc[1]) block_hash_rows_kernel<1024><<<hc[1], 256, 0, s>>>(l + count, rowoff, rowcnt, tk, tw, dcnt);
-    if (hc[2]) block_hash_rows_kernel<2048><<<hc[2], 256, 0, s>>>(l + 2 * count, rowoff, rowcnt, tk, tw, dcnt);
-    if (hc[3]) block_hash_rows_kernel<4096><<<hc[3], 256, 0, s>>>(l + 3 * count, rowoff, rowcnt, tk, tw, dcnt);
-    if (hc[4]) block_hash_rows_kernel<8192><<<hc[4], 256, 0, s>>>(l + 4 * count, rowoff, rowcnt, tk, tw, dcnt);
-    LAUNCHCHK();
-}
-
 // Long rows (unsorted) merged by buckets; false if a bucket's distinct
 // neighbours overflowed its LDS table (tk/tw untouched then).
 bool bucket_merge_long_rows(uint32_t nl, const int32_t* llist, int64_t nch, const int32_t* crow,
@@ -916,40 +940,37 @@ bool bucket_merge_long_rows(uint32_t nl, const int32_t* llist, int64_t nch, cons
                             hipStream_t s) {
     ProfScope ps("contract_long_buckets", 40.0 * static_cast<double>(ml), s);
     DBuf<int32_t> nbk(nl, s);
-    DBuf<int64_t> bfirst(static_cast<size_t>(nl) + 1, s), tot(2, s);
+    DBuf<int64_t> bfirst(static_cast<size_t>(nl) + 1, s);
     long_bucket_counts_kernel<<<grid_for(nl, 256), 256, 0, s>>>(nl, loff, mean, llist, cfirst, dcnt, nbk.get());
     LAUNCHCHK();
-    exclusive_scan_i32_to_i64(nbk.get(), bfirst.get(), nl, tot.get(), s);
+    exclusive_scan_i32_to_i64(nbk.get(), bfirst.get(), nl, bfirst.get() + nl, s);
     int64_t NB = 0;
-    read_back(&NB, tot.get(), sizeof(int64_t), s);
+    read_back(&NB, bfirst.get() + nl, sizeof(int64_t), s);
     if (NB == 0) return true;  // every long row was one chunk
-    fill_i64(bfirst.get() + nl, NB, 1, s);
-    DBuf<int32_t> brow(NB, s), bcount(NB, s), bfill(NB, s), qcnt(NB, s);
+    DBuf<int32_t> brow(NB, s), zeros(2 * NB + 1, s), qcnt(NB, s);  // bucket sizes, entries placed, overflow flag
+    int32_t* const bcount = zeros.get();
+    int32_t* const bfill = bcount + NB;
+    uint32_t* const overflow = reinterpret_cast<uint32_t*>(bfill + NB);
     DBuf<int64_t> boff(static_cast<size_t>(NB) + 1, s), qoff(static_cast<size_t>(NB) + 1, s);
     DBuf<int32_t> sk(std::max<int64_t>(ml, 1), s), sw(std::max<int64_t>(ml, 1), s);
-    DBuf<uint32_t> overflow(1, s);
     long_bucket_rows_kernel<<<nl, 256, 0, s>>>(nl, bfirst.get(), brow.get());
     LAUNCHCHK();
-    fill_i32(bcount.get(), 0, NB, s);
-    fill_i32(bfill.get(), 0, NB, s);
-    fill_u32(overflow.get(), 0, 1, s);
+    fill_i32(zeros.get(), 0, 2 * NB + 1, s);
     long_bucket_scatter_kernel<false><<<static_cast<unsigned>(nch), 256, 0, s>>>(
-        llist, crow, cfirst, ccnt, rowoff, bfirst.get(), tk, tw, bcount.get(), nullptr, nullptr, nullptr, nullptr);
+        llist, crow, cfirst, ccnt, rowoff, bfirst.get(), tk, tw, bcount, nullptr, nullptr, nullptr, nullptr);
     LAUNCHCHK();
-    exclusive_scan_i32_to_i64(bcount.get(), boff.get(), NB, tot.get(), s);
-    HIPCHK(hipMemcpyAsync(boff.get() + NB, tot.get(), sizeof(int64_t), hipMemcpyDeviceToDevice, s));
+    exclusive_scan_i32_to_i64(bcount, boff.get(), NB, boff.get() + NB, s);
     long_bucket_scatter_kernel<true><<<static_cast<unsigned>(nch), 256, 0, s>>>(
-        llist, crow, cfirst, ccnt, rowoff, bfirst.get(), tk, tw, nullptr, boff.get(), bfill.get(), sk.get(),
+        llist, crow, cfirst, ccnt, rowoff, bfirst.get(), tk, tw, nullptr, boff.get(), bfill, sk.get(),
         sw.get());
     LAUNCHCHK();
     long_bucket_merge_kernel<<<static_cast<unsigned>(NB), 256, 0, s>>>(boff.get(), sk.get(), sw.get(), qcnt.get(),
-                                                                      overflow.get());
+                                                                      overflow);
     LAUNCHCHK();
     uint32_t over = 0;
-    read_back(&over, overflow.get(), sizeof(uint32_t), s);
+    read_back(&over, overflow, sizeof(uint32_t), s);
     if (over) return false;
-    exclusive_scan_i32_to_i64(qcnt.get(), qoff.get(), NB, tot.get() + 1, s);
-    HIPCHK(hipMemcpyAsync(qoff.get() + NB, tot.get() + 1, sizeof(int64_t), hipMemcpyDeviceToDevice, s));
+    exclusive_scan_i32_to_i64(qcnt.get(), qoff.get(), NB, qoff.get() + NB, s);
     long_bucket_write_kernel<<<static_cast<unsigned>(NB), 256, 0, s>>>(llist, brow.get(), bfirst.get(), boff.get(),
                                                                       qoff.get(), qcnt.get(), rowoff, sk.get(),
                                                                       sw.get(), tk, tw, dcnt);
@@ -959,49 +980,46 @@ bool bucket_merge_long_rows(uint32_t nl, const int32_t* llist, int64_t nch, cons
 
 }  // namespace
 
-// Merges (and, if `sorted`, orders by neighbour id) every row r of the
-// entries tk/tw[rowoff[r] .. rowoff[r] + rowcnt[r]) in place; dcnt[r]
-// receives the number of distinct neighbours, written at the row's start.
+// Merges every row r of the entries tk/tw[rowoff[r] .. rowoff[r] + rowcnt[r])
+// in place; dcnt[r] receives the number of distinct neighbours, written at the
+// row's start in no particular order.
 void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* rowcnt, int32_t* tk, int32_t* tw,
-                int32_t* dcnt, bool sorted, hipStream_t s, int32_t bucket_mean = 0) {
-    DBuf<int32_t> lists(3 * static_cast<size_t>(nc), s);
-    DBuf<uint32_t> counts(3, s);
-    uint32_t hc[3] = {0, 0, 0};
+                int32_t* dcnt, hipStream_t s, int32_t bucket_mean = 0) {
+    DBuf<int32_t> lists(kRowClasses * static_cast<size_t>(nc), s);
+    DBuf<uint32_t> counts(kRowClasses, s);
+    uint32_t hc[kRowClasses] = {};
+    auto list_of = [&](int c) { return lists.get() + static_cast<size_t>(c) * nc; };
     {
         ProfScope ps("contract_rows", 16.0 * static_cast<double>(m), s);
-        fill_u32(counts.get(), 0, 3, s);
+        fill_u32(counts.get(), 0, kRowClasses, s);
         row_classify_kernel<<<std::min(grid_for(nc, 256 * kClassifyIters), 1024u), 256, 0, s>>>(
             nc, rowcnt, dcnt, lists.get(), nc, counts.get());
         LAUNCHCHK();
         read_back(hc, counts.get(), sizeof(hc), s);
-        if (hc[0] > 0) {
-            wave_rows_kernel<<<grid_for(static_cast<int64_t>(hc[0]) * 64, 256), 256, 0, s>>>(
-                lists.get(), hc[0], rowoff, rowcnt, tk, tw, dcnt);
-            LAUNCHCHK();
-        }
-        if (hc[1] > 0) {
-            if (sorted)
-                block_rows_kernel<<<hc[1], 256, 0, s>>>(lists.get() + nc, rowoff, rowcnt, tk, tw, dcnt);
-            else
-                hash_block_rows(lists.get() + nc, hc[1], rowoff, rowcnt, tk, tw, dcnt, s);
-            LAUNCHCHK();
-        }
+        if (hc[5]) block_hash_rows_kernel<8192><<<hc[5], 256, 0, s>>>(list_of(5), rowoff, rowcnt, tk, tw, dcnt);
+        if (hc[4]) block_hash_rows_kernel<4096><<<hc[4], 256, 0, s>>>(list_of(4), rowoff, rowcnt, tk, tw, dcnt);
+        if (hc[3]) block_hash_rows_kernel<2048><<<hc[3], 256, 0, s>>>(list_of(3), rowoff, rowcnt, tk, tw, dcnt);
+        if (hc[2]) block_hash_rows_kernel<1024><<<hc[2], 256, 0, s>>>(list_of(2), rowoff, rowcnt, tk, tw, dcnt);
+        if (hc[1]) block_hash_rows_kernel<512><<<hc[1], 256, 0, s>>>(list_of(1), rowoff, rowcnt, tk, tw, dcnt);
+        if (hc[0])
+            wave_rows_kernel<<<grid_for(static_cast<int64_t>(hc[0]) * 64, 256), 256, 0, s>>>(list_of(0), hc[0], rowoff,
+                                                                                            rowcnt, tk, tw, dcnt);
+        LAUNCHCHK();
     }
-    if (hc[2] > 0) {
+    if (hc[kRowClasses - 1] > 0) {
         ProfScope ps("contract_long_rows", 0, s);
-        const uint32_t nl = hc[2];
-        const int32_t* llist = lists.get() + 2 * static_cast<size_t>(nc);
+        const uint32_t nl = hc[kRowClasses - 1];
+        const int32_t* llist = list_of(kRowClasses - 1);
         // chunks of the long rows, each merged in LDS first
         DBuf<int32_t> lens(nl, s);
-        DBuf<int64_t> cfirst(static_cast<size_t>(nl) + 1, s), ctot(1, s);
+        DBuf<int64_t> cfirst(static_cast<size_t>(nl) + 1, s);
         long_lens_kernel<<<grid_for(nl, 256), 256, 0, s>>>(llist, nl, rowcnt, lens.get(), kLongChunk);
         LAUNCHCHK();
-        exclusive_scan_i32_to_i64(lens.get(), cfirst.get(), nl, ctot.get(), s);
+        exclusive_scan_i32_to_i64(lens.get(), cfirst.get(), nl, cfirst.get() + nl, s);
         int64_t nch = 0;
-        read_back(&nch, ctot.get(), sizeof(int64_t), s);
-        fill_i64(cfirst.get() + nl, nch, 1, s);
+        read_back(&nch, cfirst.get() + nl, sizeof(int64_t), s);
         DBuf<int32_t> crow(nch, s), ccnt(nch, s);
-        DBuf<int64_t> coff(static_cast<size_t>(nch) + 1, s), mtot2(1, s), loff(static_cast<size_t>(nl) + 1, s);
+        DBuf<int64_t> coff(static_cast<size_t>(nch) + 1, s), loff(static_cast<size_t>(nl) + 1, s);
         {
             ProfScope ps_m("contract_long_merge", 0, s);
             long_chunks_kernel<<<nl, 256, 0, s>>>(nl, cfirst.get(), crow.get());
@@ -1010,17 +1028,16 @@ void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* row
                                                                                    rowoff, rowcnt, tk, tw, ccnt.get());
             LAUNCHCHK();
         }
-        exclusive_scan_i32_to_i64(ccnt.get(), coff.get(), nch, mtot2.get(), s);
+        exclusive_scan_i32_to_i64(ccnt.get(), coff.get(), nch, coff.get() + nch, s);
         int64_t ml = 0;
-        read_back(&ml, mtot2.get(), sizeof(int64_t), s);
-        fill_i64(coff.get() + nch, ml, 1, s);
+        read_back(&ml, coff.get() + nch, sizeof(int64_t), s);
         long_offsets_kernel<<<grid_for(static_cast<int64_t>(nl) + 1, 256), 256, 0, s>>>(nl, cfirst.get(), coff.get(),
                                                                                          loff.get());
         LAUNCHCHK();
-        if (!sorted && bucket_merge_long_rows(nl, llist, nch, crow.get(), cfirst.get(), ccnt.get(), loff.get(), ml,
+        if (bucket_merge_long_rows(nl, llist, nch, crow.get(), cfirst.get(), ccnt.get(), loff.get(), ml,
                                               rowoff, tk, tw, dcnt, bucket_mean > 0 ? bucket_mean : kBucketMean, s))
             return;
-        if (!sorted) {  // a bucket overflowed: per-row tables in HBM
+        {  // a bucket overflowed: per-row tables in HBM
             DBuf<int64_t> tsz(nl, s), tch(nl, s), toff(static_cast<size_t>(nl) + 1, s),
                 tcfirst(static_cast<size_t>(nl) + 1, s);
             long_table_sizes_kernel<<<grid_for(nl, 256), 256, 0, s>>>(nl, loff.get(), tsz.get(), tch.get());
@@ -1057,41 +1074,60 @@ void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* row
                                                                             toff.get(), qoff.get(), rowoff, gk.get(),
                                                                             gv.get(), tk, tw, dcnt);
             LAUNCHCHK();
-            return;
         }
-        const int bn = std::max(1, bits_for(static_cast<uint64_t>(nc - 1)));
-        DBuf<uint64_t> keys(ml, s), ktmp(ml, s);
-        DBuf<uint32_t> vals(ml, s), vtmp(ml, s);
-        long_keys_kernel<<<static_cast<unsigned>(nch), 256, 0, s>>>(llist, crow.get(), cfirst.get(), ccnt.get(),
-                                                                    coff.get(), rowoff, tk, tw, bn, keys.get(),
-                                                                    vals.get());
-        LAUNCHCHK();
-        {
-            ProfScope ps2("contract_long_sort", 0, s);
-            RadixScratch rs;
-            radix_sort_pairs(keys.get(), vals.get(), ktmp.get(), vtmp.get(), ml, 0,
-                             bn + std::max(1, bits_for(static_cast<uint64_t>(nl - 1))), rs, s);
-        }
-        DBuf<int32_t> head(ml, s);
-        DBuf<int64_t> pos(ml, s), psum(ml, s), dtot(1, s), run_start(ml, s);
-        ktmp.release();
-        vtmp.release();
-        long_heads_kernel<<<grid_for(ml, 256), 256, 0, s>>>(keys.get(), vals.get(), ml, head.get(), psum.get());
-        LAUNCHCHK();
-        exclusive_scan_i32_to_i64(head.get(), pos.get(), ml, dtot.get(), s);
-        inclusive_scan_i64(psum.get(), psum.get(), ml, s);
-        long_runs_kernel<<<grid_for(ml, 256), 256, 0, s>>>(llist, loff.get(), rowoff, keys.get(), ml,
-                                                           head.get(), pos.get(), bn, run_start.get(), tk,
-                                                           dcnt);
-        LAUNCHCHK();
-        long_tails_kernel<<<grid_for(ml, 256), 256, 0, s>>>(llist, loff.get(), rowoff, keys.get(), ml,
-                                                            head.get(), pos.get(), psum.get(), bn, run_start.get(),
-                                                            tw);
-        LAUNCHCHK();
     }
-
 }
 
+// Orders every row of a CSR of distinct entries by neighbour id, in place.
+void order_rows(int32_t n, const int64_t* xadj, int32_t* adj, int32_t* ew, hipStream_t s) {
+    if (n <= 0) return;
+    const int bn = std::max(1, bits_for(static_cast<uint64_t>(n - 1)));
+    DBuf<int32_t> lists(kOrderClasses * static_cast<size_t>(n), s);
+    DBuf<uint32_t> counts(kOrderClasses, s);
+    uint32_t hc[kOrderClasses] = {};
+    auto list_of = [&](int c) { return lists.get() + static_cast<size_t>(c) * n; };
+    fill_u32(counts.get(), 0, kOrderClasses, s);
+    order_classify_kernel<<<std::min(grid_for(n, 256 * kClassifyIters), 1024u), 256, 0, s>>>(n, xadj, lists.get(),
+                                                                                             counts.get());
+    LAUNCHCHK();
+    read_back(hc, counts.get(), sizeof(hc), s);
+    if (hc[3]) order_rows_kernel<16><<<hc[3], 1024, 0, s>>>(list_of(3), xadj, adj, ew, bn);
+    if (hc[2]) order_rows_kernel<4><<<hc[2], 256, 0, s>>>(list_of(2), xadj, adj, ew, bn);
+    if (hc[1]) order_rows_kernel<1><<<hc[1], 64, 0, s>>>(list_of(1), xadj, adj, ew, bn);
+    if (hc[0])
+        order_wave_rows_kernel<<<grid_for(static_cast<int64_t>(hc[0]) * 64, 256), 256, 0, s>>>(list_of(0), hc[0], xadj,
+                                                                                              adj, ew);
+    LAUNCHCHK();
+    const uint32_t nl = hc[4];
+    if (nl == 0) return;
+    ProfScope ps("contract_long_sort", 0, s);
+    DBuf<int32_t> lens(nl, s);
+    DBuf<int64_t> loff(static_cast<size_t>(nl) + 1, s);
+    long_degrees_kernel<<<grid_for(nl, 256), 256, 0, s>>>(list_of(4), nl, xadj, lens.get());
+    LAUNCHCHK();
+    exclusive_scan_i32_to_i64(lens.get(), loff.get(), nl, loff.get() + nl, s);
+    int64_t ml = 0;
+    read_back(&ml, loff.get() + nl, sizeof(int64_t), s);
+    DBuf<uint64_t> keys(ml, s), ktmp(ml, s);
+    DBuf<uint32_t> vals(ml, s), vtmp(ml, s);
+    // rows in groups that fit the grid's second dimension
+    constexpr uint32_t kRows = 32768;
+    for (uint32_t l0 = 0; l0 < nl; l0 += kRows) {
+        const uint32_t cnt = std::min(kRows, nl - l0);
+        long_keys_kernel<<<dim3(16, cnt), 256, 0, s>>>(list_of(4), l0, loff.get(), xadj, adj, ew, bn, keys.get(),
+                                                       vals.get());
+        LAUNCHCHK();
+    }
+    RadixScratch rs;
+    radix_sort_pairs(keys.get(), vals.get(), ktmp.get(), vtmp.get(), ml, 0,
+                     bn + std::max(1, bits_for(static_cast<uint64_t>(nl - 1))), rs, s);
+    for (uint32_t l0 = 0; l0 < nl; l0 += kRows) {
+        const uint32_t cnt = std::min(kRows, nl - l0);
+        long_write_kernel<<<dim3(16, cnt), 256, 0, s>>>(list_of(4), l0, loff.get(), xadj, keys.get(), vals.get(), bn,
+                                                        adj, ew);
+        LAUNCHCHK();
+    }
+}
 
 void contract(const DevGraph& g, const int32_t* labels, int32_t* C, OwnedDevGraph& coarse, hipStream_t s,
               const int32_t* probe, int32_t nprobe, int32_t* probe_out, bool sorted, int32_t bucket_mean) {
@@ -1105,47 +1141,49 @@ void contract(const DevGraph& g, const int32_t* labels, int32_t* C, OwnedDevGrap
         return;
     }
     // coarse ids: ranks of the used labels
-    DBuf<int32_t> q(n, s);
+    DBuf<int32_t> node_zeros(3 * static_cast<size_t>(n), s);  // ranks, inter-cluster slots, slots placed, per node
+    int32_t* const q = node_zeros.get();
+    int32_t* const cross = q + n;
+    int32_t* const nfill = cross + n;
     DBuf<int32_t> total(1, s);
-    fill_i32(q.get(), 0, n, s);
-    mark_used_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, labels, q.get());
+    fill_i32(q, 0, 3 * static_cast<int64_t>(n), s);
+    mark_used_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, labels, q);
     LAUNCHCHK();
-    exclusive_scan_i32(q.get(), q.get(), n, total.get(), s);
+    exclusive_scan_i32(q, q, n, total.get(), s);
     if (nprobe > 0) {
-        probe_kernel<<<grid_for(nprobe, 256), 256, 0, s>>>(probe, nprobe, q.get(), n, total.get(), probe_out);
+        probe_kernel<<<grid_for(nprobe, 256), 256, 0, s>>>(probe, nprobe, q, n, total.get(), probe_out);
         LAUNCHCHK();
     }
     int32_t nc = 0;
     read_back(&nc, total.get(), sizeof(int32_t), s);
     coarse.n = nc;
     coarse.vw.alloc(nc, s);
+    DBuf<int32_t> row_zeros(2 * static_cast<size_t>(nc), s);  // entries and entries placed, per coarse row
+    int32_t* const rowcnt = row_zeros.get();
+    int32_t* const fill = rowcnt + nc;
     fill_i32(coarse.vw.get(), 0, nc, s);
-    map_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, labels, q.get(), g.vw, C, coarse.vw.get());
+    fill_i32(rowcnt, 0, 2 * static_cast<int64_t>(nc), s);
+    map_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, labels, q, g.vw, C, coarse.vw.get());
     LAUNCHCHK();
-    q.release();
     coarse.xadj.alloc(static_cast<size_t>(nc) + 1, s);
     const int64_t ntiles = (g.S + kTile - 1) / kTile;
 
     // 1 + 2: inter-cluster slots bucketed by coarse source row
-    DBuf<int32_t> rowcnt(nc, s);
-    DBuf<int64_t> rowoff(static_cast<size_t>(nc) + 1, s), mtot(1, s);
-    fill_i32(rowcnt.get(), 0, nc, s);
+    DBuf<int64_t> rowoff(static_cast<size_t>(nc) + 1, s);
     int64_t m = 0;
-    DBuf<int32_t> cross(n, s);
     DBuf<int32_t> cvs(g.S > 0 ? g.S : 1, s);  // C(v) of every slot
     TileRows gtiles(g.xadj, n, g.S, s);
-    fill_i32(cross.get(), 0, n, s);
     if (g.S > 0) {
         ProfScope ps("contract_count", (8.0 + 8.0) * static_cast<double>(g.S) + 8.0 * n, s);
         cross_count_kernel<<<static_cast<unsigned>(ntiles), kTileThreads, 0, s>>>(g.xadj, g.adj, n, g.S, C,
-                                                                                   cross.get(), cvs.get(),
+                                                                                   cross, cvs.get(),
                                                                                    gtiles.trow.get());
         LAUNCHCHK();
-        row_count_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, C, cross.get(), rowcnt.get());
+        row_count_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, C, cross, rowcnt);
         LAUNCHCHK();
     }
-    exclusive_scan_i32_to_i64(rowcnt.get(), rowoff.get(), nc, mtot.get(), s);
-    read_back(&m, mtot.get(), sizeof(int64_t), s);
+    exclusive_scan_i32_to_i64(rowcnt, rowoff.get(), nc, rowoff.get() + nc, s);
+    read_back(&m, rowoff.get() + nc, sizeof(int64_t), s);
     if (m == 0) {
         coarse.S = 0;
         coarse.adj.alloc(1, s);
@@ -1154,33 +1192,27 @@ void contract(const DevGraph& g, const int32_t* labels, int32_t* C, OwnedDevGrap
         HIPCHK(hipStreamSynchronize(s));
         return;
     }
-    fill_i64(rowoff.get() + nc, m, 1, s);
     DBuf<int32_t> tk(m, s), tw(m, s);
     {
         ProfScope ps("contract_emit", (4.0 + (g.ew ? 4.0 : 0.0)) * static_cast<double>(g.S) + 8.0 * n + 8.0 * m, s);
-        DBuf<int32_t> fill(nc, s), nfill(n, s);
         DBuf<int64_t> nbase(n, s);
-        fill_i32(fill.get(), 0, nc, s);
-        fill_i32(nfill.get(), 0, n, s);
-        node_base_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, C, cross.get(), rowoff.get(), fill.get(), nbase.get());
+        node_base_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, C, cross, rowoff.get(), fill, nbase.get());
         LAUNCHCHK();
         row_scatter_kernel<<<static_cast<unsigned>(ntiles), kTileThreads, 0, s>>>(
-            g.xadj, cvs.get(), g.ew, n, g.S, C, nbase.get(), nfill.get(), tk.get(), tw.get(), gtiles.trow.get());
+            g.xadj, cvs.get(), g.ew, n, g.S, C, nbase.get(), nfill, tk.get(), tw.get(), gtiles.trow.get());
         LAUNCHCHK();
     }
     cvs.release();
 
-    // 3: merge (and order) every row
+    // 3: merge every row
     DBuf<int32_t> dcnt(nc, s);
-    merge_rows(nc, m, rowoff.get(), rowcnt.get(), tk.get(), tw.get(), dcnt.get(), sorted, s, bucket_mean);
+    merge_rows(nc, m, rowoff.get(), rowcnt, tk.get(), tw.get(), dcnt.get(), s, bucket_mean);
 
     // 4: coarse offsets and the merged rows
     ProfScope ps_copy("contract_copy", 16.0 * static_cast<double>(m), s);
-    DBuf<int64_t> stot(1, s);
-    exclusive_scan_i32_to_i64(dcnt.get(), coarse.xadj.get(), nc, stot.get(), s);
+    exclusive_scan_i32_to_i64(dcnt.get(), coarse.xadj.get(), nc, coarse.xadj.get() + nc, s);
     int64_t Sc = 0;
-    read_back(&Sc, stot.get(), sizeof(int64_t), s);
-    fill_i64(coarse.xadj.get() + nc, Sc, 1, s);
+    read_back(&Sc, coarse.xadj.get() + nc, sizeof(int64_t), s);
     coarse.S = Sc;
     coarse.adj.alloc(std::max<int64_t>(Sc, 1), s);
     coarse.ew.alloc(std::max<int64_t>(Sc, 1), s);
@@ -1191,16 +1223,16 @@ void contract(const DevGraph& g, const int32_t* labels, int32_t* C, OwnedDevGrap
                                                                            coarse.adj.get(), coarse.ew.get(),
                                                                            ctiles.trow.get());
     LAUNCHCHK();
+    // 5: and, for the canonical form, every row in order (of its distinct
+    // entries, which are a third to a half of those merged above)
+    if (sorted) order_rows(nc, coarse.xadj.get(), coarse.adj.get(), coarse.ew.get(), s);
     HIPCHK(hipStreamSynchronize(s));
 }
 
 void sort_rows(OwnedDevGraph& g, hipStream_t s) {
     if (g.n == 0 || g.S == 0) return;
     ProfScope ps("contract_sort_rows", 16.0 * static_cast<double>(g.S), s);
-    DBuf<int32_t> deg(g.n, s), dcnt(g.n, s);
-    row_degrees_kernel<<<grid_for(g.n, 256), 256, 0, s>>>(g.n, g.xadj.get(), deg.get());
-    LAUNCHCHK();
-    merge_rows(g.n, g.S, g.xadj.get(), deg.get(), g.adj.get(), g.ew.get(), dcnt.get(), true, s);
+    order_rows(g.n, g.xadj.get(), g.adj.get(), g.ew.get(), s);
     HIPCHK(hipStreamSynchronize(s));
 }
 

@@ -782,8 +782,7 @@ void multilevel_cycle(const DevGraph& g0, int32_t k, int64_t cV, int64_t cmax0, 
         if (lev > 0) node_weight_stats(G, &cvl, &cmax, s);
         const int64_t U = std::max(cmax, W);
         DBuf<int32_t> labels(n, s), w(n, s);
-        iota_u32(reinterpret_cast<uint32_t*>(labels.get()), n, s);
-        label_weights(G, labels.get(), w.get(), n, s);
+        singletons(G, labels.get(), w.get(), s);
         OwnedDevGraph inside;
         DevGraph Gc = G;  // the graph clustering looks at
         if (blk0) {
@@ -969,8 +968,7 @@ LPTuning autotune(const DevGraph& g_in, int32_t k, const Opts& o, hipStream_t s)
     auto measure = [&](const LPTuning& t) {
         double ms = 1e300;
         for (int rep = 0; rep < 2; ++rep) {
-            iota_u32(reinterpret_cast<uint32_t*>(labels.get()), g.n, s);
-            label_weights(g, labels.get(), w.get(), g.n, s);
+            singletons(g, labels.get(), w.get(), s);
             HIPCHK(hipMemcpyAsync(part.get(), part0.get(), g.n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
             HIPCHK(hipEventRecord(e0, s));
             run_lp(g, kCluster, 0, 1, o.nsub, 1, U, labels.get(), w.get(), g.n, nullptr, t, s);
@@ -1560,8 +1558,7 @@ int partition_batch_impl(const DevGraph& g0_in, int32_t G, const int32_t* node_b
             upload_vec(d_nbase, base, s);
             upload_vec(d_active, act, s);
             DBuf<int32_t> labels(n, s), wl(n, s);
-            iota_u32(reinterpret_cast<uint32_t*>(labels.get()), n, s);
-            label_weights(B.g, labels.get(), wl.get(), n, s);
+            singletons(B.g, labels.get(), wl.get(), s);
             MultiGraph mg;
             mg.G = G;
             mg.gid = B.gid.get();

@@ -2147,7 +2147,8 @@ __global__ void __launch_bounds__(256) large_move_kernel(Admission A) {
 }
 
 // Admission state before the first sub-round: no candidates, no segments, no
-// large segments in progress, no candidates counted in any round.
+// large segments in progress, no candidates counted in any round; and the
+// narrow copy of the labels, if one is kept.
 __global__ void __launch_bounds__(256) init_admission_kernel(unsigned long long* __restrict__ acc,
                                                              int64_t acc_n, int32_t* __restrict__ seg_off,
                                                              int64_t off_n, int32_t* __restrict__ seg_fill,
@@ -2155,7 +2156,9 @@ __global__ void __launch_bounds__(256) init_admission_kernel(unsigned long long*
                                                              uint32_t* __restrict__ lhist, int64_t lhist_n,
                                                              uint32_t* __restrict__ ldone, int64_t ldone_n,
                                                              uint32_t* __restrict__ rcnt, int32_t rounds,
-                                                             Counters* ctr) {
+                                                             Counters* ctr, const int32_t* __restrict__ label,
+                                                             int32_t n, uint8_t* __restrict__ label8,
+                                                             uint16_t* __restrict__ label16) {
     const int64_t i0 = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
     for (int64_t i = i0; i < acc_n; i += stride) acc[i] = 0;
@@ -2164,16 +2167,14 @@ __global__ void __launch_bounds__(256) init_admission_kernel(unsigned long long*
     for (int64_t i = i0; i < lhist_n; i += stride) lhist[i] = 0;
     for (int64_t i = i0; i < ldone_n; i += stride) ldone[i] = 0;
     for (int64_t i = i0; i < rounds; i += stride) rcnt[i] = 0;
+    if (label8)
+        for (int64_t i = i0; i < n; i += stride) label8[i] = static_cast<uint8_t>(label[i]);
+    if (label16)
+        for (int64_t i = i0; i < n; i += stride) label16[i] = static_cast<uint16_t>(label[i]);
     if (i0 == 0) {
         clear_subround(ctr);
         clear_subround(ctr + 1);
     }
-}
-
-template <typename T>
-__global__ void narrow_kernel(const int32_t* __restrict__ label, int32_t n, T* __restrict__ out) {
-    const int32_t v = blockIdx.x * 256 + threadIdx.x;
-    if (v < n) out[v] = static_cast<T>(label[v]);
 }
 
 // After a sub-round: every neighbour of a node that moved is no longer quiet.
@@ -2208,75 +2209,180 @@ struct Thresholds {
     int32_t t[kNB - 1];
 };
 
-// Category of a node: colour * kNB + degree bucket; degree-0 nodes never move
-// and go to the extra category ncat.
-__global__ void __launch_bounds__(256) classify_kernel(int32_t n, const int64_t* __restrict__ xadj,
-                                                       const int32_t* __restrict__ color_override, uint64_t hc,
-                                                       const int32_t* __restrict__ gid, const uint64_t* __restrict__ g_hc,
-                                                       const int32_t* __restrict__ g_nbase,
-                                                       const uint8_t* __restrict__ g_active,
-                                                       int32_t nsub, Thresholds th,
-                                                       uint64_t* __restrict__ keys,
-                                                       uint32_t* __restrict__ vals, uint32_t* __restrict__ cat_count,
+// The schedule takes three launches: every wave counts the categories of its
+// run of 64 * R consecutive nodes (classify), a prefix sum over (category, run)
+// gives each run its places (place), and every wave ranks its nodes and writes
+// their rows (scatter); ids ascend inside a category.  A general radix sort of
+// (category, node) pairs, copies back, and a launch for the rows took eleven.
+
+// Category of a node: colour * kNB + degree bucket; degree-0 nodes and nodes of
+// inactive graphs never move and go to the extra category ncat.
+struct Classes {
+    int32_t n;
+    const int64_t* xadj;
+    const int32_t* color_override;
+    uint64_t hc;
+    const int32_t* gid;  // several graphs (null: one): the graph of each node, its hash, first node and state
+    const uint64_t* g_hc;
+    const int32_t* g_nbase;
+    const uint8_t* g_active;
+    int32_t nsub;
+    Thresholds th;
+};
+
+constexpr int kMaxCat = 16 * kNB + 1;
+constexpr int kSlotCopies = 8;  // arrays of slot totals the workgroups add to in turn
+
+template <int R>
+__global__ void __launch_bounds__(256) classify_kernel(Classes K, uint8_t* __restrict__ cat, int32_t nruns,
+                                                       uint32_t* __restrict__ run_cnt,
                                                        unsigned long long* __restrict__ cat_slots, Counters* ctr) {
-    __shared__ uint32_t hist[16 * kNB + 1];
-    __shared__ unsigned long long shist[16 * kNB + 1];
-    const int ncat = nsub * kNB;
-    for (int j = threadIdx.x; j <= ncat; j += 256) {
-        hist[j] = 0;
-        shist[j] = 0;
-    }
+    __shared__ uint32_t hist[4][kMaxCat];
+    __shared__ unsigned long long shist[kMaxCat];
+    const int ncat = K.nsub * kNB;
+    const int w = threadIdx.x >> 6;
+    const int lane = lane_id();
+    for (int j = threadIdx.x; j < 4 * kMaxCat; j += 256) hist[j / kMaxCat][j % kMaxCat] = 0;
+    for (int j = threadIdx.x; j < kMaxCat; j += 256) shist[j] = 0;
     __syncthreads();
-    // grid-stride: few workgroups, so the per-category totals cost few global
-    // atomics on their handful of addresses
-    for (int32_t v = blockIdx.x * 256 + threadIdx.x; v < n; v += gridDim.x * 256) {
-        const int64_t d = xadj[v + 1] - xadj[v];
-        uint64_t hcv = hc;
+    const int32_t run = blockIdx.x * 4 + w;
+#pragma unroll 4
+    for (int r = 0; r < R; ++r) {
+        const int64_t v64 = static_cast<int64_t>(run) * (64 * R) + r * 64 + lane;
+        if (v64 >= K.n) continue;
+        const int32_t v = static_cast<int32_t>(v64);
+        const int64_t d = K.xadj[v + 1] - K.xadj[v];
+        uint64_t hcv = K.hc;
         int32_t lv = v;  // graph-local id
         bool act = true;
-        if (gid) {
-            const int32_t g = gid[v];
-            hcv = g_hc[g];
-            lv = v - g_nbase[g];
-            act = g_active[g] != 0;
+        if (K.gid) {
+            const int32_t g = K.gid[v];
+            hcv = K.g_hc[g];
+            lv = v - K.g_nbase[g];
+            act = K.g_active[g] != 0;
         }
         int32_t col;
-        if (color_override) {
-            col = color_override[v];
-            if (col < 0 || col >= nsub) {
-                atomicOr(&ctr->bad_color, 1u);
+        if (K.color_override) {
+            col = K.color_override[v];
+            if (col < 0 || col >= K.nsub) {
+                ctr->bad_color = 1;
                 col = 0;
             }
         } else {
             col = static_cast<int32_t>(mix64(hcv ^ static_cast<uint64_t>(static_cast<uint32_t>(lv))) %
-                                       static_cast<uint64_t>(nsub));
+                                       static_cast<uint64_t>(K.nsub));
         }
         int32_t bucket = kHubBucket;
 #pragma unroll
         for (int j = kHubBucket - 1; j >= 0; --j)
-            if (d <= th.t[j]) bucket = j;
-        const int32_t cat = (d == 0 || !act) ? ncat : col * kNB + bucket;
-        keys[v] = static_cast<uint64_t>(cat);
-        vals[v] = static_cast<uint32_t>(v);
-        atomicAdd(&hist[cat], 1u);
-        if (d) atomicAdd(&shist[cat], static_cast<unsigned long long>(d));
+            if (d <= K.th.t[j]) bucket = j;
+        const int32_t c = (d == 0 || !act) ? ncat : col * kNB + bucket;
+        cat[v] = static_cast<uint8_t>(c);
+        atomicAdd(&hist[w][c], 1u);
+        if (d) atomicAdd(&shist[c], static_cast<unsigned long long>(d));
     }
     __syncthreads();
-    for (int j = threadIdx.x; j <= ncat; j += 256) {
-        if (hist[j]) atomicAdd(&cat_count[j], hist[j]);
-        if (shist[j]) atomicAdd(&cat_slots[j], shist[j]);
+    for (int j = threadIdx.x; j < 4 * (ncat + 1); j += 256) {
+        const int32_t q = blockIdx.x * 4 + (j & 3), c = j >> 2;
+        if (q < nruns) run_cnt[static_cast<int64_t>(c) * nruns + q] = hist[j & 3][c];
+    }
+    unsigned long long* slots = cat_slots + (blockIdx.x % kSlotCopies) * kMaxCat;
+    for (int j = threadIdx.x; j <= ncat; j += 256)
+        if (shist[j]) atomicAdd(&slots[j], shist[j]);
+}
+
+// run_cnt[c][q] to the first place of run q in category c, one workgroup per
+// category; cat_count[c] its nodes.
+__global__ void __launch_bounds__(1024) place_kernel(int32_t nruns, uint32_t* __restrict__ run_cnt,
+                                                     const uint32_t* __restrict__ counts_in,
+                                                     uint32_t* __restrict__ cat_count) {
+    __shared__ uint32_t s_w[16];
+    const int tid = threadIdx.x;
+    const int64_t c = blockIdx.x;
+    auto block_sum = [&](uint32_t x) {
+        x = wave_sum(x);
+        if (lane_id() == 0) s_w[tid >> 6] = x;
+        __syncthreads();
+        uint32_t t = 0;
+        for (int q = 0; q < 16; ++q) t += s_w[q];
+        __syncthreads();
+        return t;
+    };
+    uint32_t before = 0;
+    for (int64_t j = tid; j < c * nruns; j += 1024) before += counts_in[j];
+    uint32_t base = block_sum(before);
+    const uint32_t first = base;
+    for (int32_t q0 = 0; q0 < nruns; q0 += 1024) {
+        const uint32_t x = q0 + tid < nruns ? counts_in[c * nruns + q0 + tid] : 0;
+        uint32_t incl = x;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t u = __shfl_up(incl, o, 64);
+            if (lane_id() >= o) incl += u;
+        }
+        if (lane_id() == 63) s_w[tid >> 6] = incl;
+        __syncthreads();
+        uint32_t pre = 0, total = 0;
+        for (int q = 0; q < 16; ++q) {
+            pre += q < (tid >> 6) ? s_w[q] : 0;
+            total += s_w[q];
+        }
+        __syncthreads();
+        if (q0 + tid < nruns) run_cnt[c * nruns + q0 + tid] = base + pre + incl - x;
+        base += total;
+    }
+    if (tid == 0) cat_count[c] = base - first;
+}
+
+// The rows of the schedule.  A row of 2^31 slots or more does not occur: its
+// slots would be distinct neighbours or repeated edges whose weights sum past
+// 2^31 - 1.  Nodes that never move have no row.
+template <int R>
+__global__ void __launch_bounds__(256) schedule_kernel(int32_t n, const int64_t* __restrict__ xadj,
+                                                       const uint8_t* __restrict__ cat, int32_t ncat, int32_t nruns,
+                                                       const uint32_t* __restrict__ place, Row* __restrict__ rows,
+                                                       int32_t* __restrict__ nodes) {
+    __shared__ uint32_t at[4][kMaxCat];
+    const int w = threadIdx.x >> 6;
+    const int lane = lane_id();
+    const int32_t run = blockIdx.x * 4 + w;
+    if (run >= nruns) return;  // whole waves; no workgroup barrier below
+    for (int c = lane; c < ncat; c += 64) at[w][c] = place[static_cast<int64_t>(c) * nruns + run];
+    wave_sync();
+    const uint64_t lt = lanemask_lt();
+#pragma unroll 2
+    for (int r = 0; r < R; ++r) {
+        const int64_t v64 = static_cast<int64_t>(run) * (64 * R) + r * 64 + lane;
+        const bool in = v64 < n;
+        const int32_t v = static_cast<int32_t>(in ? v64 : 0);
+        const int32_t c = in ? cat[v] : ncat;
+        const int64_t b = xadj[v];
+        const int64_t e = xadj[v + 1];
+        uint64_t match = __ballot(c < ncat);
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const uint64_t bal = __ballot((c >> q) & 1);
+            match &= ((c >> q) & 1) ? bal : ~bal;
+        }
+        uint32_t pos = 0;
+        if (c < ncat) pos = at[w][c] + static_cast<uint32_t>(__popcll(match & lt));
+        wave_sync();
+        if (c < ncat && (match & lt) == 0) at[w][c] += static_cast<uint32_t>(__popcll(match));
+        wave_sync();
+        if (c < ncat) {
+            rows[pos] = Row{b, static_cast<int32_t>(e - b), v};
+            nodes[pos] = v;
+        }
     }
 }
 
-// The schedule's rows.  A row of 2^31 slots or more does not occur: its slots
-// would be distinct neighbours or repeated edges whose weights sum past 2^31-1.
-__global__ void schedule_rows_kernel(const int32_t* __restrict__ nodes, int32_t count, const int64_t* __restrict__ xadj,
-                                     Row* __restrict__ rows) {
-    const int32_t i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= count) return;
-    const int32_t v = nodes[i];
-    const int64_t b = xadj[v];
-    rows[i] = Row{b, static_cast<int32_t>(xadj[v + 1] - b), v};
+// Every node its own cluster: labels[v] = v, w[v] = c(v).
+__global__ void __launch_bounds__(256) singletons_kernel(int32_t n, const int32_t* __restrict__ vw,
+                                                         int32_t* __restrict__ labels, int32_t* __restrict__ w) {
+    const int32_t v = blockIdx.x * 256 + threadIdx.x;
+    if (v >= n) return;
+    labels[v] = v;
+    w[v] = vw ? vw[v] : 1;
 }
 
 // Per-graph hash prefixes H(seed_g, tag, level, phase[, round]).
@@ -2499,6 +2605,12 @@ unsigned capped_grid(int64_t items) {
 
 }  // namespace
 
+void singletons(const DevGraph& g, int32_t* labels, int32_t* w, hipStream_t s) {
+    if (g.n <= 0) return;
+    singletons_kernel<<<grid_for(g.n, 256), 256, 0, s>>>(g.n, g.vw, labels, w);
+    LAUNCHCHK();
+}
+
 void label_weights(const DevGraph& g, const int32_t* label, int32_t* w, int32_t nw, hipStream_t s) {
     fill_i32(w, 0, nw, s);
     if (g.n > 0) {
@@ -2545,14 +2657,20 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
         th.t[6] = std::min(block, std::max(th.t[5], kBlock2Max));
         th.t[7] = block;
     }
-    DBuf<uint64_t> ckeys(n, s), ckeys_tmp(n, s);
-    DBuf<uint32_t> order(n, s), order_tmp(n, s);
+    // nodes per wave of the scheduling kernels: enough waves for a small graph,
+    // few runs for a large one
+    const int per_run = n <= (1 << 16) ? 1 : (n <= (1 << 20) ? 4 : 16);
+    const int32_t nruns = static_cast<int32_t>((static_cast<int64_t>(n) + 64 * per_run - 1) / (64 * per_run));
+    DBuf<uint8_t> cat(n, s);
+    DBuf<uint32_t> run_cnt(static_cast<size_t>(ncat + 1) * nruns, s), place(static_cast<size_t>(ncat + 1) * nruns, s);
     DBuf<uint32_t> cat_count(ncat + 1, s);
-    DBuf<unsigned long long> cat_slots(ncat + 1, s);
-    DBuf<Counters> ctr(2, s);
-    fill_u32(cat_count.get(), 0, ncat + 1, s);
-    HIPCHK(hipMemsetAsync(cat_slots.get(), 0, (ncat + 1) * sizeof(unsigned long long), s));
-    HIPCHK(hipMemsetAsync(ctr.get(), 0, 2 * sizeof(Counters), s));
+    DBuf<int32_t> order(n, s);
+    DBuf<Row> sched(n, s);
+    // slot totals of the categories, then the two counter sets
+    constexpr size_t kSlotWords = kSlotCopies * kMaxCat;
+    DBuf<unsigned long long> cat_slots(kSlotWords + 2 * sizeof(Counters) / 8, s);
+    Counters* const ctr = reinterpret_cast<Counters*>(cat_slots.get() + kSlotWords);
+    fill_u32(reinterpret_cast<uint32_t*>(cat_slots.get()), 0, 2 * (kSlotWords + 2 * sizeof(Counters) / 8), s);
     const uint64_t hc = hash_prefix({seed, 1, static_cast<uint64_t>(static_cast<uint32_t>(level)),
                                      static_cast<uint64_t>(static_cast<uint32_t>(phase))});
     const uint64_t lvl64 = static_cast<uint64_t>(static_cast<uint32_t>(level));
@@ -2566,36 +2684,33 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     }
     {
         ProfScope ps("lp_schedule", 0, s);
-        classify_kernel<<<capped_grid(n), 256, 0, s>>>(n, g.xadj, color_override, hc, mg ? mg->gid : nullptr,
-                                                         g_hc.get(), mg ? mg->nbase : nullptr,
-                                                         mg ? mg->active : nullptr, nsub, th,
-                                                         ckeys.get(), order.get(), cat_count.get(), cat_slots.get(),
-                                                         ctr.get());
+        const Classes K{n, g.xadj, color_override, hc, mg ? mg->gid : nullptr, g_hc.get(), mg ? mg->nbase : nullptr,
+                        mg ? mg->active : nullptr, nsub, th};
+        const unsigned gb = grid_for(nruns, 4);
+        auto classify = per_run == 1 ? classify_kernel<1> : per_run == 4 ? classify_kernel<4> : classify_kernel<16>;
+        classify<<<gb, 256, 0, s>>>(K, cat.get(), nruns, run_cnt.get(), cat_slots.get(), ctr);
+        LAUNCHCHK();
+        place_kernel<<<ncat + 1, 1024, 0, s>>>(nruns, place.get(), run_cnt.get(), cat_count.get());
+        LAUNCHCHK();
+        auto schedule = per_run == 1 ? schedule_kernel<1> : per_run == 4 ? schedule_kernel<4> : schedule_kernel<16>;
+        schedule<<<gb, 256, 0, s>>>(n, g.xadj, cat.get(), ncat, nruns, place.get(), sched.get(), order.get());
         LAUNCHCHK();
     }
-    RadixScratch rs;
-    radix_sort_pairs(ckeys.get(), order.get(), ckeys_tmp.get(), order_tmp.get(), n, 0, bits_for(ncat), rs, s);
-    ckeys.release();
-    ckeys_tmp.release();
-    order_tmp.release();
     std::vector<uint32_t> cnt(ncat + 1);
-    std::vector<unsigned long long> cslots(ncat + 1);
+    std::vector<unsigned long long> cslots(kSlotWords);
     Counters hctr;
     {
         const ReadItem items[3] = {{cnt.data(), cat_count.get(), (ncat + 1) * sizeof(uint32_t)},
-                                   {cslots.data(), cat_slots.get(), (ncat + 1) * sizeof(unsigned long long)},
-                                   {&hctr, ctr.get(), sizeof(Counters)}};
+                                   {cslots.data(), cat_slots.get(), kSlotWords * sizeof(unsigned long long)},
+                                   {&hctr, ctr, sizeof(Counters)}};
         read_back(items, 3, s);
     }
+    for (size_t q = kMaxCat; q < kSlotWords; ++q) cslots[q % kMaxCat] += cslots[q];
     if (hctr.bad_color) fail(-1, "color_override value outside [0, subrounds)");
     std::vector<int64_t> off(ncat + 2, 0);
     for (int32_t j = 0; j <= ncat; ++j) off[j + 1] = off[j] + cnt[j];
-    const int32_t* nodes = reinterpret_cast<const int32_t*>(order.get());
-
-    DBuf<Row> sched(n, s);
+    const int32_t* nodes = order.get();
     const Row* rows = sched.get();
-    schedule_rows_kernel<<<grid_for(n, 256), 256, 0, s>>>(nodes, n, g.xadj, sched.get());
-    LAUNCHCHK();
 
     // --- hub plans per colour: the hubs' rows in one read, all plans in one copy
     std::vector<HubPlan> plans(nsub);
@@ -2736,9 +2851,14 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             ? std::min(tune.select_launches, max_launches)
             : std::min(max_launches, (bits_for(static_cast<uint64_t>(n - 1)) + 12 + kLDigit - 1) / kLDigit);
     DBuf<uint32_t> rcnt(std::max(rounds, 1), s);  // candidates per round, read back one round late (see stopped())
-    init_admission_kernel<<<capped_grid(std::max<int64_t>(fill_n, max_large * kLBins)), 256, 0, s>>>(
+    DBuf<uint8_t> lab8;
+    DBuf<uint16_t> lab16;
+    if (nw <= 256) lab8.alloc(n, s);
+    else if (nw <= 65536) lab16.alloc(n, s);
+    const int64_t init_items = std::max({fill_n, max_large * kLBins, nw <= 65536 ? static_cast<int64_t>(n) : 0});
+    init_admission_kernel<<<std::min(grid_for(init_items, 256), 4096u), 256, 0, s>>>(
         acc.get(), acc_n, seg_off.get(), direct ? 0 : nw, seg_fill.get(), fill_n, lhist.get(), max_large * kLBins, ldone.get(), max_large,
-        rcnt.get(), rounds, ctr.get());
+        rcnt.get(), rounds, ctr, label, n, lab8.get(), lab16.get());
     LAUNCHCHK();
 
     EvalArgs A;
@@ -2765,17 +2885,6 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
         for (const HubPlan& P : plans) max_hubs = std::max<int64_t>(max_hubs, P.count);
         hub_sum.alloc(max_hubs * A.dense_k, s);
         fill_i32(hub_sum.get(), 0, max_hubs * A.dense_k, s);
-    }
-    DBuf<uint8_t> lab8;
-    DBuf<uint16_t> lab16;
-    if (nw <= 256) {
-        lab8.alloc(n, s);
-        narrow_kernel<uint8_t><<<grid_for(n, 256), 256, 0, s>>>(label, n, lab8.get());
-        LAUNCHCHK();
-    } else if (nw <= 65536) {
-        lab16.alloc(n, s);
-        narrow_kernel<uint16_t><<<grid_for(n, 256), 256, 0, s>>>(label, n, lab16.get());
-        LAUNCHCHK();
     }
     A.label8 = lab8.get();
     A.label16 = lab16.get();
@@ -3047,8 +3156,8 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             // flight.
             M.nodes = cnodes;
             M.count = static_cast<int32_t>(ccount);
-            M.ctr = ctr.get() + (step & 1);
-            M.ctr_next = ctr.get() + (~step & 1);
+            M.ctr = ctr + (step & 1);
+            M.ctr_next = ctr + (~step & 1);
             M.gate = gate;
             M.round_cnt = rcnt.get() + r;
             M.host_cnt = sc == last_sub ? hrc + r : nullptr;

@@ -64,6 +64,9 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
 // The row length up to which a graph of n nodes evaluates one node per lane.
 int32_t default_lane_max(int32_t n);
 
+// Every node its own label: labels[v] = v, w[v] = c(v).
+void singletons(const DevGraph& g, int32_t* labels, int32_t* w, hipStream_t s);
+
 // w[x] = sum of c(v) over label(v) = x, for x in [0, nw).
 void label_weights(const DevGraph& g, const int32_t* label, int32_t* w, int32_t nw, hipStream_t s);
 

@@ -33,7 +33,7 @@ def star(leaves, seed):
     return {"n": leaves + 1, "xadj": xadj, "adjncy": adj, "adjwgt": np.concatenate([w, w]), "vwgt": vw}
 
 
-@pytest.mark.parametrize("leaves", [1, 2, 63, 64, 65, 1023, 1024, 1025, 16384, 16385, 65536, 65537, 70001, 262145])
+@pytest.mark.parametrize("leaves", [1, 2, 63, 64, 65, 256, 257, 512, 513, 1023, 1024, 1025, 16384, 16385, 65536, 65537, 70001, 262145])
 @pytest.mark.parametrize("knobs", [dict(), dict(select_small_max=64), dict(select_small_max=1, select_launches=1)])
 def test_one_segment(sc, leaves, knobs):
     g = star(leaves, leaves)
@@ -76,7 +76,7 @@ def centres(n, degrees, seed):
 DEGREES = [1, 4, 5, 16, 17, 32, 33, 64, 65, 256, 257, 1024, 1025, 4096, 4097, 8192, 8193, 16385, 25000]
 
 
-@pytest.mark.parametrize("k", [0, 3, 64, 300])
+@pytest.mark.parametrize("k", [0, 1, 3, 8, 16, 64, 65, 300])
 @pytest.mark.parametrize("knobs", [dict(), dict(lane_max_degree=16), dict(fused_eval=-1), dict(block_table=16384),
                                    dict(hub_part_limit=1), dict(skip_quiet=1)])
 def test_row_lengths(sc, k, knobs):
@@ -93,3 +93,21 @@ def test_row_lengths(sc, k, knobs):
                                     **knobs)
             ref, rr_ref, _ = oracle.refine(g, k, lmax, part, rounds=3, seed=5, nsub=nsub)
         assert rr == rr_ref and np.array_equal(lab.cpu().numpy(), ref)
+
+
+def test_contracted_row_lengths(sc):
+    # singleton clusters: every row passes the merge and the ordering and comes out as it went in
+    g = centres(60000, [1, 2, 63, 64, 65, 256, 257, 512, 513, 2047, 2048, 2049, 4096, 4097, 8191, 8192, 8193, 16385, 50000],
+                11)
+    d = sc.to_device(g)
+    C, cg = sc.contract_dev(d, torch.arange(g["n"], dtype=torch.int32, device="cuda"))
+    assert torch.equal(C.cpu(), torch.arange(g["n"], dtype=torch.int32))
+    for key in ("xadj", "adjncy", "adjwgt", "vwgt"):
+        assert np.array_equal(cg[key].cpu().numpy(), g[key]), key
+    # pairs of nodes: parallel edges merge
+    lab = torch.arange(g["n"], dtype=torch.int32, device="cuda") // 2
+    C, cg = sc.contract_dev(d, lab)
+    ref_C, ref = oracle.contract(g, lab.cpu().numpy())
+    assert np.array_equal(C.cpu().numpy(), ref_C)
+    for key in ("xadj", "adjncy", "adjwgt", "vwgt"):
+        assert np.array_equal(cg[key].cpu().numpy(), ref[key]), key
