@@ -127,6 +127,7 @@ int cluster_impl(const DevGraph& g_in, int64_t U, int32_t rounds, uint64_t seed,
         within_blocks(g, block, inside, s);
         gc = inside.view();
         gc.vw = g.vw;
+        gc.symmetric = g.symmetric;
     }
     DBuf<int32_t> dcol;
     if (o.degree_order && !color_dev && g.n > 0) {

@@ -93,6 +93,7 @@ void check_graph(DevGraph& g, bool validate, int64_t* cV, int64_t* cmax, hipStre
         if (st == SCLAP_ERR_NOT_SYMMETRIC) fail(st, "graph is not symmetric");
         if (st == SCLAP_ERR_OVERFLOW) fail(st, "node or edge weight total exceeds 2^31-1");
         if (st != 0) fail(st, "graph validation failed");
+        g.symmetric = true;
         if (drop_units) {
             if (unit[0]) g.vw = nullptr;
             if (unit[1]) g.ew = nullptr;
@@ -789,6 +790,7 @@ void multilevel_cycle(const DevGraph& g0, int32_t k, int64_t cV, int64_t cmax0, 
             within_blocks(G, blk_of(lev), inside, s);
             Gc = inside.view();
             Gc.vw = G.vw;
+            Gc.symmetric = G.symmetric;
         }
         DBuf<int32_t> dcol;
         if (o.degree_order) {
@@ -814,6 +816,7 @@ void multilevel_cycle(const DevGraph& g0, int32_t k, int64_t cV, int64_t cmax0, 
         }
         L[lev].C = std::move(C);
         nx.g = nx.own.view();
+        nx.g.symmetric = L[lev].g.symmetric;
         L.push_back(std::move(nx));
         blk.push_back(std::move(cb));
         ++lev;
@@ -1574,6 +1577,7 @@ int partition_batch_impl(const DevGraph& g0_in, int32_t G, const int32_t* node_b
                 within_blocks(B.g, blk_of(lev), inside, s);
                 Gc = inside.view();
                 Gc.vw = B.g.vw;
+                Gc.symmetric = B.g.symmetric;
             }
             DBuf<int32_t> dcol;
             if (o.degree_order) {
@@ -1648,6 +1652,7 @@ int partition_batch_impl(const DevGraph& g0_in, int32_t G, const int32_t* node_b
                 coarse = OwnedDevGraph();
             }
             N.g = N.own.view();
+            N.g.symmetric = B.g.symmetric;
             N.gid.alloc(std::max(N.g.n, 1), s);
             member_ids(N.g.n, N.nb, N.ids, N.gid.get(), s);
             std::vector<int32_t> delta(G, INT_MIN);

@@ -38,6 +38,7 @@
 
 #include "lp.hpp"
 #include "profile.hpp"
+#include "sclap.h"
 
 namespace sclap {
 
@@ -72,6 +73,9 @@ constexpr int kSmallSeg = 16384;         // large colours: segments up to this l
 constexpr int kSegChunk = 16384;         // entries per workgroup in the multi-workgroup selection
 constexpr int kLargeBlocks = 256;        // grid of the multi-workgroup selection kernel
 constexpr int kLargeThreads = 1024;      // and its workgroup size
+constexpr int64_t kKeptMinSlots = 1 << 24;  // with fewer slots in long enough rows no sums are kept
+constexpr int32_t kKeptPerSlot = 4;         // a row keeps its sums when it has at least dense_k / 4 slots
+constexpr int kUpkeepLongBlocks = 512;      // grid of upkeep_long_kernel
 
 struct Counters {
     unsigned long long segs;  // segments claimed (high word), entries reserved in them (low word)
@@ -80,7 +84,7 @@ struct Counters {
     uint32_t nlarge;    // segments longer than one workgroup selects from
     uint32_t nlchunks;  // kSegChunk-entry chunks of those segments
     uint32_t bad_color;
-    uint32_t pad;
+    uint32_t nlong;     // chunks of long rows whose node moved (upkeep of kept sums)
 };
 
 // One schedule entry: a node and where its row lies.  Laid out in schedule
@@ -134,6 +138,7 @@ struct EvalArgs {
     // their own, which sums in LDS first); entry of label t: t << acc_shift
     unsigned long long* acc;
     int32_t acc_shift;
+    int32_t* sums;  // kept block sums of the launch's rows, dense_k per entry (null: not kept)
 };
 
 // A round runs only while the previous one had candidates (gate: that
@@ -1067,6 +1072,8 @@ __device__ __forceinline__ void eval_dense_group_body(const EvalArgs& A, int32_t
     dense_slots<G>(A, kx, row.begin, row.deg, conn, gl);
     wave_sync();
     const int32_t own = conn[a - kx.lbase];
+    if (A.sums)
+        for (int32_t j = gl; j < A.dense_k; j += G) A.sums[static_cast<int64_t>(node_i) * A.dense_k + j] = conn[j];
     Best best;
     best_init(best);
     bool blocked = false;
@@ -1113,6 +1120,8 @@ __device__ __forceinline__ void eval_dense_block_body(const EvalArgs& A, int32_t
     dense_slots<NT>(A, kx, row.begin, row.deg, conn, tid);
     __syncthreads();
     const int32_t own = conn[a - kx.lbase];
+    if (A.sums)
+        for (int32_t j = tid; j < A.dense_k; j += NT) A.sums[static_cast<int64_t>(bid) * A.dense_k + j] = conn[j];
     Best best;
     best_init(best);
     bool blocked = false;
@@ -1184,7 +1193,65 @@ __device__ void hub_dense_decide(const EvalArgs& A, const HubArgs& H, int32_t h)
     block_combine(fc, ft, fx);
     if (tid == 0) store_result(A, h, fx, fc, own, over, c);
     __syncthreads();  // every thread has read the row
-    for (int32_t j = tid; j < A.dense_k; j += 256) conn[j] = 0;
+    for (int32_t j = tid; j < A.dense_k; j += 256) {
+        if (A.sums) A.sums[static_cast<int64_t>(h) * A.dense_k + j] = conn[j];
+        conn[j] = 0;
+    }
+}
+
+// Kept sums: after the first round of a refinement few nodes move (power-law
+// graph, 2^22 nodes, 64 blocks: 14 % of the slots belong to nodes that moved in
+// the first round, 0.1-4 % in each later one), so the block sums of long rows
+// stay in HBM.  The first round's evaluation writes them, the neighbours of
+// every node that moves are corrected (upkeep), and later rounds read dense_k
+// integers per row, hubs included, instead of gathering a label per slot.  The
+// sums are the same integers a new count would give.  G lanes per row, each
+// with its U sums loaded before anything else is known about the row: the
+// kernel is a stream of 4 * dense_k bytes per row (2^24 nodes, 512 M slots, 64
+// blocks, one colour: 180 k rows in 110 us beside the short rows, where the
+// gathers of those rows took 700 us).
+template <int G>
+__global__ void __launch_bounds__(256) eval_kept_kernel(EvalArgs A) {
+    constexpr int U = 4;  // G * U >= dense_k
+    const int gl = threadIdx.x % G;
+    const int32_t i = static_cast<int32_t>(blockIdx.x) * (256 / G) + static_cast<int32_t>(threadIdx.x) / G;
+    if (i >= A.count) return;  // uniform per group
+    const Row row = A.rows[i];
+    if (stopped(A.gate)) return;
+    const int32_t* conn = A.sums + static_cast<int64_t>(i) * A.dense_k;
+    int32_t cn[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) cn[u] = gl + u * G < A.dense_k ? conn[gl + u * G] : 0;
+    const int qm = quiet_mode(A);
+    const int32_t v = row.node;
+    const Ctx kx = ctx_of(A, v);
+    if (skip_quiet(A, qm, v, kx)) {
+        if (gl == 0) store_result(A, i, -1, 0, 0, false, 0);
+        return;
+    }
+    const int32_t a = A.label[v];
+    const int32_t c = A.vw ? A.vw[v] : 1;
+    const bool over = A.w[a] > kx.bound;
+    const int32_t la = a - kx.lbase;
+    int32_t own = 0;
+    int32_t x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int32_t at = __shfl(cn[u], la % G, G);
+        if (la / G == u) own = at;
+        x[u] = cn[u] == 0 || gl + u * G == la ? -1 : gl + u * G + kx.lbase;
+    }
+    Best best;
+    best_init(best);
+    bool blocked = false;
+    consider_group<U>(A, kx, x, cn, c, own, over, best, blocked);
+    int32_t bx, bconn;
+    group_argmax<G>(best, kx, bx, bconn);
+    const bool any_blocked = group_any<G>(blocked);
+    if (gl == 0) {
+        store_result(A, i, bx, bconn, own, over, c);
+        if (qm) A.quiet[v] = (!over && !any_blocked) ? 1 : 0;
+    }
 }
 
 // ------------------------------------------------- small colours, fused
@@ -1202,6 +1269,7 @@ constexpr int kFusedDense = 9;   // buckets 0..7 and the hub chunks
 
 struct FusedBuckets {
     const Row* rows[kFusedDense];
+    int32_t* sums[kFusedDense];
     int32_t* ct[kFusedDense];
     int32_t* cg[kFusedDense];
     int32_t count[kFusedDense];
@@ -1225,6 +1293,7 @@ __global__ void __launch_bounds__(256) eval_fused_kernel(EvalArgs A, FusedBucket
     A.count = F.count[b];
     A.ct = F.ct[b];
     A.cg = F.cg[b];
+    A.sums = F.sums[b];
     int32_t* l32 = reinterpret_cast<int32_t*>(lds);
     switch (b) {  // uniform over the workgroup
         case 0:
@@ -1476,6 +1545,7 @@ struct Admission {
     int32_t* label;
     uint8_t* label8;
     uint16_t* label16;
+    uint16_t* prev;      // [n] label that a node left in this sub-round, else kStayed (null: not needed)
     Counters* ctr;       // this sub-round's counters
     Counters* ctr_next;  // the next sub-round's: cleared here, no kernel reads them any more
     const uint32_t* gate;
@@ -1924,6 +1994,7 @@ __device__ __forceinline__ void clear_subround(Counters* ctr) {
     ctr->gmax = INT_MIN;
     ctr->nlarge = 0;
     ctr->nlchunks = 0;
+    ctr->nlong = 0;
 }
 
 // Moves node v (weight c) to label t.  The departure goes to delta (LDS, small
@@ -1932,6 +2003,7 @@ template <bool kSmall>
 __device__ __forceinline__ void depart_and_move(const Admission& A, int32_t v, int32_t a, int32_t t, int32_t c,
                                                 int32_t* delta) {
     A.label[v] = t;
+    if (A.prev) A.prev[v] = static_cast<uint16_t>(a);
     if (A.label8) A.label8[v] = static_cast<uint8_t>(t);
     if (A.label16) A.label16[v] = static_cast<uint16_t>(t);
     if (c) {
@@ -2199,6 +2271,201 @@ __global__ void __launch_bounds__(256) unquiet_kernel(const int32_t* __restrict_
         const int32_t u = nodes[base + i];
         const int64_t e = xadj[u + 1];
         for (int64_t j = xadj[u] + lane; j < e; j += 64) quiet[adj[j]] = 0;
+    }
+}
+
+// ----------------------------------------------------- upkeep of kept sums
+
+// After a sub-round, on the way to the next one's evaluation: the nodes that
+// moved are found by their entries of prev (a stream of 2 bytes per node) and
+// each of their slots corrects two sums of the neighbour at its end, if that
+// keeps sums.  A workgroup lays the rows of its movers end to end and takes a
+// slot per thread, since most movers have a handful; rows over kUpkeepLong
+// slots become chunks for a second launch, so that no workgroup is left with
+// a hub (20 M slots per colour, first later rounds: 49 + 23 -> 20 + 11 us).
+// Two dependent reads and two atomics per slot; on random lines those ran at
+// 18 G/s.
+
+// Index of every scheduled node's kept sums, -1 for short rows; the colours'
+// kept rows follow each other.
+struct KeptRanges {
+    int32_t nsub;
+    int32_t from[16], to[16];  // schedule positions of each colour's kept rows
+    int32_t base[16];          // index of the first
+    int32_t end[16];           // schedule position after the colour
+};
+
+__global__ void __launch_bounds__(256) kept_index_kernel(KeptRanges K, const int32_t* __restrict__ nodes, int32_t count,
+                                                         int32_t* __restrict__ kidx) {
+    const int32_t p = static_cast<int32_t>(blockIdx.x) * 256 + static_cast<int32_t>(threadIdx.x);
+    if (p >= count) return;
+    int sc = 0;
+    while (sc < K.nsub - 1 && p >= K.end[sc]) ++sc;
+    kidx[nodes[p]] = p >= K.from[sc] && p < K.to[sc] ? K.base[sc] + (p - K.from[sc]) : -1;
+}
+
+constexpr uint32_t kStayed = 0xFFFF;
+constexpr int kUpkeepPer = 8;           // nodes per thread: one 16-byte load of prev
+constexpr int kUpkeepLong = 1024;       // longer rows are cut into chunks of this many slots
+
+struct Upkeep {
+    int32_t n;
+    uint16_t* prev;
+    const int32_t* label;
+    const int64_t* xadj;
+    const int32_t* adj;
+    const int32_t* ew;
+    const int32_t* gid;
+    const int32_t* g_lbase;
+    const int32_t* kidx;
+    int32_t built;  // rows with a lower index have sums
+    int32_t* sums;
+    int32_t k;
+    int4* chunks;  // node, old label, new label, chunk
+    Counters* ctr;
+    const uint32_t* gate;
+};
+
+// U slots of rows whose nodes moved from block `from` to `to` (slot -1: none).
+template <int U>
+__device__ __forceinline__ void upkeep_slots(const Upkeep& K, const int64_t* slot, const int32_t* from,
+                                             const int32_t* to) {
+    int32_t v[U], wt[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        v[u] = slot[u] >= 0 ? K.adj[slot[u]] : -1;
+        wt[u] = slot[u] >= 0 && K.ew ? K.ew[slot[u]] : 1;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = v[u] >= 0 ? K.kidx[v[u]] : -1;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (v[u] < 0 || v[u] >= K.built) continue;
+        int32_t* conn = K.sums + static_cast<int64_t>(v[u]) * K.k;
+        atomicSub(&conn[from[u]], wt[u]);
+        atomicAdd(&conn[to[u]], wt[u]);
+    }
+}
+
+__global__ void __launch_bounds__(256) upkeep_kernel(Upkeep K) {
+    constexpr int kNodes = 256 * kUpkeepPer;
+    __shared__ int32_t s_node[kNodes];
+    __shared__ uint16_t s_from[kNodes];
+    __shared__ int64_t s_begin[256];
+    __shared__ int32_t s_pre[256], s_f[256], s_t[256];
+    __shared__ int32_t s_wave[4];
+    if (stopped(K.gate)) return;  // uniform over the grid
+    const int tid = threadIdx.x;
+    const int lane = lane_id();
+    const int wid = tid >> 6;
+    const int64_t v0 = (static_cast<int64_t>(blockIdx.x) * 256 + tid) * kUpkeepPer;
+    uint32_t pv[kUpkeepPer];
+    if (v0 + kUpkeepPer <= K.n) {
+        const uint4 q = *reinterpret_cast<const uint4*>(K.prev + v0);
+        const uint32_t w4[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int j = 0; j < kUpkeepPer; ++j) pv[j] = (w4[j / 2] >> (16 * (j & 1))) & 0xFFFFu;
+    } else {
+#pragma unroll
+        for (int j = 0; j < kUpkeepPer; ++j) pv[j] = v0 + j < K.n ? K.prev[v0 + j] : kStayed;
+    }
+    int32_t mine = 0;
+#pragma unroll
+    for (int j = 0; j < kUpkeepPer; ++j) mine += pv[j] != kStayed;
+    if (__syncthreads_or(mine) == 0) return;
+    // exclusive sum of v over the workgroup; *total gets the whole
+    auto block_prefix = [&](int32_t v, int32_t* total) {
+        int32_t inc = v;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t t = __shfl_up(inc, o, 64);
+            if (lane >= o) inc += t;
+        }
+        __syncthreads();  // s_wave may still be read
+        if (lane == 63) s_wave[wid] = inc;
+        __syncthreads();
+        int32_t before = 0, all = 0;
+        for (int w = 0; w < 4; ++w) {
+            if (w < wid) before += s_wave[w];
+            all += s_wave[w];
+        }
+        *total = all;
+        return before + inc - v;
+    };
+    int32_t m;
+    int32_t at = block_prefix(mine, &m);
+#pragma unroll
+    for (int j = 0; j < kUpkeepPer; ++j) {
+        if (pv[j] == kStayed) continue;
+        s_node[at] = static_cast<int32_t>(v0 + j);
+        s_from[at] = static_cast<uint16_t>(pv[j]);
+        K.prev[v0 + j] = static_cast<uint16_t>(kStayed);
+        ++at;
+    }
+    __syncthreads();
+    // 256 movers at a time: their rows one after the other, a thread per slot
+    for (int32_t m0 = 0; m0 < m; m0 += 256) {
+        int32_t d = 0;
+        if (m0 + tid < m) {
+            const int32_t v = s_node[m0 + tid];
+            const int64_t b = K.xadj[v], e = K.xadj[v + 1];
+            const int32_t lb = K.gid ? K.g_lbase[K.gid[v]] : 0;
+            const int32_t f = static_cast<int32_t>(s_from[m0 + tid]) - lb, t = K.label[v] - lb;
+            if (e - b > kUpkeepLong) {
+                const int32_t nch = static_cast<int32_t>((e - b + kUpkeepLong - 1) / kUpkeepLong);
+                const uint32_t c0 = atomicAdd(&K.ctr->nlong, static_cast<uint32_t>(nch));
+                for (int32_t q = 0; q < nch; ++q) K.chunks[c0 + q] = make_int4(v, f, t, q);
+            } else {
+                d = static_cast<int32_t>(e - b);
+            }
+            s_begin[tid] = b;
+            s_f[tid] = f;
+            s_t[tid] = t;
+        }
+        int32_t total;
+        const int32_t pre = block_prefix(d, &total);
+        s_pre[tid] = pre;
+        __syncthreads();
+        constexpr int U = 4;
+        for (int32_t j0 = tid; j0 < total; j0 += 256 * U) {
+            int64_t slot[U];
+            int32_t f[U], t[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t j = j0 + u * 256;
+                int lo = 0;  // the last mover whose slots begin at or before j
+#pragma unroll
+                for (int step = 128; step > 0; step >>= 1)
+                    if (s_pre[lo + step] <= j) lo += step;
+                slot[u] = j < total ? s_begin[lo] + (j - s_pre[lo]) : -1;
+                f[u] = s_f[lo];
+                t[u] = s_t[lo];
+            }
+            upkeep_slots<U>(K, slot, f, t);
+        }
+        __syncthreads();
+    }
+}
+
+__global__ void __launch_bounds__(256) upkeep_long_kernel(Upkeep K) {
+    if (stopped(K.gate)) return;
+    const uint32_t nch = K.ctr->nlong;
+    for (uint32_t q = blockIdx.x; q < nch; q += gridDim.x) {
+        const int4 c = K.chunks[q];
+        const int64_t b = K.xadj[c.x] + static_cast<int64_t>(c.w) * kUpkeepLong;
+        const int64_t e = min(b + kUpkeepLong, K.xadj[c.x + 1]);
+        constexpr int U = 4;
+        for (int64_t j0 = b + threadIdx.x; j0 < e; j0 += 256 * U) {
+            int64_t slot[U];
+            int32_t f[U], t[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                slot[u] = j0 + u * 256 < e ? j0 + u * 256 : -1;
+                f[u] = c.y;
+                t[u] = c.z;
+            }
+            upkeep_slots<U>(K, slot, f, t);
+        }
     }
 }
 
@@ -2900,6 +3167,53 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     }
     A.quiet = quiet.get();
     A.quiet_n = n;
+    // Kept sums (see eval_kept_kernel).  A row keeps its sums when reading them
+    // is no more work than its slots: at least one slot per kKeptPerSlot blocks,
+    // which also bounds the memory by 16 bytes per slot.  The upkeep finds a
+    // mover's neighbours in its row, so the graph must be known to be symmetric.
+    // Below kKeptMinSlots the two launches of the upkeep and the separate
+    // launch for the kept rows cost more than the gathers (refinement of a
+    // power-law graph, 10 rounds, 16 blocks: whole partition of 2^20 nodes, 31 M
+    // slots, 29.7 ms without, 28.7 ms with; levels of 2 to 16 M slots kept too:
+    // 31.0 ms).  Where the memory is not to be had, nothing is kept.
+    int32_t kept_bucket = 2;
+    while (kept_bucket < kHubBucket && (th.t[kept_bucket - 1] + 1) * kKeptPerSlot < A.dense_k) ++kept_bucket;
+    int64_t kept_slots = 0;
+    for (int32_t j = 0; j < ncat; ++j)
+        if (j % kNB >= kept_bucket) kept_slots += static_cast<int64_t>(cslots[j]);
+    KeptRanges kr = {};
+    kr.nsub = nsub;
+    int32_t kept_rows = 0;
+    for (int32_t sc = 0; sc < nsub; ++sc) {
+        kr.from[sc] = static_cast<int32_t>(off[sc * kNB + kept_bucket]);
+        kr.to[sc] = kr.end[sc] = static_cast<int32_t>(off[(sc + 1) * kNB]);
+        kr.base[sc] = kept_rows;
+        kept_rows += kr.to[sc] - kr.from[sc];
+    }
+    bool keep = dense && g.symmetric && rounds > 2 && kept_slots >= kKeptMinSlots && nw < static_cast<int32_t>(kStayed);
+    DBuf<int32_t> sums, kidx;
+    DBuf<uint16_t> prev;
+    DBuf<int4> up_chunks;
+    if (keep) {
+        try {
+            sums.alloc(static_cast<size_t>(kept_rows) * A.dense_k, s);
+            kidx.alloc(n, s);
+            prev.alloc(static_cast<size_t>(n) + 8, s);
+            up_chunks.alloc(static_cast<size_t>(g.S / (kUpkeepLong / 2) + 1), s);
+        } catch (const Error& e) {
+            if (e.status != SCLAP_ERR_NO_MEMORY) throw;
+            keep = false;
+            sums.release();
+            kidx.release();
+            prev.release();
+        }
+    }
+    if (keep) {
+        fill_u32(reinterpret_cast<uint32_t*>(prev.get()), 0xFFFFFFFFu, (static_cast<int64_t>(n) + 8) / 2, s);
+        kept_index_kernel<<<grid_for(off[ncat], 256), 256, 0, s>>>(kr, nodes, static_cast<int32_t>(off[ncat]), kidx.get());
+        LAUNCHCHK();
+    }
+    A.sums = nullptr;
 
     // Algorithmic bytes of one evaluation launch, the figure of one round's
     // minimal traffic per unit: per evaluated node 24 (its row offsets, own
@@ -2968,6 +3282,21 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     M.label = label;
     M.label8 = lab8.get();
     M.label16 = lab16.get();
+    M.prev = keep ? prev.get() : nullptr;
+    Upkeep up = {};
+    up.n = n;
+    up.prev = prev.get();
+    up.label = label;
+    up.xadj = g.xadj;
+    up.adj = g.adj;
+    up.ew = g.ew;
+    up.gid = A.gid;
+    up.g_lbase = A.g_lbase;
+    up.kidx = kidx.get();
+    up.sums = sums.get();
+    up.k = A.dense_k;
+    up.chunks = up_chunks.get();
+    bool upkeep_due = false;  // the last sub-round's moves have not reached the kept sums
     int32_t step = 0;  // sub-rounds enqueued: they use the two counter sets in turn
 
     for (int32_t r = 0; r < rounds && !halted; ++r) {
@@ -2993,12 +3322,23 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             for (int32_t bk = 0; bk < kNB; ++bk) colour_slots += cslots[c0 + bk];
             const bool side = colour_slots >= (1ULL << 22);  // small colours stay on one stream
             if (side) evs.fork(s);
+            // the previous sub-round's moves reach the kept sums while the
+            // evaluation streams take the short rows, which need none
+            if (upkeep_due) {
+                ProfScope ps("lp_upkeep", 0, s);
+                upkeep_kernel<<<grid_for(n, 256 * kUpkeepPer), 256, 0, s>>>(up);
+                LAUNCHCHK();
+                upkeep_long_kernel<<<kUpkeepLongBlocks, 256, 0, s>>>(up);
+                LAUNCHCHK();
+                upkeep_due = false;
+            }
             // hubs first: their chain (chunks, partitions, decision) is the
             // longest, so its workgroups should be dispatched before the
             // other buckets fill the device
             const HubPlan& P = plans[sc];
             HubArgs H = {};
-            if (P.count > 0) {
+            const bool kept_eval = keep && r > 0;  // rows from kept_bucket on: from their kept sums
+            if (P.count > 0 && !kept_eval) {
                 const int32_t Hn = P.count;
                 H.count = Hn;
                 const int64_t* pb = plan_buf.get();
@@ -3036,12 +3376,16 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 F.cg[bk] = cg.get() + (off[c0 + bk] - off[c0]);
                 F.count[bk] = static_cast<int32_t>(off[c0 + bk + 1] - off[c0 + bk]);
                 F.end[bk] = 0;
+                F.sums[bk] = keep && bk >= kept_bucket
+                                 ? sums.get() + (kr.base[sc] + off[c0 + bk] - kr.from[sc]) * A.dense_k
+                                 : nullptr;
             }
             auto use_bucket = [&](int32_t bk) {
                 A.rows = F.rows[bk];
                 A.count = F.count[bk];
                 A.ct = F.ct[bk];
                 A.cg = F.cg[bk];
+                A.sums = F.sums[bk];
             };
             // workgroups of buckets hi..lo, the longest rows first
             auto lay_out = [&](int32_t hi, int32_t lo, double* bytes) {
@@ -3062,7 +3406,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             // are stored: one launch less.  Adds to one address are served one
             // every 12 ns, so the colour has at most 2^14 nodes and its
             // candidates at least eight targets to spread over.
-            const bool count_in_eval = fused && P.count == 0 && ccount <= kCountInEval && nw >= 8;
+            const bool count_in_eval = fused && H.count == 0 && ccount <= kCountInEval && nw >= 8;
             A.acc = count_in_eval ? acc.get() : nullptr;
             A.acc_shift = direct ? kAccShift : 0;
             const bool big = fused && !dense && tune.block_table != kBlockTablePow2;
@@ -3070,7 +3414,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             if (fused) {
                 bk_from = dense ? kNB : kFusedHash;
                 double bytes;
-                const int32_t blocks = lay_out(bk_from - 1, 0, &bytes);
+                const int32_t blocks = lay_out(kept_eval ? kept_bucket - 1 : bk_from - 1, 0, &bytes);
                 if (blocks > 0) {
                     ProfScope ps(A.refine ? "lp_refine_fused" : "lp_eval_fused", bytes, s);
                     if (dense) eval_fused_kernel<true><<<blocks, 256, 0, s>>>(A, F, H);
@@ -3088,7 +3432,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                     LAUNCHCHK();
                 }
             }
-            if (P.count > 0 && !(fused && dense)) {
+            if (H.count > 0 && !(fused && dense)) {
                 use_bucket(kHubBucket);
                 if (dense) {
                     ProfScope ps("lp_refine_hub_dense", eval_bytes(P.count, cslots[c0 + kHubBucket]), s);
@@ -3106,7 +3450,20 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                     LAUNCHCHK();
                 }
             }
-            for (int32_t bk = bk_from; bk < kHubBucket; ++bk) {
+            if (kept_eval) {
+                use_bucket(kept_bucket);
+                A.count = kr.to[sc] - kr.from[sc];
+                ProfScope ps("lp_refine_kept", 4.0 * A.dense_k * A.count, s);
+                if (A.count > 0) {
+                    if (A.dense_k <= 32) eval_kept_kernel<8><<<grid_for(A.count, 32), 256, 0, s>>>(A);
+                    else if (A.dense_k <= 64) eval_kept_kernel<16><<<grid_for(A.count, 16), 256, 0, s>>>(A);
+                    else if (A.dense_k <= 128) eval_kept_kernel<32><<<grid_for(A.count, 8), 256, 0, s>>>(A);
+                    else eval_kept_kernel<64><<<grid_for(A.count, 4), 256, 0, s>>>(A);
+                    LAUNCHCHK();
+                }
+            }
+            const int32_t bk_to = kept_eval ? kept_bucket : kHubBucket;
+            for (int32_t bk = bk_from; bk < bk_to; ++bk) {
                 const hipStream_t bs = side ? evs.bucket(bk) : s;
                 const int64_t count = F.count[bk];
                 if (count == 0) continue;
@@ -3216,6 +3573,12 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 if (small) large_move_kernel<true><<<kMaxBlocks, 256, 0, s>>>(M);
                 else large_move_kernel<false><<<kMaxBlocks, 256, 0, s>>>(M);
                 LAUNCHCHK();
+            }
+            if (keep) {
+                up.built = r > 0 || sc == nsub - 1 ? kept_rows : kr.base[sc + 1];
+                up.ctr = M.ctr;
+                up.gate = gate;
+                upkeep_due = true;
             }
             if (A.quiet) {
                 ProfScope ps("lp_unquiet", 0, s);

@@ -17,6 +17,7 @@ struct DevGraph {
     const int32_t* adj = nullptr;
     const int32_t* ew = nullptr;  // null => unit edge weights
     const int32_t* vw = nullptr;  // null => unit node weights
+    bool symmetric = false;  // known to hold every edge in both directions (checked, or made from such a graph)
 };
 
 struct LPTuning {

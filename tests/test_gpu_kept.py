@@ -1,0 +1,50 @@
+"""Refinement with block sums kept between rounds: graphs above the size where
+that starts, block counts around every lane-group size, short rows, long rows
+and hubs.  Integer results, compared with the oracle element by element."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def sc():
+    import paper_1404_4797_amd as m
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    m.load()
+    return m
+
+
+@pytest.fixture(scope="module")
+def graph():
+    """2^18 nodes, 25 million slots, row lengths from a dozen to beyond a hub's."""
+    n, rng = 1 << 18, np.random.default_rng(3)
+    u = (n * rng.random(13_200_000) ** 3).astype(np.int64)
+    v = (n * rng.random(len(u)) ** 3).astype(np.int64)
+    key = np.unique(np.minimum(u, v) * n + np.maximum(u, v))
+    u, v = key // n, key % n
+    u, v = u[u != v], v[u != v]
+    w = rng.integers(1, 6, size=len(u)).astype(np.int32)
+    src, dst, wt = np.concatenate([u, v]), np.concatenate([v, u]), np.concatenate([w, w])
+    order = np.argsort(src * n + dst)
+    deg = np.bincount(src, minlength=n)
+    assert deg[deg > 64].sum() > 1 << 24 and deg.max() > 8192 and deg.min() <= 32
+    return {"n": n, "xadj": np.concatenate([[0], np.cumsum(deg)]).astype(np.int64), "adjncy": dst[order].astype(np.int32),
+            "adjwgt": wt[order], "vwgt": rng.integers(1, 4, size=n).astype(np.int32)}
+
+
+@pytest.mark.parametrize("k,knobs", [(2, dict()), (32, dict(skip_quiet=1)), (33, dict(graph_capture=1)), (64, dict()),
+                                     (65, dict(fused_eval=-1)), (128, dict()), (129, dict(subrounds=1)), (256, dict())])
+def test_kept_sums(sc, graph, k, knobs):
+    rng = np.random.default_rng(k)
+    part = np.minimum(rng.integers(0, k, size=graph["n"]), rng.integers(0, k, size=graph["n"])).astype(np.int32)
+    bw = np.bincount(part, weights=graph["vwgt"], minlength=k)
+    lmax = int(bw.mean() * 1.2) + 1  # the first blocks are overloaded: several rounds of moves
+    p, rr = sc.refine_dev(sc.to_device(graph), k, lmax, torch.from_numpy(part.copy()).cuda(), rounds=3, seed=k, **knobs)
+    ref, rr_ref, _ = oracle.refine(graph, k, lmax, part, rounds=3, seed=k, nsub=knobs.get("subrounds", 4))
+    assert rr == rr_ref and np.array_equal(p.cpu().numpy(), ref)
