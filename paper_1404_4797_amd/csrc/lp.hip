@@ -227,23 +227,6 @@ __device__ __forceinline__ void best_consider(Best& b, int32_t x, int32_t conn, 
 
 __device__ __forceinline__ uint64_t best_tie(const Best& b, const Ctx& kx) { return b.tv ? b.tie : tie_of(kx, b.x); }
 
-// Wave-wide argmax; every lane gets the winning (x, conn) or x = -1.
-__device__ __forceinline__ void wave_argmax(const Best& b, const Ctx& kx, int32_t& out_x, int32_t& out_conn) {
-    const int32_t bc = b.x >= 0 ? b.conn : -1;
-    const int32_t maxc = wave_max(bc);
-    if (maxc < 0) {
-        out_x = -1;
-        out_conn = -1;
-        return;
-    }
-    const bool top = b.x >= 0 && bc == maxc;
-    const uint64_t tk = top ? best_tie(b, kx) : ~0ULL;
-    const uint64_t mt = wave_min_u64(tk);
-    const int32_t xx = (top && tk == mt) ? b.x : INT_MAX;
-    out_x = wave_min(xx);
-    out_conn = maxc;
-}
-
 // Reductions over aligned groups of G lanes of a wave (G a power of two <= 64).
 template <int G>
 __device__ __forceinline__ int32_t group_max(int32_t v) {
@@ -285,20 +268,22 @@ __device__ __forceinline__ bool group_any(bool b) {
     return ((m >> base) & ((1ULL << G) - 1)) != 0;
 }
 
-// Group-wide argmax; every lane of the group gets the winning (x, conn).
+// Group-wide argmax; every lane of the group gets the winning (x, conn) and
+// its tie key.  Most nodes have no eligible label of positive gain after the
+// first rounds, which one vote of the lanes tells.
 template <int G>
-__device__ __forceinline__ void group_argmax(const Best& b, const Ctx& kx, int32_t& out_x, int32_t& out_conn) {
+__device__ __forceinline__ void group_argmax(const Best& b, const Ctx& kx, int32_t& out_x, int32_t& out_conn,
+                                             uint64_t& out_tie) {
+    out_x = -1;
+    out_conn = -1;
+    out_tie = ~0ULL;
+    if (!group_any<G>(b.x >= 0)) return;
     const int32_t bc = b.x >= 0 ? b.conn : -1;
     const int32_t maxc = group_max<G>(bc);
-    if (maxc < 0) {
-        out_x = -1;
-        out_conn = -1;
-        return;
-    }
     const bool top = b.x >= 0 && bc == maxc;
     const uint64_t tk = top ? best_tie(b, kx) : ~0ULL;
-    const uint64_t mt = group_min_u64<G>(tk);
-    const int32_t xx = (top && tk == mt) ? b.x : INT_MAX;
+    out_tie = group_min_u64<G>(tk);
+    const int32_t xx = (top && tk == out_tie) ? b.x : INT_MAX;
     out_x = group_min<G>(xx);
     out_conn = maxc;
 }
@@ -374,13 +359,14 @@ __device__ __forceinline__ uint32_t table_size_for(int32_t d, uint32_t lo, uint3
 
 // Linear-probing insert of (x, wt) into a table of 2^k entries (key -1 =
 // empty), in LDS or HBM.  The table always has a free entry for a new key.
-__device__ __forceinline__ void table_add(int32_t* keys, int32_t* vals, uint32_t mask, int32_t x, int32_t wt) {
+// Returns the entry if x is new to the table, else -1.
+__device__ __forceinline__ int32_t table_add(int32_t* keys, int32_t* vals, uint32_t mask, int32_t x, int32_t wt) {
     uint32_t h = slot_hash(static_cast<uint32_t>(x)) & mask;
     while (true) {
         const int32_t prev = atomicCAS(&keys[h], -1, x);
         if (prev == -1 || prev == x) {
             atomicAdd(&vals[h], wt);
-            return;
+            return prev == -1 ? static_cast<int32_t>(h) : -1;
         }
         h = (h + 1) & mask;
     }
@@ -388,13 +374,13 @@ __device__ __forceinline__ void table_add(int32_t* keys, int32_t* vals, uint32_t
 
 // The same for a table of any size tsz: the first probe is the hash scaled
 // to [0, tsz), and probing wraps at tsz.
-__device__ __forceinline__ void table_add_sized(int32_t* keys, int32_t* vals, uint32_t tsz, int32_t x, int32_t wt) {
+__device__ __forceinline__ int32_t table_add_sized(int32_t* keys, int32_t* vals, uint32_t tsz, int32_t x, int32_t wt) {
     uint32_t h = static_cast<uint32_t>((static_cast<uint64_t>(slot_hash(static_cast<uint32_t>(x))) * tsz) >> 32);
     while (true) {
         const int32_t prev = atomicCAS(&keys[h], -1, x);
         if (prev == -1 || prev == x) {
             atomicAdd(&vals[h], wt);
-            return;
+            return prev == -1 ? static_cast<int32_t>(h) : -1;
         }
         h = h + 1 == tsz ? 0u : h + 1;
     }
@@ -433,31 +419,69 @@ __device__ __forceinline__ void scan_table(const EvalArgs& A, const Ctx& kx, con
     }
 }
 
-// Adds the slots [b, b+d) of a row to a table of tsz entries; each thread
-// keeps U gathers in flight before inserting.  kPow2: tsz is a power of two
-// (masked probes), else any size (table_add_sized).
+// Empties a table of tsz entries (a multiple of 4) with 16-byte stores.
+template <int NT>
+__device__ __forceinline__ void table_clear(int32_t* keys, int32_t* vals, uint32_t tsz, int tid) {
+    for (uint32_t j = 4 * tid; j < tsz; j += 4 * NT) {
+        *reinterpret_cast<int4*>(keys + j) = make_int4(-1, -1, -1, -1);
+        *reinterpret_cast<int4*>(vals + j) = make_int4(0, 0, 0, 0);
+    }
+}
+
+// A thread's slots of a row of up to NT * U: the neighbours' labels, and for
+// each the table entry if this slot brought the label into the table (else
+// -1).  A table's distinct labels are then found through these entries: reading
+// a table of two to four entries per slot from end to end took more
+// instructions than filling it (with the vote in group_argmax: clustering of a
+// weighted power-law graph, 2^22 nodes, 10 rounds, 20.8 -> 19.9 ms; partition
+// of 2^24 nodes 228.4 -> 223.0 ms).
+template <int U>
+struct RowSlots {
+    int32_t x[U];
+    int32_t at[U];
+};
+
+// Adds the slots [b, b+d) of a row, d <= NT * U, to an empty table of tsz
+// entries; all of the thread's gathers are in flight before it inserts.  kPow2:
+// tsz is a power of two (masked probes), else any size (table_add_sized).
 template <int NT, int U, bool kPow2 = true>
 __device__ __forceinline__ void insert_slots(const EvalArgs& A, int64_t b, int32_t d, int32_t* keys, int32_t* vals,
-                                             uint32_t tsz, int tid) {
-    for (int32_t j0 = tid; j0 < d; j0 += NT * U) {
-        int32_t x[U], wt[U];
+                                             uint32_t tsz, int tid, RowSlots<U>& R) {
+    int32_t wt[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t j = j0 + u * NT;
-            x[u] = j < d ? A.adj[b + j] : 0;
-            wt[u] = j < d ? (A.ew ? A.ew[b + j] : 1) : 0;
-        }
+    for (int u = 0; u < U; ++u) {
+        const int32_t j = tid + u * NT;
+        R.x[u] = j < d ? A.adj[b + j] : 0;
+        wt[u] = j < d ? (A.ew ? A.ew[b + j] : 1) : 0;
+    }
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t j = j0 + u * NT;
-            x[u] = j < d ? nbr_label(A, x[u]) : -1;
-        }
+    for (int u = 0; u < U; ++u) R.x[u] = tid + u * NT < d ? nbr_label(A, R.x[u]) : -1;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (x[u] < 0) continue;
-            if (kPow2) table_add(keys, vals, tsz - 1, x[u], wt[u]);
-            else table_add_sized(keys, vals, tsz, x[u], wt[u]);
+    for (int u = 0; u < U; ++u) {
+        R.at[u] = -1;
+        if (R.x[u] < 0) continue;
+        R.at[u] = kPow2 ? table_add(keys, vals, tsz - 1, R.x[u], wt[u])
+                        : table_add_sized(keys, vals, tsz, R.x[u], wt[u]);
+    }
+}
+
+// Looks at the labels that the thread's slots brought into the table for the
+// best eligible one other than a.
+template <int U>
+__device__ __forceinline__ void consider_slots(const EvalArgs& A, const Ctx& kx, const RowSlots<U>& R,
+                                               const int32_t* vals, int32_t a, int32_t c, int32_t own, bool over,
+                                               Best& best, bool& blocked) {
+    constexpr int V = U < 4 ? U : 4;
+#pragma unroll
+    for (int u0 = 0; u0 < U; u0 += V) {
+        int32_t x[V], cn[V];
+#pragma unroll
+        for (int u = 0; u < V; ++u) {
+            const int32_t at = R.at[u0 + u];
+            x[u] = at >= 0 && R.x[u0 + u] != a ? R.x[u0 + u] : -1;
+            cn[u] = x[u] >= 0 ? vals[at] : 0;
         }
+        consider_group<V>(A, kx, x, cn, c, own, over, best, blocked);
     }
 }
 
@@ -580,7 +604,7 @@ __global__ void __launch_bounds__(256) eval_lane_kernel(EvalArgs A) {
 // G lanes per node (G = 16, 32 or 64: 256 / G nodes per workgroup), each
 // group with an open-addressing table of T entries in LDS.
 // LDS: 2 * (256 / G) * T int32 (the groups' key tables, then their sums).
-template <int G, int T>
+template <int G, int T>  // rows of up to T / 2 slots
 __device__ __forceinline__ void eval_group_body(const EvalArgs& A, int32_t bid, int32_t* lds) {
     constexpr int NG = 256 / G;
     const int grp = threadIdx.x / G;
@@ -602,20 +626,19 @@ __device__ __forceinline__ void eval_group_body(const EvalArgs& A, int32_t bid, 
     const int32_t c = A.vw ? A.vw[v] : 1;
     const bool over = A.refine && A.w[a] > kx.bound;
     const uint32_t tsz = table_size_for(row.deg, T < 64 ? T : 64, T);
-    for (uint32_t j = gl; j < tsz; j += G) {
-        keys[j] = -1;
-        vals[j] = 0;
-    }
+    table_clear<G>(keys, vals, tsz, gl);
     wave_sync();
-    insert_slots<G, 4>(A, row.begin, row.deg, keys, vals, tsz, gl);
+    RowSlots<T / 2 / G> slots;
+    insert_slots<G, T / 2 / G>(A, row.begin, row.deg, keys, vals, tsz, gl, slots);
     wave_sync();
     const int32_t own = table_find<true>(keys, vals, tsz, a);
     Best best;
     best_init(best);
     bool blocked = false;  // some other neighbouring label is connected more strongly
-    scan_table<G, 4>(A, kx, keys, vals, tsz, gl, a, c, own, over, best, blocked);
+    consider_slots(A, kx, slots, vals, a, c, own, over, best, blocked);
     int32_t bx, bconn;
-    group_argmax<G>(best, kx, bx, bconn);
+    uint64_t btie;
+    group_argmax<G>(best, kx, bx, bconn, btie);
     const bool any_blocked = group_any<G>(blocked);
     if (gl == 0) {
         store_result(A, node_i, bx, bconn, own, over, c);
@@ -625,7 +648,7 @@ __device__ __forceinline__ void eval_group_body(const EvalArgs& A, int32_t bid, 
 
 template <int G, int T>
 __global__ void __launch_bounds__(256) eval_group_kernel(EvalArgs A) {
-    __shared__ int32_t lds[2 * (256 / G) * T];
+    __shared__ __align__(16) int32_t lds[2 * (256 / G) * T];
     eval_group_body<G, T>(A, blockIdx.x, lds);
 }
 
@@ -640,8 +663,9 @@ struct BlockScratch {
     int32_t x[NT / 64];
 };
 
-// LDS: BlockScratch<NT> then 2 * TABLE int32 (keys, then sums).
-template <int NT, int TABLE>
+// Rows of up to NT * U slots.  LDS: BlockScratch<NT> then 2 * TABLE int32
+// (keys, then sums).
+template <int NT, int TABLE, int U>
 __device__ __forceinline__ void eval_block_body(const EvalArgs& A, int32_t bid, unsigned char* lds) {
     BlockScratch<NT>& S = *reinterpret_cast<BlockScratch<NT>*>(lds);
     int32_t* keys = reinterpret_cast<int32_t*>(lds + sizeof(BlockScratch<NT>));
@@ -667,24 +691,23 @@ __device__ __forceinline__ void eval_block_body(const EvalArgs& A, int32_t bid, 
     const bool over = A.refine && A.w[a] > kx.bound;
     constexpr bool kPow2 = (TABLE & (TABLE - 1)) == 0;
     const uint32_t tsz = kPow2 ? table_size_for(d, 512, TABLE) : static_cast<uint32_t>(TABLE);
-    for (uint32_t j = tid; j < tsz; j += NT) {
-        keys[j] = -1;
-        vals[j] = 0;
-    }
+    table_clear<NT>(keys, vals, tsz, tid);
     __syncthreads();
-    insert_slots<NT, 4, kPow2>(A, row.begin, d, keys, vals, tsz, tid);
+    RowSlots<U> slots;
+    insert_slots<NT, U, kPow2>(A, row.begin, d, keys, vals, tsz, tid, slots);
     __syncthreads();
     const int32_t own = table_find<kPow2>(keys, vals, tsz, a);
     Best best;
     best_init(best);
     bool blocked = false;
-    scan_table<NT, 4>(A, kx, keys, vals, tsz, tid, a, c, own, over, best, blocked);
+    consider_slots(A, kx, slots, vals, a, c, own, over, best, blocked);
     int32_t bx, bconn;
-    wave_argmax(best, kx, bx, bconn);
+    uint64_t btie;
+    group_argmax<64>(best, kx, bx, bconn, btie);
     if (lane == 0) {
         s_conn[wid] = bconn;
         s_x[wid] = bx;
-        s_tie[wid] = bx >= 0 ? tie_of(kx, bx) : ~0ULL;
+        s_tie[wid] = btie;
     }
     const int any_blocked = __syncthreads_or(blocked);
     if (tid == 0) {
@@ -696,10 +719,10 @@ __device__ __forceinline__ void eval_block_body(const EvalArgs& A, int32_t bid, 
     }
 }
 
-template <int NT, int TABLE>
+template <int NT, int TABLE, int U>
 __global__ void __launch_bounds__(NT) eval_block_kernel(EvalArgs A) {
     __shared__ __align__(16) unsigned char lds[sizeof(BlockScratch<NT>) + 2 * TABLE * sizeof(int32_t)];
-    eval_block_body<NT, TABLE>(A, blockIdx.x, lds);
+    eval_block_body<NT, TABLE, U>(A, blockIdx.x, lds);
 }
 
 // ------------------------------------------------------------- hub bucket
@@ -752,7 +775,7 @@ __device__ __forceinline__ void hub_chunk_body(const EvalArgs& A, const HubArgs&
     int32_t* vals = keys + kHubTable;
     uint32_t* pcount = reinterpret_cast<uint32_t*>(vals + kHubTable);
     int32_t* pbase = vals + kHubTable + (1 << kMaxPartLog);
-    constexpr int kPer = kHubTable / kHubThreads;
+    constexpr int U = kHubChunk / kHubThreads;
     if (stopped(A.gate)) return;  // uniform over the grid
     const int tid = threadIdx.x;
     const int32_t h = H.chunk_hub[bid];
@@ -762,40 +785,37 @@ __device__ __forceinline__ void hub_chunk_body(const EvalArgs& A, const HubArgs&
     const uint32_t tsz = table_size_for(static_cast<int32_t>(end - begin), 1024, kHubTable);
     const int32_t plog = H.hub_plog[h];
     const int32_t P = 1 << plog;
-    for (uint32_t j = tid; j < tsz; j += kHubThreads) {
-        keys[j] = -1;
-        vals[j] = 0;
-    }
+    table_clear<kHubThreads>(keys, vals, tsz, tid);
     for (int32_t j = tid; j < P; j += kHubThreads) pcount[j] = 0;
     __syncthreads();
-    insert_slots<kHubThreads, 4>(A, begin, static_cast<int32_t>(end - begin), keys, vals, tsz, tid);
-    __syncthreads();
-    for (int j = 0; j < kPer; ++j) {
-        const uint32_t e = static_cast<uint32_t>(tid) * kPer + j;
-        if (e < tsz && keys[e] >= 0) atomicAdd(&pcount[part_of(keys[e], plog)], 1u);
-    }
+    RowSlots<U> slots;
+    insert_slots<kHubThreads, U>(A, begin, static_cast<int32_t>(end - begin), keys, vals, tsz, tid, slots);
+    uint32_t rank[U];  // of the label within its partition's list
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+        rank[u] = slots.at[u] >= 0 ? atomicAdd(&pcount[part_of(slots.x[u], plog)], 1u) : 0;
     __syncthreads();
     for (int32_t j = tid; j < P; j += kHubThreads) {
         const uint32_t c = pcount[j];
         pbase[j] = c ? atomicAdd(&H.rcount[H.hub_pbase[h] + j], static_cast<int32_t>(c)) : 0;
-        pcount[j] = 0;
     }
     __syncthreads();
     const int32_t cap = H.hub_cap[h];
     const int64_t rb = H.hub_rbase[h];
-    for (int j = 0; j < kPer; ++j) {
-        const uint32_t e = static_cast<uint32_t>(tid) * kPer + j;
-        if (e >= tsz || keys[e] < 0) continue;
-        const uint32_t p = part_of(keys[e], plog);
-        const int32_t idx = pbase[p] + static_cast<int32_t>(atomicAdd(&pcount[p], 1u));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (slots.at[u] < 0) continue;
+        const int32_t x = slots.x[u], wt = vals[slots.at[u]];
+        const uint32_t p = part_of(x, plog);
+        const int32_t idx = pbase[p] + static_cast<int32_t>(rank[u]);
         if (idx < cap) {
             const int64_t at = rb + static_cast<int64_t>(p) * cap + idx;
-            H.ekeys[at] = keys[e];
-            H.evals[at] = vals[e];
+            H.ekeys[at] = x;
+            H.evals[at] = wt;
         } else {  // region full: the rest of the partition goes to the hub's overflow list
             const int64_t at = H.hub_obase[h] + atomicAdd(&H.ocount[h], 1);
-            H.okeys[at] = keys[e];
-            H.ovals[at] = vals[e];
+            H.okeys[at] = x;
+            H.ovals[at] = wt;
         }
     }
 }
@@ -819,8 +839,8 @@ __device__ __forceinline__ int32_t block_sum_part(int32_t v, int32_t* s_red) {
 // in LDS and writes the partition's best eligible label.  A partition with
 // more than part_limit entries marks its hub for the HBM table path.
 __global__ void __launch_bounds__(kPartThreads) hub_part_kernel(EvalArgs A, HubArgs H) {
-    __shared__ int32_t keys[kPartTable];
-    __shared__ int32_t vals[kPartTable];
+    __shared__ __align__(16) int32_t keys[kPartTable];
+    __shared__ __align__(16) int32_t vals[kPartTable];
     __shared__ int32_t s_red[kPartThreads / 64];
     __shared__ int32_t s_conn[kPartThreads / 64];
     __shared__ int32_t s_x[kPartThreads / 64];
@@ -844,13 +864,22 @@ __global__ void __launch_bounds__(kPartThreads) hub_part_kernel(EvalArgs A, HubA
     }
     const uint32_t tsz = table_size_for(total, 256, kPartTable);
     const uint32_t mask = tsz - 1;
-    for (uint32_t j = tid; j < tsz; j += kPartThreads) {
-        keys[j] = -1;
-        vals[j] = 0;
-    }
+    table_clear<kPartThreads>(keys, vals, tsz, tid);
     __syncthreads();
     const int64_t r0 = H.hub_rbase[h] + static_cast<int64_t>(p) * cap;
-    for (int32_t j = tid; j < in_region; j += kPartThreads) table_add(keys, vals, mask, H.ekeys[r0 + j], H.evals[r0 + j]);
+    constexpr int U = kPartTable / 2 / kPartThreads;
+    RowSlots<U> slots;
+    {
+        int32_t wt[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t j = tid + u * kPartThreads;
+            slots.x[u] = j < in_region ? H.ekeys[r0 + j] : -1;
+            wt[u] = j < in_region ? H.evals[r0 + j] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) slots.at[u] = slots.x[u] >= 0 ? table_add(keys, vals, mask, slots.x[u], wt[u]) : -1;
+    }
     for (int32_t j = tid; j < ov; j += kPartThreads) {
         const int32_t x = H.okeys[ob + j];
         if (part_of(x, plog) == static_cast<uint32_t>(p)) table_add(keys, vals, mask, x, H.ovals[ob + j]);
@@ -866,14 +895,17 @@ __global__ void __launch_bounds__(kPartThreads) hub_part_kernel(EvalArgs A, HubA
     Best best;
     best_init(best);
     bool blocked = false;
-    scan_table<kPartThreads, 4>(A, kx, keys, vals, tsz, tid, a, c, 0, true, best, blocked);
+    // labels that only the overflow list names are found in the table itself
+    if (ov > 0) scan_table<kPartThreads, 4>(A, kx, keys, vals, tsz, tid, a, c, 0, true, best, blocked);
+    else consider_slots(A, kx, slots, vals, a, c, 0, true, best, blocked);
     int32_t bx, bconn;
-    wave_argmax(best, kx, bx, bconn);
+    uint64_t btie;
+    group_argmax<64>(best, kx, bx, bconn, btie);
     const int wid = tid >> 6;
     if (lane_id() == 0) {
         s_conn[wid] = bconn;
         s_x[wid] = bx;
-        s_tie[wid] = bx >= 0 ? tie_of(kx, bx) : ~0ULL;
+        s_tie[wid] = btie;
     }
     __syncthreads();
     if (tid == 0) {
@@ -1079,7 +1111,8 @@ __device__ __forceinline__ void eval_dense_group_body(const EvalArgs& A, int32_t
     bool blocked = false;
     dense_best<G>(A, kx, conn, a, c, own, over, gl, best, blocked);
     int32_t bx, bconn;
-    group_argmax<G>(best, kx, bx, bconn);
+    uint64_t btie;
+    group_argmax<G>(best, kx, bx, bconn, btie);
     const bool any_blocked = group_any<G>(blocked);
     if (gl == 0) {
         store_result(A, node_i, bx, bconn, own, over, c);
@@ -1127,11 +1160,12 @@ __device__ __forceinline__ void eval_dense_block_body(const EvalArgs& A, int32_t
     bool blocked = false;
     dense_best<NT>(A, kx, conn, a, c, own, over, tid, best, blocked);
     int32_t bx, bconn;
-    wave_argmax(best, kx, bx, bconn);
+    uint64_t btie;
+    group_argmax<64>(best, kx, bx, bconn, btie);
     if (lane_id() == 0) {
         s_conn[wid] = bconn;
         s_x[wid] = bx;
-        s_tie[wid] = bx >= 0 ? tie_of(kx, bx) : ~0ULL;
+        s_tie[wid] = btie;
     }
     const int any_blocked = __syncthreads_or(blocked);
     if (tid == 0) {
@@ -1246,7 +1280,8 @@ __global__ void __launch_bounds__(256) eval_kept_kernel(EvalArgs A) {
     bool blocked = false;
     consider_group<U>(A, kx, x, cn, c, own, over, best, blocked);
     int32_t bx, bconn;
-    group_argmax<G>(best, kx, bx, bconn);
+    uint64_t btie;
+    group_argmax<G>(best, kx, bx, bconn, btie);
     const bool any_blocked = group_any<G>(blocked);
     if (gl == 0) {
         store_result(A, i, bx, bconn, own, over, c);
@@ -1319,7 +1354,7 @@ __global__ void __launch_bounds__(256) eval_fused_kernel(EvalArgs A, FusedBucket
             break;
         default:
             if (kDense) eval_dense_block_body<256>(A, bid, lds);
-            else eval_block_body<256, 2 * kBlock1Max>(A, bid, lds);
+            else eval_block_body<256, 2 * kBlock1Max, kBlock1Max / 256>(A, bid, lds);
             break;
     }
 }
@@ -1343,8 +1378,8 @@ __global__ void __launch_bounds__(kHubThreads) eval_big_kernel(EvalArgs A, Fused
     A.count = F.count[b];
     A.ct = F.ct[b];
     A.cg = F.cg[b];
-    if (b == 7) eval_block_body<kHubThreads, kBigTable>(A, bid - F.end[kHubBucket], lds);
-    else eval_block_body<kHubThreads, 2 * kBlock2Max>(A, bid - F.end[7], lds);
+    if (b == 7) eval_block_body<kHubThreads, kBigTable, kBlockMaxDeg / kHubThreads>(A, bid - F.end[kHubBucket], lds);
+    else eval_block_body<kHubThreads, 2 * kBlock2Max, kBlock2Max / kHubThreads>(A, bid - F.end[7], lds);
 }
 
 // ------------------------------------------------- candidates and admission
@@ -3493,14 +3528,14 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 } else if (bk == 4) {
                     eval_group_kernel<64, kWaveTable><<<grid_for(count, 4), 256, 0, bs>>>(A);
                 } else if (bk == 5) {
-                    eval_block_kernel<256, 2 * kBlock1Max><<<nb, 256, 0, bs>>>(A);
+                    eval_block_kernel<256, 2 * kBlock1Max, kBlock1Max / 256><<<nb, 256, 0, bs>>>(A);
                 } else if (bk == 6) {
-                    eval_block_kernel<1024, 2 * kBlock2Max><<<nb, 1024, 0, bs>>>(A);
+                    eval_block_kernel<1024, 2 * kBlock2Max, kBlock2Max / 1024><<<nb, 1024, 0, bs>>>(A);
                 } else {
                     if (tune.block_table == kBlockTablePow2)
-                        eval_block_kernel<1024, kBlockTablePow2><<<nb, 1024, 0, bs>>>(A);
+                        eval_block_kernel<1024, kBlockTablePow2, kBlockMaxDeg / 1024><<<nb, 1024, 0, bs>>>(A);
                     else
-                        eval_block_kernel<1024, kBlockTable><<<nb, 1024, 0, bs>>>(A);
+                        eval_block_kernel<1024, kBlockTable, kBlockMaxDeg / 1024><<<nb, 1024, 0, bs>>>(A);
                 }
                 LAUNCHCHK();
             }
