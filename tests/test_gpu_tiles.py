@@ -1,4 +1,4 @@
-"""Slot-parallel kernels (validation, cut, block weights) at the sizes where a
+"""Slot-parallel kernels (validation, cut, block weights, contraction) at the sizes where a
 tile of 2048 slots, a thread's 8 slots or a workgroup's run of tiles ends, and
 on arrays that do not start on a 16-byte boundary.  Compared with the oracle."""
 import numpy as np
@@ -107,3 +107,32 @@ def test_project_range(sc):
         C[4321] = bad
         with pytest.raises(sc.SclapError):
             sc.project_dev(C, coarse)
+
+
+def fans(lengths):
+    """Node i joined to lengths[i] leaves of its own (one shared by all), rows of exactly those lengths first."""
+    k = len(lengths)
+    src = np.repeat(np.arange(k), lengths)
+    dst = np.concatenate([np.r_[k, k + 1 + sum(lengths[:i]) + np.arange(d - 1)] for i, d in enumerate(lengths) if d])
+    n = int(dst.max()) + 3
+    u, v = np.concatenate([src, dst]), np.concatenate([dst, src])
+    order = np.argsort(u * n + v)
+    w = np.concatenate([1 + src % 7, 1 + src % 7])[order].astype(np.int32)
+    xadj = np.concatenate([[0], np.cumsum(np.bincount(u, minlength=n))]).astype(np.int64)
+    return {"n": n, "xadj": xadj, "adjncy": v[order].astype(np.int32), "adjwgt": w, "vwgt": np.ones(n, dtype=np.int32)}
+
+
+@pytest.mark.parametrize("lengths", [[1], [2047, 1, 2048], [2048, 2048, 1], [0, 2049, 0, 2047], [5000, 3, 1093, 2, 64],
+                                     [6144, 0, 0, 1], [700, 1348, 1, 1, 9000]])
+@pytest.mark.parametrize("unit", [False, True])
+@pytest.mark.parametrize("group", [1, 2, 5])
+def test_contract_tiles(sc, lengths, unit, group):
+    g = fans(lengths)
+    if unit:
+        g = {**g, "adjwgt": None, "vwgt": None}
+    labels = (np.arange(g["n"]) // group * group).astype(np.int32)
+    C, cg = sc.contract_dev(sc.to_device(g), torch.from_numpy(labels).cuda())
+    ref_C, ref = oracle.contract(g, labels)
+    assert np.array_equal(C.cpu().numpy(), ref_C)
+    for key in ("xadj", "adjncy", "adjwgt", "vwgt"):
+        assert np.array_equal(cg[key].cpu().numpy(), ref[key]), key
