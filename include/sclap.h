@@ -83,18 +83,22 @@ typedef struct {
     int32_t cluster_divisor; /* W = floor(c(V) / (cluster_divisor * k)) (default 18) */
     int32_t coarsest_nodes;  /* stop coarsening at <= this many nodes (default 10000) */
     int32_t max_levels;      /* at most this many contractions, 0..64 (default 64) */
-    int32_t validate;        /* 1: check the input graph first (default 1) */
+    int32_t validate;        /* 1: check the input graph first (default 1); a large refinement
+                                is faster on a graph that was checked, see fused_eval */
     /* Replaces the hash colour of every node (values in [0, subrounds)) in
      * sclap_cluster, sclap_refine and their _dev variants only; host or device
      * memory to match the entry point; NULL = hash colours. */
     const int32_t* color_override;
     /* tuning knobs (never change results; 0 = library default) */
-    int32_t lane_max_degree;  /* rows up to this degree: one lane per node */
+    int32_t lane_max_degree;  /* rows up to this degree: one lane per node (default 16, or 4 for
+                                 graphs of at most 2^17 nodes) */
     int32_t wave_max_degree;  /* up to this: one wave64 per node, LDS table */
     int32_t block_max_degree; /* up to this: one workgroup per node, LDS table; above: hub path */
-    int32_t hub_part_limit;   /* hub label partitions summed in LDS up to this many entries */
+    int32_t hub_part_limit;   /* hub label partitions summed in LDS up to this many entries; a hub
+                                 with a longer one is summed in a table in device memory */
     int32_t hub_region_cap;   /* entries a hub partition keeps before spilling to its overflow list */
-    int32_t select_small_max; /* overflowing targets with more candidates: multi-workgroup selection */
+    int32_t select_small_max; /* overflowing targets with more candidates: multi-workgroup selection
+                                 (default 65536 in colours of at most 65536 nodes, else 16384) */
     int32_t skip_quiet;       /* 1: once few nodes move, skip nodes that emitted nothing, had no
                                  neighbouring label stronger than their own and saw no neighbour move
                                  since (their decision is unchanged); -1: evaluate every node;
@@ -131,8 +135,11 @@ typedef struct {
                                      with no host work between rounds; 0 (default) or -1: kernels are
                                      launched one by one, the host one round ahead of the device */
     int32_t fused_eval;           /* tuning (never changes results): 0 (default) or 1: a colour with
-                                     fewer than 2^22 adjacency slots evaluates its buckets of up to
-                                     1 024 slots per node in one launch; -1: one launch per bucket */
+                                     fewer than 2^22 adjacency slots evaluates its rows in one launch
+                                     (refinement of at most 256 blocks) or two (rows of up to and of
+                                     more than 1 024 slots); -1: one launch per bucket.  Either way, a
+                                     refinement of a checked graph with 2^24 slots in long rows keeps
+                                     their block sums (up to 16 bytes per slot) between rounds */
     int32_t block_table;          /* tuning (never changes results): entries of the LDS table of the
                                      workgroup-per-node bucket with the longest rows, 10240 (80 KB,
                                      probed modulo its size; 0 = 10240) or 16384 (128 KB) */

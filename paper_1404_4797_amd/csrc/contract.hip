@@ -8,7 +8,7 @@
 //      a cluster has at most U members, however many slots its rows hold);
 //   2. scan the row counts into row offsets, give every node a block of its
 //      row and scatter (C(v), w) of every such slot into its node's block
-//      (each wave's run of a row reserves its part with one atomic);
+//      (at its rank; a row that spans slot tiles reserves each tile's part);
 //   3. merge equal neighbours of each row, summing weights: rows of up to 64
 //      entries in the registers of one wave (bitonic network over lanes), up
 //      to 4096 in an LDS table of one workgroup, longer rows by chunks and then

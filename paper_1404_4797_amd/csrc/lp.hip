@@ -24,7 +24,9 @@
 //          list in LDS, and the launch that counts the candidates picks the
 //          best partition winner
 // Large colours launch the buckets side by side on three streams; small ones
-// run them in one launch, or two where rows need a table over 16 KB.
+// run them in one launch, or two where rows need a table over 16 KB.  Large
+// refinements count a long row's block sums once and keep them up to date
+// (kept sums) instead of evaluating the row's slots in every round.
 // The per-node connection table maps a neighbour label to the summed weight
 // of the edges to it (Section 4.1 uses hashing with linear probing for this).
 //
