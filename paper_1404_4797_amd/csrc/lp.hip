@@ -72,6 +72,7 @@ constexpr int kSmallLabels = 4096;       // LDS-private histograms up to this ma
 constexpr int kCountInEval = 1 << 14;    // colours up to this size count candidates while they evaluate
 constexpr int kMaxBlocks = 512;          // grid cap of the grid-stride candidate kernels
 constexpr int kSmallSeg = 16384;         // large colours: segments up to this length have one selecting workgroup
+constexpr int kMidColour = 1 << 18;      // up to this size: up to kFinishMax, and one launch for the others
 constexpr int kSegChunk = 16384;         // entries per workgroup in the multi-workgroup selection
 constexpr int kLargeBlocks = 256;        // grid of the multi-workgroup selection kernel
 constexpr int kLargeThreads = 1024;      // and its workgroup size
@@ -2059,7 +2060,10 @@ __device__ __forceinline__ void arrive(const Admission& A, int32_t t, int32_t c,
 constexpr int kFinishThreads = 1024;
 constexpr int kFinishMax = 65536;  // longest segment one workgroup of finish_kernel selects from
 // workgroups for the segments and (at most) for the admitted candidates; in
-// small label spaces every workgroup adds to the same few lines of weights
+// small label spaces every workgroup adds to the same few lines of weights, so
+// fewer move, and with at most kDirectLabels labels (each with one segment at
+// most) fewer select; a batch's blocks are more (64 graphs, 2 000 labels, 32 ->
+// 96 selecting workgroups: 36.9 -> 36.1 ms per batch)
 constexpr int kSegBlocks = 96;
 constexpr int kMoveBlocks = 192;
 constexpr int kSegBlocksSmall = 32;
@@ -2287,7 +2291,10 @@ __global__ void __launch_bounds__(256) init_admission_kernel(unsigned long long*
 }
 
 // After a sub-round: every neighbour of a node that moved is no longer quiet.
-// One wave per 64 schedule positions; the wave walks each mover's row.
+// A workgroup lays the rows of the movers among its 256 schedule entries end to
+// end and takes a slot per thread: a wave that walked one mover's row after the
+// other waited for two dependent reads per mover (64 graphs of a batch: 11.1 -> 8.2 us
+// per launch, hubs among the movers).
 __global__ void __launch_bounds__(256) unquiet_kernel(const int32_t* __restrict__ ct,
                                                       const int32_t* __restrict__ label,
                                                       const int32_t* __restrict__ nodes, int32_t count,
@@ -2295,19 +2302,50 @@ __global__ void __launch_bounds__(256) unquiet_kernel(const int32_t* __restrict_
                                                       const int32_t* __restrict__ adj, uint8_t* __restrict__ quiet,
                                                       const uint32_t* __restrict__ gate,
                                                       const uint32_t* __restrict__ rcnt, int32_t round, int32_t qn) {
-    if (stopped(gate) || quiet_mode(quiet, rcnt, round, qn) == 0) return;
-    const int64_t base = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) & ~63LL;
+    __shared__ int64_t s_pre[256], s_begin[256], s_wave[4];
+    if (stopped(gate) || quiet_mode(quiet, rcnt, round, qn) == 0) return;  // uniform over the grid
+    const int tid = threadIdx.x;
     const int lane = lane_id();
-    const int64_t p = base + lane;
+    const int wid = tid >> 6;
+    const int64_t p = static_cast<int64_t>(blockIdx.x) * 256 + tid;
     // a candidate that holds its target label now (its own differed before)
-    const bool mover = p < count && ct[p] >= 0 && label[nodes[p]] == ct[p];
-    uint64_t m = __ballot(mover);
-    while (m) {
-        const int i = __ffsll(static_cast<long long>(m)) - 1;
-        m &= m - 1;
-        const int32_t u = nodes[base + i];
-        const int64_t e = xadj[u + 1];
-        for (int64_t j = xadj[u] + lane; j < e; j += 64) quiet[adj[j]] = 0;
+    const int32_t t = p < count ? ct[p] : -1;
+    const int32_t v = t >= 0 ? nodes[p] : 0;
+    const bool mover = t >= 0 && label[v] == t;
+    if (!__syncthreads_or(mover)) return;
+    const int64_t b = mover ? xadj[v] : 0;
+    const int64_t d = mover ? xadj[v + 1] - b : 0;
+    int64_t incl = d;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int64_t x = static_cast<int64_t>(shfl_up_u64(static_cast<uint64_t>(incl), o));
+        if (lane >= o) incl += x;
+    }
+    if (lane == 63) s_wave[wid] = incl;
+    __syncthreads();
+    int64_t before = incl - d, total = 0;
+    for (int w = 0; w < 4; ++w) {
+        if (w < wid) before += s_wave[w];
+        total += s_wave[w];
+    }
+    s_pre[tid] = before;
+    s_begin[tid] = b;
+    __syncthreads();
+    constexpr int U = 4;
+    for (int64_t j0 = tid; j0 < total; j0 += 256 * U) {
+        int32_t x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int64_t at = j0 + u * 256;
+            int lo = 0;  // the last entry whose slots begin at or before this one
+#pragma unroll
+            for (int step = 128; step > 0; step >>= 1)
+                if (s_pre[lo + step] <= at) lo += step;
+            x[u] = at < total ? adj[s_begin[lo] + (at - s_pre[lo])] : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (x[u] >= 0) quiet[x[u]] = 0;
     }
 }
 
@@ -3133,9 +3171,13 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     // default a colour of up to kFinishMax nodes leaves every segment to one
     // workgroup and launches no further kernel (three to four launches of
     // 2 us each, against 20-80 us in the first sub-rounds, whose segments
-    // alone are that long); larger colours split segments over kSmallSeg.
+    // alone are that long).  Up to kMidColour nodes longer segments are so rare
+    // that one selection launch does, the rest of whose digits one workgroup
+    // finishes (partition of 2^20 nodes, 16 blocks, 27.97 -> 27.57 ms); with
+    // larger colours split segments over kSmallSeg in a launch per digit
+    // (refinement of 2^21 nodes, colours of 2^19: 7.65 ms, 8.45 the other way).
     const int32_t small_max = tune.select_small_max > 0 ? std::min(tune.select_small_max, kFinishMax)
-                              : cap <= kFinishMax       ? kFinishMax
+                              : cap <= kMidColour       ? kFinishMax
                                                         : kSmallSeg;
     const bool use_large = cap > small_max;
     const int64_t max_large = use_large ? cap / small_max + 1 : 0;
@@ -3153,6 +3195,8 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     const int sel_launches =
         tune.select_launches > 0
             ? std::min(tune.select_launches, max_launches)
+        : tune.select_small_max <= 0 && cap <= kMidColour
+            ? 1
             : std::min(max_launches, (bits_for(static_cast<uint64_t>(n - 1)) + 12 + kLDigit - 1) / kLDigit);
     DBuf<uint32_t> rcnt(std::max(rounds, 1), s);  // candidates per round, read back one round late (see stopped())
     DBuf<uint8_t> lab8;
@@ -3591,7 +3635,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             }
             {
                 ProfScope ps("lp_apply", 0, s);
-                const unsigned gseg = small ? kSegBlocksSmall : kSegBlocks;
+                const unsigned gseg = small && direct ? kSegBlocksSmall : kSegBlocks;
                 const unsigned gmov = static_cast<unsigned>(std::min<int64_t>(
                     grid_for(ccount, kFinishThreads), small ? kMoveBlocksSmall : kMoveBlocks));
                 if (small) finish_kernel<true><<<gseg + gmov, kFinishThreads, 0, s>>>(M, gseg);
