@@ -94,8 +94,8 @@ typedef struct {
                                  graphs of at most 2^17 nodes) */
     int32_t wave_max_degree;  /* up to this: one wave64 per node, LDS table */
     int32_t block_max_degree; /* up to this: one workgroup per node, LDS table; above: hub path */
-    int32_t hub_part_limit;   /* hub label partitions summed in LDS up to this many entries; a hub
-                                 with a longer one is summed in a table in device memory */
+    int32_t hub_part_limit;   /* hub label partitions summed in LDS up to this many entries (at most
+                                 2048); longer ones are summed in a table in device memory */
     int32_t hub_region_cap;   /* entries a hub partition keeps before spilling to its overflow list */
     int32_t select_small_max; /* overflowing targets with more candidates: multi-workgroup selection
                                  (default 65536 in colours of at most 2^18 nodes, else 16384) */

@@ -375,10 +375,11 @@ __device__ __forceinline__ int32_t table_add(int32_t* keys, int32_t* vals, uint3
     }
 }
 
-// The same for a table of any size tsz: the first probe is the hash scaled
+// The same for a table of any size tsz: the first probe is a hash of x scaled
 // to [0, tsz), and probing wraps at tsz.
-__device__ __forceinline__ int32_t table_add_sized(int32_t* keys, int32_t* vals, uint32_t tsz, int32_t x, int32_t wt) {
-    uint32_t h = static_cast<uint32_t>((static_cast<uint64_t>(slot_hash(static_cast<uint32_t>(x))) * tsz) >> 32);
+__device__ __forceinline__ int32_t table_add_scaled(int32_t* keys, int32_t* vals, uint32_t tsz, uint32_t hash,
+                                                    int32_t x, int32_t wt) {
+    uint32_t h = static_cast<uint32_t>((static_cast<uint64_t>(hash) * tsz) >> 32);
     while (true) {
         const int32_t prev = atomicCAS(&keys[h], -1, x);
         if (prev == -1 || prev == x) {
@@ -387,6 +388,10 @@ __device__ __forceinline__ int32_t table_add_sized(int32_t* keys, int32_t* vals,
         }
         h = h + 1 == tsz ? 0u : h + 1;
     }
+}
+
+__device__ __forceinline__ int32_t table_add_sized(int32_t* keys, int32_t* vals, uint32_t tsz, int32_t x, int32_t wt) {
+    return table_add_scaled(keys, vals, tsz, slot_hash(static_cast<uint32_t>(x)), x, wt);
 }
 
 // Value of key x in such a table (0: absent; the table has a free entry or
@@ -738,12 +743,11 @@ struct HubArgs {
     const int32_t* part_hub;     // [nparts]
     const int64_t* hub_rbase;    // [H] first region entry of the hub
     const int64_t* hub_obase;    // [H] first overflow entry of the hub
-    const int64_t* hub_toff;     // [H] HBM table offset
+    const int64_t* hub_toff;     // [H] first entry of the hub's HBM table (two per slot)
     const int64_t* chunk_begin;  // [nchunks] first slot of the chunk
-    const uint32_t* hub_tmask;   // [H] HBM table size - 1
     int32_t* rcount;   // [nparts] entries reserved per partition    } zero before
     int32_t* ocount;   // [H] overflow entries                      } and after
-    int32_t* big;      // [H] hub needs the HBM table               } every
+    uint32_t* tfill;   // [H] entries of the HBM table given out    } every
     int32_t* hub_own;  // [H] connection to the own label           } sub-round
     int32_t* ekeys;    // partition regions (label, summed weight)
     int32_t* evals;
@@ -754,7 +758,7 @@ struct HubArgs {
     int32_t* w_conn;   // winners per partition
     uint64_t* w_tie;
     int32_t* w_x;
-    int32_t part_limit;  // partitions with more entries take the HBM table path
+    int32_t part_limit;  // partitions with more entries are summed in HBM
     int32_t count;       // hubs of the colour (0: none); their entries are the colour's last
     int32_t* hub_sum;    // dense refinement: a row of dense_k sums per hub, else null
 };
@@ -838,9 +842,66 @@ __device__ __forceinline__ int32_t block_sum_part(int32_t v, int32_t* s_red) {
     return t;
 }
 
+// Orders a workgroup's accesses to a table in device memory that no other
+// workgroup touches: its waves share one L1 and one L2, so it is enough that
+// every wave's stores and atomics have reached the L2.  A device-scope fence
+// also writes back and invalidates the L2 (hub of 2^22 slots, 2048 partitions:
+// 123 us per launch with two fences per wave, 85 us like this).
+__device__ __forceinline__ void table_sync() {
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+}
+
+// Best eligible label of a hub partition of more than part_limit entries.
+// Partitions share no label, so the partition's workgroup sums it alone, in its
+// own stretch of the hub's table in HBM (twice its entries; all partitions
+// together have at most as many entries as the hub has slots).  One workgroup
+// that summed every partition of such a hub in turn took 54 ms for a hub of
+// 2^22 slots with distinct labels; side by side the partitions take 85 us.
+__device__ void hub_part_in_hbm(const EvalArgs& A, const HubArgs& H, const Ctx& kx, int32_t h, int32_t p,
+                                int64_t r0, int32_t in_region, int32_t ov, int32_t total, int32_t a, int32_t c,
+                                Best& best) {
+    __shared__ uint32_t s_first;
+    const int tid = threadIdx.x;
+    const uint32_t tsz = 2u * static_cast<uint32_t>(total);
+    if (tid == 0) s_first = atomicAdd(&H.tfill[h], tsz);
+    __syncthreads();
+    int32_t* gk = H.gkeys + H.hub_toff[h] + s_first;
+    int32_t* gv = H.gvals + H.hub_toff[h] + s_first;
+    for (int64_t j = tid; j < tsz; j += kPartThreads) {
+        __hip_atomic_store(&gk[j], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(&gv[j], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    table_sync();
+    // the partition's labels share the top plog bits of their hash
+    const int32_t plog = H.hub_plog[h];
+    auto add = [&](int32_t x, int32_t wt) {
+        table_add_scaled(gk, gv, tsz, slot_hash(static_cast<uint32_t>(x)) << plog, x, wt);
+    };
+    for (int32_t j = tid; j < in_region; j += kPartThreads) add(H.ekeys[r0 + j], H.evals[r0 + j]);
+    const int64_t ob = H.hub_obase[h];
+    for (int32_t j = tid; j < ov; j += kPartThreads) {
+        const int32_t x = H.okeys[ob + j];
+        if (part_of(x, plog) == static_cast<uint32_t>(p)) add(x, H.ovals[ob + j]);
+    }
+    table_sync();
+    for (int64_t j = tid; j < tsz; j += kPartThreads) {
+        const int32_t x = __hip_atomic_load(&gk[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (x < 0) continue;
+        const int32_t conn = __hip_atomic_load(&gv[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (x == a) {
+            H.hub_own[h] = conn;
+            continue;
+        }
+        if (best.x >= 0 && conn < best.conn) continue;
+        if (!eligible(A, x, c, kx)) continue;
+        best_consider(best, x, conn, kx);
+    }
+}
+
 // One workgroup per label partition of a hub: sums the partition's entries
-// in LDS and writes the partition's best eligible label.  A partition with
-// more than part_limit entries marks its hub for the HBM table path.
+// in LDS (more than part_limit of them: in HBM) and writes the partition's best
+// eligible label.
 __global__ void __launch_bounds__(kPartThreads) hub_part_kernel(EvalArgs A, HubArgs H) {
     __shared__ __align__(16) int32_t keys[kPartTable];
     __shared__ __align__(16) int32_t vals[kPartTable];
@@ -861,46 +922,48 @@ __global__ void __launch_bounds__(kPartThreads) hub_part_kernel(EvalArgs A, HubA
     int32_t mine = 0;
     for (int32_t j = tid; j < ov; j += kPartThreads) mine += part_of(H.okeys[ob + j], plog) == static_cast<uint32_t>(p);
     const int32_t total = in_region + (ov > 0 ? block_sum_part(mine, s_red) : 0);
-    if (total > H.part_limit) {
-        if (tid == 0) H.big[h] = 1;
-        return;
-    }
-    const uint32_t tsz = table_size_for(total, 256, kPartTable);
-    const uint32_t mask = tsz - 1;
-    table_clear<kPartThreads>(keys, vals, tsz, tid);
-    __syncthreads();
     const int64_t r0 = H.hub_rbase[h] + static_cast<int64_t>(p) * cap;
-    constexpr int U = kPartTable / 2 / kPartThreads;
-    RowSlots<U> slots;
-    {
-        int32_t wt[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t j = tid + u * kPartThreads;
-            slots.x[u] = j < in_region ? H.ekeys[r0 + j] : -1;
-            wt[u] = j < in_region ? H.evals[r0 + j] : 0;
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) slots.at[u] = slots.x[u] >= 0 ? table_add(keys, vals, mask, slots.x[u], wt[u]) : -1;
-    }
-    for (int32_t j = tid; j < ov; j += kPartThreads) {
-        const int32_t x = H.okeys[ob + j];
-        if (part_of(x, plog) == static_cast<uint32_t>(p)) table_add(keys, vals, mask, x, H.ovals[ob + j]);
-    }
-    __syncthreads();
     const int32_t v = A.rows[h].node;
     const Ctx kx = ctx_of(A, v);
     const int32_t a = A.label[v];
     const int32_t c = A.vw ? A.vw[v] : 1;
     // only the partition of a holds a; the others' best labels are compared
     // with its connection by hub_decide
-    if (tid == 0 && part_of(a, plog) == static_cast<uint32_t>(p)) H.hub_own[h] = table_find<true>(keys, vals, tsz, a);
     Best best;
     best_init(best);
-    bool blocked = false;
-    // labels that only the overflow list names are found in the table itself
-    if (ov > 0) scan_table<kPartThreads, 4>(A, kx, keys, vals, tsz, tid, a, c, 0, true, best, blocked);
-    else consider_slots(A, kx, slots, vals, a, c, 0, true, best, blocked);
+    if (total > H.part_limit) {  // uniform over the workgroup
+        hub_part_in_hbm(A, H, kx, h, p, r0, in_region, ov, total, a, c, best);
+    } else {
+        const uint32_t tsz = table_size_for(total, 256, kPartTable);
+        const uint32_t mask = tsz - 1;
+        table_clear<kPartThreads>(keys, vals, tsz, tid);
+        __syncthreads();
+        constexpr int U = kPartTable / 2 / kPartThreads;
+        RowSlots<U> slots;
+        {
+            int32_t wt[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int32_t j = tid + u * kPartThreads;
+                slots.x[u] = j < in_region ? H.ekeys[r0 + j] : -1;
+                wt[u] = j < in_region ? H.evals[r0 + j] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                slots.at[u] = slots.x[u] >= 0 ? table_add(keys, vals, mask, slots.x[u], wt[u]) : -1;
+        }
+        for (int32_t j = tid; j < ov; j += kPartThreads) {
+            const int32_t x = H.okeys[ob + j];
+            if (part_of(x, plog) == static_cast<uint32_t>(p)) table_add(keys, vals, mask, x, H.ovals[ob + j]);
+        }
+        __syncthreads();
+        if (tid == 0 && part_of(a, plog) == static_cast<uint32_t>(p))
+            H.hub_own[h] = table_find<true>(keys, vals, tsz, a);
+        bool blocked = false;
+        // labels that only the overflow list names are found in the table itself
+        if (ov > 0) scan_table<kPartThreads, 4>(A, kx, keys, vals, tsz, tid, a, c, 0, true, best, blocked);
+        else consider_slots(A, kx, slots, vals, a, c, 0, true, best, blocked);
+    }
     int32_t bx, bconn;
     uint64_t btie;
     group_argmax<64>(best, kx, bx, bconn, btie);
@@ -945,10 +1008,7 @@ __device__ __forceinline__ void block_combine(int32_t& fc, uint64_t& ft, int32_t
 }
 
 // Decision of hub h by one workgroup of 256, from the winners of its
-// partitions; afterwards the hub's counters are zero again.  A hub with a
-// partition too long for its LDS table is summed by this workgroup alone in an
-// exact table in HBM (each partition holds about 1024 entries by its hash, so
-// this is an exception that hardly occurs).
+// partitions; afterwards the hub's counters are zero again.
 __device__ void hub_decide(const EvalArgs& A, const HubArgs& H, int32_t h) {
     const int tid = threadIdx.x;
     const int32_t v = A.rows[h].node;
@@ -957,68 +1017,20 @@ __device__ void hub_decide(const EvalArgs& A, const HubArgs& H, int32_t h) {
     const int32_t p0 = H.hub_pbase[h], p1 = H.hub_pbase[h + 1];
     int32_t fc = -1, fx = -1;
     uint64_t ft = ~0ULL;
-    int32_t own = H.hub_own[h];
-    if (!H.big[h]) {
-        constexpr int U = 4;
-        for (int32_t j = p0 + tid; j < p1; j += 256 * U) {
-            int32_t cn[U], x[U];
-            uint64_t ti[U];
+    const int32_t own = H.hub_own[h];
+    constexpr int U = 4;
+    for (int32_t j = p0 + tid; j < p1; j += 256 * U) {
+        int32_t cn[U], x[U];
+        uint64_t ti[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const bool in = j + u * 256 < p1;
-                cn[u] = in ? H.w_conn[j + u * 256] : -1;
-                x[u] = in ? H.w_x[j + u * 256] : -1;
-                ti[u] = in ? H.w_tie[j + u * 256] : ~0ULL;
-            }
+        for (int u = 0; u < U; ++u) {
+            const bool in = j + u * 256 < p1;
+            cn[u] = in ? H.w_conn[j + u * 256] : -1;
+            x[u] = in ? H.w_x[j + u * 256] : -1;
+            ti[u] = in ? H.w_tie[j + u * 256] : ~0ULL;
+        }
 #pragma unroll
-            for (int u = 0; u < U; ++u) combine_into(fc, ft, fx, cn[u], ti[u], x[u]);
-        }
-    } else {
-        int32_t* gk = H.gkeys + H.hub_toff[h];
-        int32_t* gv = H.gvals + H.hub_toff[h];
-        const uint32_t gmask = H.hub_tmask[h];
-        for (int64_t j = tid; j <= static_cast<int64_t>(gmask); j += 256) {
-            __hip_atomic_store(&gk[j], -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&gv[j], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        __threadfence();
-        __syncthreads();
-        const int32_t cap = H.hub_cap[h];
-        for (int32_t gp = p0; gp < p1; ++gp) {
-            const int32_t in_region = H.rcount[gp] < cap ? H.rcount[gp] : cap;
-            const int64_t r0 = H.hub_rbase[h] + static_cast<int64_t>(gp - p0) * cap;
-            for (int32_t j = tid; j < in_region; j += 256) table_add(gk, gv, gmask, H.ekeys[r0 + j], H.evals[r0 + j]);
-        }
-        const int64_t ob = H.hub_obase[h];
-        const int32_t ov = H.ocount[h];
-        for (int32_t j = tid; j < ov; j += 256) table_add(gk, gv, gmask, H.okeys[ob + j], H.ovals[ob + j]);
-        __threadfence();
-        __syncthreads();
-        const int32_t c = A.vw ? A.vw[v] : 1;
-        __shared__ int32_t s_own;
-        if (tid == 0) s_own = 0;
-        __syncthreads();
-        Best best;
-        best_init(best);
-        for (int64_t j = tid; j <= static_cast<int64_t>(gmask); j += 256) {
-            const int32_t x = __hip_atomic_load(&gk[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (x < 0) continue;
-            const int32_t conn = __hip_atomic_load(&gv[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (x == a) {
-                s_own = conn;
-                continue;
-            }
-            if (best.x >= 0 && conn < best.conn) continue;
-            if (!eligible(A, x, c, kx)) continue;
-            best_consider(best, x, conn, kx);
-        }
-        __syncthreads();
-        own = s_own;
-        if (best.x >= 0) {
-            fc = best.conn;
-            fx = best.x;
-            ft = best_tie(best, kx);
-        }
+        for (int u = 0; u < U; ++u) combine_into(fc, ft, fx, cn[u], ti[u], x[u]);
     }
     block_combine(fc, ft, fx);
     if (tid == 0) store_result(A, h, fx, fc, own, A.refine && A.w[a] > kx.bound, A.vw ? A.vw[v] : 1);
@@ -1026,7 +1038,7 @@ __device__ void hub_decide(const EvalArgs& A, const HubArgs& H, int32_t h) {
     for (int32_t j = p0 + tid; j < p1; j += 256) H.rcount[j] = 0;
     if (tid == 0) {
         H.ocount[h] = 0;
-        H.big[h] = 0;
+        H.tfill[h] = 0;
         H.hub_own[h] = 0;
     }
 }
@@ -2813,7 +2825,7 @@ struct HubPlan {
     int32_t count = 0;
     int32_t nchunks = 0;
     int32_t nparts = 0;
-    int64_t at[10] = {};  // first 8-byte word of each array in the plans' buffer
+    int64_t at[9] = {};  // first 8-byte word of each array in the plans' buffer
 };
 
 // Side streams for the independent evaluation launches of a sub-round
@@ -3087,7 +3099,6 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             if (H == 0) continue;
             std::vector<int32_t> plog(H), pbase(H + 1), cap(H), chub, phub;
             std::vector<int64_t> rbase(H), obase(H), toff(H), cbeg;
-            std::vector<uint32_t> tmask(H);
             int64_t rtot = 0, otot = 0, ttot = 0;
             int32_t np = 0;
             for (int32_t h = 0; h < H; ++h) {
@@ -3107,11 +3118,8 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 rtot += static_cast<int64_t>(cap[h]) << lg;
                 obase[h] = otot;
                 otot += hd;
-                uint64_t tsz = 1;
-                while (tsz < 2 * static_cast<uint64_t>(hd)) tsz <<= 1;
                 toff[h] = ttot;
-                tmask[h] = static_cast<uint32_t>(tsz - 1);
-                ttot += static_cast<int64_t>(tsz);
+                ttot += 2 * hd;
                 for (int64_t sl = 0; sl < hd; sl += hub_chunk) {
                     chub.push_back(h);
                     cbeg.push_back(hr[h].begin + sl);
@@ -3129,7 +3137,6 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             P.at[6] = put(obase);
             P.at[7] = put(toff);
             P.at[8] = put(cbeg);
-            P.at[9] = put(tmask);
             max_region = std::max(max_region, rtot);
             max_over = std::max(max_over, otot);
             max_table = std::max(max_table, ttot);
@@ -3433,11 +3440,10 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 H.hub_obase = pb + P.at[6];
                 H.hub_toff = pb + P.at[7];
                 H.chunk_begin = pb + P.at[8];
-                H.hub_tmask = reinterpret_cast<const uint32_t*>(pb + P.at[9]);
                 H.rcount = hub_ints.get();
                 H.ocount = H.rcount + P.nparts;
-                H.big = H.ocount + Hn;
-                H.hub_own = H.big + Hn;
+                H.tfill = reinterpret_cast<uint32_t*>(H.ocount + Hn);
+                H.hub_own = H.ocount + 2 * Hn;
                 H.ekeys = ekeys.get();
                 H.evals = evals.get();
                 H.okeys = okeys.get();

@@ -24,7 +24,7 @@ struct LPTuning {
     int32_t lane_max = 0;     // <= 16; 0: by the number of nodes
     int32_t wave_max = 256;   // <= 256
     int32_t block_max = 8192; // <= 8192
-    int32_t hub_part_limit = 4096;  // <= 4096; larger hub partitions use the HBM table
+    int32_t hub_part_limit = 2048;  // <= 2048; longer hub partitions are summed in HBM
     int32_t hub_region_cap = 0;     // 0: about twice a partition's expected share
     int32_t select_small_max = 0;     // larger overflow segments: multi-workgroup selection (0: by the colour's size)
     int32_t select_launches = 0;      // multi-workgroup selection launches per sub-round (0: default)

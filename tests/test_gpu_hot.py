@@ -1,0 +1,71 @@
+"""Graphs that bring most of a sub-round's work to one place: a hub whose
+neighbours all carry different labels, a label that every node of a colour wants.
+Integer results, compared with the oracle element by element; times only against
+other calls of the same run, with bounds far from both sides."""
+import time
+
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def sc():
+    import paper_1404_4797_amd as m
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    m.load()
+    return m
+
+
+def star(leaves, seed):
+    """Node 0 joined to every leaf."""
+    w = np.random.default_rng(seed).integers(1, 500, size=leaves).astype(np.int32)
+    xadj = np.concatenate([[0], leaves + np.arange(leaves + 1)]).astype(np.int64)
+    adj = np.concatenate([np.arange(1, leaves + 1), np.zeros(leaves)]).astype(np.int32)
+    return {"n": leaves + 1, "xadj": xadj, "adjncy": adj, "adjwgt": np.concatenate([w, w]),
+            "vwgt": np.ones(leaves + 1, dtype=np.int32)}
+
+
+def seconds(call, reps=3):
+    call()
+    best = 1e9
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        call()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best
+
+
+# hub_part_limit: partitions of a hub summed in LDS and in HBM, side by side (at 1024 about half of them; 2^21 slots
+# are the last with 1024 expected entries per partition, beyond them the default's 2048 are passed too)
+@pytest.mark.parametrize("leaves,knobs", [(20000, dict(hub_part_limit=1024)), (20000, dict(hub_part_limit=1024, hub_region_cap=700)),
+                                          (2100000, dict(hub_part_limit=1024)), (4000000, dict()),
+                                          (4000000, dict(hub_region_cap=1900))])
+def test_hub_partitions_in_hbm(sc, leaves, knobs):
+    g = star(leaves, leaves)
+    d = sc.to_device(g)
+    lab, rr = sc.cluster_dev(d, leaves // 5, rounds=2, seed=3, **knobs)
+    ref, rr_ref, _ = oracle.cluster(g, leaves // 5, rounds=2, seed=3, nsub=4)
+    assert rr == rr_ref and np.array_equal(lab.cpu().numpy(), ref)
+    k = leaves // 700
+    part = np.random.default_rng(k).integers(0, k, size=g["n"]).astype(np.int32)
+    p, rr = sc.refine_dev(d, k, 5000, torch.from_numpy(part.copy()).cuda(), rounds=2, seed=5, **knobs)
+    ref, rr_ref, _ = oracle.refine(g, k, 5000, part, rounds=2, seed=5, nsub=4)
+    assert rr == rr_ref and np.array_equal(p.cpu().numpy(), ref)
+
+
+def test_hub_partitions_in_hbm_run_side_by_side(sc):
+    # four times the slots: 2.4 times the time where every partition has its own workgroup, 210 times where one has them all
+    t = {}
+    for leaves in (1 << 20, 1 << 22):
+        d = sc.to_device(star(leaves, 1))
+        t[leaves] = seconds(lambda: sc.cluster_dev(d, leaves // 36, rounds=3, seed=1))
+    assert t[1 << 22] < 40 * t[1 << 20]
