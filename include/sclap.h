@@ -98,7 +98,7 @@ typedef struct {
                                  2048); longer ones are summed in a table in device memory */
     int32_t hub_region_cap;   /* entries a hub partition keeps before spilling to its overflow list */
     int32_t select_small_max; /* overflowing targets with more candidates: multi-workgroup selection
-                                 (default 65536 in colours of at most 2^18 nodes, else 16384) */
+                                 (default 65536 in colours of at most 65536 nodes, else 16384) */
     int32_t skip_quiet;       /* 1: once few nodes move, skip nodes that emitted nothing, had no
                                  neighbouring label stronger than their own and saw no neighbour move
                                  since (their decision is unchanged); -1: evaluate every node;

@@ -72,7 +72,6 @@ constexpr int kSmallLabels = 4096;       // LDS-private histograms up to this ma
 constexpr int kCountInEval = 1 << 14;    // colours up to this size count candidates while they evaluate
 constexpr int kMaxBlocks = 512;          // grid cap of the grid-stride candidate kernels
 constexpr int kSmallSeg = 16384;         // large colours: segments up to this length have one selecting workgroup
-constexpr int kMidColour = 1 << 18;      // up to this size: up to kFinishMax, and one launch for the others
 constexpr int kSegChunk = 16384;         // entries per workgroup in the multi-workgroup selection
 constexpr int kLargeBlocks = 256;        // grid of the multi-workgroup selection kernel
 constexpr int kLargeThreads = 1024;      // and its workgroup size
@@ -3178,13 +3177,14 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     // default a colour of up to kFinishMax nodes leaves every segment to one
     // workgroup and launches no further kernel (three to four launches of
     // 2 us each, against 20-80 us in the first sub-rounds, whose segments
-    // alone are that long).  Up to kMidColour nodes longer segments are so rare
-    // that one selection launch does, the rest of whose digits one workgroup
-    // finishes (partition of 2^20 nodes, 16 blocks, 27.97 -> 27.57 ms); with
-    // larger colours split segments over kSmallSeg in a launch per digit
-    // (refinement of 2^21 nodes, colours of 2^19: 7.65 ms, 8.45 the other way).
+    // alone are that long); larger colours split segments over kSmallSeg in a
+    // launch per digit.  Up to 65 536 entries per workgroup and one launch for
+    // the others, in colours of up to 2^18 nodes, gained nothing on a partition
+    // of 2^20 nodes (28.25 and 27.21 ms, 28.35 and 27.30 like this) and lost
+    // where the segments are that long (8 hubs of 500 000 slots, refinement
+    // into 1 000 blocks: 2.09 ms, 1.47 like this).
     const int32_t small_max = tune.select_small_max > 0 ? std::min(tune.select_small_max, kFinishMax)
-                              : cap <= kMidColour       ? kFinishMax
+                              : cap <= kFinishMax       ? kFinishMax
                                                         : kSmallSeg;
     const bool use_large = cap > small_max;
     const int64_t max_large = use_large ? cap / small_max + 1 : 0;
@@ -3202,8 +3202,6 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     const int sel_launches =
         tune.select_launches > 0
             ? std::min(tune.select_launches, max_launches)
-        : tune.select_small_max <= 0 && cap <= kMidColour
-            ? 1
             : std::min(max_launches, (bits_for(static_cast<uint64_t>(n - 1)) + 12 + kLDigit - 1) / kLDigit);
     DBuf<uint32_t> rcnt(std::max(rounds, 1), s);  // candidates per round, read back one round late (see stopped())
     DBuf<uint8_t> lab8;

@@ -44,6 +44,18 @@ def seconds(call, reps=3):
     return best
 
 
+def kernel_ms(sc, call, names, reps=5):
+    """Least summed device time of the named kernel groups over a few calls."""
+    call()
+    best = 1e9
+    for _ in range(reps):
+        sc.profile_begin()
+        call()
+        stats = sc.profile_end()
+        best = min(best, sum(v["ms"] for name, v in stats.items() if name in names))
+    return best
+
+
 # hub_part_limit: partitions of a hub summed in LDS and in HBM, side by side (at 1024 about half of them; 2^21 slots
 # are the last with 1024 expected entries per partition, beyond them the default's 2048 are passed too)
 @pytest.mark.parametrize("leaves,knobs", [(20000, dict(hub_part_limit=1024)), (20000, dict(hub_part_limit=1024, hub_region_cap=700)),
@@ -69,3 +81,24 @@ def test_hub_partitions_in_hbm_run_side_by_side(sc):
         d = sc.to_device(star(leaves, 1))
         t[leaves] = seconds(lambda: sc.cluster_dev(d, leaves // 36, rounds=3, seed=1))
     assert t[1 << 22] < 40 * t[1 << 20]
+
+
+def test_long_segments_of_mid_sized_colours(sc):
+    # colours of 250 000 nodes, each with half of 8 hubs for neighbours: segments of 16384 to 131072 entries.  A workgroup
+    # for up to 16384 and a launch per digit beyond take 0.6 of the time of one workgroup for up to 65536 and one launch
+    n, k = 1_000_000, 1000
+    rng = np.random.default_rng(6)
+    hub, leaf = np.nonzero(rng.random((8, n - 8)) < 0.5)
+    src, dst = np.concatenate([hub, leaf + 8]), np.concatenate([leaf + 8, hub])
+    order = np.argsort(src * n + dst)
+    d = sc.to_device({"n": n, "xadj": np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n))]).astype(np.int64),
+                      "adjncy": dst[order].astype(np.int32), "adjwgt": None, "vwgt": None})
+    part = torch.from_numpy(rng.integers(0, k, size=n).astype(np.int32)).cuda()
+
+    def refine(**knobs):
+        return sc.refine_dev(d, k, 8 * (n // k), part.clone(), rounds=3, seed=1, **knobs)
+
+    assert torch.equal(refine()[0], refine(select_small_max=16384)[0])
+    groups = ("lp_apply", "lp_refine_admit_select")
+    t = kernel_ms(sc, refine, groups)
+    assert t < 1.35 * kernel_ms(sc, lambda: refine(select_small_max=16384), groups)
