@@ -69,7 +69,8 @@ constexpr int kHubTable = 8192;          // LDS table of a hub chunk workgroup (
 constexpr int kHubChunk = kHubTable / 2; // slots per hub workgroup (table load <= 1/2)
 constexpr int kHubDenseChunk = 8192;     // slots per hub workgroup with dense block arrays
 constexpr int kSmallLabels = 4096;       // LDS-private histograms up to this many labels
-constexpr int kCountInEval = 1 << 14;    // colours up to this size count candidates while they evaluate
+constexpr int kCountInEval = 1 << 13;    // colours up to this size count candidates while they evaluate,
+constexpr int kCountShortRows = 1 << 14;  // and up to this one where no row has more than 256 slots
 constexpr int kMaxBlocks = 512;          // grid cap of the grid-stride candidate kernels
 constexpr int kSmallSeg = 16384;         // large colours: segments up to this length have one selecting workgroup
 constexpr int kSegChunk = 16384;         // entries per workgroup in the multi-workgroup selection
@@ -334,9 +335,9 @@ __device__ __forceinline__ void consider_group(const EvalArgs& A, const Ctx& kx,
 
 // Decision for a node given its best eligible label (x, conn) and the
 // connection to its own label: a move needs a positive gain, or an overloaded
-// own block during refinement.
-__device__ __forceinline__ void store_result(const EvalArgs& A, int32_t i, int32_t x, int32_t conn, int32_t own,
-                                             bool over, int32_t c) {
+// own block during refinement.  Returns the target or -1.
+__device__ __forceinline__ int32_t store_decision(const EvalArgs& A, int32_t i, int32_t x, int32_t conn, int32_t own,
+                                                  bool over) {
     int32_t t = -1, gain = 0;
     if (x >= 0) {
         gain = conn - own;
@@ -344,7 +345,37 @@ __device__ __forceinline__ void store_result(const EvalArgs& A, int32_t i, int32
     }
     A.ct[i] = t;
     A.cg[i] = gain;
+    return t;
+}
+
+// The same, and the candidate counted if the evaluation counts them.
+__device__ __forceinline__ void store_result(const EvalArgs& A, int32_t i, int32_t x, int32_t conn, int32_t own,
+                                             bool over, int32_t c) {
+    const int32_t t = store_decision(A, i, x, conn, own, over);
     if (A.acc && t >= 0) atomicAdd(&A.acc[t << A.acc_shift], acc_of(1, c));
+}
+
+// Counts the candidates of a whole wave (t: -1 or the lane's target).  Nodes of
+// few neighbours often want the same label (all the leaves of a star do), and
+// adds to one address are served one every 12 ns, so a target that many lanes
+// share gets one add: the first lane's target is looked at, and the next one's.
+__device__ __forceinline__ void count_lanes(const EvalArgs& A, int32_t t, int32_t c) {
+    constexpr int kMany = 8;
+    uint64_t todo = __ballot(t >= 0);
+#pragma unroll
+    for (int tries = 0; tries < 2; ++tries) {
+        if (__popcll(todo) < kMany) break;  // uniform
+        const int first = __ffsll(static_cast<long long>(todo)) - 1;
+        const int32_t t0 = __builtin_amdgcn_readlane(t, first);
+        const uint64_t same = __ballot(t == t0);
+        todo &= ~same;
+        const int cnt = __popcll(same);
+        if (cnt < kMany) continue;
+        const int32_t weight = A.vw ? wave_sum(t == t0 ? c : 0) : cnt;
+        if (lane_id() == first) atomicAdd(&A.acc[t0 << A.acc_shift], acc_of(cnt, weight));
+        if (t == t0) t = -1;
+    }
+    if (t >= 0) atomicAdd(&A.acc[t << A.acc_shift], acc_of(1, c));
 }
 
 // True if v is quiet and may skip evaluation (its block is not overloaded).
@@ -557,22 +588,18 @@ __device__ __forceinline__ void lane_row(const EvalArgs& A, int64_t b, int d, in
     }
 }
 
+// The target of the node at entry i, or -1; c gets its weight.
 template <int MAXD>
-__device__ __forceinline__ void eval_lane_body(const EvalArgs& A, int32_t bid) {
-    const int i = bid * 256 + threadIdx.x;
-    if (i >= A.count) return;
+__device__ __forceinline__ int32_t eval_lane_node(const EvalArgs& A, int32_t i, int32_t& c) {
     const Row row = A.rows[i];
-    if (stopped(A.gate)) return;
+    if (stopped(A.gate)) return -1;
     const int qm = quiet_mode(A);
     const int32_t v = row.node;
     const Ctx kx = ctx_of(A, v);
-    if (skip_quiet(A, qm, v, kx)) {
-        store_result(A, i, -1, 0, 0, false, 0);
-        return;
-    }
+    if (skip_quiet(A, qm, v, kx)) return store_decision(A, i, -1, 0, 0, false);
     const int d = row.deg;
     const int32_t a = A.label[v];
-    const int32_t c = A.vw ? A.vw[v] : 1;
+    c = A.vw ? A.vw[v] : 1;
     int32_t lab[MAXD], conn[MAXD];
     const bool over = A.refine && A.w[a] > kx.bound;
     lane_row<MAXD>(A, row.begin, d, lab, conn);
@@ -597,8 +624,16 @@ __device__ __forceinline__ void eval_lane_body(const EvalArgs& A, int32_t bid) {
     constexpr int U = MAXD < 8 ? MAXD : 8;
 #pragma unroll
     for (int j = 0; j < MAXD; j += U) consider_group<U>(A, kx, lab + j, conn + j, c, own, over, best, blocked);
-    store_result(A, i, best.x, best.conn, own, over, c);
     if (qm) A.quiet[v] = (!over && !blocked) ? 1 : 0;
+    return store_decision(A, i, best.x, best.conn, own, over);
+}
+
+template <int MAXD>
+__device__ __forceinline__ void eval_lane_body(const EvalArgs& A, int32_t bid) {
+    const int32_t i = bid * 256 + static_cast<int32_t>(threadIdx.x);
+    int32_t c = 0;
+    const int32_t t = i < A.count ? eval_lane_node<MAXD>(A, i, c) : -1;
+    if (A.acc) count_lanes(A, t, c);
 }
 
 template <int MAXD>
@@ -3253,6 +3288,8 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     }
     A.quiet = quiet.get();
     A.quiet_n = n;
+    bool long_rows = false;  // longer than the wave bucket's
+    for (int32_t j = 0; j < ncat; ++j) long_rows |= j % kNB > 4 && cnt[j] > 0;
     // Kept sums (see eval_kept_kernel).  A row keeps its sums when reading them
     // is no more work than its slots: at least one slot per kKeptPerSlot blocks,
     // which also bounds the memory by 16 bytes per slot.  The upkeep finds a
@@ -3489,9 +3526,16 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             const bool fused = !side && tune.fuse >= 0;
             // A small colour without hubs counts its candidates as the results
             // are stored: one launch less.  Adds to one address are served one
-            // every 12 ns, so the colour has at most 2^14 nodes and its
-            // candidates at least eight targets to spread over.
-            const bool count_in_eval = fused && H.count == 0 && ccount <= kCountInEval && nw >= 8;
+            // every 12 ns, and the candidates of a colour may all want the same
+            // label.  Rows of a few slots then add once per wave (count_lanes);
+            // longer ones add one by one, so the colour has at most 2^13 nodes
+            // (with 2^14: 10 rounds over 15 000 nodes per colour of a power-law
+            // graph 1.87 ms, 1.61 like this; 6 hubs as every node's neighbours
+            // 0.66 and 0.48), or 2^14 where no row is long, so that no label
+            // draws many to begin with (partition of a mesh with 12 500 nodes
+            // per colour 3.47 ms, 3.64 with 2^13).
+            const bool count_in_eval =
+                fused && H.count == 0 && ccount <= (long_rows ? kCountInEval : kCountShortRows) && nw >= 8;
             A.acc = count_in_eval ? acc.get() : nullptr;
             A.acc_shift = direct ? kAccShift : 0;
             const bool big = fused && !dense && tune.block_table != kBlockTablePow2;

@@ -102,3 +102,27 @@ def test_long_segments_of_mid_sized_colours(sc):
     groups = ("lp_apply", "lp_refine_admit_select")
     t = kernel_ms(sc, refine, groups)
     assert t < 1.35 * kernel_ms(sc, lambda: refine(select_small_max=16384), groups)
+
+
+@pytest.mark.parametrize("hubs,leaves", [(1, 32000), (2, 32000), (6, 32000)])
+def test_colours_that_want_one_label(sc, hubs, leaves):
+    # Every leaf has the same neighbours and wants the same block.  One launch per bucket sums the candidates in LDS
+    # before it adds them up; the fused launch takes 3 to 4 times as long if it adds the leaves of one or two hubs one by one.
+    n = hubs + leaves
+    rng = np.random.default_rng(hubs)
+    w = np.tile(rng.integers(1, 9, size=hubs), leaves).astype(np.int32)
+    g = {"n": n, "xadj": np.concatenate([np.arange(hubs) * leaves, hubs * leaves + np.arange(leaves + 1) * hubs]).astype(np.int64),
+         "adjncy": np.concatenate([np.tile(np.arange(hubs, n), hubs), np.tile(np.arange(hubs), leaves)]).astype(np.int32),
+         "adjwgt": np.concatenate([w.reshape(leaves, hubs).T.ravel(), w]), "vwgt": rng.integers(0, 4, size=n).astype(np.int32)}
+    d = sc.to_device(g)
+    part = rng.integers(0, 8, size=n).astype(np.int32)
+
+    def refine(**knobs):
+        return sc.refine_dev(d, 8, 4 * n, torch.from_numpy(part).cuda(), rounds=1, seed=2, **knobs)
+
+    ref, rr_ref, _ = oracle.refine(g, 8, 4 * n, part, rounds=1, seed=2, nsub=4)
+    for knobs in (dict(), dict(fused_eval=-1)):
+        p, rr = refine(**knobs)
+        assert rr == rr_ref and np.array_equal(p.cpu().numpy(), ref)
+    groups = ["lp_refine_fused", "lp_refine_admit"] + ["lp_refine_" + b for b in ("lane4", "lane16", "group16", "hub_dense")]
+    assert kernel_ms(sc, refine, groups) < 1.5 * kernel_ms(sc, lambda: refine(fused_eval=-1), groups)
