@@ -231,7 +231,8 @@ int sclap_contract_dev(const sclap_graph* g, const int32_t* labels, int32_t* C, 
 void sclap_graph_free(sclap_graph_owned* g);
 
 /* Uncoarsening (Section 3.1; Section 4.3): part[v] = coarse_part[C[v]] for
- * v < n; C values must lie in [0, n_coarse) (checked). */
+ * v < n; C values must lie in [0, n_coarse) (checked before anything is
+ * written: a refused call leaves part as it was).  part may be C itself. */
 int sclap_project(int32_t n, int32_t n_coarse, const int32_t* C, const int32_t* coarse_part, int32_t* part);
 int sclap_project_dev(int32_t n, int32_t n_coarse, const int32_t* C, const int32_t* coarse_part, int32_t* part,
                       void* stream);

@@ -20,16 +20,11 @@ __global__ void project_kernel(int32_t n, const int32_t* __restrict__ C, const i
     if (v < n) part[v] = cp[C[v]];
 }
 
-// The same for ids that nobody has looked at: one outside [0, nc) raises the
-// flag and projects nothing.
-__global__ void project_checked_kernel(int32_t n, int32_t nc, const int32_t* __restrict__ C,
-                                       const int32_t* __restrict__ cp, int32_t* __restrict__ part,
-                                       uint32_t* __restrict__ bad) {
+// The same unless the flag is up.  part may be C itself.
+__global__ void project_if_kernel(int32_t n, const int32_t* C, const int32_t* __restrict__ cp, int32_t* part,
+                                  const uint32_t* __restrict__ bad) {
     const int32_t v = blockIdx.x * 256 + threadIdx.x;
-    if (v >= n) return;
-    const int32_t c = C[v];
-    if (c < 0 || c >= nc) *bad = 1;
-    else part[v] = cp[c];
+    if (v < n && *bad == 0) part[v] = cp[C[v]];
 }
 
 // ---------------------------------------------------------- cut and weights
@@ -279,6 +274,13 @@ __global__ void __launch_bounds__(256) range_kernel(const int32_t* __restrict__ 
     }
 }
 
+// Raises *bad if a value lies outside [lo, hi).
+void raise_out_of_range(const int32_t* a, int64_t count, int32_t lo, int32_t hi, uint32_t* bad, hipStream_t s) {
+    range_kernel<<<static_cast<unsigned>(std::min<int64_t>((count + 2047) / 2048, 4096)), 256, 0, s>>>(a, count, lo, hi,
+                                                                                                      bad);
+    LAUNCHCHK();
+}
+
 unsigned capped_tiles(int64_t S) {
     const int64_t t = (S + kTile - 1) / kTile;
     return static_cast<unsigned>(t < 1 ? 1 : (t > 2048 ? 2048 : t));
@@ -302,7 +304,11 @@ bool project_checked(int32_t n, int32_t nc, const int32_t* C, const int32_t* coa
     if (n <= 0) return true;
     DBuf<uint32_t> bad(1, s);
     fill_u32(bad.get(), 0, 1, s);
-    project_checked_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, nc, C, coarse_part, part, bad.get());
+    // every id is looked at before the first block is written: a refused call
+    // leaves part as it was.  The flag stays on the device, so that the host
+    // waits once.
+    raise_out_of_range(C, n, 0, nc, bad.get(), s);
+    project_if_kernel<<<grid_for(n, 256), 256, 0, s>>>(n, C, coarse_part, part, bad.get());
     LAUNCHCHK();
     uint32_t h = 0;
     read_back(&h, bad.get(), sizeof(h), s);
@@ -547,9 +553,7 @@ bool all_in_range(const int32_t* a, int64_t count, int32_t lo, int32_t hi, hipSt
     if (count <= 0) return true;
     DBuf<uint32_t> bad(1, s);
     fill_u32(bad.get(), 0, 1, s);
-    range_kernel<<<static_cast<unsigned>(std::min<int64_t>((count + 2047) / 2048, 4096)), 256, 0, s>>>(a, count, lo, hi,
-                                                                                                      bad.get());
-    LAUNCHCHK();
+    raise_out_of_range(a, count, lo, hi, bad.get(), s);
     uint32_t h = 0;
     read_back(&h, bad.get(), sizeof(uint32_t), s);
     return h == 0;

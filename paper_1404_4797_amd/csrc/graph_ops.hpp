@@ -46,7 +46,8 @@ void sort_rows(OwnedDevGraph& g, hipStream_t s);
 
 // part[v] = coarse_part[C[v]]
 void project(int32_t n, const int32_t* C, const int32_t* coarse_part, int32_t* part, hipStream_t s);
-// The same with a look at every id: false if one lies outside [0, nc).
+// The same with a look at every id first: false, with part as it was, if one
+// lies outside [0, nc).
 bool project_checked(int32_t n, int32_t nc, const int32_t* C, const int32_t* coarse_part, int32_t* part,
                      hipStream_t s);
 

@@ -136,3 +136,22 @@ def test_contract_tiles(sc, lengths, unit, group):
     assert np.array_equal(C.cpu().numpy(), ref_C)
     for key in ("xadj", "adjncy", "adjwgt", "vwgt"):
         assert np.array_equal(cg[key].cpu().numpy(), ref[key]), key
+
+
+@pytest.mark.parametrize("n", [1, 256, 257, 100003])
+def test_refused_projection_writes_nothing(sc, n):
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    coarse = torch.randint(0, 100, (50,), generator=gen, device="cuda", dtype=torch.int32)
+    C = torch.randint(0, 50, (n,), generator=gen, device="cuda", dtype=torch.int32)
+    expect = coarse[C.long()]
+    for at, id_ in ((0, 50), (n // 2, -1), (n - 1, 1 << 30)):
+        bad = C.clone()
+        bad[at] = id_
+        before, part = bad.clone(), torch.full((n,), 7, device="cuda", dtype=torch.int32)
+        with pytest.raises(sc.SclapError):
+            sc.project_dev(bad, coarse, part=part)
+        assert bool((part == 7).all())
+        with pytest.raises(sc.SclapError):
+            sc.project_dev(bad, coarse, part=bad)
+        assert torch.equal(bad, before)
+    assert torch.equal(sc.project_dev(C, coarse, part=C), expect) and torch.equal(C, expect)
