@@ -448,7 +448,7 @@ int sclap_cut_dev_noalloc(const sclap_graph* g, const int32_t* part, int32_t k, 
     return guarded([&] {
         hipStream_t s = as_stream(stream);
         if (k < 1 || !cut || !block_w) fail(SCLAP_ERR_INVALID, "bad k or NULL output");
-        const DevGraph d = dev_view(g, s);
+        const DevGraph d = dev_view(g, s, false);
         if (d.n > 0 && !part) fail(SCLAP_ERR_INVALID, "part is NULL");
         cut_and_weights_noalloc(d, part, k, cut, block_w, s);
         return SCLAP_OK;

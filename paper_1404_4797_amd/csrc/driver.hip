@@ -66,8 +66,7 @@ Opts resolve(const sclap_options* o) {
     return r;
 }
 
-// Device view of a caller graph with device pointers; reads S = xadj[n].
-DevGraph dev_view(const sclap_graph* g, hipStream_t s) {
+DevGraph dev_view(const sclap_graph* g, hipStream_t s, bool may_allocate) {
     if (!g) fail(SCLAP_ERR_INVALID, "graph is NULL");
     if (g->n < 0) fail(SCLAP_ERR_INVALID, "n < 0");
     DevGraph d;
@@ -78,7 +77,12 @@ DevGraph dev_view(const sclap_graph* g, hipStream_t s) {
     d.vw = g->vwgt;
     if (g->n > 0) {
         if (!g->xadj) fail(SCLAP_ERR_INVALID, "xadj is NULL");
-        read_back(&d.S, g->xadj + g->n, sizeof(int64_t), s);
+        if (may_allocate) {
+            read_back(&d.S, g->xadj + g->n, sizeof(int64_t), s);
+        } else {
+            HIPCHK(hipMemcpyAsync(&d.S, g->xadj + g->n, sizeof(int64_t), hipMemcpyDeviceToHost, s));
+            HIPCHK(hipStreamSynchronize(s));
+        }
         if (d.S < 0) fail(SCLAP_ERR_INVALID, "xadj[n] < 0");
         if (d.S > 0 && !g->adjncy) fail(SCLAP_ERR_INVALID, "adjncy is NULL");
     }

@@ -33,8 +33,9 @@ uint64_t cycle_seed(uint64_t seed, int32_t cycle);
 // Defaults for NULL; checks ranges (throws Error).
 Opts resolve(const sclap_options* o);
 
-// Device view of a caller graph with device pointers; reads S = xadj[n].
-DevGraph dev_view(const sclap_graph* g, hipStream_t s);
+// Device view of a caller graph with device pointers; reads S = xadj[n], by a
+// plain copy if the call must not allocate (a thread's first read_back does).
+DevGraph dev_view(const sclap_graph* g, hipStream_t s, bool may_allocate = true);
 
 // Validates (or only measures) a device graph: c(V) and max c(v).
 // drop_units: weight arrays that hold only ones are dropped from g (read as

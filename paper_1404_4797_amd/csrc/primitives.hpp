@@ -7,7 +7,8 @@
 namespace sclap {
 
 // A few values from device memory to host variables, once the work enqueued on
-// s so far is done (sizes in multiples of 4 bytes).
+// s so far is done (sizes in multiples of 4 bytes).  A thread's first call
+// allocates pinned host memory.
 struct ReadItem {
     void* host;
     const void* dev;
