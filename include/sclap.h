@@ -172,7 +172,9 @@ const char* sclap_last_error(void);
  * later calls on that stream (at most a quarter of the device's memory).
  * sclap_trim_memory returns every cached block of the current device to the
  * device's memory pool; call it when the memory is needed elsewhere or before
- * destroying a stream that was passed to _dev calls.  Returns 0.
+ * destroying a stream that was passed to _dev calls.  It also frees the pinned
+ * host memory (128 KiB per thread) kept from threads that made calls and have
+ * ended.  Returns 0.
  */
 int sclap_trim_memory(void);
 

@@ -189,6 +189,7 @@ int sclap_trim_memory(void) {
     return guarded([&] {
         release_cached(nullptr, true);
         HIPCHK(hipDeviceSynchronize());
+        release_mail();
         return SCLAP_OK;
     });
 }

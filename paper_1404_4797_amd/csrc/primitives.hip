@@ -26,7 +26,8 @@ struct Mail {
     uint32_t out[kMailWords];  // host to device
 };
 
-// Mailboxes of threads that have ended, for threads to come.
+// Mailboxes of threads that have ended, for threads to come (at most one for
+// every thread that ever ran beside others; release_mail frees them).
 struct MailPool {
     std::mutex mu;
     std::vector<Mail*> free;
@@ -111,12 +112,30 @@ void read_back(const ReadItem* items, int count, hipStream_t s) {
         if (!there && i % 64 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(300)) break;
         if (!there) __builtin_ia32_pause();
     }
-    if (!there) HIPCHK(hipStreamSynchronize(s));
+    if (!there) {
+        const hipError_t e = hipStreamSynchronize(s);
+        if (e != hipSuccess) t_mail.m = nullptr;  // the kernel may still write there: no thread gets it
+        HIPCHK(e);
+    }
     size_t at = 0;
     for (int i = 0; i < count; ++i) {
         std::memcpy(items[i].host, m->in + at, items[i].bytes);
         at += items[i].bytes / 4;
     }
+}
+
+void release_mail() {
+    std::vector<Mail*> idle;
+    {
+        std::lock_guard<std::mutex> lk(mail_pool().mu);
+        idle.swap(mail_pool().free);
+    }
+    hipError_t e = hipSuccess;
+    for (Mail* m : idle) {
+        const hipError_t one = hipHostFree(m);
+        if (e == hipSuccess) e = one;
+    }
+    HIPCHK(e);
 }
 
 void upload_once(void* dev, const void* host, size_t bytes, hipStream_t s) {

@@ -20,11 +20,13 @@ inline void read_back(void* host, const void* dev, size_t bytes, hipStream_t s) 
     read_back(&it, 1, s);
 }
 
+// Frees the pinned memory that read_back keeps from threads that have ended.
+void release_mail();
+
 // Copies host data to device memory in stream order; the source may go away
 // when the call returns.  One such copy per thread may be under way: the caller
 // waits for the stream before the next.
 void upload_once(void* dev, const void* host, size_t bytes, hipStream_t s);
-
 
 void fill_i32(int32_t* p, int32_t value, int64_t count, hipStream_t s);
 void fill_i64(int64_t* p, int64_t value, int64_t count, hipStream_t s);
