@@ -3292,12 +3292,12 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     for (int32_t j = 0; j < ncat; ++j) long_rows |= j % kNB > 4 && cnt[j] > 0;
     // Kept sums (see eval_kept_kernel).  A row keeps its sums when reading them
     // is no more work than its slots: at least one slot per kKeptPerSlot blocks,
-    // which also bounds the memory by 16 bytes per slot.  The upkeep finds a
-    // mover's neighbours in its row, so the graph must be known to be symmetric.
-    // Below kKeptMinSlots the two launches of the upkeep and the separate
-    // launch for the kept rows cost more than the gathers (refinement of a
-    // power-law graph, 10 rounds, 16 blocks: whole partition of 2^20 nodes, 31 M
-    // slots, 29.7 ms without, 28.7 ms with; levels of 2 to 16 M slots kept too:
+    // which also bounds the memory, by 16 bytes per slot of those rows.  The
+    // upkeep finds a mover's neighbours in its row, so the graph must be known to
+    // be symmetric.  Below kKeptMinSlots the two launches of the upkeep and the
+    // separate launch for the kept rows cost more than the gathers (refinement of
+    // a power-law graph, 10 rounds, 16 blocks: whole partition of 2^20 nodes, 31
+    // M slots, 29.7 ms without, 28.7 ms with; levels of 2 to 16 M slots kept too:
     // 31.0 ms).  Where the memory is not to be had, nothing is kept.
     int32_t kept_bucket = 2;
     while (kept_bucket < kHubBucket && (th.t[kept_bucket - 1] + 1) * kKeptPerSlot < A.dense_k) ++kept_bucket;
@@ -3314,6 +3314,8 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
         kept_rows += kr.to[sc] - kr.from[sc];
     }
     bool keep = dense && g.symmetric && rounds > 2 && kept_slots >= kKeptMinSlots && nw < static_cast<int32_t>(kStayed);
+    // hub rows are kept whatever their length, which the options may set low
+    if (static_cast<int64_t>(kept_rows) * A.dense_k > kKeptPerSlot * kept_slots) keep = false;
     DBuf<int32_t> sums, kidx;
     DBuf<uint16_t> prev;
     DBuf<int4> up_chunks;

@@ -48,3 +48,26 @@ def test_kept_sums(sc, graph, k, knobs):
     p, rr = sc.refine_dev(sc.to_device(graph), k, lmax, torch.from_numpy(part.copy()).cuda(), rounds=3, seed=k, **knobs)
     ref, rr_ref, _ = oracle.refine(graph, k, lmax, part, rounds=3, seed=k, nsub=knobs.get("subrounds", 4))
     assert rr == rr_ref and np.array_equal(p.cpu().numpy(), ref)
+
+
+def test_sums_stay_within_16_bytes_per_slot(sc):
+    # rows of some 24 slots, which these thresholds make hubs: their sums for 256 blocks would take 43 bytes per slot
+    n, rng = 760_000, np.random.default_rng(11)
+    u, v = rng.integers(0, n, size=9_300_000), rng.integers(0, n, size=9_300_000)
+    key = np.unique(np.minimum(u, v) * n + np.maximum(u, v))
+    u, v = key // n, key % n
+    u, v = u[u != v], v[u != v]
+    src, dst = np.concatenate([u, v]), np.concatenate([v, u])
+    order = np.argsort(src * n + dst)
+    deg = np.bincount(src, minlength=n)
+    assert deg[deg > 16].sum() > 1 << 24
+    g = {"n": n, "xadj": np.concatenate([[0], np.cumsum(deg)]).astype(np.int64), "adjncy": dst[order].astype(np.int32),
+         "adjwgt": None, "vwgt": None}
+    d, k, lmax = sc.to_device(g), 256, n // 128
+    part = rng.integers(0, k, size=n).astype(np.int32)
+    knobs = dict(lane_max_degree=16, wave_max_degree=16, block_max_degree=16)
+    sc.profile_begin()
+    p, rr = sc.refine_dev(d, k, lmax, torch.from_numpy(part).cuda(), rounds=3, seed=1, **knobs)
+    assert "lp_refine_kept" not in sc.profile_end()
+    ref, rr_ref, _ = oracle.refine(g, k, lmax, part, rounds=3, seed=1, nsub=4)
+    assert rr == rr_ref and np.array_equal(p.cpu().numpy(), ref)
