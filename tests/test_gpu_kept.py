@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
+import synth
 
 pytestmark = pytest.mark.gpu
 
@@ -71,3 +72,26 @@ def test_sums_stay_within_16_bytes_per_slot(sc):
     assert "lp_refine_kept" not in sc.profile_end()
     ref, rr_ref, _ = oracle.refine(g, k, lmax, part, rounds=3, seed=1, nsub=4)
     assert rr == rr_ref and np.array_equal(p.cpu().numpy(), ref)
+
+
+def test_kept_sums_in_the_device_initial_partitioner(sc, graph):
+    k, cV = 40, int(graph["vwgt"].sum())
+    T, lmax = -(-cV // k), oracle.lmax(cV, k, 0.03)
+    sc.profile_begin()
+    part, visits = sc.initial_partition_lp_dev(sc.to_device(graph), k, T, lmax, seed=7, rounds=4)
+    assert {"lp_refine_kept", "lp_upkeep"} <= sc.profile_end().keys()
+    ref, _, ref_visits = oracle.initial_partition_lp(graph, k, T, lmax, seed=7, rounds=4)
+    assert visits == ref_visits and np.array_equal(part.cpu().numpy(), ref)
+
+
+def test_kept_sums_in_a_batch(sc, graph):
+    # graph-local blocks: the second graph's begin at 40, and its rows keep sums for 40 blocks of which it has 7
+    graphs, ks, opts = [graph, synth.ba(60000, 16, seed=9, weighted=True)], [40, 7], dict(max_levels=0, refine_rounds=4)
+    u, base = sc.union(graphs)
+    sc.profile_begin()
+    r = sc.partition_batch_dev(sc.to_device(u), base, ks, [0.05, 0.03], [3, 4], **opts)
+    assert {"lp_refine_kept", "lp_upkeep"} <= sc.profile_end().keys()
+    part = r["part"].cpu().numpy()
+    for i, g in enumerate(graphs):
+        ref = oracle.partition(g, ks[i], [0.05, 0.03][i], 3 + i, **opts)
+        assert np.array_equal(part[base[i]:base[i + 1]], ref["part"]) and r["cut"][i] == ref["cut"]
