@@ -83,8 +83,11 @@ typedef struct {
     int32_t cluster_divisor; /* W = floor(c(V) / (cluster_divisor * k)) (default 18) */
     int32_t coarsest_nodes;  /* stop coarsening at <= this many nodes (default 10000) */
     int32_t max_levels;      /* at most this many contractions, 0..64 (default 64) */
-    int32_t validate;        /* 1: check the input graph first (default 1); a large refinement
-                                is faster on a graph that was checked, see fused_eval */
+    int32_t validate;        /* 1: check the input graph first (default 1).  A refinement into at
+                                most 256 blocks of a checked graph with 2^24 slots in long rows
+                                keeps their block sums between rounds (at most 16 bytes of device
+                                memory per slot of those rows) and is faster for it; where that
+                                memory cannot be had, it runs as on an unchecked graph */
     /* Replaces the hash colour of every node (values in [0, subrounds)) in
      * sclap_cluster, sclap_refine and their _dev variants only; host or device
      * memory to match the entry point; NULL = hash colours. */
@@ -137,9 +140,7 @@ typedef struct {
     int32_t fused_eval;           /* tuning (never changes results): 0 (default) or 1: a colour with
                                      fewer than 2^22 adjacency slots evaluates its rows in one launch
                                      (refinement of at most 256 blocks) or two (rows of up to and of
-                                     more than 1 024 slots); -1: one launch per bucket.  Either way, a
-                                     refinement of a checked graph with 2^24 slots in long rows keeps
-                                     their block sums (up to 16 bytes per slot) between rounds */
+                                     more than 1 024 slots); -1: one launch per bucket */
     int32_t block_table;          /* tuning (never changes results): entries of the LDS table of the
                                      workgroup-per-node bucket with the longest rows, 10240 (80 KB,
                                      probed modulo its size; 0 = 10240) or 16384 (128 KB) */
@@ -410,8 +411,12 @@ int32_t sclap_server_plan_batch(const int64_t* nodes, const int64_t* slots, cons
  * other table size of the longest-row workgroup bucket (block_table).
  * Coordinate search from the library defaults: capture, then block, wave and
  * lane thresholds, then the table size; a value is kept only if it is at
- * least 3 % faster.  Semantic fields of opt
- * are read, not changed; results of later calls do not depend on the choice.
+ * least 3 % faster.  lane_max_degree stays 0 on graphs of more than 2^17 nodes
+ * unless a fixed value wins: the default differs between the levels of a call.
+ * One round keeps no block sums (see validate), so what is chosen for long rows
+ * is what suits clustering and a large refinement's first round.  Semantic
+ * fields of opt are read, not changed; results of later calls do not depend on
+ * the choice.
  */
 int sclap_autotune_dev(const sclap_graph* g, int32_t k, sclap_options* opt, void* stream);
 

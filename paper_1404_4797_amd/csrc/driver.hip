@@ -997,8 +997,12 @@ LPTuning autotune(const DevGraph& g_in, int32_t k, const Opts& o, hipStream_t s)
     // size of the longest-row workgroup bucket (10240 or 16384 entries) is
     // searched as well; the capture choice decides whether the rounds run as
     // one HIP graph.  A value is taken only if it is at least 3 % faster than
-    // the current best.
-    best.lane_max = default_lane_max(g.n);
+    // the current best.  The lane threshold's default depends on a graph's
+    // size: where coarser levels would get another one, it is left open (0)
+    // unless a fixed value wins, so that tuned calls choose it level by level
+    // as untuned ones do.
+    const int32_t lane_default = default_lane_max(g.n);
+    best.lane_max = lane_default == default_lane_max(1) ? lane_default : 0;
     best.wave_max = 256;
     best.block_max = 8192;
     best.block_table = 10240;
@@ -1006,7 +1010,7 @@ LPTuning autotune(const DevGraph& g_in, int32_t k, const Opts& o, hipStream_t s)
     auto try_values = [&](int32_t LPTuning::*field, std::initializer_list<int32_t> values) {
         const int32_t keep = best.*field;
         for (int32_t val : values) {
-            if (val == keep) continue;
+            if (val == keep || (field == &LPTuning::lane_max && val == lane_default)) continue;
             LPTuning t = best;
             t.*field = val;
             const double ms = measure(t);

@@ -179,3 +179,10 @@ def test_batch_mix512_oracle_digests(sc, golden_dir):
         if not ok:
             bad.append(i)
     assert not bad, "graphs differing from the oracle: %s" % bad[:20]
+
+
+@pytest.mark.parametrize("scale", [14, 20])
+def test_autotuner_leaves_the_lane_threshold_to_the_levels(sc, scale):
+    # untuned calls take 4 up to 2^17 nodes and 16 above: that value, which would fix the coarser levels too, is not returned
+    o = sc.autotune_dev(sc.to_device(synth.rmat(scale, 16, seed=5), "cuda"), 8)
+    assert o.lane_max_degree in ((4, 8, 16) if scale <= 17 else (0, 4, 8))
