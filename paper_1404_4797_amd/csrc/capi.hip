@@ -128,6 +128,7 @@ int cluster_impl(const DevGraph& g_in, int64_t U, int32_t rounds, uint64_t seed,
         gc = inside.view();
         gc.vw = g.vw;
         gc.symmetric = g.symmetric;
+        gc.heavy = g.heavy;
     }
     DBuf<int32_t> dcol;
     if (o.degree_order && !color_dev && g.n > 0) {

@@ -103,7 +103,9 @@ void check_graph(DevGraph& g, bool validate, int64_t* cV, int64_t* cmax, hipStre
             if (unit[1]) g.ew = nullptr;
         }
     } else {
-        node_weight_stats(g, cV, cmax, s);
+        bool bad = false;
+        node_weight_stats(g, cV, cmax, s, &bad);
+        g.heavy = bad || *cV > 2147483647LL;
         if (!drop_units) return;
         if (g.ew && all_in_range(g.ew, g.S, 1, 2, s)) g.ew = nullptr;
         if (g.vw && all_in_range(g.vw, g.n, 1, 2, s)) g.vw = nullptr;
@@ -795,6 +797,7 @@ void multilevel_cycle(const DevGraph& g0, int32_t k, int64_t cV, int64_t cmax0, 
             Gc = inside.view();
             Gc.vw = G.vw;
             Gc.symmetric = G.symmetric;
+            Gc.heavy = G.heavy;
         }
         DBuf<int32_t> dcol;
         if (o.degree_order) {
@@ -821,6 +824,7 @@ void multilevel_cycle(const DevGraph& g0, int32_t k, int64_t cV, int64_t cmax0, 
         L[lev].C = std::move(C);
         nx.g = nx.own.view();
         nx.g.symmetric = L[lev].g.symmetric;
+        nx.g.heavy = L[lev].g.heavy;
         L.push_back(std::move(nx));
         blk.push_back(std::move(cb));
         ++lev;
@@ -1480,6 +1484,8 @@ int partition_batch_impl(const DevGraph& g0_in, int32_t G, const int32_t* node_b
     }
     int64_t cVu = 0, cmu = 0;
     check_graph(g0, o.validate != 0, &cVu, &cmu, s, true);
+    // the total that counts is each graph's own, looked at below
+    if (cVu > 2147483647LL) g0.heavy = g0.vw && !all_in_range(g0.vw, g0.n, 0, INT_MAX, s);
     if (o.validate && !members_closed(g0, L[0].nb, L[0].sb, s))
         fail(SCLAP_ERR_INVALID, "an edge joins two graphs of the batch");
     L[0].g = g0;
@@ -1586,6 +1592,7 @@ int partition_batch_impl(const DevGraph& g0_in, int32_t G, const int32_t* node_b
                 Gc = inside.view();
                 Gc.vw = B.g.vw;
                 Gc.symmetric = B.g.symmetric;
+                Gc.heavy = B.g.heavy;
             }
             DBuf<int32_t> dcol;
             if (o.degree_order) {
@@ -1661,6 +1668,7 @@ int partition_batch_impl(const DevGraph& g0_in, int32_t G, const int32_t* node_b
             }
             N.g = N.own.view();
             N.g.symmetric = B.g.symmetric;
+            N.g.heavy = B.g.heavy;
             N.gid.alloc(std::max(N.g.n, 1), s);
             member_ids(N.g.n, N.nb, N.ids, N.gid.get(), s);
             std::vector<int32_t> delta(G, INT_MIN);

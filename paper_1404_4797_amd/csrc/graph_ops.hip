@@ -534,7 +534,7 @@ int validate_graph(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s,
     return 0;
 }
 
-void node_weight_stats(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s) {
+void node_weight_stats(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s, bool* bad) {
     if (g.n == 0) {
         *cV = 0;
         *cmax = 0;
@@ -547,6 +547,7 @@ void node_weight_stats(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_
     const VStats h = sum_stats(st.get(), s);
     *cV = static_cast<int64_t>(h.cV);
     *cmax = h.cmax;
+    if (bad) *bad = h.bad != 0;
 }
 
 bool all_in_range(const int32_t* a, int64_t count, int32_t lo, int32_t hi, hipStream_t s) {

@@ -66,8 +66,9 @@ void cut_and_weights_noalloc(const DevGraph& g, const int32_t* part, int32_t k, 
 // unit (two flags, may be null): whether all node and all edge weights are 1.
 int validate_graph(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s, bool* unit = nullptr);
 
-// c(V) and max_v c(v) without validation.
-void node_weight_stats(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s);
+// c(V) and max_v c(v) without validation, negative weights left out.  bad (may
+// be null): whether there are any, or offsets that do not ascend from 0.
+void node_weight_stats(const DevGraph& g, int64_t* cV, int64_t* cmax, hipStream_t s, bool* bad = nullptr);
 
 // True iff every value of a[0..count) lies in [lo, hi).
 bool all_in_range(const int32_t* a, int64_t count, int32_t lo, int32_t hi, hipStream_t s);

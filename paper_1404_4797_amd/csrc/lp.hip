@@ -307,7 +307,8 @@ __device__ __forceinline__ bool eligible(const EvalArgs& A, int32_t x, int32_t c
 }
 
 // Candidate total of a target: count in the high word, weight in the low one
-// (a label's weight never exceeds c(V) <= 2^31 - 1, so no carry).
+// (a label's weight never exceeds c(V) <= 2^31 - 1, so no carry; the candidates
+// of a heavy graph are counted without their weights, see Admission::heavy).
 __device__ __forceinline__ unsigned long long acc_of(int32_t cnt, int32_t weight) {
     return (static_cast<unsigned long long>(static_cast<uint32_t>(cnt)) << 32) | static_cast<uint32_t>(weight);
 }
@@ -1486,7 +1487,8 @@ constexpr int kFillShift = 5;   // seg_fill[t << kFillShift] (4-byte entries)
 template <bool kDirect, int R>
 __global__ void __launch_bounds__(256) accumulate_kernel(EvalArgs E, HubArgs H, const int32_t* __restrict__ ct,
                                                          const int32_t* __restrict__ nodes, int32_t count,
-                                                         unsigned long long* __restrict__ acc, int32_t nw) {
+                                                         unsigned long long* __restrict__ acc, int32_t nw,
+                                                         bool heavy) {
     if (stopped(E.gate)) return;  // uniform over the grid
     const int32_t* vw = E.vw;
     if (static_cast<int32_t>(blockIdx.x) < H.count) {
@@ -1495,7 +1497,8 @@ __global__ void __launch_bounds__(256) accumulate_kernel(EvalArgs E, HubArgs H, 
         else hub_decide(E, H, h);
         if (threadIdx.x == 0 && E.ct[h] >= 0) {
             const int32_t t = E.ct[h];
-            atomicAdd(&acc[kDirect ? t << kAccShift : t], acc_of(1, vw ? vw[E.rows[h].node] : 1));
+            const int32_t c = heavy ? 0 : vw ? vw[E.rows[h].node] : 1;
+            atomicAdd(&acc[kDirect ? t << kAccShift : t], acc_of(1, c));
         }
         return;
     }
@@ -1525,7 +1528,7 @@ __global__ void __launch_bounds__(256) accumulate_kernel(EvalArgs E, HubArgs H, 
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int64_t p = base + r * 256 + threadIdx.x;
-            cr[r] = tr[r] >= 0 ? (vw ? vw[nodes[p]] : 1) : 0;
+            cr[r] = tr[r] >= 0 && !heavy ? (vw ? vw[nodes[p]] : 1) : 0;
         }
 #pragma unroll
         for (int r = 0; r < R; ++r) {
@@ -1596,7 +1599,7 @@ struct LargeSel {
     int32_t* len;       // [nlarge] its entries
     int32_t* chunk0;    // [nlarge] its first chunk
     int32_t* owner;     // [nlchunks] large segment of each chunk
-    uint32_t* hist;     // [nlarge][kLBins] weight per digit
+    uint32_t* hist;     // [nlarge][kLBins] weight per digit (heavy graphs: 64 bits each)
     uint64_t* prefix;   // [nlarge] digits fixed so far, at the end the boundary key
     int32_t* room;      // [nlarge] weight still admissible below the prefix
     uint32_t* done;     // [nlarge] chunks finished with the current digit
@@ -1614,6 +1617,9 @@ struct Admission {
     int32_t* w;
     int32_t nw;
     unsigned long long* acc;
+    // A heavy graph's candidates may weigh more than 32 bits hold: every target
+    // selects, from their count alone, and the selection sums in 64 bits.
+    bool heavy;
     Bounds B;
     uint8_t* ok;
     int32_t* seg_off;   // [nw] first entry of the target's segment, -1 none, -2 being claimed
@@ -1636,6 +1642,11 @@ struct Admission {
     uint32_t* round_cnt;  // candidates of the round
     uint32_t* host_cnt;   // where the round's last sub-round reports them to the host (null: not the last)
 };
+
+// A segment's room: below its candidates' weight, or no more than a label may weigh.
+__device__ __forceinline__ int32_t room32(int64_t room) {
+    return static_cast<int32_t>(room < INT_MAX ? room : INT_MAX);
+}
 
 // Records segment sid and, when it is longer than small_max, gives it a large
 // index.
@@ -1726,8 +1737,8 @@ __global__ void __launch_bounds__(256) admit_kernel(Admission A) {
             bool slow = false;
             if (tr[r] >= 0) {
                 const int64_t room = bound_of(A.B, tr[r]) - static_cast<int64_t>(wr[r]);
-                slow = static_cast<int64_t>(ar[r] & 0xFFFFFFFFULL) > room;
-                wr[r] = static_cast<int32_t>(room);  // used where it is below the candidates' weight
+                slow = A.heavy || static_cast<int64_t>(ar[r] & 0xFFFFFFFFULL) > room;
+                wr[r] = room32(room);
                 ++found;
             }
             if (p < A.count) A.ok[p] = tr[r] >= 0 && !slow ? 1 : 0;
@@ -1810,9 +1821,9 @@ __global__ void __launch_bounds__(256) admit_direct_kernel(Admission A) {
         const unsigned long long a = A.acc[t << kAccShift];
         if (a == 0) continue;
         const int64_t room = bound_of(A.B, t) - static_cast<int64_t>(A.w[t]);
-        if (static_cast<int64_t>(a & 0xFFFFFFFFULL) <= room) continue;
+        if (!A.heavy && static_cast<int64_t>(a & 0xFFFFFFFFULL) <= room) continue;
         g[q].len = static_cast<int32_t>(a >> 32);
-        g[q].room = static_cast<int32_t>(room);
+        g[q].room = room32(room);
         mine += acc_of(1, g[q].len);
     }
     unsigned long long incl = mine;
@@ -1904,44 +1915,56 @@ __device__ __forceinline__ int key_bits(const Counters* ctr, int bits_v) {
     return bits_of(static_cast<uint64_t>(static_cast<int64_t>(ctr->gmax) - ctr->gmin)) + bits_v;
 }
 
+// Sums of candidates' weights, and the histogram bins they are summed in: 32 bits
+// (the weights sum to at most 2^31 - 1), for heavy graphs 64.
+template <bool kHeavy>
+struct Sums {
+    using S = int32_t;
+    using Bin = uint32_t;
+};
+template <>
+struct Sums<true> {
+    using S = int64_t;
+    using Bin = unsigned long long;
+};
+
 // Boundary digit of a histogram held as kPerT consecutive digits per thread
 // (hv): the first digit whose cumulative weight exceeds room (the last digit
 // when none below it does); *s_d and *s_run (the weight of the digits before
-// it) are set for the whole block.  Weights sum to at most 2^31 - 1.
-template <int NT, int kPerT>
-__device__ __forceinline__ void block_pick_digit(const int32_t* hv, int32_t room, int32_t* s_wave, int* s_d,
-                                                 int32_t* s_run) {
+// it) are set for the whole block.  S: the type of the weight sums (Sums).
+template <int NT, int kPerT, typename S>
+__device__ __forceinline__ void block_pick_digit(const S* hv, int32_t room, S* s_wave, int* s_d, int32_t* s_run) {
     const int j = threadIdx.x;
     const int lane = lane_id();
-    int32_t local = 0;
+    S local = 0;
 #pragma unroll
     for (int q = 0; q < kPerT; ++q) local += hv[q];
-    int32_t incl = local;
+    S incl = local;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
-        const int32_t u = __shfl_up(incl, o, 64);
+        const S u = __shfl_up(incl, o, 64);
         if (lane >= o) incl += u;
     }
     if (lane == 63) s_wave[j >> 6] = incl;
     __syncthreads();
-    int32_t before = 0, total = 0;
+    S before = 0, total = 0;
 #pragma unroll
     for (int q = 0; q < NT / 64; ++q) {
-        const int32_t x = s_wave[q];
+        const S x = s_wave[q];
         before += q < (j >> 6) ? x : 0;
         total += x;
     }
     incl += before;
-    const int32_t excl = incl - local;
+    const S excl = incl - local;
     // the digit where the admissible weight runs out (monotone: one thread),
     // else the last digit
     if (total <= room) {
         if (j == NT - 1) {
             *s_d = NT * kPerT - 1;
-            *s_run = incl - hv[kPerT - 1];
+            *s_run = static_cast<int32_t>(incl - hv[kPerT - 1]);  // at most room, here and below
         }
     } else if (incl > room && excl <= room) {
-        int32_t run = excl;
+        S run = excl;
         int d = kPerT * j + kPerT - 1;
         for (int q = 0; q < kPerT - 1; ++q) {
             if (run + hv[q] > room) {
@@ -1951,7 +1974,7 @@ __device__ __forceinline__ void block_pick_digit(const int32_t* hv, int32_t room
             run += hv[q];
         }
         *s_d = d;
-        *s_run = run;
+        *s_run = static_cast<int32_t>(run);
     }
     __syncthreads();
 }
@@ -1964,6 +1987,7 @@ __device__ __forceinline__ void block_pick_digit(const int32_t* hv, int32_t room
 // when they do, the last block of each segment in the final launch finishes
 // the remaining digits alone, over the whole segment.  After the last digit
 // L.prefix holds the segment's boundary key.
+template <bool kHeavy>
 __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, int launch, int nlaunch, int bits_v,
                                                                    const uint64_t* __restrict__ sent,
                                                                    const int32_t* __restrict__ swt,
@@ -1971,8 +1995,10 @@ __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, i
     constexpr int NT = kLargeThreads;
     constexpr int kPerT = kLBins / NT;
     constexpr int U = 4;
-    __shared__ uint32_t h[kLBins];
-    __shared__ int32_t s_wave[NT / 64];
+    using S = typename Sums<kHeavy>::S;
+    using Bin = typename Sums<kHeavy>::Bin;
+    __shared__ Bin h[kLBins];
+    __shared__ S s_wave[NT / 64];
     __shared__ int s_last, s_d;
     __shared__ int32_t s_run;
     const int total_bits = key_bits(ctr, bits_v);
@@ -2002,7 +2028,7 @@ __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, i
             for (int u = 0; u < U; ++u) {
                 const uint64_t key = key_of(k[u], gmax, bits_v);
                 if (wt[u] && (key & ab) == prefix)
-                    atomicAdd(&h[(key >> sh) & (kLBins - 1)], static_cast<uint32_t>(wt[u]));
+                    atomicAdd(&h[(key >> sh) & (kLBins - 1)], static_cast<Bin>(wt[u]));
             }
         }
     };
@@ -2013,7 +2039,7 @@ __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, i
         const int32_t i0 = (c - L.chunk0[l]) * kSegChunk;
         const int32_t i1 = i0 + kSegChunk < len ? i0 + kSegChunk : len;
         const uint64_t prefix = L.prefix[l];
-        uint32_t* hl = L.hist + static_cast<size_t>(l) * kLBins;
+        Bin* hl = reinterpret_cast<Bin*>(L.hist) + static_cast<size_t>(l) * kLBins;
         for (int q = j; q < kLBins; q += NT) h[q] = 0;
         __syncthreads();
         accumulate(base, i0, i1, prefix, above, shift);
@@ -2035,10 +2061,10 @@ __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, i
         __syncthreads();
         if (s_last) {  // block-uniform
             // thread j holds digits kPerT*j .. kPerT*j + kPerT-1
-            int32_t hv[kPerT];
+            S hv[kPerT];
 #pragma unroll
             for (int q = 0; q < kPerT; ++q)
-                hv[q] = static_cast<int32_t>(
+                hv[q] = static_cast<S>(
                     __hip_atomic_load(&hl[kPerT * j + q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
             int32_t room = L.room[l];
             block_pick_digit<NT, kPerT>(hv, room, s_wave, &s_d, &s_run);
@@ -2055,7 +2081,7 @@ __global__ void __launch_bounds__(kLargeThreads) large_pass_kernel(LargeSel L, i
                     accumulate(base, 0, len, np, ~0ULL << (sh + kLDigit), sh);
                     __syncthreads();
 #pragma unroll
-                    for (int q = 0; q < kPerT; ++q) hv[q] = static_cast<int32_t>(h[kPerT * j + q]);
+                    for (int q = 0; q < kPerT; ++q) hv[q] = static_cast<S>(h[kPerT * j + q]);
                     block_pick_digit<NT, kPerT>(hv, room, s_wave, &s_d, &s_run);
                     np |= static_cast<uint64_t>(s_d) << sh;
                     room -= s_run;
@@ -2125,13 +2151,15 @@ constexpr int kMoveBlocksSmall = 64;
 // Segments hold 2-50 entries in most sub-rounds and thousands in the first
 // ones; one launch for all lengths replaced a scatter, a selection and an
 // apply launch of about 5 us each.
-template <bool kSmall>
+template <bool kSmall, bool kHeavy>
 __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uint32_t seg_blocks) {
     constexpr int NT = kFinishThreads;
     constexpr int kPerT = kLBins / NT;
-    __shared__ uint32_t hist[kLBins];
+    using S = typename Sums<kHeavy>::S;
+    using Bin = typename Sums<kHeavy>::Bin;
+    __shared__ Bin hist[kLBins];
     __shared__ int32_t delta[kSmall ? kSmallLabels : 1];
-    __shared__ int32_t s_wave[NT / 64];
+    __shared__ S s_wave[NT / 64];
     __shared__ int s_d;
     __shared__ int32_t s_run;
     const int tid = threadIdx.x;
@@ -2162,7 +2190,7 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uin
         const int32_t v = node_of(e);
         const int32_t a = lane < sg.len ? A.label[v] : 0;
         const uint64_t k = key_of(e, gmax, A.bits_v);
-        int32_t incl = 0;
+        S incl = 0;
         for (int j = 0; j < sg.len; ++j) {
             const uint32_t klo = __builtin_amdgcn_readlane(static_cast<uint32_t>(k), j);
             const uint32_t khi = __builtin_amdgcn_readlane(static_cast<uint32_t>(k >> 32), j);
@@ -2191,7 +2219,7 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uin
             const uint64_t above = sh + kLDigit >= 64 ? 0ULL : ~0ULL << (sh + kLDigit);
             for (int q = tid; q < kLBins; q += NT) hist[q] = 0;
             __syncthreads();
-            if (c0 && (k0 & above) == np) atomicAdd(&hist[(k0 >> sh) & (kLBins - 1)], static_cast<uint32_t>(c0));
+            if (c0 && (k0 & above) == np) atomicAdd(&hist[(k0 >> sh) & (kLBins - 1)], static_cast<Bin>(c0));
             constexpr int U = 4;
             for (int32_t i = tid + NT; i < sg.len; i += NT * U) {
                 uint64_t e[U];
@@ -2206,13 +2234,13 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uin
                 for (int u = 0; u < U; ++u) {
                     const uint64_t k = key_of(e[u], gmax, A.bits_v);
                     if (c[u] && (k & above) == np)
-                        atomicAdd(&hist[(k >> sh) & (kLBins - 1)], static_cast<uint32_t>(c[u]));
+                        atomicAdd(&hist[(k >> sh) & (kLBins - 1)], static_cast<Bin>(c[u]));
                 }
             }
             __syncthreads();
-            int32_t hv[kPerT];
+            S hv[kPerT];
 #pragma unroll
-            for (int q = 0; q < kPerT; ++q) hv[q] = static_cast<int32_t>(hist[kPerT * tid + q]);
+            for (int q = 0; q < kPerT; ++q) hv[q] = static_cast<S>(hist[kPerT * tid + q]);
             block_pick_digit<NT, kPerT>(hv, room, s_wave, &s_d, &s_run);
             np |= static_cast<uint64_t>(s_d) << sh;
             room -= s_run;
@@ -3226,7 +3254,8 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     const int64_t max_lchunks = use_large ? cap / kSegChunk + max_large : 0;
     DBuf<int32_t> ltarget(max_large, s), lbase(max_large, s), llen(max_large, s), lchunk0(max_large, s);
     DBuf<int32_t> lowner(max_lchunks, s);
-    DBuf<uint32_t> lhist(max_large * kLBins, s);
+    const int64_t lhist_n = max_large * kLBins * (g.heavy ? 2 : 1);
+    DBuf<uint32_t> lhist(lhist_n, s);
     DBuf<uint64_t> lprefix(max_large, s);
     DBuf<int32_t> lroom(max_large, s);
     DBuf<uint32_t> ldone(max_large, s);
@@ -3243,10 +3272,10 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     DBuf<uint16_t> lab16;
     if (nw <= 256) lab8.alloc(n, s);
     else if (nw <= 65536) lab16.alloc(n, s);
-    const int64_t init_items = std::max({fill_n, max_large * kLBins, nw <= 65536 ? static_cast<int64_t>(n) : 0});
+    const int64_t init_items = std::max({fill_n, lhist_n, nw <= 65536 ? static_cast<int64_t>(n) : 0});
     init_admission_kernel<<<std::min(grid_for(init_items, 256), 4096u), 256, 0, s>>>(
-        acc.get(), acc_n, seg_off.get(), direct ? 0 : nw, seg_fill.get(), fill_n, lhist.get(), max_large * kLBins, ldone.get(), max_large,
-        rcnt.get(), rounds, ctr, label, n, lab8.get(), lab16.get());
+        acc.get(), acc_n, seg_off.get(), direct ? 0 : nw, seg_fill.get(), fill_n, lhist.get(), lhist_n, ldone.get(),
+        max_large, rcnt.get(), rounds, ctr, label, n, lab8.get(), lab16.get());
     LAUNCHCHK();
 
     EvalArgs A;
@@ -3391,6 +3420,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     M.w = w;
     M.nw = nw;
     M.acc = acc.get();
+    M.heavy = g.heavy;
     M.B = BB;
     M.ok = ok.get();
     M.seg_off = seg_off.get();
@@ -3537,7 +3567,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             // draws many to begin with (partition of a mesh with 12 500 nodes
             // per colour 3.47 ms, 3.64 with 2^13).
             const bool count_in_eval =
-                fused && H.count == 0 && ccount <= (long_rows ? kCountInEval : kCountShortRows) && nw >= 8;
+                fused && H.count == 0 && ccount <= (long_rows ? kCountInEval : kCountShortRows) && nw >= 8 && !g.heavy;
             A.acc = count_in_eval ? acc.get() : nullptr;
             A.acc_shift = direct ? kAccShift : 0;
             const bool big = fused && !dense && tune.block_table != kBlockTablePow2;
@@ -3662,7 +3692,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                                            : per == 4 ? accumulate_kernel<false, 4>
                                                       : accumulate_kernel<false, 8>);
                     use_bucket(kHubBucket);
-                    accum<<<gc + H.count, 256, 0, s>>>(A, H, ct.get(), cnodes, M.count - H.count, acc.get(), nw);
+                    accum<<<gc + H.count, 256, 0, s>>>(A, H, ct.get(), cnodes, M.count - H.count, acc.get(), nw, g.heavy);
                     LAUNCHCHK();
                 }
                 auto admit = direct     ? admit_direct_kernel
@@ -3688,8 +3718,9 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 const unsigned gseg = small && direct ? kSegBlocksSmall : kSegBlocks;
                 const unsigned gmov = static_cast<unsigned>(std::min<int64_t>(
                     grid_for(ccount, kFinishThreads), small ? kMoveBlocksSmall : kMoveBlocks));
-                if (small) finish_kernel<true><<<gseg + gmov, kFinishThreads, 0, s>>>(M, gseg);
-                else finish_kernel<false><<<gseg + gmov, kFinishThreads, 0, s>>>(M, gseg);
+                auto finish = small ? (g.heavy ? finish_kernel<true, true> : finish_kernel<true, false>)
+                                    : (g.heavy ? finish_kernel<false, true> : finish_kernel<false, false>);
+                finish<<<gseg + gmov, kFinishThreads, 0, s>>>(M, gseg);
                 LAUNCHCHK();
             }
             // a target has at most ccount candidates: no longer segment
@@ -3697,8 +3728,9 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             if (ccount > small_max) {
                 ProfScope ps(A.refine ? "lp_refine_admit_select" : "lp_admit_select", 0, s);
                 for (int launch = 0; launch < sel_launches; ++launch) {
-                    large_pass_kernel<<<kLargeBlocks, kLargeThreads, 0, s>>>(M.L, launch, sel_launches, bits_v,
-                                                                             sent.get(), swt.get(), M.ctr);
+                    auto pass = g.heavy ? large_pass_kernel<true> : large_pass_kernel<false>;
+                    pass<<<kLargeBlocks, kLargeThreads, 0, s>>>(M.L, launch, sel_launches, bits_v, sent.get(),
+                                                                swt.get(), M.ctr);
                     LAUNCHCHK();
                 }
                 if (small) large_move_kernel<true><<<kMaxBlocks, 256, 0, s>>>(M);

@@ -18,6 +18,7 @@ struct DevGraph {
     const int32_t* ew = nullptr;  // null => unit edge weights
     const int32_t* vw = nullptr;  // null => unit node weights
     bool symmetric = false;  // known to hold every edge in both directions (checked, or made from such a graph)
+    bool heavy = false;  // an unchecked graph whose node weights sum past 2^31 - 1, or with negative ones
 };
 
 struct LPTuning {
