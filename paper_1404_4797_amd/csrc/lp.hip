@@ -79,6 +79,7 @@ constexpr int kLargeThreads = 1024;      // and its workgroup size
 constexpr int64_t kKeptMinSlots = 1 << 24;  // with fewer slots in long enough rows no sums are kept
 constexpr int32_t kKeptPerSlot = 4;         // a row keeps its sums when it has at least dense_k / 4 slots
 constexpr int kUpkeepLongBlocks = 512;      // grid of upkeep_long_kernel
+constexpr int kFreshShare = 6;  // after a sub-round that moved more than this part of its slots no sums hold
 
 struct Counters {
     unsigned long long segs;  // segments claimed (high word), entries reserved in them (low word)
@@ -88,7 +89,19 @@ struct Counters {
     uint32_t nlchunks;  // kSegChunk-entry chunks of those segments
     uint32_t bad_color;
     uint32_t nlong;     // chunks of long rows whose node moved (upkeep of kept sums)
+    unsigned long long moved;  // slots of the nodes that moved, about (where sums are kept)
 };
+
+// Which colours' kept sums hold (see eval_kept_kernel): the mask as the last
+// sub-round left it, unless that sub-round moved too much for the upkeep to be
+// worth it; then no sums hold until their colour's rows are counted afresh.
+struct Fresh {
+    const uint32_t* mask;  // bit per colour (null: no sums are kept, or every row is counted)
+    const Counters* last;  // the last sub-round's counters
+    unsigned long long limit;  // slots it may have moved
+};
+
+__device__ __forceinline__ uint32_t fresh_mask(const Fresh& F) { return F.last->moved > F.limit ? 0u : *F.mask; }
 
 // One schedule entry: a node and where its row lies.  Laid out in schedule
 // order, so that an evaluation reads 16 consecutive bytes per node instead of
@@ -142,7 +155,13 @@ struct EvalArgs {
     unsigned long long* acc;
     int32_t acc_shift;
     int32_t* sums;  // kept block sums of the launch's rows, dense_k per entry (null: not kept)
+    Fresh fresh;
+    int32_t colour;  // of the launch's rows
 };
+
+__device__ __forceinline__ bool sums_hold(const EvalArgs& A) {
+    return A.fresh.mask && ((fresh_mask(A.fresh) >> A.colour) & 1u);
+}
 
 // A round runs only while the previous one had candidates (gate: that
 // round's candidate count, null for the first round).  Rounds are enqueued
@@ -1283,13 +1302,23 @@ __device__ void hub_dense_decide(const EvalArgs& A, const HubArgs& H, int32_t h)
     }
 }
 
-// Kept sums: after the first round of a refinement few nodes move (power-law
-// graph, 2^22 nodes, 64 blocks: 14 % of the slots belong to nodes that moved in
-// the first round, 0.1-4 % in each later one), so the block sums of long rows
-// stay in HBM.  The first round's evaluation writes them, the neighbours of
+// Kept sums: where a refinement starts from a good partition few nodes move
+// (levels of a power-law graph of 2^22 nodes, 64 blocks: 0.1-2.5 % of a colour's
+// slots belong to nodes that move in a sub-round; a partition a tenth of whose
+// nodes were placed anew: 3-10 % in the first round), so the block sums of long
+// rows stay in HBM.  The first round's evaluation writes them, the neighbours of
 // every node that moves are corrected (upkeep), and later rounds read dense_k
 // integers per row, hubs included, instead of gathering a label per slot.  The
-// sums are the same integers a new count would give.  G lanes per row, each
+// sums are the same integers a new count would give.  From a bad start up to all
+// of a colour's slots move, and two atomics per slot, many on the same hubs' few
+// words, cost far more than a new count (power-law graph of 2^22 nodes, 10 rounds
+// from 2 random blocks 14.4 ms and 5.8 without sums, from a single pool 23.6 and
+// 5.1; into one of 64 random blocks 29.3 and 12.2).  After a sub-round that moved
+// over a sixth of its slots no correction is made, the sums hold no longer, and
+// each colour's rows are counted afresh when their turn comes (Fresh): 6.0, 6.4
+// and 8.2 ms.  A sixth, because a mesh of 2^22 nodes whose 64 random blocks move an
+// eighth to a seventh of the slots in most of ten rounds is corrected in 14.0 ms
+// and counted afresh in 15.3.  G lanes per row, each
 // with its U sums loaded before anything else is known about the row: the
 // kernel is a stream of 4 * dense_k bytes per row (2^24 nodes, 512 M slots, 64
 // blocks, one colour: 180 k rows in 110 us beside the short rows, where the
@@ -1301,7 +1330,7 @@ __global__ void __launch_bounds__(256) eval_kept_kernel(EvalArgs A) {
     const int32_t i = static_cast<int32_t>(blockIdx.x) * (256 / G) + static_cast<int32_t>(threadIdx.x) / G;
     if (i >= A.count) return;  // uniform per group
     const Row row = A.rows[i];
-    if (stopped(A.gate)) return;
+    if (stopped(A.gate) || !sums_hold(A)) return;
     const int32_t* conn = A.sums + static_cast<int64_t>(i) * A.dense_k;
     int32_t cn[U];
 #pragma unroll
@@ -1368,12 +1397,12 @@ constexpr size_t kFusedLds =
               cmax(16 * kDenseMax * sizeof(int32_t), sizeof(BlockScratch<256>) + kDenseMax * sizeof(int32_t))));
 
 template <bool kDense>
-__global__ void __launch_bounds__(256) eval_fused_kernel(EvalArgs A, FusedBuckets F, HubArgs H) {
-    __shared__ __align__(16) unsigned char lds[kFusedLds];
+__device__ __forceinline__ void eval_fused_body(EvalArgs& A, const FusedBuckets& F, const HubArgs& H, int32_t block,
+                                                unsigned char* lds) {
     int b = (kDense ? kFusedDense : kFusedHash) - 1;
     int32_t first = 0;
-    while (b > 0 && static_cast<int32_t>(blockIdx.x) >= F.end[b]) first = F.end[b--];
-    const int32_t bid = static_cast<int32_t>(blockIdx.x) - first;
+    while (b > 0 && block >= F.end[b]) first = F.end[b--];
+    const int32_t bid = block - first;
     A.rows = F.rows[b];
     A.count = F.count[b];
     A.ct = F.ct[b];
@@ -1406,6 +1435,26 @@ __global__ void __launch_bounds__(256) eval_fused_kernel(EvalArgs A, FusedBucket
             if (kDense) eval_dense_block_body<256>(A, bid, lds);
             else eval_block_body<256, 2 * kBlock1Max, kBlock1Max / 256>(A, bid, lds);
             break;
+    }
+}
+
+template <bool kDense>
+__global__ void __launch_bounds__(256) eval_fused_kernel(EvalArgs A, FusedBuckets F, HubArgs H) {
+    __shared__ __align__(16) unsigned char lds[kFusedLds];
+    eval_fused_body<kDense>(A, F, H, blockIdx.x, lds);
+}
+
+// The rows with kept sums counted afresh, where the sums hold no longer (after
+// the first round seldom: the workgroups, few enough to come and go in a
+// launch's time, take the places of the buckets in turn).
+constexpr int kRecountBlocks = 2048;
+
+__global__ void __launch_bounds__(256) eval_recount_kernel(EvalArgs A, FusedBuckets F, HubArgs H, int32_t blocks) {
+    __shared__ __align__(16) unsigned char lds[kFusedLds];
+    if (stopped(A.gate) || sums_hold(A)) return;  // uniform over the grid
+    for (int32_t block = blockIdx.x; block < blocks; block += gridDim.x) {
+        eval_fused_body<true>(A, F, H, block, lds);
+        __syncthreads();  // the buffer is used again
     }
 }
 
@@ -1493,8 +1542,13 @@ __global__ void __launch_bounds__(256) accumulate_kernel(EvalArgs E, HubArgs H, 
     const int32_t* vw = E.vw;
     if (static_cast<int32_t>(blockIdx.x) < H.count) {
         const int32_t h = blockIdx.x;
-        if (H.hub_sum) hub_dense_decide(E, H, h);
-        else hub_decide(E, H, h);
+        if (sums_hold(E)) {
+            // decided from its sums, with the other rows that keep theirs
+        } else if (H.hub_sum) {
+            hub_dense_decide(E, H, h);
+        } else {
+            hub_decide(E, H, h);
+        }
         if (threadIdx.x == 0 && E.ct[h] >= 0) {
             const int32_t t = E.ct[h];
             const int32_t c = heavy ? 0 : vw ? vw[E.rows[h].node] : 1;
@@ -1636,6 +1690,10 @@ struct Admission {
     uint8_t* label8;
     uint16_t* label16;
     uint16_t* prev;      // [n] label that a node left in this sub-round, else kStayed (null: not needed)
+    const int64_t* xadj;  // for the slots of the nodes that moved (where prev is kept)
+    uint32_t* fresh;      // the mask of Fresh: this colour's sums hold from here on (null: none are kept)
+    unsigned long long fresh_limit;  // of the last sub-round, whose counters are ctr_next
+    int32_t colour;
     Counters* ctr;       // this sub-round's counters
     Counters* ctr_next;  // the next sub-round's: cleared here, no kernel reads them any more
     const uint32_t* gate;
@@ -2105,6 +2163,7 @@ __device__ __forceinline__ void clear_subround(Counters* ctr) {
     ctr->nlarge = 0;
     ctr->nlchunks = 0;
     ctr->nlong = 0;
+    ctr->moved = 0;
 }
 
 // Moves node v (weight c) to label t.  The departure goes to delta (LDS, small
@@ -2120,6 +2179,27 @@ __device__ __forceinline__ void depart_and_move(const Admission& A, int32_t v, i
         if (kSmall) atomicSub(&delta[a], c);
         else atomicSub(&A.w[a], c);
     }
+}
+
+// Slots of a node that moved, where they are counted.  They only decide how the
+// next sub-rounds come by the sums, so a thread looks one of its nodes up and
+// takes the others it moves at the same time for as long: two more reads per
+// moved node took 15 us of a launch that moves 120 000.
+__device__ __forceinline__ int64_t moved_slots(const Admission& A, int32_t v) {
+    return A.prev ? A.xadj[v + 1] - A.xadj[v] : 0;
+}
+
+// Adds the workgroup's moved slots up (nothing where they are not counted).
+template <int NT>
+__device__ __forceinline__ void note_moved(const Admission& A, int64_t moved) {
+    if (!A.prev) return;  // uniform over the grid
+    __shared__ int64_t s_moved[NT / 64];
+    moved = wave_sum(moved);
+    if (lane_id() == 0) s_moved[threadIdx.x >> 6] = moved;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < NT / 64; ++w) moved += s_moved[w];
+    if (moved) atomicAdd(&A.ctr->moved, static_cast<unsigned long long>(moved));
 }
 
 template <bool kSmall>
@@ -2166,7 +2246,12 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uin
     if (A.host_cnt && blockIdx.x == 0 && tid == 0) *A.host_cnt = *A.round_cnt;
     if (stopped(A.gate)) return;  // uniform over the grid: nothing was counted either
     const int lane = lane_id();
-    if (blockIdx.x == 0 && tid == 0) clear_subround(A.ctr_next);
+    if (blockIdx.x == 0 && tid == 0) {
+        // before this sub-round's moves, which its counters tell the next one
+        if (A.fresh) *A.fresh = fresh_mask(Fresh{A.fresh, A.ctr_next, A.fresh_limit}) | (1u << A.colour);
+        clear_subround(A.ctr_next);
+    }
+    int64_t moved = 0;
     if (kSmall) {
         for (int j = tid; j < A.nw; j += NT) delta[j] = 0;
         __syncthreads();
@@ -2198,7 +2283,10 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uin
             incl += ((static_cast<uint64_t>(khi) << 32) | klo) <= k ? cj : 0;
         }
         const bool in = lane < sg.len && incl <= sg.room;
-        if (in) depart_and_move<kSmall>(A, v, a, sg.t, c, delta);
+        if (in) {
+            moved += moved_slots(A, v);
+            depart_and_move<kSmall>(A, v, a, sg.t, c, delta);
+        }
         const int32_t sum = wave_sum(in ? c : 0);
         if (lane == 0) arrive<kSmall>(A, sg.t, sum, delta);
     }
@@ -2246,15 +2334,19 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uin
             room -= s_run;
             __syncthreads();  // s_d, s_run and hist are written again by the next pass
         }
-        int32_t sum = 0;
+        int32_t sum = 0, cnt = 0;
+        int64_t slots = 0;
         for (int32_t i = tid; i < sg.len; i += NT) {
             const uint64_t e = i == tid ? e0 : A.sent[sg.base + i];
             if (key_of(e, gmax, A.bits_v) >= np) continue;
             const int32_t c = i == tid ? c0 : A.swt[sg.base + i];
             const int32_t v = node_of(e);
-            depart_and_move<kSmall>(A, v, A.label[v], sg.t, c, delta);
+            const int32_t a = A.label[v];
+            if (cnt++ == 0) slots = moved_slots(A, v);
+            depart_and_move<kSmall>(A, v, a, sg.t, c, delta);
             sum += c;
         }
+        moved += slots * cnt;
         sum = wave_sum(sum);
         if (lane == 0) arrive<kSmall>(A, sg.t, sum, delta);
     }
@@ -2278,6 +2370,13 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uin
             aq[u] = oq[u] ? A.label[vq[u]] : 0;
             cq[u] = oq[u] ? (A.vw ? A.vw[vq[u]] : 1) : 0;
         }
+        int32_t cnt = 0, v1 = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            v1 = oq[u] ? vq[u] : v1;
+            cnt += oq[u];
+        }
+        const int64_t slots = cnt ? moved_slots(A, v1) : 0;
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (tq[u] < 0) continue;
@@ -2286,7 +2385,9 @@ __global__ void __launch_bounds__(kFinishThreads) finish_kernel(Admission A, uin
             depart_and_move<kSmall>(A, vq[u], aq[u], tq[u], cq[u], delta);
             arrive<kSmall>(A, tq[u], cq[u], delta);
         }
+        moved += slots * cnt;
     }
+    note_moved<NT>(A, moved);
     if (kSmall) {
         __syncthreads();
         for (int j = tid; j < A.nw; j += NT)
@@ -2304,6 +2405,7 @@ __global__ void __launch_bounds__(256) large_move_kernel(Admission A) {
         __syncthreads();
     }
     const int32_t gmax = A.ctr->gmax;
+    int64_t moved = 0;
     const int32_t nch = static_cast<int32_t>(A.ctr->nlchunks);
     constexpr int kParts = kSegChunk / 1024;  // a workgroup takes 1024 entries of a chunk at a time
     for (int32_t cp = blockIdx.x; cp < nch * kParts; cp += gridDim.x) {
@@ -2314,18 +2416,23 @@ __global__ void __launch_bounds__(256) large_move_kernel(Admission A) {
         const int32_t i1 = min(i0 + 1024, A.L.len[l]);
         const uint64_t end = A.L.prefix[l];
         const int32_t t = A.L.target[l];
-        int32_t sum = 0;
+        int32_t sum = 0, cnt = 0;
+        int64_t slots = 0;
         for (int32_t i = i0 + static_cast<int32_t>(threadIdx.x); i < i1; i += 256) {
             const uint64_t e = A.sent[base + i];
             if (key_of(e, gmax, A.bits_v) >= end) continue;
             const int32_t wt = A.swt[base + i];
             const int32_t v = node_of(e);
-            depart_and_move<kSmall>(A, v, A.label[v], t, wt, delta);
+            const int32_t a = A.label[v];
+            if (cnt++ == 0) slots = moved_slots(A, v);
+            depart_and_move<kSmall>(A, v, a, t, wt, delta);
             sum += wt;
         }
+        moved += slots * cnt;
         sum = wave_sum(sum);
         if (lane_id() == 0) arrive<kSmall>(A, t, sum, delta);
     }
+    note_moved<256>(A, moved);
     if (kSmall) {
         __syncthreads();
         for (int j = threadIdx.x; j < A.nw; j += 256)
@@ -2435,8 +2542,10 @@ __global__ void __launch_bounds__(256) unquiet_kernel(const int32_t* __restrict_
 // Two dependent reads and two atomics per slot; on random lines those ran at
 // 18 G/s.
 
-// Index of every scheduled node's kept sums, -1 for short rows; the colours'
-// kept rows follow each other.
+// Index of every scheduled node's kept sums with its colour above, -1 for short
+// rows; the colours' kept rows follow each other.
+constexpr int kKeptBits = 27;
+
 struct KeptRanges {
     int32_t nsub;
     int32_t from[16], to[16];  // schedule positions of each colour's kept rows
@@ -2450,7 +2559,7 @@ __global__ void __launch_bounds__(256) kept_index_kernel(KeptRanges K, const int
     if (p >= count) return;
     int sc = 0;
     while (sc < K.nsub - 1 && p >= K.end[sc]) ++sc;
-    kidx[nodes[p]] = p >= K.from[sc] && p < K.to[sc] ? K.base[sc] + (p - K.from[sc]) : -1;
+    kidx[nodes[p]] = p >= K.from[sc] && p < K.to[sc] ? (sc << kKeptBits) | (K.base[sc] + (p - K.from[sc])) : -1;
 }
 
 constexpr uint32_t kStayed = 0xFFFF;
@@ -2467,7 +2576,7 @@ struct Upkeep {
     const int32_t* gid;
     const int32_t* g_lbase;
     const int32_t* kidx;
-    int32_t built;  // rows with a lower index have sums
+    Fresh fresh;
     int32_t* sums;
     int32_t k;
     int4* chunks;  // node, old label, new label, chunk
@@ -2477,7 +2586,7 @@ struct Upkeep {
 
 // U slots of rows whose nodes moved from block `from` to `to` (slot -1: none).
 template <int U>
-__device__ __forceinline__ void upkeep_slots(const Upkeep& K, const int64_t* slot, const int32_t* from,
+__device__ __forceinline__ void upkeep_slots(const Upkeep& K, uint32_t fresh, const int64_t* slot, const int32_t* from,
                                              const int32_t* to) {
     int32_t v[U], wt[U];
 #pragma unroll
@@ -2489,8 +2598,9 @@ __device__ __forceinline__ void upkeep_slots(const Upkeep& K, const int64_t* slo
     for (int u = 0; u < U; ++u) v[u] = v[u] >= 0 ? K.kidx[v[u]] : -1;
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        if (v[u] < 0 || v[u] >= K.built) continue;
-        int32_t* conn = K.sums + static_cast<int64_t>(v[u]) * K.k;
+        // rows whose sums do not hold are left alone: they may be being counted
+        if (v[u] < 0 || !((fresh >> (v[u] >> kKeptBits)) & 1u)) continue;
+        int32_t* conn = K.sums + static_cast<int64_t>(v[u] & ((1 << kKeptBits) - 1)) * K.k;
         atomicSub(&conn[from[u]], wt[u]);
         atomicAdd(&conn[to[u]], wt[u]);
     }
@@ -2504,6 +2614,7 @@ __global__ void __launch_bounds__(256) upkeep_kernel(Upkeep K) {
     __shared__ int32_t s_pre[256], s_f[256], s_t[256];
     __shared__ int32_t s_wave[4];
     if (stopped(K.gate)) return;  // uniform over the grid
+    const uint32_t fresh = fresh_mask(K.fresh);
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int wid = tid >> 6;
@@ -2521,6 +2632,12 @@ __global__ void __launch_bounds__(256) upkeep_kernel(Upkeep K) {
     int32_t mine = 0;
 #pragma unroll
     for (int j = 0; j < kUpkeepPer; ++j) mine += pv[j] != kStayed;
+    if (fresh == 0) {  // uniform over the grid: nothing to correct, but the moves are dealt with
+#pragma unroll
+        for (int j = 0; j < kUpkeepPer; ++j)
+            if (pv[j] != kStayed) K.prev[v0 + j] = static_cast<uint16_t>(kStayed);
+        return;
+    }
     if (__syncthreads_or(mine) == 0) return;
     // exclusive sum of v over the workgroup; *total gets the whole
     auto block_prefix = [&](int32_t v, int32_t* total) {
@@ -2590,7 +2707,7 @@ __global__ void __launch_bounds__(256) upkeep_kernel(Upkeep K) {
                 f[u] = s_f[lo];
                 t[u] = s_t[lo];
             }
-            upkeep_slots<U>(K, slot, f, t);
+            upkeep_slots<U>(K, fresh, slot, f, t);
         }
         __syncthreads();
     }
@@ -2598,6 +2715,7 @@ __global__ void __launch_bounds__(256) upkeep_kernel(Upkeep K) {
 
 __global__ void __launch_bounds__(256) upkeep_long_kernel(Upkeep K) {
     if (stopped(K.gate)) return;
+    const uint32_t fresh = fresh_mask(K.fresh);
     const uint32_t nch = K.ctr->nlong;
     for (uint32_t q = blockIdx.x; q < nch; q += gridDim.x) {
         const int4 c = K.chunks[q];
@@ -2613,7 +2731,7 @@ __global__ void __launch_bounds__(256) upkeep_long_kernel(Upkeep K) {
                 f[u] = c.y;
                 t[u] = c.z;
             }
-            upkeep_slots<U>(K, slot, f, t);
+            upkeep_slots<U>(K, fresh, slot, f, t);
         }
     }
 }
@@ -3344,10 +3462,11 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     }
     bool keep = dense && g.symmetric && rounds > 2 && kept_slots >= kKeptMinSlots && nw < static_cast<int32_t>(kStayed);
     // hub rows are kept whatever their length, which the options may set low
-    if (static_cast<int64_t>(kept_rows) * A.dense_k > kKeptPerSlot * kept_slots) keep = false;
+    if (static_cast<int64_t>(kept_rows) * A.dense_k > kKeptPerSlot * kept_slots || kept_rows >= 1 << kKeptBits) keep = false;
     DBuf<int32_t> sums, kidx;
     DBuf<uint16_t> prev;
     DBuf<int4> up_chunks;
+    DBuf<uint32_t> fresh(1, s);
     if (keep) {
         try {
             sums.alloc(static_cast<size_t>(kept_rows) * A.dense_k, s);
@@ -3366,8 +3485,11 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
         fill_u32(reinterpret_cast<uint32_t*>(prev.get()), 0xFFFFFFFFu, (static_cast<int64_t>(n) + 8) / 2, s);
         kept_index_kernel<<<grid_for(off[ncat], 256), 256, 0, s>>>(kr, nodes, static_cast<int32_t>(off[ncat]), kidx.get());
         LAUNCHCHK();
+        fill_u32(fresh.get(), 0, 1, s);
     }
     A.sums = nullptr;
+    A.fresh = Fresh{};
+    A.colour = 0;
 
     // Algorithmic bytes of one evaluation launch, the figure of one round's
     // minimal traffic per unit: per evaluated node 24 (its row offsets, own
@@ -3438,6 +3560,9 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     M.label8 = lab8.get();
     M.label16 = lab16.get();
     M.prev = keep ? prev.get() : nullptr;
+    M.xadj = g.xadj;
+    M.fresh = keep ? fresh.get() : nullptr;
+    M.fresh_limit = 0;  // before the first sub-round nothing has moved
     Upkeep up = {};
     up.n = n;
     up.prev = prev.get();
@@ -3477,9 +3602,11 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             for (int32_t bk = 0; bk < kNB; ++bk) colour_slots += cslots[c0 + bk];
             const bool side = colour_slots >= (1ULL << 22);  // small colours stay on one stream
             if (side) evs.fork(s);
+            const Fresh now{fresh.get(), ctr + (~step & 1), M.fresh_limit};  // as the last sub-round left the sums
             // the previous sub-round's moves reach the kept sums while the
             // evaluation streams take the short rows, which need none
             if (upkeep_due) {
+                up.fresh = now;
                 ProfScope ps("lp_upkeep", 0, s);
                 upkeep_kernel<<<grid_for(n, 256 * kUpkeepPer), 256, 0, s>>>(up);
                 LAUNCHCHK();
@@ -3492,8 +3619,10 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             // other buckets fill the device
             const HubPlan& P = plans[sc];
             HubArgs H = {};
-            const bool kept_eval = keep && r > 0;  // rows from kept_bucket on: from their kept sums
-            if (P.count > 0 && !kept_eval) {
+            const bool kept_eval = keep && r > 0;  // rows from kept_bucket on: from their kept sums, if those hold
+            A.fresh = kept_eval ? now : Fresh{};
+            A.colour = sc;
+            if (P.count > 0) {
                 const int32_t Hn = P.count;
                 H.count = Hn;
                 const int64_t* pb = plan_buf.get();
@@ -3593,7 +3722,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                     LAUNCHCHK();
                 }
             }
-            if (H.count > 0 && !(fused && dense)) {
+            if (H.count > 0 && !(fused && dense) && !kept_eval) {
                 use_bucket(kHubBucket);
                 if (dense) {
                     ProfScope ps("lp_refine_hub_dense", eval_bytes(P.count, cslots[c0 + kHubBucket]), s);
@@ -3611,17 +3740,24 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                     LAUNCHCHK();
                 }
             }
-            if (kept_eval) {
+            if (kept_eval && kr.to[sc] > kr.from[sc]) {
+                double bytes;
+                const int32_t blocks = lay_out(kHubBucket, kept_bucket, &bytes);
+                {
+                    // beside the upkeep and the kept rows, which are the longer chain
+                    const hipStream_t bs = side ? evs.bucket(2) : s;
+                    ProfScope ps("lp_refine_recount", 0, bs);
+                    eval_recount_kernel<<<std::min(blocks, kRecountBlocks), 256, 0, bs>>>(A, F, H, blocks);
+                    LAUNCHCHK();
+                }
                 use_bucket(kept_bucket);
                 A.count = kr.to[sc] - kr.from[sc];
                 ProfScope ps("lp_refine_kept", 4.0 * A.dense_k * A.count, s);
-                if (A.count > 0) {
-                    if (A.dense_k <= 32) eval_kept_kernel<8><<<grid_for(A.count, 32), 256, 0, s>>>(A);
-                    else if (A.dense_k <= 64) eval_kept_kernel<16><<<grid_for(A.count, 16), 256, 0, s>>>(A);
-                    else if (A.dense_k <= 128) eval_kept_kernel<32><<<grid_for(A.count, 8), 256, 0, s>>>(A);
-                    else eval_kept_kernel<64><<<grid_for(A.count, 4), 256, 0, s>>>(A);
-                    LAUNCHCHK();
-                }
+                if (A.dense_k <= 32) eval_kept_kernel<8><<<grid_for(A.count, 32), 256, 0, s>>>(A);
+                else if (A.dense_k <= 64) eval_kept_kernel<16><<<grid_for(A.count, 16), 256, 0, s>>>(A);
+                else if (A.dense_k <= 128) eval_kept_kernel<32><<<grid_for(A.count, 8), 256, 0, s>>>(A);
+                else eval_kept_kernel<64><<<grid_for(A.count, 4), 256, 0, s>>>(A);
+                LAUNCHCHK();
             }
             const int32_t bk_to = kept_eval ? kept_bucket : kHubBucket;
             for (int32_t bk = bk_from; bk < bk_to; ++bk) {
@@ -3679,6 +3815,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             M.gate = gate;
             M.round_cnt = rcnt.get() + r;
             M.host_cnt = sc == last_sub ? hrc + r : nullptr;
+            M.colour = sc;
             ++step;
             const int per = ccount <= (1 << 16) ? 1 : (ccount <= (1 << 18) ? 4 : 8);
             const unsigned gc = static_cast<unsigned>(std::min<int64_t>(grid_for(ccount, 256 * per), kMaxBlocks));
@@ -3738,7 +3875,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
                 LAUNCHCHK();
             }
             if (keep) {
-                up.built = r > 0 || sc == nsub - 1 ? kept_rows : kr.base[sc + 1];
+                M.fresh_limit = colour_slots / kFreshShare;
                 up.ctr = M.ctr;
                 up.gate = gate;
                 upkeep_due = true;

@@ -95,3 +95,37 @@ def test_kept_sums_in_a_batch(sc, graph):
     for i, g in enumerate(graphs):
         ref = oracle.partition(g, ks[i], [0.05, 0.03][i], 3 + i, **opts)
         assert np.array_equal(part[base[i]:base[i + 1]], ref["part"]) and r["cut"][i] == ref["cut"]
+
+
+@pytest.mark.parametrize("k,anew,knobs", [(2, 0.02, dict()), (31, 0.5, dict(graph_capture=1)), (64, 0.15, dict(subrounds=3)),
+                                          (64, 0.5, dict()), (100, 0.02, dict(skip_quiet=1)), (200, 0.15, dict(subrounds=16)),
+                                          (256, 0.02, dict(fused_eval=-1))])
+def test_kept_sums_hold_and_are_counted_afresh(sc, graph, k, anew, knobs):
+    # a settled partition of which a part is placed anew: few moves, whose neighbours' sums are corrected; moves about the
+    # limit of that; and so many that the colours' rows are counted afresh, until the moves get few again
+    d, n, rng = sc.to_device(graph), graph["n"], np.random.default_rng(k)
+    lmax = oracle.lmax(int(graph["vwgt"].sum()), k, 0.1)
+    part = torch.from_numpy(rng.integers(0, k, size=n).astype(np.int32)).cuda()
+    sc.refine_dev(d, k, lmax, part, rounds=8, seed=1, validate=0)
+    part = part.cpu().numpy()
+    part = np.where(rng.random(n) < anew, rng.integers(0, k, size=n), part).astype(np.int32)
+    p, rr = sc.refine_dev(d, k, lmax, torch.from_numpy(part.copy()).cuda(), rounds=5, seed=k, **knobs)
+    ref, rr_ref, _ = oracle.refine(graph, k, lmax, part, rounds=5, seed=k, nsub=knobs.get("subrounds", 4))
+    assert rr == rr_ref and np.array_equal(p.cpu().numpy(), ref)
+
+
+@pytest.mark.parametrize("k", [2, 64])
+def test_kept_sums_where_most_nodes_move(sc, graph, k):
+    # without a bound on the blocks all nodes gather in one within a few rounds: correcting every mover's neighbours took
+    # twice the time of evaluating every slot in every round
+    d = sc.to_device(graph)
+    part = torch.from_numpy(np.random.default_rng(k).integers(0, k, size=graph["n"]).astype(np.int32)).cuda()
+    ms = {}
+    for validate in (0, 1):
+        best = 1e9
+        for _ in range(4):
+            sc.profile_begin()
+            sc.refine_dev(d, k, int(graph["vwgt"].sum()), part.clone(), rounds=6, seed=1, validate=validate)
+            best = min(best, sum(v["ms"] for v in sc.profile_end().values()))
+        ms[validate] = best
+    assert ms[1] < 1.25 * ms[0]
