@@ -2213,10 +2213,11 @@ constexpr int kFinishThreads = 1024;
 constexpr int kFinishMax = 65536;  // longest segment one workgroup of finish_kernel selects from
 // workgroups for the segments and (at most) for the admitted candidates; in
 // small label spaces every workgroup adds to the same few lines of weights, so
-// fewer move, and with at most kDirectLabels labels (each with one segment at
-// most) fewer select; a batch's blocks are more (64 graphs, 2 000 labels, 32 ->
-// 96 selecting workgroups: 36.9 -> 36.1 ms per batch)
-constexpr int kSegBlocks = 96;
+// fewer move, and no more select than there are labels, each with one segment
+// at most (mesh of 2^22 nodes, 5 rounds, 300, 1 000 and 5 000 blocks with a
+// segment each: 9.0, 11.0 and 15.2 ms with 32 to 96 selecting workgroups, 7.5,
+// 8.0 and 12.3 like this; refinement of 2^21 nodes into 100 blocks 7.52 -> 7.34)
+constexpr int kSegBlocks = 256;
 constexpr int kMoveBlocks = 192;
 constexpr int kSegBlocksSmall = 32;
 constexpr int kMoveBlocksSmall = 64;
@@ -3852,7 +3853,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             }
             {
                 ProfScope ps("lp_apply", 0, s);
-                const unsigned gseg = small && direct ? kSegBlocksSmall : kSegBlocks;
+                const unsigned gseg = small ? std::max(kSegBlocksSmall, std::min(nw, kSegBlocks)) : kSegBlocks;
                 const unsigned gmov = static_cast<unsigned>(std::min<int64_t>(
                     grid_for(ccount, kFinishThreads), small ? kMoveBlocksSmall : kMoveBlocks));
                 auto finish = small ? (g.heavy ? finish_kernel<true, true> : finish_kernel<true, false>)

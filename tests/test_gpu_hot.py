@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
+import synth
 
 pytestmark = pytest.mark.gpu
 
@@ -126,3 +127,21 @@ def test_colours_that_want_one_label(sc, hubs, leaves):
         assert rr == rr_ref and np.array_equal(p.cpu().numpy(), ref)
     groups = ["lp_refine_fused", "lp_refine_admit"] + ["lp_refine_" + b for b in ("lane4", "lane16", "group16", "hub_dense")]
     assert kernel_ms(sc, refine, groups) < 1.5 * kernel_ms(sc, lambda: refine(fused_eval=-1), groups)
+
+
+@pytest.fixture(scope="module")
+def mesh():
+    return synth.rgg(1 << 21, seed=7, weighted=True)
+
+
+@pytest.mark.parametrize("k", [300, 1000])
+def test_a_segment_for_each_of_many_blocks(sc, mesh, k):
+    # random blocks without room: every block is what some nodes of the one colour want, and selects.  The launches
+    # that count, admit and select took 1.6 and 2.2 times as long for 300 and 1000 blocks as for 64
+    n, d, ms = mesh["n"], sc.to_device(mesh), {}
+    groups = ("lp_apply", "lp_refine_admit", "lp_refine_admit_select")
+    for blocks in (64, k):
+        part = torch.from_numpy(np.random.default_rng(blocks).integers(0, blocks, size=n).astype(np.int32)).cuda()
+        ms[blocks] = kernel_ms(sc, lambda: sc.refine_dev(d, blocks, int(1.03 * n / blocks), part.clone(), rounds=3,
+                                                         subrounds=1), groups)
+    assert ms[k] < 1.4 * ms[64]
