@@ -1522,8 +1522,13 @@ __device__ __forceinline__ int32_t agg_insert(int32_t* keys, int32_t t) {
 // Label spaces up to this size (blocks of a refinement): LDS sums are indexed
 // by the label itself, every workgroup lays the segments out by itself, and the
 // counters all workgroups add to stand one per 128-byte line (adds to one line
-// are served one after the other, some 3 ns each).
+// are served one after the other, some 3 ns each).  Up to kSmallLabels in large
+// colours, whose 512 workgroups would otherwise each add to most of the labels,
+// 16 or 32 of them in a line, for every 2048 entries (mesh of 2^22 nodes, 1 500
+// blocks: totals and admission 340 us a sub-round, 76 like this); not in a
+// batch, where the entries of a workgroup have few targets.
 constexpr int kDirectLabels = 1024;
+constexpr int64_t kDirectColour = 1 << 18;  // colours above this size
 constexpr int kAccShift = 4;    // acc[t << kAccShift] (8-byte entries)
 constexpr int kFillShift = 5;   // seg_fill[t << kFillShift] (4-byte entries)
 
@@ -1533,11 +1538,13 @@ constexpr int kFillShift = 5;   // seg_fill[t << kFillShift] (4-byte entries)
 // in LDS first so that a label many nodes aim at (a hub's cluster) costs one
 // global atomic per block and chunk, not one per candidate.  Each block takes
 // R * 256 consecutive entries at a time.
-template <bool kDirect, int R>
+// kLabels: label spaces up to this size are summed directly, 0: through a table.
+template <int kLabels, int R>
 __global__ void __launch_bounds__(256) accumulate_kernel(EvalArgs E, HubArgs H, const int32_t* __restrict__ ct,
                                                          const int32_t* __restrict__ nodes, int32_t count,
                                                          unsigned long long* __restrict__ acc, int32_t nw,
                                                          bool heavy) {
+    constexpr bool kDirect = kLabels > 0;
     if (stopped(E.gate)) return;  // uniform over the grid
     const int32_t* vw = E.vw;
     if (static_cast<int32_t>(blockIdx.x) < H.count) {
@@ -1559,7 +1566,7 @@ __global__ void __launch_bounds__(256) accumulate_kernel(EvalArgs E, HubArgs H, 
     const int32_t bid = static_cast<int32_t>(blockIdx.x) - H.count;
     const int32_t nblocks = static_cast<int32_t>(gridDim.x) - H.count;
     constexpr int T = 512 * R;
-    constexpr int kSlots = kDirect ? kDirectLabels : T;
+    constexpr int kSlots = kDirect ? kLabels : T;
     __shared__ int32_t keys[kDirect ? 1 : T];
     __shared__ int32_t lsum[kSlots];
     __shared__ int32_t lcnt[kSlots];
@@ -1684,7 +1691,7 @@ struct Admission {
     LargeSel L;
     int32_t small_max;  // longer segments: multi-workgroup selection
     int32_t acc_shift;   // acc[t << acc_shift], seg_fill[t << fill_shift]: kAccShift
-    int32_t fill_shift;  // and kFillShift for at most kDirectLabels labels (no seg_off then), else 0
+    int32_t fill_shift;  // and kFillShift where segments are laid out directly (no seg_off then), else 0
     int bits_v;
     int32_t* label;
     uint8_t* label8;
@@ -1855,16 +1862,17 @@ __global__ void __launch_bounds__(256) admit_kernel(Admission A) {
     note_gains(A, found, gmin, gmax);
 }
 
-// The same for at most kDirectLabels labels: the segments' layout follows from
+// The same for at most kLabels labels: the segments' layout follows from
 // the candidate totals alone (a prefix sum over the labels), so every
 // workgroup computes it, claims and waits are not needed, and each workgroup
 // reserves its entries of a segment once, for a whole run of the colour.  With
 // claims and a reservation per 2048 entries, 500 workgroups adding to the same
 // 64 or 100 labels took 74-128 us a sub-round on R-MAT 2^21 and 2^24.
+template <int kLabels>
 __global__ void __launch_bounds__(256) admit_direct_kernel(Admission A) {
-    constexpr int kPer = kDirectLabels / 256;
-    __shared__ int32_t lcnt[kDirectLabels];
-    __shared__ int32_t lbase[kDirectLabels];  // first entry of the label's segment, -1: takes all its candidates
+    constexpr int kPer = kLabels / 256;
+    __shared__ int32_t lcnt[kLabels];
+    __shared__ int32_t lbase[kLabels];  // first entry of the label's segment, -1: takes all its candidates
     __shared__ unsigned long long s_wave[4];
     if (stopped(A.gate)) return;  // uniform over the grid
     const int tid = threadIdx.x;
@@ -3347,7 +3355,7 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     int64_t max_color = 0;
     for (int32_t sc = 0; sc < nsub; ++sc) max_color = std::max(max_color, off[(sc + 1) * kNB] - off[sc * kNB]);
     const int64_t cap = std::max<int64_t>(max_color, 1);
-    const bool direct = nw <= kDirectLabels;
+    const bool direct = nw <= kDirectLabels || (nw <= kSmallLabels && cap > kDirectColour && !mg);
     const int64_t acc_n = static_cast<int64_t>(nw) << (direct ? kAccShift : 0);
     const int64_t fill_n = static_cast<int64_t>(nw) << (direct ? kFillShift : 0);
     DBuf<int32_t> ct(cap, s), cg(cap, s), seg_off(direct ? 0 : nw, s), seg_fill(fill_n, s), swt(cap, s);
@@ -3820,20 +3828,23 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
             ++step;
             const int per = ccount <= (1 << 16) ? 1 : (ccount <= (1 << 18) ? 4 : 8);
             const unsigned gc = static_cast<unsigned>(std::min<int64_t>(grid_for(ccount, 256 * per), kMaxBlocks));
+            // every directly summing workgroup adds to every label
+            const unsigned ga = direct ? std::min(gc, std::max(64u, static_cast<unsigned>(kMaxBlocks * kDirectLabels / nw))) : gc;
             {
                 ProfScope ps(A.refine ? "lp_refine_admit" : "lp_admit", 0, s);
                 if (!count_in_eval) {
-                    auto accum = direct ? (per == 1   ? accumulate_kernel<true, 1>
-                                           : per == 4 ? accumulate_kernel<true, 4>
-                                                      : accumulate_kernel<true, 8>)
-                                        : (per == 1   ? accumulate_kernel<false, 1>
-                                           : per == 4 ? accumulate_kernel<false, 4>
-                                                      : accumulate_kernel<false, 8>);
+                    auto accum = direct && nw > kDirectLabels ? accumulate_kernel<kSmallLabels, 8>
+                                 : direct ? (per == 1   ? accumulate_kernel<kDirectLabels, 1>
+                                             : per == 4 ? accumulate_kernel<kDirectLabels, 4>
+                                                        : accumulate_kernel<kDirectLabels, 8>)
+                                          : (per == 1   ? accumulate_kernel<0, 1>
+                                             : per == 4 ? accumulate_kernel<0, 4>
+                                                        : accumulate_kernel<0, 8>);
                     use_bucket(kHubBucket);
-                    accum<<<gc + H.count, 256, 0, s>>>(A, H, ct.get(), cnodes, M.count - H.count, acc.get(), nw, g.heavy);
+                    accum<<<ga + H.count, 256, 0, s>>>(A, H, ct.get(), cnodes, M.count - H.count, acc.get(), nw, g.heavy);
                     LAUNCHCHK();
                 }
-                auto admit = direct     ? admit_direct_kernel
+                auto admit = direct ? (nw > kDirectLabels ? admit_direct_kernel<kSmallLabels> : admit_direct_kernel<kDirectLabels>)
                              : per == 1 ? admit_kernel<1>
                              : per == 4 ? admit_kernel<4>
                                         : admit_kernel<8>;
