@@ -85,9 +85,10 @@ typedef struct {
     int32_t max_levels;      /* at most this many contractions, 0..64 (default 64) */
     int32_t validate;        /* 1: check the input graph first (default 1).  A refinement into at
                                 most 256 blocks of a checked graph with 2^24 slots in long rows
-                                keeps their block sums between rounds (at most 16 bytes of device
-                                memory per slot of those rows) and is faster for it; where that
-                                memory cannot be had, it runs as on an unchecked graph */
+                                (and 2^22 per sub-round) keeps their block sums between rounds
+                                (at most 16 bytes of device memory per slot of those rows) and is
+                                faster for it; where that memory cannot be had, it runs as on an
+                                unchecked graph */
     /* Replaces the hash colour of every node (values in [0, subrounds)) in
      * sclap_cluster, sclap_refine and their _dev variants only; host or device
      * memory to match the entry point; NULL = hash colours. */

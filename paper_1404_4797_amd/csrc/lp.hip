@@ -76,7 +76,8 @@ constexpr int kSmallSeg = 16384;         // large colours: segments up to this l
 constexpr int kSegChunk = 16384;         // entries per workgroup in the multi-workgroup selection
 constexpr int kLargeBlocks = 256;        // grid of the multi-workgroup selection kernel
 constexpr int kLargeThreads = 1024;      // and its workgroup size
-constexpr int64_t kKeptMinSlots = 1 << 24;  // with fewer slots in long enough rows no sums are kept
+constexpr int64_t kKeptMinSlots = 1 << 24;  // with fewer slots in long enough rows no sums are kept,
+constexpr int64_t kKeptColourSlots = 1 << 22;  // nor with fewer of them per colour
 constexpr int32_t kKeptPerSlot = 4;         // a row keeps its sums when it has at least dense_k / 4 slots
 constexpr int kUpkeepLongBlocks = 512;      // grid of upkeep_long_kernel
 constexpr int kFreshShare = 6;  // after a sub-round that moved more than this part of its slots no sums hold
@@ -3454,7 +3455,11 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     // separate launch for the kept rows cost more than the gathers (refinement of
     // a power-law graph, 10 rounds, 16 blocks: whole partition of 2^20 nodes, 31
     // M slots, 29.7 ms without, 28.7 ms with; levels of 2 to 16 M slots kept too:
-    // 31.0 ms).  Where the memory is not to be had, nothing is kept.
+    // 31.0 ms).  Nor with colours of under 2^22 slots, which evaluate all rows in
+    // one launch and have nothing beside which the upkeep could run (refinement
+    // of that graph, 16 colours of 2 M slots, 100 blocks: 12.1 ms with, 10.4
+    // without; 4 colours 5.5 and 6.2).  Where the memory is not to be had, nothing
+    // is kept.
     int32_t kept_bucket = 2;
     while (kept_bucket < kHubBucket && (th.t[kept_bucket - 1] + 1) * kKeptPerSlot < A.dense_k) ++kept_bucket;
     int64_t kept_slots = 0;
@@ -3469,7 +3474,8 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
         kr.base[sc] = kept_rows;
         kept_rows += kr.to[sc] - kr.from[sc];
     }
-    bool keep = dense && g.symmetric && rounds > 2 && kept_slots >= kKeptMinSlots && nw < static_cast<int32_t>(kStayed);
+    bool keep = dense && g.symmetric && rounds > 2 && kept_slots >= std::max(kKeptMinSlots, nsub * kKeptColourSlots) &&
+                nw < static_cast<int32_t>(kStayed);
     // hub rows are kept whatever their length, which the options may set low
     if (static_cast<int64_t>(kept_rows) * A.dense_k > kKeptPerSlot * kept_slots || kept_rows >= 1 << kKeptBits) keep = false;
     DBuf<int32_t> sums, kidx;
