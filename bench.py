@@ -438,20 +438,24 @@ def main():
     lp_gb = sum(v["bytes"] for k, v in kstats.items()
                 if k.startswith("lp_eval") or k.startswith("lp_refine")) / 1e9
     # the whole label-propagation phase against the HBM roofline: per round
-    # executed at level l, 24 B per node and 12 B per slot scanned (a round's
-    # minimal traffic), over the wall time of all rounds
+    # executed at level l, 24 B per node and 12 B per slot visited, over the
+    # wall time of all rounds.  This is a model of the work, not of the bytes
+    # moved: a row whose block sums are kept between refinement rounds counts
+    # with all its slots, of which later rounds read 4 bytes per block
     lp_nodes = sum(st["level_n"][l] * st["cluster_rounds"][l] for l in range(len(st["cluster_rounds"])))
     lp_nodes += sum(st["level_n"][l] * st["refine_rounds"][l] for l in range(len(st["refine_rounds"])))
     lp_bytes = 24.0 * lp_nodes + 12.0 * visits
     lp_phase = {"bytes_per_step": lp_bytes, "ms": round(st["ms_lp"], 3),
                 "achieved_GBps": round(lp_bytes / (st["ms_lp"] / 1e3) / 1e9, 1),
                 "frac": round(lp_bytes / (st["ms_lp"] / 1e3) / 1e9 / HBM_PEAK_GBS, 4),
-                "edge_visits_per_s": visits / (st["ms_lp"] / 1e3)}
+                "edge_visits_per_s": visits / (st["ms_lp"] / 1e3),
+                "bytes_from": "model: 24 per node and 12 per slot visited, kept rows included"}
 
     # the access that bounds evaluation: one neighbour-label gather per slot,
     # measured by the library's probe kernel on this graph (4-byte labels as
-    # in clustering, 1-byte labels as in refinement); the label-propagation
-    # rounds' visits at those rates bound their time from below
+    # in clustering, 1-byte labels as in refinement).  The rounds' visits at
+    # those rates are the time of rounds that gather every label; refinement
+    # rounds that read kept block sums can be faster
     gather = None
     if S > 0:
         g4 = sc.gather_probe_dev(d, 4, reps=3, stream=stream)

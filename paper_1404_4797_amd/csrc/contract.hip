@@ -647,9 +647,9 @@ __global__ void long_offsets_kernel(uint32_t nl, const int64_t* __restrict__ cfi
 
 // Unsorted merge of rows of 65..4096 entries: one workgroup per row sums
 // equal neighbours in an LDS table of kT >= 2 len slots and writes the
-// distinct entries (in table order) to the row's start.  Rows are grouped by
-// length so that short rows get small tables (less to clear, more workgroups
-// per CU).
+// distinct entries to the row's start, in the order of the slots that brought
+// them into the table.  Rows are grouped by length so that short rows get small
+// tables (less to clear, more workgroups per CU).
 template <int kT>
 __global__ void __launch_bounds__(256) block_hash_rows_kernel(const int32_t* __restrict__ list,
                                                               const int64_t* __restrict__ rowoff,
@@ -1042,10 +1042,11 @@ bool bucket_merge_long_rows(uint32_t nl, const int32_t* llist, int64_t nch, cons
 }  // namespace
 
 // Merges every row r of the entries tk/tw[rowoff[r] .. rowoff[r] + rowcnt[r])
-// in place (unit: every weight is 1, and tw is written but not read); dcnt[r] receives the number of distinct neighbours, written at the
-// row's start in no particular order.
-void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* rowcnt, int32_t* tk, int32_t* tw,
-                bool unit, int32_t* dcnt, hipStream_t s, int32_t bucket_mean = 0) {
+// in place (unit: every weight is 1, and tw is written but not read); dcnt[r]
+// receives the number of distinct neighbours, written at the row's start in no
+// particular order.
+static void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* rowcnt, int32_t* tk, int32_t* tw,
+                       bool unit, int32_t* dcnt, hipStream_t s, int32_t bucket_mean = 0) {
     DBuf<int32_t> lists(kRowClasses * static_cast<size_t>(nc), s);
     DBuf<uint32_t> counts(kRowClasses, s);
     uint32_t hc[kRowClasses] = {};
@@ -1140,7 +1141,7 @@ void merge_rows(int32_t nc, int64_t m, const int64_t* rowoff, const int32_t* row
 }
 
 // Orders every row of a CSR of distinct entries by neighbour id, in place.
-void order_rows(int32_t n, const int64_t* xadj, int32_t* adj, int32_t* ew, hipStream_t s) {
+static void order_rows(int32_t n, const int64_t* xadj, int32_t* adj, int32_t* ew, hipStream_t s) {
     if (n <= 0) return;
     const int bn = std::max(1, bits_for(static_cast<uint64_t>(n - 1)));
     DBuf<int32_t> lists(kOrderClasses * static_cast<size_t>(n), s);

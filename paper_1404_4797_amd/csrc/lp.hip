@@ -26,7 +26,8 @@
 // Large colours launch the buckets side by side on three streams; small ones
 // run them in one launch, or two where rows need a table over 16 KB.  Large
 // refinements count a long row's block sums once and keep them up to date
-// (kept sums) instead of evaluating the row's slots in every round.
+// (kept sums) instead of evaluating the row's slots in every round; after a
+// sub-round that moved much they are counted afresh.
 // The per-node connection table maps a neighbour label to the summed weight
 // of the edges to it (Section 4.1 uses hashing with linear probing for this).
 //
@@ -64,7 +65,7 @@ constexpr int kBlockTable = 10240;
 constexpr int kBlockTablePow2 = 16384;
 constexpr int kBlockMaxDeg = kBlockTablePow2 / 2;
 constexpr int kBlock1Max = 1024;  // 256 threads, 16 KB table
-constexpr int kBlock2Max = 4096;  // 512 threads, 64 KB table
+constexpr int kBlock2Max = 4096;  // 1024 threads, 64 KB table (512 with dense sums)
 constexpr int kHubTable = 8192;          // LDS table of a hub chunk workgroup (64 KB: two per CU)
 constexpr int kHubChunk = kHubTable / 2; // slots per hub workgroup (table load <= 1/2)
 constexpr int kHubDenseChunk = 8192;     // slots per hub workgroup with dense block arrays
@@ -1622,9 +1623,6 @@ __global__ void __launch_bounds__(256) accumulate_kernel(EvalArgs E, HubArgs H, 
             if (lcnt[j]) atomicAdd(&acc[j << kAccShift], acc_of(lcnt[j], lsum[j]));
     }
 }
-
-// Outcome of a candidate in ok[p]: 0 not a candidate or in a segment, 1
-// admitted.  Segment entries are decided by the target's boundary.
 
 // A target that cannot take all its candidates: `len` entries from `base` in
 // the segment arrays, of which the longest prefix in key order whose weight
