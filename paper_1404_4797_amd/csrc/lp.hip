@@ -3369,9 +3369,10 @@ LPResult run_lp(const DevGraph& g, int32_t phase, int32_t level, uint64_t seed, 
     // alone are that long); larger colours split segments over kSmallSeg in a
     // launch per digit.  Up to 65 536 entries per workgroup and one launch for
     // the others, in colours of up to 2^18 nodes, gained nothing on a partition
-    // of 2^20 nodes (28.25 and 27.21 ms, 28.35 and 27.30 like this) and lost
-    // where the segments are that long (8 hubs of 500 000 slots, refinement
-    // into 1 000 blocks: 2.09 ms, 1.47 like this).
+    // of 2^20 nodes (28.25 and 27.21 ms, 28.35 and 27.30 like this) and 5 % on
+    // a mesh of 741 000 (8.6 and 9.1 ms), and lost where the segments are that
+    // long (8 hubs of 500 000 slots, refinement into 1 000 blocks: 2.09 ms, 1.47
+    // like this).
     const int32_t small_max = tune.select_small_max > 0 ? std::min(tune.select_small_max, kFinishMax)
                               : cap <= kFinishMax       ? kFinishMax
                                                         : kSmallSeg;
